@@ -587,9 +587,9 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     };
     PartialOut po = splitk_out(p, slice < 0 ? 0 : slice);
     if (p.sk_tiles != 0) {
-        po = PartialOut{nullptr, 0, 0, 0, false};
+        po = PartialOut{nullptr, 0, 0, 0};
         if (slice >= 0)     // partial tile, stored densely: [slice][position among the cut tiles][BM][BN]
-            po = PartialOut{p.ws + ((int64_t)slice * p.sk_tiles + sk_pos) * (C::BM * C::BN), C::BN, m0, n0, true};
+            po = PartialOut{p.ws + ((int64_t)slice * p.sk_tiles + sk_pos) * (C::BM * C::BN), C::BN, m0, n0};
     }
     epilogue_slabs<C, C::WTM / 32>(p, lds, wave, lane, wm, wn, m0, n0, po, write_slab, write16);
 #ifdef PEAK_TRACE

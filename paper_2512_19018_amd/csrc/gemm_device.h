@@ -31,12 +31,7 @@ enum { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2 };
 
 // flags in GemmArgs::flags
 enum {
-    GF_A_VEC = 1,      // A base and row stride are 16-byte aligned
-    GF_B_VEC = 2,      // B likewise
-    GF_C_VEC = 4,      // C rows allow 4-element vector access
-    GF_WS_VEC = 8,     // workspace rows (N floats) allow 16-byte access
-    GF_C_VEC16 = 16,   // C base and row stride are 16-byte aligned
-    GF_C_F32 = 32      // C is stored as fp32 although A and B are 16-bit
+    GF_C_F32 = 1       // C is stored as fp32 although A and B are 16-bit
 };
 
 // Fused output step: v <- act(v + bias), applied to alpha*acc + beta*C in fp32
@@ -188,24 +183,54 @@ struct Cfg {
 };
 
 // ---------------------------------------------------------------------------
-// Register-staged tile loads.
+// Memory accesses of up to 16 bytes at element alignment.  gfx950 takes vector loads and stores at any
+// alignment; what a misaligned one costs was measured on 16-byte loads of 128-byte row pieces from the L2, one
+// CU's rate: 110 bytes per ns on 16-byte boundaries, 66 on 4-byte ones, 54 with half of the rows on odd 2-byte
+// ones, 36 with all of them.  Eight 2-byte loads in place of one of these took ten times as long.
+// ---------------------------------------------------------------------------
+template <class V, int ALIGN>
+struct __attribute__((packed, aligned(ALIGN))) Loose { V v; };
+template <class V, int ALIGN>
+PEAK_DEV V load_loose(const void *p) { return ((const Loose<V, ALIGN> *)p)->v; }
+template <class V, int ALIGN>
+PEAK_DEV void store_loose(void *p, const V &v) { ((Loose<V, ALIGN> *)p)->v = v; }
+
+// Elements s .. of a 16-byte chunk moved to its front, zeros behind them (0 <= s; s past the chunk leaves zeros).
+template <int DT>
+PEAK_DEV u32x4 shift_down(u32x4 v, int s)
+{
+    constexpr int DW = DT == DT_F32 ? 0 : 1;                              // elements per dword, log2
+    const int d = s >> DW;                                                // whole dwords
+    if (d & 2) v = u32x4{v[2], v[3], 0u, 0u};
+    if (d & 1) v = u32x4{v[1], v[2], v[3], 0u};
+    if (d & ~3) v = u32x4{0u, 0u, 0u, 0u};
+    if (DT != DT_F32 && (s & 1))
+        v = u32x4{v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16, v[2] >> 16 | v[3] << 16, v[3] >> 16};
+    return v;
+}
+
+// ---------------------------------------------------------------------------
+// Register-staged tile loads, at any alignment.  A 16-byte chunk that K or the matrix edge cuts is fetched so that
+// it ends on the last element instead and is shifted into place: every chunk is one load inside the matrix, on edge
+// tiles as well (cut into its elements, the edge workgroups of a 1023 x 2047 product held up all others).  Operands
+// of fewer elements per row than a chunk are fetched one by one.
 // ---------------------------------------------------------------------------
 template <int DT>
-PEAK_DEV u32x4 load_chunk_elems(const void *base, int64_t idx0, int64_t stride, int nvalid)
+PEAK_DEV u32x4 load_chunk_elems(const void *base, int64_t idx0, int nvalid)
 {
-    // nvalid leading elements of the chunk come from memory (element idx0 + e*stride), the rest are zero.
+    // nvalid leading elements of the chunk come from memory, the rest are zero.
     constexpr int EPC = DT == DT_F32 ? 4 : 8;
     u32x4 v = {0u, 0u, 0u, 0u};
     if (DT == DT_F32) {
         const uint32_t *p = (const uint32_t *)base;
 #pragma unroll
         for (int e = 0; e < EPC; ++e)
-            if (e < nvalid) v[e] = p[idx0 + e * stride];
+            if (e < nvalid) v[e] = p[idx0 + e];
     } else {
         const uint16_t *p = (const uint16_t *)base;
 #pragma unroll
         for (int e = 0; e < EPC; ++e)
-            if (e < nvalid) v[e >> 1] |= (uint32_t)p[idx0 + e * stride] << ((e & 1) * 16);
+            if (e < nvalid) v[e >> 1] |= (uint32_t)p[idx0 + e] << ((e & 1) * 16);
     }
     return v;
 }
@@ -215,27 +240,39 @@ template <class C, int ROWS>
 struct LoaderK {
     static constexpr int NCH = (ROWS * C::CPR + C::NT - 1) / C::NT;
     u32x4 v[NCH];
+    const char *row_ptr[NCH];                                     // start (k = 0) of the chunk's row
 
-    PEAK_DEVM void load(const void *base, int64_t ld, int64_t row0, int64_t nrows, int64_t k0, int64_t kend,
-                       bool vec, int tid)
+    PEAK_DEVM void init(const void *base, int64_t ld, int64_t row0, int64_t nrows, int tid)
     {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
-            const int idx = tid + C::NT * i;
-            const int row = idx / C::CPR, c = idx % C::CPR;
-            u32x4 val = {0u, 0u, 0u, 0u};
-            if (ROWS * C::CPR % C::NT == 0 || idx < ROWS * C::CPR) {
-                int64_t gr = row0 + row;
-                if (gr > nrows - 1) gr = nrows - 1;          // duplicate of a valid row; its results are never stored
-                const int64_t k = k0 + (int64_t)c * C::EPC;
-                const int64_t left = kend - k;
-                if (vec && left >= C::EPC) {
-                    val = *(const u32x4 *)((const char *)base + (gr * ld + k) * C::ESZ);
-                } else if (left > 0) {
-                    val = load_chunk_elems<C::DT>(base, gr * ld + k, 1, left < C::EPC ? (int)left : C::EPC);
-                }
+            int64_t gr = row0 + (tid + C::NT * i) / C::CPR;
+            if (gr > nrows - 1) gr = nrows - 1;                   // duplicate of a valid row; its results are never stored
+            row_ptr[i] = (const char *)base + gr * ld * C::ESZ;
+        }
+    }
+
+    PEAK_DEVM void load(int64_t k0, int64_t kend, int tid)
+    {
+        if (kend - k0 >= C::BK) {                                 // (the same for the whole workgroup)
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int c = (tid + C::NT * i) % C::CPR;
+                v[i] = load_loose<u32x4, C::ESZ>(row_ptr[i] + (k0 + (int64_t)c * C::EPC) * C::ESZ);
             }
-            v[i] = val;
+        } else if (kend >= C::EPC) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int64_t k = k0 + (int64_t)((tid + C::NT * i) % C::CPR) * C::EPC;
+                const int64_t kc = k > kend - C::EPC ? kend - C::EPC : k;
+                v[i] = shift_down<C::DT>(load_loose<u32x4, C::ESZ>(row_ptr[i] + kc * C::ESZ), (int)(k - kc));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int64_t k = k0 + (int64_t)((tid + C::NT * i) % C::CPR) * C::EPC;
+                v[i] = load_chunk_elems<C::DT>(row_ptr[i], k, k < kend ? (int)(kend - k) : 0);
+            }
         }
     }
 
@@ -261,29 +298,54 @@ struct LoaderT {
     static constexpr int NBLK = RBLK * C::CPR;
     static constexpr int NB = (NBLK + C::NT - 1) / C::NT;
     u32x4 v[NB][E];                                               // [block][k within chunk] -> E row-elements
+    const char *col_ptr[NB];                                      // k-row 0, first element that the block fetches
+    int shift[NB];                                                // elements by which that lies before the block's own first
+    int64_t step;                                                 // bytes from one k-row to the next
+    int left;                                                     // tile rows inside the matrix (at most ROWS)
+    bool narrow;                                                  // the matrix has fewer than E of them
 
-    PEAK_DEVM void load(const void *base, int64_t ld, int64_t row0, int64_t nrows, int64_t k0, int64_t kend,
-                       bool vec, int tid)
+    PEAK_DEVM void init(const void *base, int64_t ld, int64_t row0, int64_t nrows, int tid)
+    {
+        step = ld * C::ESZ;
+        left = nrows - row0 < ROWS ? (int)(nrows - row0) : ROWS;
+        narrow = nrows < E;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int64_t r = row0 + (int64_t)((tid + C::NT * b) % RBLK) * E;
+            const int64_t rc = narrow ? r : r > nrows - E ? nrows - E : r;
+            col_ptr[b] = (const char *)base + rc * C::ESZ;
+            shift[b] = (int)(r - rc);
+        }
+    }
+
+    PEAK_DEVM void load(int64_t k0, int64_t kend, int tid)
     {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             const int id = tid + C::NT * b;
             const int rb = id % RBLK, c = id / RBLK;
-            const int64_t r = row0 + (int64_t)rb * E;             // first tile row of the block, as a global row/col index
 #pragma unroll
             for (int kk = 0; kk < E; ++kk) {
-                u32x4 val = {0u, 0u, 0u, 0u};
                 const int64_t k = k0 + (int64_t)c * E + kk;
-                if ((NBLK % C::NT == 0 || id < NBLK) && k < kend) {
-                    const int64_t left = nrows - r;
-                    if (vec && left >= E) {
-                        val = *(const u32x4 *)((const char *)base + (k * ld + r) * C::ESZ);
-                    } else if (left > 0) {
-                        val = load_chunk_elems<C::DT>(base, k * ld + r, 1, left < E ? (int)left : E);
-                    }
-                }
+                const int64_t kc = k < kend ? k : kend - 1;       // past the end: a valid row, zeroed below
+                u32x4 val;
+                if (!narrow) val = load_loose<u32x4, C::ESZ>(col_ptr[b] + kc * step);
+                else val = load_chunk_elems<C::DT>(col_ptr[b] + kc * step, 0, left - rb * E);
                 v[b][kk] = val;
             }
+        }
+        if (left < ROWS && !narrow) {                             // edge tile
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int kk = 0; kk < E; ++kk) v[b][kk] = shift_down<C::DT>(v[b][kk], shift[b]);
+        }
+        if (kend - k0 < C::BK) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int kk = 0; kk < E; ++kk)
+                    if (k0 + (int64_t)((tid + C::NT * b) / RBLK) * E + kk >= kend) v[b][kk] = u32x4{0u, 0u, 0u, 0u};
         }
     }
 
@@ -541,32 +603,32 @@ PEAK_DEV void hook_bias4(const Hook &h, int64_t m, int64_t n, int nvalid, float 
 // C[idx + e] = act(alpha * x[e] + beta * C[idx + e] + b[e]); the fused step (act, b)
 // only with `hooked`.
 template <int DT>
-PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, bool vec, int nvalid,
+PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, int nvalid,
                      bool hooked, int act, bool has_bias, const float (&b)[4])
 {
-    if (vec && nvalid == 4) {
+    if (nvalid == 4) {
         float o[4] = {alpha * x[0], alpha * x[1], alpha * x[2], alpha * x[3]};
         if (DT == DT_F32) {
             if (beta != 0.0f) {
-                const f32x4 c = *(const f32x4 *)((const float *)C + idx);
+                const f32x4 c = load_loose<f32x4, 4>((const float *)C + idx);
                 o[0] += beta * c[0]; o[1] += beta * c[1]; o[2] += beta * c[2]; o[3] += beta * c[3];
             }
             if (hooked) hook_apply(act, has_bias, o, b);
-            const f32x4 ov = {o[0], o[1], o[2], o[3]};
-            *(f32x4 *)((float *)C + idx) = ov;
+            store_loose<f32x4, 4>((float *)C + idx, f32x4{o[0], o[1], o[2], o[3]});
         } else {
+            union { u32x2 u; _Float16 h[4]; __bf16 b[4]; } pk;
             if (beta != 0.0f) {
+                pk.u = load_loose<u32x2, 2>((const uint16_t *)C + idx);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] += beta * elem_to_float<DT>(C, idx + e);
+                for (int e = 0; e < 4; ++e) o[e] += beta * (DT == DT_F16 ? (float)pk.h[e] : (float)pk.b[e]);
             }
             if (hooked) hook_apply(act, has_bias, o, b);
-            union { u32x2 u; _Float16 h[4]; __bf16 b[4]; } pk;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (DT == DT_F16) pk.h[e] = (_Float16)o[e];
                 else pk.b[e] = (__bf16)o[e];
             }
-            *(u32x2 *)((uint16_t *)C + idx) = pk.u;
+            store_loose<u32x2, 2>((uint16_t *)C + idx, pk.u);
         }
     } else {
 #pragma unroll
@@ -584,20 +646,20 @@ PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float 
 
 // ... without a fused step (split-K partials)
 template <int DT>
-PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, bool vec, int nvalid)
+PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, int nvalid)
 {
     const float none[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    store4<DT>(C, idx, x, alpha, beta, vec, nvalid, false, ACT_NONE, false, none);
+    store4<DT>(C, idx, x, alpha, beta, nvalid, false, ACT_NONE, false, none);
 }
 
 // ... with the fused step of `hk` for row m, columns n.. (fetches the bias itself)
 template <int DT>
-PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, bool vec, int nvalid,
+PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float beta, int nvalid,
                      const Hook hk, int64_t m, int64_t n)
 {
     float b[4];
     hook_bias4(hk, m, n, nvalid, b);
-    store4<DT>(C, idx, x, alpha, beta, vec, nvalid, hook_active(hk), hk.act, hk.bias_kind != BIAS_NONE, b);
+    store4<DT>(C, idx, x, alpha, beta, nvalid, hook_active(hk), hk.act, hk.bias_kind != BIAS_NONE, b);
 }
 
 // Tile order (the paper's Block-Swizzle, made XCD-aware): consecutive workgroup
@@ -634,27 +696,25 @@ PEAK_DEV void tile_of_block(int t, int tiles_m, int tiles_n, int group_m, int &t
 struct PartialOut {
     float *base;
     int64_t ld, m_org, n_org;
-    bool vec;                 // rows allow 16-byte access
 };
 
 // Split-K: slice s of every tile goes to its own M x N plane of the workspace.
 PEAK_DEV PartialOut splitk_out(const GemmArgs &p, int slice)
 {
-    if (p.split <= 1) return PartialOut{nullptr, 0, 0, 0, false};
-    return PartialOut{p.ws + (int64_t)slice * p.M * p.N, p.N, 0, 0, (p.flags & GF_WS_VEC) != 0};
+    if (p.split <= 1) return PartialOut{nullptr, 0, 0, 0};
+    return PartialOut{p.ws + (int64_t)slice * p.M * p.N, p.N, 0, 0};
 }
 
 template <class C, int SLABS, class WriteSlab, class Write16>
 PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, int wm, int wn, int64_t m0, int64_t n0,
                              const PartialOut &po, WriteSlab &&write_slab, Write16 &&write16)
 {
-    const bool c_vec = p.flags & GF_C_VEC, ws_vec = po.vec;
     float *wsl = po.base;
     const bool interior = m0 + C::BM <= p.M && n0 + C::BN <= p.N;      // whole tile inside C: no masks
     // Each wave turns its 32-row slabs around in LDS (fp32, padded rows) so that a
     // store instruction writes whole row segments of the wave tile (16 bytes per
     // lane, WTN elements per row) instead of 32 scattered 8-byte pieces.  Interior
-    // tiles with 16-byte aligned C rows store vectors; edge tiles, unaligned rows and
+    // tiles store vectors, whatever the alignment of C's rows; tiles on a ragged right edge and
     // split-K partials leave through the same turnaround with masked stores, so the
     // accumulators have one way out and never wait in ordinary registers.
     constexpr int SROW = C::WTN * 4 + 16;                              // scratch row stride, bytes
@@ -686,7 +746,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
         // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
         // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
         if constexpr (C::DT != DT_F32) {
-            if (interior && !wsl && (p.flags & GF_C_VEC16) && !c_f32 && p.beta == 0.0f && !hooked) {
+            if (interior && !wsl && !c_f32 && p.beta == 0.0f && !hooked) {
                 constexpr int SROW16 = C::WTN * 2 + 16;
                 constexpr int G = 32 / RPI;
                 char *scr16 = lds + wave * (32 * SROW16);
@@ -703,7 +763,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                         const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
                         const int64_t n = n0 + wn * C::WTN + ocol;
                         const u32x4 o = (((g * RPI) >> 4) & 1) ? u32x4{v[g][2], v[g][3], v[g][0], v[g][1]} : v[g];
-                        *(u32x4 *)((uint16_t *)p.C + m * p.ldc + n) = o;
+                        store_loose<u32x4, 2>((uint16_t *)p.C + m * p.ldc + n, o);
                     }
                 }
                 return;
@@ -722,9 +782,9 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             }
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
-            // 16-byte stores need aligned rows; on edge tiles also that no lane's column group
-            // straddles N (then a group is either stored whole or not at all)
-            const bool vec_ok = !wsl && (p.flags & GF_C_VEC16) && !c_f32 && (interior || p.N % EPL == 0);
+            // 16-byte stores need, on edge tiles, that no lane's column group straddles N (then a group is
+            // either stored whole or not at all)
+            const bool vec_ok = !wsl && !c_f32 && (interior || p.N % EPL == 0);
             if (!vec_ok) {
                 // masked 4-element stores
 #pragma unroll 1
@@ -742,16 +802,16 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                                 const int nvalid = left >= 4 ? 4 : (int)left;
                                 const f32x4 t = *(const f32x4 *)(src + q * 16);
                                 const float x[4] = {t[0], t[1], t[2], t[3]};
-                                if (wsl) store4<DT_F32>(wsl, (m - po.m_org) * po.ld + (nn - po.n_org), x, 1.0f, 0.0f, ws_vec, nvalid);
+                                if (wsl) store4<DT_F32>(wsl, (m - po.m_org) * po.ld + (nn - po.n_org), x, 1.0f, 0.0f, nvalid);
                                 else {
                                     const bool per_row = p.hook.bias_kind == BIAS_PER_ROW;
                                     const float b[4] = {per_row ? br : bcol[q * 4 + 0], per_row ? br : bcol[q * 4 + 1],
                                                         per_row ? br : bcol[q * 4 + 2], per_row ? br : bcol[q * 4 + 3]};
                                     if (c_f32)
-                                        store4<DT_F32>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, c_vec, nvalid,
+                                        store4<DT_F32>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, nvalid,
                                                        hooked, p.hook.act, has_bias, b);
                                     else
-                                        store4<C::DT>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, c_vec, nvalid,
+                                        store4<C::DT>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, nvalid,
                                                       hooked, p.hook.act, has_bias, b);
                                 }
                             }
@@ -776,7 +836,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                             const int64_t n = n0 + wn * C::WTN + ocol;
                             cin[g] = u32x4{0u, 0u, 0u, 0u};
                             if (interior || (m < p.M && n + EPL <= p.N))
-                                cin[g] = *(const u32x4 *)((const char *)p.C + (m * p.ldc + n) * C::ESZ);
+                                cin[g] = load_loose<u32x4, C::ESZ>((const char *)p.C + (m * p.ldc + n) * C::ESZ);
                         }
                     }
                     f32x4 lo[G], hi[G];
@@ -819,7 +879,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                                 hook_apply(p.hook.act, has_bias, oh, b);
                                 o[0] = oh[0]; o[1] = oh[1]; o[2] = oh[2]; o[3] = oh[3];
                             }
-                            *(f32x4 *)dst = o;
+                            store_loose<f32x4, 4>(dst, o);
                         } else {
                             float o[8] = {p.alpha * lo[g][0], p.alpha * lo[g][1], p.alpha * lo[g][2], p.alpha * lo[g][3],
                                           p.alpha * hi[g][0], p.alpha * hi[g][1], p.alpha * hi[g][2], p.alpha * hi[g][3]};
@@ -836,7 +896,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                                 if (C::DT == DT_F16) pk.h[e] = (_Float16)o[e];
                                 else pk.b[e] = (__bf16)o[e];
                             }
-                            *(u32x4 *)dst = pk.u;
+                            store_loose<u32x4, 2>(dst, pk.u);
                         }
                     }
                 };
@@ -893,8 +953,6 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     const int KT = __builtin_amdgcn_readfirstlane(kt_end - kt_begin);   // >= 1 by construction of the plan
     const int64_t kbase = (int64_t)kt_begin * C::BK;
     const int64_t kend = p.K;                               // zero fill beyond K (only the last slice can reach it)
-
-    const bool a_vec = p.flags & GF_A_VEC, b_vec = p.flags & GF_B_VEC;
 
     f32x16 acc[C::MI][C::NI];
 #pragma unroll
@@ -997,6 +1055,10 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     if (A_DIRECT && C::A_TR) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && !C::B_TR) dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && C::B_TR) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
+    if (!A_DIRECT && C::A_T) tA.init(p.A, p.lda, m0, p.M, tid);
+    if (!A_DIRECT && !C::A_T) kA.init(p.A, p.lda, m0, p.M, tid);
+    if (!B_DIRECT && C::B_T) tB.init(p.B, p.ldb, n0, p.N, tid);
+    if (!B_DIRECT && !C::B_T) kB.init(p.B, p.ldb, n0, p.N, tid);
 
     auto a_stage = [&](int s) { return lds + s * C::A_BYTES; };
     auto b_stage = [&](int s) { return lds + C::NSA * C::A_BYTES + s * C::B_BYTES; };   // for the loaders
@@ -1014,12 +1076,12 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     auto load_regs = [&](int kt) {                          // kt relative to the slice
         const int64_t k0 = kbase + (int64_t)rotated(kt) * C::BK;
         if (!A_DIRECT) {
-            if (C::A_T) tA.load(p.A, p.lda, m0, p.M, k0, kend, a_vec, tid);
-            else        kA.load(p.A, p.lda, m0, p.M, k0, kend, a_vec, tid);
+            if (C::A_T) tA.load(k0, kend, tid);
+            else        kA.load(k0, kend, tid);
         }
         if (!B_DIRECT) {
-            if (C::B_T) tB.load(p.B, p.ldb, n0, p.N, k0, kend, b_vec, tid);
-            else        kB.load(p.B, p.ldb, n0, p.N, k0, kend, b_vec, tid);
+            if (C::B_T) tB.load(k0, kend, tid);
+            else        kB.load(k0, kend, tid);
         }
     };
     auto store_regs = [&](int sa, int sb) {
@@ -1628,30 +1690,35 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
 
 // ---------------------------------------------------------------------------
 // Split-K, second step: C = alpha * (sum over slices, in slice order) + beta*C.
-// One thread per 4 consecutive outputs of a row.
+// One thread per 4 consecutive outputs of a row, a workgroup per 8 rows x 128 columns (a row of the workgroup's
+// index space in 64 bits, one division per thread, took as long as the sums themselves where the partials are few).
 // ---------------------------------------------------------------------------
+constexpr int REDUCE_ROWS = 8, REDUCE_COLS = 128;
 template <int DT>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs p)
 {
-    const int64_t quads_per_row = (p.N + 3) / 4;
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= p.M * quads_per_row) return;
-    const int64_t m = q / quads_per_row, n = (q % quads_per_row) * 4;
+    const uint32_t nbx = (uint32_t)((p.N + REDUCE_COLS - 1) / REDUCE_COLS);
+    const uint32_t by = blockIdx.x / nbx, bx = blockIdx.x - by * nbx;
+    const int64_t m = (int64_t)by * REDUCE_ROWS + threadIdx.x / (REDUCE_COLS / 4);
+    const int64_t n = (int64_t)bx * REDUCE_COLS + threadIdx.x % (REDUCE_COLS / 4) * 4;
+    if (m >= p.M || n >= p.N) return;
     const int nvalid = p.N - n >= 4 ? 4 : (int)(p.N - n);
-    const bool ws_vec = p.flags & GF_WS_VEC;
     float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s = 0; s < p.split; ++s) {
-        const float *w = p.ws + ((int64_t)s * p.M + m) * p.N + n;
-        if (ws_vec && nvalid == 4) {
-            const f32x4 t = *(const f32x4 *)w;
+    const float *w = p.ws + m * p.N + n;
+    const int64_t plane = p.M * p.N;
+    if (nvalid == 4) {
+#pragma unroll 4
+        for (int s = 0; s < p.split; ++s, w += plane) {
+            const f32x4 t = load_loose<f32x4, 4>(w);
             x[0] += t[0]; x[1] += t[1]; x[2] += t[2]; x[3] += t[3];
-        } else {
+        }
+    } else {
+        for (int s = 0; s < p.split; ++s, w += plane)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (e < nvalid) x[e] += w[e];
-        }
     }
-    store4<DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+    store4<DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
 }
 
 // Hybrid stream-K, second step: the tiles that were cut along K are summed over their slices,
@@ -1674,8 +1741,8 @@ __global__ __launch_bounds__(256) void streamk_reduce_kernel(const GemmArgs p)
         const f32x4 t = *(const f32x4 *)(p.ws + ((int64_t)s * p.sk_tiles + r) * (BM * BN) + row * BN + col);
         x[0] += t[0]; x[1] += t[1]; x[2] += t[2]; x[3] += t[3];
     }
-    if (p.flags & GF_C_F32) store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
-    else store4<DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+    if (p.flags & GF_C_F32) store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
+    else store4<DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
 }
 
 // C = hook(beta * C) (alpha == 0 or K == 0).  beta == 0 writes without reading.

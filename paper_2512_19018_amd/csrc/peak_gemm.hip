@@ -95,8 +95,6 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
     a.alpha = alpha; a.beta = beta;
     a.hook = hook;
     a.split = 1;
-    if ((uintptr_t)C % (4 * es_c) == 0 && (d.ldc * es_c) % (4 * es_c) == 0) a.flags |= GF_C_VEC;
-    if ((uintptr_t)C % 16 == 0 && (d.ldc * es_c) % 16 == 0) a.flags |= GF_C_VEC16;
     if (c_dt != d.dtype) a.flags |= GF_C_F32;
 
     const bool no_product = (d.K == 0 || alpha == 0.0f);
@@ -116,7 +114,7 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
     if (p->g.variant < 0) return PEAK_ERR_UNSUPPORTED;
 
     // (a plan that stages A reads its own aligned copy, whatever the base and rows of A)
-    bool a_al = (uintptr_t)A % 16 == 0 && (d.lda * es) % 16 == 0;
+    const bool a_al = (uintptr_t)A % 16 == 0 && (d.lda * es) % 16 == 0;
     const bool b_al = (uintptr_t)B % 16 == 0 && (d.ldb * es) % 16 == 0;
     // the selected variant, or its stand-in when it copies 16-byte chunks and a base is off that alignment
     const Geometry *g = &p->g;
@@ -130,10 +128,7 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
         if (!workspace || workspace_bytes < g->ws_bytes) return PEAK_ERR_WORKSPACE;
         if ((uintptr_t)workspace % 256) return PEAK_ERR_INVALID_ARG;
     }
-    if (g->split > 1) {
-        a.ws = (float *)workspace;
-        if (d.N % 4 == 0) a.flags |= GF_WS_VEC;
-    }
+    if (g->split > 1) a.ws = (float *)workspace;
     if (g->a_copy) {
         if (d.M > 64) return PEAK_ERR_UNSUPPORTED;          // (the planner admits no such plan)
         void *copy = (char *)workspace + g->a_copy_off;
@@ -143,10 +138,7 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
         if (hipGetLastError() != hipSuccess) return PEAK_ERR_HIP;
         a.A = copy;
         a.lda = d.K;
-        a_al = true;
     }
-    if (a_al) a.flags |= GF_A_VEC;
-    if (b_al) a.flags |= GF_B_VEC;
 #ifdef PEAK_TRACE
     // diagnostic build: an unsplit run writes 64 bytes of time stamps per wave into the workspace, if one that large is given
     if (g->split == 1 && workspace && workspace_bytes >= (size_t)g->tiles_m * g->tiles_n * (v.nt / 64) * 64) a.ws = (float *)workspace;
@@ -173,8 +165,7 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
             hipLaunchKernelGGL((streamk_reduce_kernel<DT_F16, 256, 256>), rgrid, dim3(256), 0, stream, a);
         if (hipGetLastError() != hipSuccess) return PEAK_ERR_HIP;
     } else if (g->split > 1) {
-        const int64_t quads = d.M * cdiv(d.N, 4);
-        dim3 rgrid((unsigned)cdiv(quads, 256));
+        dim3 rgrid((unsigned)(cdiv(d.N, REDUCE_COLS) * cdiv(d.M, REDUCE_ROWS)));
         if (c_dt == PEAK_DT_F32) hipLaunchKernelGGL(splitk_reduce_kernel<DT_F32>, rgrid, dim3(256), 0, stream, a);
         else if (c_dt == PEAK_DT_F16) hipLaunchKernelGGL(splitk_reduce_kernel<DT_F16>, rgrid, dim3(256), 0, stream, a);
         else hipLaunchKernelGGL(splitk_reduce_kernel<DT_BF16>, rgrid, dim3(256), 0, stream, a);

@@ -281,12 +281,12 @@ __global__ __launch_bounds__(C::NT) void skinny_kernel(const GemmArgs p)
             const int nvalid = left >= 4 ? 4 : (int)left;
             const float x[4] = {acc[mb][0], acc[mb][1], acc[mb][2], acc[mb][3]};
             if (p.split > 1)
-                store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, p.flags & GF_WS_VEC, nvalid);
+                store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, nvalid);
             else {
                 if (p.flags & GF_C_F32)
-                    store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                    store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
                 else
-                    store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                    store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
             }
         }
     }
@@ -374,12 +374,12 @@ __global__ __launch_bounds__(C::NT) void skinny_reg_kernel(const GemmArgs p)
         const int nvalid = left >= 4 ? 4 : (int)left;
         const float x[4] = {acc0[0] + acc1[0], acc0[1] + acc1[1], acc0[2] + acc1[2], acc0[3] + acc1[3]};
         if (p.split > 1)
-            store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, p.flags & GF_WS_VEC, nvalid);
+            store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, nvalid);
         else {
             if (p.flags & GF_C_F32)
-                store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
             else
-                store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
         }
     }
 }
@@ -587,12 +587,12 @@ __global__ __launch_bounds__(C::NT) void skinny_kn_kernel(const GemmArgs p)
                 const int nvalid = left >= 4 ? 4 : (int)left;
                 const float x[4] = {acc[mb][i][0], acc[mb][i][1], acc[mb][i][2], acc[mb][i][3]};
                 if (p.split > 1)
-                    store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, p.flags & GF_WS_VEC, nvalid);
+                    store4<DT_F32>(p.ws + (int64_t)slice * p.M * p.N, m * p.N + n, x, 1.0f, 0.0f, nvalid);
                 else {
                     if (p.flags & GF_C_F32)
-                        store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                        store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
                     else
-                        store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, p.flags & GF_C_VEC, nvalid, p.hook, m, n);
+                        store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
                 }
             }
         }
