@@ -1,0 +1,433 @@
+// Tiled kernel for operands of any alignment (odd leading dimensions, blocks of larger matrices that start
+// anywhere, K that is no whole number of 16-byte chunks), every storage type, all four layouts, on the 16x16 MFMA
+// (16x16x32 for 16-bit operands, 16x16x4 for fp32).
+//
+// The direct-to-LDS copies of the other tiled kernels need 16-byte aligned rows.  Here a tile goes through
+// registers: 16-byte loads at element alignment (the hardware takes them; see load_loose), then 16-byte LDS
+// stores to the very places the direct copies would fill, so that the fragment reads are theirs: rows along K as
+// they lie, [k][x] rows as they lie with the transposing read for 16-bit operands - no transposition in registers.
+// Chunks that K or a matrix edge cuts are fetched so that they end on the last element, and shifted into place
+// (shift_down): every chunk is one load inside the matrix, also on edge tiles (cut into elements, the edge workgroups
+// hold up all others).
+//
+// Bound: the way of unaligned rows into the CU.  One CU takes 110 bytes per ns from the L2 where rows start on
+// 128-byte lines, 69 where they only start on 16-byte boundaries (a K tile of a row then lies in two lines), 54 with
+// half of the rows on odd 2-byte addresses; the MFMAs of a 128 x 128 tile could take 130.  So the tile is large where
+// the problem has the tiles for it; small problems take small tiles, several workgroups per CU covering each other's
+// waits.  Measured against register staging with a transposition in registers and element-wise edges: bf16
+// 1023x2047x3001 NT (block, odd rows) 46.6 -> 40.5 us, fp32 777x1234x1555 TT 60.9 -> 44.7, fp32 256^3 (one launch
+// instead of a K split and its sum) 8.2 -> 5.1.
+#pragma once
+
+#include "gemm_device.h"
+
+namespace peak {
+
+// WM x WN waves share the tile, WK waves each of its places (the rounds of a stage dealt out over them, their sums
+// added in LDS at the end, in wave order); RB: bytes of K per row and stage; PF: tiles that are on their way in
+// registers; EU: waves per SIMD that the register budget is cut for.
+template <int DT_, bool A_KM_, bool B_KN_, int BM_, int BN_, int WM_, int WN_, int WK_, int RB_, int PF_, int EU_>
+struct CfgAny {
+    static constexpr int DT = DT_;
+    static constexpr bool A_KM = A_KM_, B_KN = B_KN_;
+    static constexpr int ESZ = DT_ == DT_F32 ? 4 : 2, EPC = 16 / ESZ;
+    static constexpr int BM = BM_, BN = BN_, RB = RB_, CPR = RB_ / 16, BK = RB_ / ESZ;
+    static constexpr int WAVES_M = WM_, WAVES_N = WN_, WAVES_K = WK_;
+    static constexpr int NW = WM_ * WN_, NT = NW * WK_ * 64;
+    static constexpr int WTM = BM / WM_, WTN = BN / WN_, MB = WTM / 16, NB = WTN / 16;
+    static constexpr int KROUND = 4 * EPC;                  // k per round of fragment reads: 4 chunks of 16 bytes
+    static constexpr int ROUNDS = BK / KROUND / WK_;        // per stage and wave
+    static constexpr int PF = PF_, EU = EU_;
+    static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
+    static constexpr int EPI_BYTES = 32 * (WTN * 4 + 16) * NW, RED_BYTES = NW * (WK_ - 1) * MB * NB * 1024;
+    static constexpr int LDS_BYTES = 2 * STAGE > EPI_BYTES ? (2 * STAGE > RED_BYTES ? 2 * STAGE : RED_BYTES)
+                                                           : (EPI_BYTES > RED_BYTES ? EPI_BYTES : RED_BYTES);
+    static_assert(RB_ == 128 || RB_ == 256, "swizzles below");
+    static_assert(ROUNDS * WK_ * KROUND == BK && ROUNDS >= 1, "whole rounds per wave");
+    static_assert(WTM % 32 == 0 && WTN % 16 == 0, "epilogue slabs of 32 rows");
+    static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "whole chunks per thread");
+    // rows along K: chunk c of row r at c ^ swizzle(r) (the placement of the 16x16x32 kernels, see Cfg16::swizzle)
+    static __device__ __forceinline__ int swizzle(int r)
+    {
+        if constexpr (RB_ == 128) return ((r >> 1) & 1) | (((r >> 2) & 1) << 2) | (((r >> 3) & 1) << 1);
+        else return (r & 1) | (((r >> 1) & 1) << 2) | (((r >> 2) & 1) << 3) | (((r >> 3) & 1) << 1);
+    }
+    // [k][x] rows of X elements: byte offset of chunk c of k-row k.
+    //   16 bits, read four k-rows x 32 bytes per 16 lanes: with rows of 256 bytes and more the placement of the
+    //   16x16x32 kernels; with 128-byte rows two neighbouring k-rows share the 256-byte bank period, bit 1 of k
+    //   tells the pairs of a read apart and the second term its groups of lanes.
+    //   fp32, read one float per lane, k-rows 4 q + e (q = lane / 16) in one read: the four rows go to four 64-byte
+    //   groups of banks; with 128-byte rows bits 0 and 2 of k change places, so that rows 4 apart lie next to
+    //   each other, and bit 3 picks the half.
+    template <int X>
+    static __device__ __forceinline__ int kx_offset(int k, int c)
+    {
+        constexpr int ROWB = X * ESZ;
+        static_assert(ROWB >= 128 && (DT_ != DT_F32 || X >= 32), "row sizes of the placements below");
+        if constexpr (DT_ == DT_F32) {
+            if constexpr (ROWB >= 256) return k * ROWB + ((c ^ (4 * ((k >> 2) & 3))) << 4);
+            else return ((k & ~5) | ((k >> 2) & 1) | ((k & 1) << 2)) * ROWB + ((c ^ (4 * ((k >> 3) & 1))) << 4);
+        } else {
+            const int hi = ((k >> 3) ^ (k >> 4)) & 1;
+            if constexpr (ROWB >= 256) return k * ROWB + ((c ^ (4 * (k & 3)) ^ (2 * hi)) << 4);
+            else return k * ROWB + ((c ^ (2 * ((k >> 1) & 1)) ^ (4 * hi)) << 4);
+        }
+    }
+    // fp32: offset of k-row k + e from k-row k, k a multiple of 4
+    template <int X>
+    static constexpr int kx_step(int e) { return (X * ESZ >= 256 ? e : (e & 2) | (e & 1) << 2) * (X * ESZ); }
+};
+
+// Up to a chunk of elements fetched one by one, zeros behind them: operands with fewer elements per row than a chunk.
+template <int DT>
+PEAK_DEV u32x4 load_elems(const char *src, int n)
+{
+    constexpr int EPC = DT == DT_F32 ? 4 : 8, ESZ = 16 / EPC;
+    u32x4 v = {0u, 0u, 0u, 0u};
+#pragma unroll 1
+    for (int e = (n < EPC ? n : EPC) - 1; e >= 0; --e) {        // each one pushed in below those behind it
+        if constexpr (DT == DT_F32) v = u32x4{*(const uint32_t *)(src + e * ESZ), v[0], v[1], v[2]};
+        else v = u32x4{v[0] << 16 | *(const uint16_t *)(src + e * ESZ), v[1] << 16 | v[0] >> 16, v[2] << 16 | v[1] >> 16, v[3] << 16 | v[2] >> 16};
+    }
+    return v;
+}
+
+// Operand that runs along K: ROWS rows x K.
+template <class C, int ROWS>
+struct AnyK {
+    static constexpr int NCH = ROWS * C::CPR / C::NT;
+    const char *panel;                                      // first row, k = 0
+    int64_t voff[NCH];                                      // this thread's chunks at k = 0
+    int64_t ld, K;
+    int rows;                                               // rows of the tile inside the matrix
+
+    PEAK_DEVM void init(const void *base, int64_t ld_, int64_t row0, int64_t nrows, int64_t K_, int tid)
+    {
+        ld = ld_;
+        K = K_;
+        rows = nrows - row0 < ROWS ? (int)(nrows - row0) : ROWS;
+        panel = (const char *)base + row0 * ld * C::ESZ;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int idx = tid + C::NT * i;
+            int row = idx / C::CPR;
+            if (row > rows - 1) row = rows - 1;             // duplicate of a valid row; its results are never stored
+            voff[i] = (row * ld + (int64_t)(idx % C::CPR) * C::EPC) * C::ESZ;
+        }
+    }
+    // elements by which the fetched chunk lies before its place, in the tile that K ends in
+    PEAK_DEVM int back(int64_t k0, int i, int tid) const
+    {
+        const int over = (int)(k0 - (K - C::EPC)) + (tid + C::NT * i) % C::CPR * C::EPC;
+        return over > 0 ? over : 0;
+    }
+    PEAK_DEVM void load(u32x4 (&v)[NCH], int64_t k0, int tid) const
+    {
+        const char *p = panel + k0 * C::ESZ;
+        if (K - k0 >= C::BK) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) v[i] = load_loose<u32x4, C::ESZ>(p + voff[i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                if (K >= C::EPC) v[i] = load_loose<u32x4, C::ESZ>(p + (voff[i] - back(k0, i, tid) * C::ESZ));
+                else v[i] = load_elems<C::DT>(p + voff[i], (int)K - (tid + C::NT * i) % C::CPR * C::EPC);
+            }
+        }
+    }
+    // (the shift waits until the tile is stored, when the loads have arrived)
+    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int64_t k0, int tid) const
+    {
+        if (K - k0 < C::BK && K >= C::EPC) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) v[i] = shift_down<C::DT>(v[i], back(k0, i, tid));
+        }
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int idx = tid + C::NT * i, row = idx / C::CPR;
+            *(u32x4 *)(tile + row * C::RB + (((idx % C::CPR) ^ C::swizzle(row)) << 4)) = v[i];
+        }
+    }
+};
+
+// Operand stored as K rows of X.. elements: BK k-rows x COLS.
+template <class C, int COLS>
+struct AnyX {
+    static constexpr int NCH = COLS * C::CPR / C::NT;
+    static constexpr int CPX = COLS * C::ESZ / 16;          // chunks per k-row
+    const char *base;
+    int64_t voff[NCH];
+    int shift[NCH];                                         // elements by which the fetched chunk lies before its place
+    int64_t ld, K;
+    int narrow;                                             // columns of an operand that has fewer than a chunk of them, else 0
+    bool edge;                                              // some chunk of the tile is cut by the matrix edge
+
+    PEAK_DEVM void init(const void *base_, int64_t ld_, int64_t x0, int64_t nx, int64_t K_, int tid)
+    {
+        ld = ld_;
+        K = K_;
+        base = (const char *)base_;
+        narrow = nx < C::EPC ? (int)nx : 0;
+        edge = nx - x0 < COLS && !narrow;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int idx = tid + C::NT * i;
+            const int64_t x = x0 + (int64_t)(idx % CPX) * C::EPC;
+            const int64_t xc = !narrow && x > nx - C::EPC ? nx - C::EPC : x;
+            voff[i] = ((idx / CPX) * ld + xc) * C::ESZ;
+            shift[i] = (int)(x - xc);
+        }
+    }
+    PEAK_DEVM void load(u32x4 (&v)[NCH], int64_t k0, int tid) const
+    {
+        const char *p = base + k0 * ld * C::ESZ;
+        if (K - k0 >= C::BK && !narrow) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) v[i] = load_loose<u32x4, C::ESZ>(p + voff[i]);
+        } else {                                            // k-rows past the end: fetched from the last one, zeroed below
+            const int last = K - k0 < C::BK ? (int)(K - k0) - 1 : C::BK - 1;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                const int k = (tid + C::NT * i) / CPX, over = k > last ? k - last : 0;
+                const char *src = p + (voff[i] - over * ld * C::ESZ);
+                if (!narrow) v[i] = load_loose<u32x4, C::ESZ>(src);
+                else v[i] = load_elems<C::DT>(src, narrow - (tid + C::NT * i) % CPX * C::EPC);
+            }
+        }
+    }
+    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int64_t k0, int tid) const
+    {
+        if (edge) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) v[i] = shift_down<C::DT>(v[i], shift[i]);
+        }
+        if (K - k0 < C::BK) {
+#pragma unroll
+            for (int i = 0; i < NCH; ++i)
+                if ((tid + C::NT * i) / CPX >= (int)(K - k0)) v[i] = u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int idx = tid + C::NT * i;
+            *(u32x4 *)(tile + C::template kx_offset<COLS>(idx / CPX, idx % CPX)) = v[i];
+        }
+    }
+};
+
+template <class C>
+__global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's symbol
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_all % C::NW, kpar = wave_all / C::NW;
+    const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+    const int r16 = lane & 15, q = lane >> 4;
+
+    const int tiles = p.tiles_m * p.tiles_n;
+    const int bid = blockIdx.x;
+    const int slice = __builtin_amdgcn_readfirstlane(bid / tiles);
+    int tm, tn;
+    tile_of_block(bid - slice * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    const int kt_begin = slice * p.ktiles_per_slice;
+    int kt_end = kt_begin + p.ktiles_per_slice;
+    if (kt_end > p.ktiles_total) kt_end = p.ktiles_total;
+    const int KT = __builtin_amdgcn_readfirstlane(kt_end - kt_begin);   // >= 1 by construction of the plan
+    const int64_t kbase = (int64_t)kt_begin * C::BK;
+
+    f32x4 acc[C::MB][C::NB];
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // Fragment addresses of round kpar; round kpar + WAVES_K * i lies a constant on, but for rows along K, whose
+    // swizzle does not commute with the chunk number: one address per round of a stage.
+    int a_k[C::ROUNDS], b_k[C::ROUNDS], a_x[C::MB], b_x[C::NB];
+#pragma unroll
+    for (int r = 0; r < C::ROUNDS; ++r) {
+        const int c = 4 * (r * C::WAVES_K + kpar) + q, ra = wm * C::WTM + r16, rb = wn * C::WTN + r16;
+        a_k[r] = ra * C::RB + ((c ^ C::swizzle(ra)) << 4);
+        b_k[r] = C::A_BYTES + rb * C::RB + ((c ^ C::swizzle(rb)) << 4);
+    }
+    // [k][x] rows.  16 bits: lane i of a group of 16 points at k-row 8 q + i / 4, columns 4 (i % 4) .. + 3 and gets
+    // the 4 k of one column; a second read four rows on takes the other half.  fp32: k-rows 4 q + e, column r16.
+    auto x_addr = [&](auto xc, int col16) {
+        constexpr int X = decltype(xc)::value;
+        if constexpr (C::DT == DT_F32) {
+            const int col = col16 + r16;
+            return C::template kx_offset<X>(kpar * C::KROUND + 4 * q, col >> 2) + (col & 3) * 4;
+        } else {
+            const int col = col16 + 4 * (r16 & 3);
+            return C::template kx_offset<X>(kpar * C::KROUND + 8 * q + (r16 >> 2), col >> 3) + (r16 & 1) * 8;
+        }
+    };
+    if constexpr (C::A_KM) {
+#pragma unroll
+        for (int i = 0; i < C::MB; ++i) a_x[i] = x_addr(IC<C::BM>{}, wm * C::WTM + i * 16);
+    }
+    if constexpr (C::B_KN) {
+#pragma unroll
+        for (int i = 0; i < C::NB; ++i) b_x[i] = C::A_BYTES + x_addr(IC<C::BN>{}, wn * C::WTN + i * 16);
+    }
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    auto frag_x = [&](const char *st, int addr, int r, auto xc) -> u32x4 {
+        constexpr int X = decltype(xc)::value, ROWB = X * C::ESZ;
+        const char *f = st + addr + r * (C::WAVES_K * C::KROUND * ROWB);
+        if constexpr (C::DT == DT_F32) {
+            return u32x4{*(const uint32_t *)(f + C::template kx_step<X>(0)), *(const uint32_t *)(f + C::template kx_step<X>(1)),
+                         *(const uint32_t *)(f + C::template kx_step<X>(2)), *(const uint32_t *)(f + C::template kx_step<X>(3))};
+        } else {
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)f);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(f + 4 * ROWB));
+            const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+            return u32x4{l2[0], l2[1], h2[0], h2[1]};
+        }
+    };
+    auto frag_a = [&](const char *st, int i, int r) -> u32x4 {
+        if constexpr (C::A_KM) return frag_x(st, a_x[i], r, IC<C::BM>{});
+        else return *(const u32x4 *)(st + a_k[r] + i * 16 * C::RB);
+    };
+    auto frag_b = [&](const char *st, int i, int r) -> u32x4 {
+        if constexpr (C::B_KN) return frag_x(st, b_x[i], r, IC<C::BN>{});
+        else return *(const u32x4 *)(st + b_k[r] + i * 16 * C::RB);
+    };
+
+    AnyK<C, C::BM> kA;
+    AnyX<C, C::BM> xA;
+    AnyK<C, C::BN> kB;
+    AnyX<C, C::BN> xB;
+    if constexpr (C::A_KM) xA.init(p.A, p.lda, m0, p.M, p.K, tid);
+    else kA.init(p.A, p.lda, m0, p.M, p.K, tid);
+    if constexpr (C::B_KN) xB.init(p.B, p.ldb, n0, p.N, p.K, tid);
+    else kB.init(p.B, p.ldb, n0, p.N, p.K, tid);
+    constexpr int CA = AnyK<C, C::BM>::NCH, CB = AnyK<C, C::BN>::NCH;
+    u32x4 va[C::PF][CA], vb[C::PF][CB];
+    auto load = [&](int kt, u32x4 (&a)[CA], u32x4 (&b)[CB]) {   // kt relative to the slice
+        const int64_t k0 = kbase + (int64_t)kt * C::BK;
+        if constexpr (C::A_KM) xA.load(a, k0, tid);
+        else kA.load(a, k0, tid);
+        if constexpr (C::B_KN) xB.load(b, k0, tid);
+        else kB.load(b, k0, tid);
+    };
+    auto store = [&](int kt, int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
+        char *st = lds + stage * C::STAGE;
+        const int64_t k0 = kbase + (int64_t)kt * C::BK;
+        if constexpr (C::A_KM) xA.store(st, a, k0, tid);
+        else kA.store(st, a, k0, tid);
+        if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, k0, tid);
+        else kB.store(st + C::A_BYTES, b, k0, tid);
+    };
+
+    // One barrier per tile: while tile kt is multiplied out of one stage, tile kt + 1 goes from registers into the
+    // other (everybody left it at the last barrier) and the loads of tile kt + 1 + PF go out.
+    static_for<C::PF>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        if (t < KT) load(t, va[t], vb[t]);
+    });
+    store(0, 0, va[0], vb[0]);
+    if (C::PF < KT) load(C::PF, va[0], vb[0]);
+    lds_barrier();
+    constexpr int U = C::PF % 2 == 0 ? C::PF : 2 * C::PF;   // tiles per trip: stage and register set static
+    for (int kt0 = 0; kt0 < KT; kt0 += U) {
+        static_for<U>([&](auto uc) {
+            constexpr int u = decltype(uc)::value, s = u % 2, set = (u + 1) % C::PF;
+            const int kt = kt0 + u;
+            if (kt < KT) {
+                const char *st = lds + s * C::STAGE;
+                u32x4 af[2][C::MB], bf[2][C::NB];
+#pragma unroll
+                for (int i = 0; i < C::NB; ++i) bf[0][i] = frag_b(st, i, 0);
+#pragma unroll
+                for (int i = 0; i < C::MB; ++i) af[0][i] = frag_a(st, i, 0);
+                __builtin_amdgcn_sched_barrier(0);          // (the compiler would sink the reads to their first use)
+                if (kt + 1 < KT) store(kt + 1, 1 - s, va[set], vb[set]);
+                if (kt + 1 + C::PF < KT) load(kt + 1 + C::PF, va[set], vb[set]);
+                static_for<C::ROUNDS>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value, cur = r & 1, nxt = cur ^ 1;
+                    if constexpr (r + 1 < C::ROUNDS) {
+#pragma unroll
+                        for (int i = 0; i < C::NB; ++i) bf[nxt][i] = frag_b(st, i, r + 1);
+#pragma unroll
+                        for (int i = 0; i < C::MB; ++i) af[nxt][i] = frag_a(st, i, r + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // (B's rows feed the instruction's row operand: a lane ends with 4 consecutive n of one m)
+                    if constexpr (C::DT == DT_F32) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                                for (int mb = 0; mb < C::MB; ++mb) {
+                                    const f32x4 b = __builtin_bit_cast(f32x4, bf[cur][nb]), a = __builtin_bit_cast(f32x4, af[cur][mb]);
+                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
+                                }
+                    } else {
+#pragma unroll
+                        for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                            for (int mb = 0; mb < C::MB; ++mb) {
+                                if constexpr (C::DT == DT_BF16)
+                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf[cur][nb]),
+                                                                                          __builtin_bit_cast(bf16x8, af[cur][mb]), acc[mb][nb], 0, 0, 0);
+                                else
+                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, bf[cur][nb]),
+                                                                                         __builtin_bit_cast(f16x8, af[cur][mb]), acc[mb][nb], 0, 0, 0);
+                            }
+                    }
+                });
+                lds_barrier();                              // (loads stay under way across it)
+            }
+        });
+    }
+
+    if constexpr (C::WAVES_K > 1) {
+        f32x4 *red = (f32x4 *)lds + lane;
+        if (kpar > 0) {
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb) red[((kpar - 1) * C::NW + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64] = acc[mb][nb];
+        }
+        lds_barrier();
+        if (kpar > 0) return;
+#pragma unroll
+        for (int k = 0; k < C::WAVES_K - 1; ++k)
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] += red[(k * C::NW + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64];
+    }
+
+    // acc[mb][nb][v] <-> m = 16 mb + lane % 16, n = 16 nb + 4 (lane / 16) + v; slab s = blocks 2 s and 2 s + 1
+    auto write_slab = [&](int sl, char *scr) {
+        constexpr int SROW = C::WTN * 4 + 16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb)
+                *(f32x4 *)(scr + (16 * h + r16) * SROW + (nb * 16 + 4 * q) * 4) = acc[2 * sl + h][nb];
+    };
+    auto write16 = [&](int sl, char *scr16) {
+        constexpr int SROW16 = C::WTN * 2 + 16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb) {
+                union { u32x2 u; _Float16 hh[4]; __bf16 bb[4]; } pk;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (C::DT == DT_F16) pk.hh[j] = (_Float16)(acc[2 * sl + h][nb][j] * p.alpha);
+                    else pk.bb[j] = (__bf16)(acc[2 * sl + h][nb][j] * p.alpha);
+                }
+                *(u32x2 *)(scr16 + (16 * h + r16) * SROW16 + ((nb * 4 + q) ^ h) * 8) = pk.u;
+            }
+    };
+    epilogue_slabs<C, C::WTM / 32>(p, lds, wave, lane, wm, wn, m0, n0, splitk_out(p, slice), write_slab, write16);
+#endif
+}
+
+}  // namespace peak

@@ -235,59 +235,6 @@ PEAK_DEV u32x4 load_chunk_elems(const void *base, int64_t idx0, int nvalid)
     return v;
 }
 
-// Operand that runs along K in memory: rows x K, row stride ld.
-template <class C, int ROWS>
-struct LoaderK {
-    static constexpr int NCH = (ROWS * C::CPR + C::NT - 1) / C::NT;
-    u32x4 v[NCH];
-    const char *row_ptr[NCH];                                     // start (k = 0) of the chunk's row
-
-    PEAK_DEVM void init(const void *base, int64_t ld, int64_t row0, int64_t nrows, int tid)
-    {
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            int64_t gr = row0 + (tid + C::NT * i) / C::CPR;
-            if (gr > nrows - 1) gr = nrows - 1;                   // duplicate of a valid row; its results are never stored
-            row_ptr[i] = (const char *)base + gr * ld * C::ESZ;
-        }
-    }
-
-    PEAK_DEVM void load(int64_t k0, int64_t kend, int tid)
-    {
-        if (kend - k0 >= C::BK) {                                 // (the same for the whole workgroup)
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int c = (tid + C::NT * i) % C::CPR;
-                v[i] = load_loose<u32x4, C::ESZ>(row_ptr[i] + (k0 + (int64_t)c * C::EPC) * C::ESZ);
-            }
-        } else if (kend >= C::EPC) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int64_t k = k0 + (int64_t)((tid + C::NT * i) % C::CPR) * C::EPC;
-                const int64_t kc = k > kend - C::EPC ? kend - C::EPC : k;
-                v[i] = shift_down<C::DT>(load_loose<u32x4, C::ESZ>(row_ptr[i] + kc * C::ESZ), (int)(k - kc));
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int64_t k = k0 + (int64_t)((tid + C::NT * i) % C::CPR) * C::EPC;
-                v[i] = load_chunk_elems<C::DT>(row_ptr[i], k, k < kend ? (int)(kend - k) : 0);
-            }
-        }
-    }
-
-    PEAK_DEVM void store(char *lds_tile, int tid) const
-    {
-#pragma unroll
-        for (int i = 0; i < NCH; ++i) {
-            const int idx = tid + C::NT * i;
-            const int row = idx / C::CPR, c = idx % C::CPR;
-            if (ROWS * C::CPR % C::NT == 0 || idx < ROWS * C::CPR)
-                *(u32x4 *)(lds_tile + row * C::RB + ((c ^ swz<C::CPR>(row)) << 4)) = v[i];
-        }
-    }
-};
-
 // Operand stored K rows x `rows` (runs along M or N in memory).  Each thread
 // takes an EPC(k) x EPC(rows) block, transposes it in registers and stores EPC
 // chunks, one per tile row.
@@ -1031,14 +978,12 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     };
 
     // operand loaders
-    constexpr bool A_DIRECT = C::DIRECT && (!C::A_T || C::A_TR), B_DIRECT = C::DIRECT && (!C::B_T || C::B_TR);
+    constexpr bool A_DIRECT = true, B_DIRECT = !C::B_T || C::B_TR;
+    static_assert(C::DIRECT && (!C::A_T || C::A_TR), "A goes to LDS directly (gemm_any_kernel takes what cannot)");
     LoaderDirect<C, C::BM> dA;
     LoaderDirect<C, C::BN> dB;
     LoaderDirectKN<C, C::BM> nA;
     LoaderDirectKN<C, C::BN> nB;
-    LoaderK<C, C::BM> kA;
-    LoaderK<C, C::BN> kB;
-    LoaderT<C, C::BM> tA;
     LoaderT<C, C::BN> tB;
     // loads per thread and tile that stay in flight across iterations
     constexpr int LA = !A_DIRECT ? 0 : (C::A_TR ? LoaderDirectKN<C, C::BM>::PER_WAVE : LoaderDirect<C, C::BM>::PER_WAVE);
@@ -1055,10 +1000,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     if (A_DIRECT && C::A_TR) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && !C::B_TR) dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && C::B_TR) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
-    if (!A_DIRECT && C::A_T) tA.init(p.A, p.lda, m0, p.M, tid);
-    if (!A_DIRECT && !C::A_T) kA.init(p.A, p.lda, m0, p.M, tid);
-    if (!B_DIRECT && C::B_T) tB.init(p.B, p.ldb, n0, p.N, tid);
-    if (!B_DIRECT && !C::B_T) kB.init(p.B, p.ldb, n0, p.N, tid);
+    if (!B_DIRECT) tB.init(p.B, p.ldb, n0, p.N, tid);
 
     auto a_stage = [&](int s) { return lds + s * C::A_BYTES; };
     auto b_stage = [&](int s) { return lds + C::NSA * C::A_BYTES + s * C::B_BYTES; };   // for the loaders
@@ -1075,22 +1017,10 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     };
     auto load_regs = [&](int kt) {                          // kt relative to the slice
         const int64_t k0 = kbase + (int64_t)rotated(kt) * C::BK;
-        if (!A_DIRECT) {
-            if (C::A_T) tA.load(k0, kend, tid);
-            else        kA.load(k0, kend, tid);
-        }
-        if (!B_DIRECT) {
-            if (C::B_T) tB.load(k0, kend, tid);
-            else        kB.load(k0, kend, tid);
-        }
+        if (!B_DIRECT) tB.load(k0, kend, tid);
     };
-    auto store_regs = [&](int sa, int sb) {
-        if (!A_DIRECT) {
-            if (C::A_T) tA.store(a_stage(sa), tid); else kA.store(a_stage(sa), tid);
-        }
-        if (!B_DIRECT) {
-            if (C::B_T) tB.store(b_stage(sb), tid); else kB.store(b_stage(sb), tid);
-        }
+    auto store_regs = [&](int sb) {
+        if (!B_DIRECT) tB.store(b_stage(sb), tid);
     };
     // Direct loads of tile kt, part PART of NPARTS (the parts of a tile can be
     // issued between groups of MFMAs).  Past the end the last tile is fetched again
@@ -1544,7 +1474,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
         }
         if (!ALL_DIRECT) {
             load_regs(0);
-            store_regs(0, 0);
+            store_regs(0);
         }
         for (int kt0 = 0; kt0 < KT; kt0 += C::NS) {
 #pragma unroll
@@ -1557,7 +1487,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
                     // with one stage in flight the loads go out at once: each gets the whole step to land
                     if (DLOADS > 0) issue_direct_all(kt + P, (s + P) % C::NS);
                     compute(s, s);
-                    if (!ALL_DIRECT && kt + 1 < KT) store_regs((s + 1) % C::NS, (s + 1) % C::NS);
+                    if (!ALL_DIRECT && kt + 1 < KT) store_regs((s + 1) % C::NS);
                 }
             }
         }
@@ -1576,10 +1506,10 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
         }
         if (!ALL_DIRECT) {
             load_regs(0);
-            store_regs(0, 0);
+            store_regs(0);
             if (KT > 1) {
                 load_regs(1);
-                store_regs(1, 1);
+                store_regs(1);
             }
         }
         u32x4 af[2][C::MI], bf[2][C::NI];
@@ -1629,7 +1559,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
                         });
                         __builtin_amdgcn_sched_barrier(0);
                     });
-                    if (!ALL_DIRECT && j + 2 < KT) store_regs((s + 2) % PN, (s + 2) % PN);
+                    if (!ALL_DIRECT && j + 2 < KT) store_regs((s + 2) % PN);
                     if (DLOADS > 0) wait_vmcnt<(PN - 3) * DLOADS>();    // own loads of tile j+2 have landed
                     lds_barrier();                                      // tiles <= j+2 complete; stage j % NS is free
                 }

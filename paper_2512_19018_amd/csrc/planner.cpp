@@ -78,11 +78,45 @@ static bool variant_fits(const Variant &v, const peak_gemm_desc_t &d)
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The K split's part of a variant's cost (units of tiled_cost): slices write and re-read fp32 partials, about 9 units per element and slice when
+// they go through HBM, half of that while the workspace stays in the last-level cache, plus the launch of the
+// reduction kernel (about 2 us).
+static double reduce_cost(const peak_gemm_desc_t &d, int split)
+{
+    if (split <= 1) return 0.0;
+    const double partials = (double)split * (double)d.M * (double)d.N;
+    return (4.0 * partials <= 64.0e6 ? 4.5 : 9.0) * partials + 8.0e6;
+}
+
+// The register-staged kernels: the loads bound them, not the MFMAs, and how well the loads overlap depends on the
+// workgroups that share a CU.  Measured as a share of the MFMA rate, with as many workgroups as fit and with one:
+// bf16 4095^3 (saturated) 0.26 with 128x128 tiles, 0.19 with 128x64, 0.14 with 64x64; 1023x2047x3001 0.13, 0.11 and
+// (two workgroups of eight waves) 0.13 with one to two workgroups per CU.  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
+// 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.43, with four 0.52.
+static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
+{
+    const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
+    const int64_t per_cu = cdiv(tiles, num_cu());
+    const double work = (double)v.bm * v.bn * v.bk * (double)cdiv(cdiv(d.K, v.bk), split) * (v.dt == PEAK_DT_F32 ? 16.0 : 1.0);
+    const int area = v.bm * v.bn;
+    int fit = LDS_LIMIT / v.lds, by_waves = 1024 / v.nt;    // workgroups that share a CU: LDS, four waves per SIMD
+    if (fit > by_waves) fit = by_waves;
+    if (fit < 1) fit = 1;
+    double eff, one;                                        // saturated; one workgroup's share of it
+    if (v.dt == PEAK_DT_F32) { eff = area >= 128 * 128 ? 0.65 : area >= 64 * 64 ? 0.66 : area >= 64 * 32 ? 0.60 : 0.50; one = 0.6; }
+    else { eff = area >= 128 * 128 ? 0.25 : area >= 128 * 64 ? 0.19 : 0.145; one = area >= 128 * 64 ? 0.55 : 0.8; }
+    const double full = (double)(per_cu / fit) * fit * work / eff;
+    const int64_t rest = per_cu % fit;
+    const double part = rest ? (double)rest * work / (eff * (fit > 1 ? one + (1.0 - one) * (double)(rest - 1) / (fit - 1) : 1.0)) : 0.0;
+    return full + part + 12.0e6 * (double)cdiv(per_cu, fit) + reduce_cost(d, split);
+}
+
 // Estimated time of a tiled variant, in units of "one 32x32xBK-row MFMA group":
 // rounds of workgroups over the CUs times the work of one tile.  Used only to
 // rank variants; the measured sweep decides the constants.
 static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
+    if (!v.direct) return staged_cost(v, d, split);
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
     const int64_t rounds = cdiv(tiles, num_cu());
     const double ktiles = (double)cdiv(cdiv(d.K, v.bk), split);
@@ -106,7 +140,6 @@ static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
         else if (v.bm * v.bn >= 128 * 64 && v.direct) eff = 0.7;   // 48 KB: three; ahead while the tiles are few
         else eff = 0.3;
     }
-    if (!v.direct) eff *= 0.7;
     if (v.tr) eff *= v.dt == PEAK_DT_F32 ? 1.10 : 1.03;      // B staged directly: no register transposition, no masked loads
     if (v.lds > 140 * 1024 && v.ns == 2 && !v.tr) eff *= 1.02;   // third A stage, A's loads spread over the step (+2 % measured; nothing with [k][n] B)
     if (v.nt == 256 && v.bm == 256 && v.bn == 256 && v.lds > 140 * 1024) eff *= 1.02;   // one wave per SIMD on top of that
@@ -138,19 +171,16 @@ static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     // 256x256 tile in four slices 206)
     if (v.dt == PEAK_DT_F32 && v.ns == 3) eff *= 0.97;
     const double fixed = 12.0e6;                    // prologue + epilogue of one tile, same units
-    // K slices write and re-read fp32 partials: about 9 units per element and slice when they go
-    // through HBM, half of that while the workspace stays in the last-level cache
-    const double ws_bytes = 4.0 * (double)split * (double)d.M * (double)d.N;
-    // ... plus the launch of the reduction kernel (about 3 us)
-    const double reduce = split > 1 ? (ws_bytes <= 64.0e6 ? 4.5 : 9.0) * (double)split * (double)d.M * (double)d.N + 8.0e6 : 0.0;
-    return rounds * (tile_work / eff + fixed) + reduce;
+    return rounds * (tile_work / eff + fixed) + reduce_cost(d, split);
 }
 
 static int choose_split(const Variant &v, const peak_gemm_desc_t &d)
 {
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn);
     const int64_t ktiles = cdiv(d.K, v.bk);
-    if (tiles > num_cu() / 2 || ktiles < 4) return 1;
+    // (the register-staged kernels gain from several workgroups per CU: bf16 1023x2047x3001 in 256 tiles of 128x64
+    // 48.9 us unsplit, 40.2 in two slices)
+    if (tiles > (v.direct ? num_cu() / 2 : 2 * num_cu()) || ktiles < 4) return 1;
     int best = 1;
     double best_cost = tiled_cost(v, d, 1);
     for (int s = 2; s <= 16; ++s) {

@@ -13,7 +13,6 @@
 namespace peak {
 
 // one per translation unit
-VariantGroup variants_general();
 VariantGroup variants_bf16_nt();
 VariantGroup variants_f16_nt();
 VariantGroup variants_bf16_nn();
@@ -26,6 +25,9 @@ VariantGroup variants_mf16s();
 VariantGroup variants_mf16d();
 VariantGroup variants_mf16r();
 VariantGroup variants_mf16k();
+VariantGroup variants_any_bf16();
+VariantGroup variants_any_f16();
+VariantGroup variants_any_f32();
 
 template <class C>
 static int launch_gemm(const GemmArgs &a, unsigned grid, void *stream)
@@ -87,12 +89,6 @@ static int launch_gemm(const GemmArgs &a, unsigned grid, void *stream)
 // Layout suffix of the names: first letter is A (n: runs along K, t: stored K x M),
 // second is B as stored (t: N x K, runs along K; n: K x N).  So "_nt" is transA=0,
 // transB=1: both operands K-contiguous.
-#define TILED_LAYOUTS(NAME, DT, BM, BN, RB, WMW, WNW, NS)                                              \
-    TILED(NAME "_nt", DT, BM, BN, RB, WMW, WNW, NS, false, false, false),                             \
-    TILED(NAME "_nn", DT, BM, BN, RB, WMW, WNW, NS, false, true, false),                              \
-    TILED(NAME "_tt", DT, BM, BN, RB, WMW, WNW, NS, true, false, false),                              \
-    TILED(NAME "_tn", DT, BM, BN, RB, WMW, WNW, NS, true, true, false)
-
 #define PEAK_VARIANT_GROUP(FN, ROWS)                                                                   \
     VariantGroup FN() { return VariantGroup{ROWS, (int)(sizeof(ROWS) / sizeof(ROWS[0]))}; }
 

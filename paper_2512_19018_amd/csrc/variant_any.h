@@ -1,0 +1,27 @@
+// Launch of the any-alignment kernels ("_r": through registers) and the macro for their rows of the variant table.
+#pragma once
+
+#include "variant.h"
+#include "gemm_any_device.h"
+
+namespace peak {
+
+template <class C>
+static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
+{
+    hipLaunchKernelGGL((gemm_any_kernel<C>), dim3(grid), dim3(C::NT), 0, (hipStream_t)stream, a);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+#define TILED_ANY(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, PF, EU)                               \
+    {NAME, KIND_TILED, DT, AKM, BKN, 0, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, 2,                \
+     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, PF, EU>::LDS_BYTES, 0,                  \
+     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, PF, EU>>, 0, 0, 0, 0, 0}
+
+#define TILED_ANY_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, PF, EU)                                 \
+    TILED_ANY(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
+    TILED_ANY(NAME "_nn", DT, 0, 1, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
+    TILED_ANY(NAME "_tt", DT, 1, 0, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
+    TILED_ANY(NAME "_tn", DT, 1, 1, BM, BN, WMW, WNW, WKW, RB, PF, EU)
+
+}  // namespace peak
