@@ -652,207 +652,203 @@ PEAK_DEV PartialOut splitk_out(const GemmArgs &p, int slice)
     return PartialOut{p.ws + (int64_t)slice * p.M * p.N, p.N, 0, 0};
 }
 
+// The way out of a wave's slabs with 16-byte stores of OES-byte elements: C in its storage type, an fp32 C of a 16-bit
+// kernel, or a split-K partial (which is an fp32 C with alpha 1, beta 0 and no fused step).  A lane holds the same
+// columns of every row group, so their bias is fetched once.  What a run of row groups adds from memory (C_in, the
+// per-row bias) is asked for before the run before it is stored, so that its way from memory overlaps a turnaround, and
+// every choice (beta, bias, activation) is made once per run, not once per row group: fp32 C with beta = 1, taken row group
+// by row group with a load and a wait in each, made bf16 4096x4096x2000 TN 88 us against 52 for a plain bf16 C.
+template <class C, int SLABS, int OES, class WriteSlab>
+PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, int wn, int64_t m0, int64_t n0, bool interior,
+                              const PartialOut &po, WriteSlab &&write_slab)
+{
+    constexpr int SROW = C::WTN * 4 + 16;
+    constexpr int EPL = 16 / OES;                                  // elements per lane and row
+    constexpr int LPR = C::WTN / EPL;                              // lanes per row
+    constexpr int RPI = 64 / LPR, G = 32 / RPI;                    // rows per store instruction, row groups per slab
+    static_assert(C::WTN % EPL == 0 && 64 % LPR == 0 && 32 % RPI == 0, "wave tile rows split into 16-byte pieces");
+    constexpr int ODT = OES == 4 ? DT_F32 : C::DT;
+    const int orow = lane / LPR, ocol = (lane % LPR) * EPL;
+    const bool partial = po.base != nullptr;
+    const float alpha = partial ? 1.0f : p.alpha, beta = partial ? 0.0f : p.beta;
+    const int act = partial ? ACT_NONE : p.hook.act, bias_kind = partial ? BIAS_NONE : p.hook.bias_kind;
+    const int64_t m_first = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
+    const int64_t ld = partial ? po.ld : p.ldc;
+    char *out = (partial ? (char *)po.base + ((m_first - po.m_org) * ld + (n - po.n_org)) * OES
+                         : (char *)p.C + (m_first * ld + n) * OES);
+    const int rows_left = interior ? 32 * SLABS : (int)(p.M - m_first < 32 * SLABS ? p.M - m_first : 32 * SLABS);
+    const int rows_ok = interior || n + EPL <= p.N ? rows_left : 0;     // rows of this lane's columns that C has
+    float bcol[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) bcol[e] = bias_kind == BIAS_PER_COLUMN && n + e < p.N ? p.hook.bias[n + e] : 0.0f;
+    // a slab's row groups go in runs of at most eight (what a run holds in registers: 8 x 16 bytes of C_in on their way,
+    // the values, their successors' C_in)
+    constexpr int GR = G < 8 ? G : 8, RUNS = G / GR;
+    u32x4 cin[GR];
+    float brow[GR];
+    auto fetch = [&](int run) {                                    // run: 32 rows x RUNS per slab, counted through
+        // (the choices are hidden from the compiler, which would otherwise write the rest of the epilogue out once for
+        // every combination of them)
+        int rows_c = beta != 0.0f ? rows_ok : 0, rows_b = bias_kind == BIAS_PER_ROW ? rows_left : 0;
+        asm volatile("" : "+v"(rows_c), "+v"(rows_b));
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            const int r = (run * GR + g) * RPI;
+            cin[g] = u32x4{0u, 0u, 0u, 0u};
+            if (r < rows_c) cin[g] = load_loose<u32x4, OES>(out + r * ld * OES);
+        }
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            const int r = (run * GR + g) * RPI;
+            brow[g] = 0.0f;
+            if (r < rows_b) brow[g] = p.hook.bias[m_first + r];
+        }
+    };
+    fetch(0);
+    write_slab(0, scr);
+#pragma unroll
+    for (int run = 0; run < SLABS * RUNS; ++run) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);             // one slab's accumulators out of the accumulation registers at a time
+        // A wave's LDS instructions execute in the order issued, so the next slab may be written into the same scratch
+        // as soon as this slab's last reads are issued.
+        float x[GR][EPL];
+#pragma unroll
+        for (int g = 0; g < GR; ++g)
+#pragma unroll
+            for (int h = 0; h < EPL / 4; ++h) {
+                const f32x4 t = *(const f32x4 *)(scr + ((run % RUNS * GR + g) * RPI + orow) * SROW + ocol * 4 + 16 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[g][4 * h + e] = t[e];
+            }
+        if (run % RUNS == RUNS - 1 && run + 1 < SLABS * RUNS) write_slab(run / RUNS + 1, scr);
+#pragma unroll
+        for (int g = 0; g < GR; ++g)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) x[g][e] *= alpha;
+        int kinds = __builtin_amdgcn_readfirstlane((beta != 0.0f ? 1 : 0) | (bias_kind != BIAS_NONE ? 2 : 0) | act << 2);
+        asm volatile("" : "+s"(kinds));
+        if (kinds & 1) {
+#pragma unroll
+            for (int g = 0; g < GR; ++g) {
+                union { u32x4 u; float f[4]; _Float16 h[8]; __bf16 b[8]; } c;
+                c.u = cin[g];
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) x[g][e] += beta * (ODT == DT_F32 ? c.f[e & 3] : ODT == DT_F16 ? (float)c.h[e] : (float)c.b[e]);
+            }
+        }
+        if (kinds & 2) {
+#pragma unroll
+            for (int g = 0; g < GR; ++g)
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) x[g][e] += bcol[e] + brow[g];      // (one of the two is zero)
+        }
+        if (kinds >> 2) {
+#pragma unroll
+            for (int g = 0; g < GR; ++g) hook_apply(kinds >> 2, false, x[g], x[g]);
+        }
+        if (run + 1 < SLABS * RUNS) fetch(run + 1);
+#pragma unroll
+        for (int g = 0; g < GR; ++g) {
+            const int r = (run * GR + g) * RPI;
+            union { u32x4 u; float f[4]; _Float16 h[8]; __bf16 b[8]; } o;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                if (ODT == DT_F32) o.f[e & 3] = x[g][e];
+                else if (ODT == DT_F16) o.h[e] = (_Float16)x[g][e];
+                else o.b[e] = (__bf16)x[g][e];
+            }
+            if (r < rows_ok) store_loose<u32x4, OES>(out + r * ld * OES, o.u);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 template <class C, int SLABS, class WriteSlab, class Write16>
 PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, int wm, int wn, int64_t m0, int64_t n0,
                              const PartialOut &po, WriteSlab &&write_slab, Write16 &&write16)
 {
-    float *wsl = po.base;
     const bool interior = m0 + C::BM <= p.M && n0 + C::BN <= p.N;      // whole tile inside C: no masks
     // Each wave turns its 32-row slabs around in LDS (fp32, padded rows) so that a
     // store instruction writes whole row segments of the wave tile (16 bytes per
-    // lane, WTN elements per row) instead of 32 scattered 8-byte pieces.  Interior
-    // tiles store vectors, whatever the alignment of C's rows; tiles on a ragged right edge and
-    // split-K partials leave through the same turnaround with masked stores, so the
+    // lane) instead of 32 scattered 8-byte pieces, whatever the alignment of C's rows; tiles on a
+    // ragged right edge leave through the same turnaround with masked stores, so the
     // accumulators have one way out and never wait in ordinary registers.
     constexpr int SROW = C::WTN * 4 + 16;                              // scratch row stride, bytes
     static_assert(32 * SROW * C::NW <= C::LDS_BYTES, "the staging buffers are large enough for the turnaround");
-    {
-        lds_barrier();                                                 // nobody still reads the last stage
-        char *scr = lds + wave * (32 * SROW);
-        constexpr int OUT_ROW = C::WTN * C::ESZ;                       // bytes of one output row of the wave tile
-        constexpr int LPR = OUT_ROW / 16;                              // lanes per row on the way out
-        constexpr int RPI = 64 / LPR;                                  // rows per store instruction
-        static_assert(OUT_ROW % 16 == 0 && 64 % LPR == 0 && 32 % RPI == 0, "wave tile rows split into 16-byte pieces");
-        const int orow = lane / LPR, ocol = (lane % LPR) * (16 / C::ESZ);   // row within the group, first column (elements)
-        // fused step: a lane stores the same columns of every row, so their bias is fetched once
-        const bool hooked = !wsl && hook_active(p.hook), has_bias = p.hook.bias_kind != BIAS_NONE;
-        const bool c_f32 = C::DT != DT_F32 && (p.flags & GF_C_F32);    // fp32 C of a 16-bit kernel: masked readout
-        constexpr int EPL = 16 / C::ESZ;                               // elements per lane and row
-        float bcol[EPL];
+    lds_barrier();                                                     // nobody still reads the last stage
+    char *scr = lds + wave * (32 * SROW);
+    const bool hooked = !po.base && hook_active(p.hook);
+    const bool c_f32 = C::DT != DT_F32 && (p.flags & GF_C_F32);        // fp32 C of a 16-bit kernel
+    // Plain runs of the 16-bit kernels on interior tiles (beta == 0, no fused step): the slab
+    // goes through LDS already scaled and rounded, 8 bytes per lane and 4-column group, which
+    // halves the LDS traffic of the turnaround; the way back is a 16-byte read and the store.
+    // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
+    // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
+    if constexpr (C::DT != DT_F32) {
+        if (interior && !po.base && !c_f32 && p.beta == 0.0f && !hooked) {
+            constexpr int LPR = C::WTN * 2 / 16, RPI = 64 / LPR;       // lanes per row, rows per store instruction
+            constexpr int SROW16 = C::WTN * 2 + 16;
+            constexpr int G = 32 / RPI;
+            const int orow = lane / LPR, ocol = (lane % LPR) * 8;
+            char *scr16 = lds + wave * (32 * SROW16);
+            write16(0, scr16);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) bcol[e] = 0.0f;
-        if (hooked && p.hook.bias_kind == BIAS_PER_COLUMN) {
-            const int64_t n = n0 + wn * C::WTN + ocol;
+            for (int mi = 0; mi < SLABS; ++mi) {
+                u32x4 v[G];
 #pragma unroll
-            for (int e = 0; e < EPL; ++e)
-                if (n + e < p.N) bcol[e] = p.hook.bias[n + e];
-        }
-        // Plain runs of the 16-bit kernels on interior tiles (beta == 0, no fused step): the slab
-        // goes through LDS already scaled and rounded, 8 bytes per lane and 4-column group, which
-        // halves the LDS traffic of the turnaround; the way back is a 16-byte read and the store.
-        // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
-        // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
-        if constexpr (C::DT != DT_F32) {
-            if (interior && !wsl && !c_f32 && p.beta == 0.0f && !hooked) {
-                constexpr int SROW16 = C::WTN * 2 + 16;
-                constexpr int G = 32 / RPI;
-                char *scr16 = lds + wave * (32 * SROW16);
-                write16(0, scr16);
+                for (int g = 0; g < G; ++g)
+                    v[g] = *(const u32x4 *)(scr16 + (g * RPI + orow) * SROW16 + ocol * 2);
+                if (mi + 1 < SLABS) write16(mi + 1, scr16);          // in-order LDS: lands after the reads above
 #pragma unroll
-                for (int mi = 0; mi < SLABS; ++mi) {
-                    u32x4 v[G];
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-                        v[g] = *(const u32x4 *)(scr16 + (g * RPI + orow) * SROW16 + ocol * 2);
-                    if (mi + 1 < SLABS) write16(mi + 1, scr16);      // in-order LDS: lands after the reads above
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
-                        const int64_t n = n0 + wn * C::WTN + ocol;
-                        const u32x4 o = (((g * RPI) >> 4) & 1) ? u32x4{v[g][2], v[g][3], v[g][0], v[g][1]} : v[g];
-                        store_loose<u32x4, 2>((uint16_t *)p.C + m * p.ldc + n, o);
-                    }
-                }
-                return;
-            }
-        }
-        // A wave's LDS instructions execute in the order issued, so the next slab may be
-        // written into the same scratch as soon as this slab's reads are issued: the writes
-        // then run while this slab is converted and stored.
-        write_slab(0, scr);
-#pragma unroll
-        for (int mi = 0; mi < SLABS; ++mi) {
-            float brow = 0.0f;                                         // per-row bias of slab row (lane % 32)
-            if (hooked && p.hook.bias_kind == BIAS_PER_ROW) {
-                const int64_t m = m0 + wm * C::WTM + mi * 32 + (lane & 31);
-                if (m < p.M) brow = p.hook.bias[m];
-            }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
-            // 16-byte stores need, on edge tiles, that no lane's column group straddles N (then a group is
-            // either stored whole or not at all)
-            const bool vec_ok = !wsl && !c_f32 && (interior || p.N % EPL == 0);
-            if (!vec_ok) {
-                // masked 4-element stores
-#pragma unroll 1
-                for (int g = 0; g < 32 / RPI; ++g) {
-                    const int row = g * RPI + orow;
-                    const int64_t m = m0 + wm * C::WTM + mi * 32 + row;
+                for (int g = 0; g < G; ++g) {
+                    const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
                     const int64_t n = n0 + wn * C::WTN + ocol;
-                    const char *src = scr + row * SROW + ocol * 4;
-                    const float br = __shfl(brow, row);                // (every lane takes part)
-                    if (m < p.M) {
-#pragma unroll
-                        for (int q = 0; q < 4 / C::ESZ; ++q) {         // 4 elements at a time
-                            const int64_t nn = n + q * 4, left = p.N - nn;
-                            if (left > 0) {
-                                const int nvalid = left >= 4 ? 4 : (int)left;
-                                const f32x4 t = *(const f32x4 *)(src + q * 16);
-                                const float x[4] = {t[0], t[1], t[2], t[3]};
-                                if (wsl) store4<DT_F32>(wsl, (m - po.m_org) * po.ld + (nn - po.n_org), x, 1.0f, 0.0f, nvalid);
-                                else {
-                                    const bool per_row = p.hook.bias_kind == BIAS_PER_ROW;
-                                    const float b[4] = {per_row ? br : bcol[q * 4 + 0], per_row ? br : bcol[q * 4 + 1],
-                                                        per_row ? br : bcol[q * 4 + 2], per_row ? br : bcol[q * 4 + 3]};
-                                    if (c_f32)
-                                        store4<DT_F32>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, nvalid,
-                                                       hooked, p.hook.act, has_bias, b);
-                                    else
-                                        store4<C::DT>(p.C, m * p.ldc + nn, x, p.alpha, p.beta, nvalid,
-                                                      hooked, p.hook.act, has_bias, b);
-                                }
-                            }
-                        }
-                    }
+                    const bool upper = RPI >= 32 ? orow >= 16 : RPI == 16 ? (g & 1) : ((g * RPI) >> 4) & 1;   // rows 16..31
+                    const u32x4 o = upper ? u32x4{v[g][2], v[g][3], v[g][0], v[g][1]} : v[g];
+                    store_loose<u32x4, 2>((uint16_t *)p.C + m * p.ldc + n, o);
                 }
-                if (mi + 1 < SLABS) write_slab(mi + 1, scr);
-            } else {
-                // All rows of the slab are fetched from LDS first, so that one LDS latency is
-                // paid per slab and not per row; PLAIN (interior, beta == 0, no fused step) is straight-line.
-                auto vector_readout = [&](auto plain_c) {
-                    constexpr bool PLAIN = decltype(plain_c)::value != 0;
-                    constexpr int G = 32 / RPI;
-                    // beta != 0: the slab's C_in is asked for first, all rows at once, so that its way
-                    // from memory overlaps the LDS turnaround instead of following it row by row
-                    u32x4 cin[G];
-                    const bool need_c = !PLAIN && p.beta != 0.0f;
-                    if (need_c) {
-#pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
-                            const int64_t n = n0 + wn * C::WTN + ocol;
-                            cin[g] = u32x4{0u, 0u, 0u, 0u};
-                            if (interior || (m < p.M && n + EPL <= p.N))
-                                cin[g] = load_loose<u32x4, C::ESZ>((const char *)p.C + (m * p.ldc + n) * C::ESZ);
-                        }
-                    }
-                    f32x4 lo[G], hi[G];
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const char *src = scr + (g * RPI + orow) * SROW + ocol * 4;
-                        lo[g] = *(const f32x4 *)src;
-                        if constexpr (C::DT != DT_F32) hi[g] = *(const f32x4 *)(src + 16);
-                    }
-                    // per-row bias of the rows this lane stores, handed round (every lane takes part)
-                    // before the next slab's writes queue up behind the shuffles
-                    float brs[G];
-                    const bool per_row = !PLAIN && hooked && p.hook.bias_kind == BIAS_PER_ROW;
-                    if (per_row) {
-#pragma unroll
-                        for (int g = 0; g < G; ++g) brs[g] = __shfl(brow, g * RPI + orow);
-                    }
-                    if (mi + 1 < SLABS) write_slab(mi + 1, scr);
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const int row = g * RPI + orow;
-                        const int64_t m = m0 + wm * C::WTM + mi * 32 + row;
-                        const int64_t n = n0 + wn * C::WTN + ocol;
-                        float b[EPL];                                  // this row's bias, if any
-                        if (!PLAIN && !interior && !(m < p.M && n + EPL <= p.N)) continue;
-                        if (!PLAIN && hooked) {
-#pragma unroll
-                            for (int e = 0; e < EPL; ++e) b[e] = per_row ? brs[g] : bcol[e];
-                        }
-                        if constexpr (C::DT == DT_F32) {
-                            f32x4 o = lo[g];
-                            o[0] *= p.alpha; o[1] *= p.alpha; o[2] *= p.alpha; o[3] *= p.alpha;
-                            float *dst = (float *)p.C + m * p.ldc + n;
-                            if (need_c) {
-                                const f32x4 c = __builtin_bit_cast(f32x4, cin[g]);
-                                o[0] += p.beta * c[0]; o[1] += p.beta * c[1]; o[2] += p.beta * c[2]; o[3] += p.beta * c[3];
-                            }
-                            if (!PLAIN && hooked) {
-                                float oh[4] = {o[0], o[1], o[2], o[3]};
-                                hook_apply(p.hook.act, has_bias, oh, b);
-                                o[0] = oh[0]; o[1] = oh[1]; o[2] = oh[2]; o[3] = oh[3];
-                            }
-                            store_loose<f32x4, 4>(dst, o);
-                        } else {
-                            float o[8] = {p.alpha * lo[g][0], p.alpha * lo[g][1], p.alpha * lo[g][2], p.alpha * lo[g][3],
-                                          p.alpha * hi[g][0], p.alpha * hi[g][1], p.alpha * hi[g][2], p.alpha * hi[g][3]};
-                            uint16_t *dst = (uint16_t *)p.C + m * p.ldc + n;
-                            union { u32x4 u; _Float16 h[8]; __bf16 b[8]; } pk;
-                            if (need_c) {
-                                pk.u = cin[g];
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) o[e] += p.beta * (C::DT == DT_F16 ? (float)pk.h[e] : (float)pk.b[e]);
-                            }
-                            if (!PLAIN && hooked) hook_apply(p.hook.act, has_bias, o, b);
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                if (C::DT == DT_F16) pk.h[e] = (_Float16)o[e];
-                                else pk.b[e] = (__bf16)o[e];
-                            }
-                            store_loose<u32x4, 2>(dst, pk.u);
-                        }
-                    }
-                };
-                if (p.beta == 0.0f && !hooked && interior) vector_readout(IC<1>{});
-                else vector_readout(IC<0>{});
             }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
+            return;
         }
+    }
+    // 16-byte stores need, on edge tiles, that no lane's column group straddles N (then a group is either stored whole
+    // or not at all)
+    const bool out32 = C::DT == DT_F32 || c_f32 || po.base;
+    if (interior || p.N % (out32 ? 4 : 8) == 0) {
+        if (out32) {
+            epilogue_vector<C, SLABS, 4>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+        } else if constexpr (C::DT != DT_F32) {
+            epilogue_vector<C, SLABS, 2>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+        }
+        return;
+    }
+    // ragged right edge: four columns per lane, masked
+    constexpr int LPR = C::WTN / 4, RPI = 64 / LPR;
+    const int orow = lane / LPR, ocol = (lane % LPR) * 4;
+    const int64_t n = n0 + wn * C::WTN + ocol, left = p.N - n;
+    const int nvalid = left >= 4 ? 4 : (int)left;
+    write_slab(0, scr);
+#pragma unroll
+    for (int mi = 0; mi < SLABS; ++mi) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+        for (int g = 0; g < 32 / RPI; ++g) {
+            const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
+            if (m < p.M && left > 0) {
+                const f32x4 t = *(const f32x4 *)(scr + (g * RPI + orow) * SROW + ocol * 4);
+                const float x[4] = {t[0], t[1], t[2], t[3]};
+                if (po.base) store4<DT_F32>(po.base, (m - po.m_org) * po.ld + (n - po.n_org), x, 1.0f, 0.0f, nvalid);
+                else if (out32) store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
+                else store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
+            }
+        }
+        asm volatile("" ::: "memory");
+        if (mi + 1 < SLABS) write_slab(mi + 1, scr);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 

@@ -1,0 +1,49 @@
+"""The tiled kernels' way out with 16-byte stores, through every tiled variant: rows and columns that end inside a slab
+of 32 rows and inside a tile, rows of C off 16 bytes, C_in, per-row and per-column bias with ReLU, an fp32 C of 16-bit
+operands and split-K partials.  Integer data: every result is exact, so a value taken from the wrong row, column or
+slab shows."""
+import itertools
+
+import numpy as np
+import pytest
+
+import peak_inputs as pi
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.F16, pi.BF16])
+@pytest.mark.parametrize("transA,transB", list(itertools.product([0, 1], [0, 1])))
+def test_vector_epilogue_exact(gu, oracle, dtype, transA, transB):
+    pg = gu.pg
+    K = 64
+    # (M, N, padding of C's rows, split, bias kind, fp32 C)
+    cases = [(296, 264, 0, None, pg.PEAK_BIAS_PER_ROW, False), (256, 512, 1, None, pg.PEAK_BIAS_PER_COLUMN, False),
+             (296, 328, 3, None, pg.PEAK_BIAS_PER_ROW, True), (264, 520, 0, 2, pg.PEAK_BIAS_PER_COLUMN, True)]
+    data = {}
+    for vid, name in gu.variants_for(dtype, transA, transB):
+        if "skinny" in name:
+            continue
+        for case, (M, N, pad, split, kind, c_f32) in enumerate(cases):
+            cdtype = pi.F32 if c_f32 else dtype
+            if case not in data:
+                A = pi.store(pi.small_int_matrix(70 + case, 0, M, K, -1, 1, dtype), bool(transA))
+                B = pi.store(pi.small_int_matrix(70 + case, 1, K, N, -1, 1, dtype), bool(transB))
+                C = pi.store(pi.small_int_matrix(70 + case, 2, M, N, -9, 9, cdtype), False, N + pad)
+                bias = (np.arange(M if kind == pg.PEAK_BIAS_PER_ROW else N) % 13 - 6).astype(np.float32)
+                ref = oracle.gemm(dtype, transA, transB, M, N, K, 1.0, A, B, 2.0, C, cdtype=cdtype)
+                data[case] = A, B, C, bias, oracle.bias_act(ref, M, kind, bias, pg.PEAK_ACT_RELU)
+            A, B, C, bias, ref = data[case]
+            got, raw, info = gu.run_gemm(dtype, transA, transB, M, N, K, 1.0, 2.0, A, B, C,
+                                         flags=pg.force_flags(vid, split), fused=(kind, bias, pg.PEAK_ACT_RELU),
+                                         cdtype=cdtype)
+            assert np.array_equal(got, ref), (name, case, info)
+            assert np.array_equal(raw[:, N:].view(np.uint8), C[:, N:].view(np.uint8)), (name, case)
