@@ -26,22 +26,22 @@ namespace peak {
 // WM x WN waves share the tile, WK waves each of its places (the rounds of a stage dealt out over them, their sums
 // added in LDS at the end, in wave order); RB: bytes of K per row and stage; PF: tiles that are on their way in
 // registers; EU: waves per SIMD that the register budget is cut for.
-template <int DT_, bool A_KM_, bool B_KN_, int BM_, int BN_, int WM_, int WN_, int WK_, int RB_, int PF_, int EU_>
+// RING: 0, or the number of LDS stages of the form that copies aligned operands to LDS directly (see the loop).
+template <int DT_, bool A_KM_, bool B_KN_, int BM_, int BN_, int WM_, int WN_, int WK_, int RB_, int PF_, int EU_, int RING_ = 0>
 struct CfgAny {
     static constexpr int DT = DT_;
     static constexpr bool A_KM = A_KM_, B_KN = B_KN_;
     static constexpr int ESZ = DT_ == DT_F32 ? 4 : 2, EPC = 16 / ESZ;
     static constexpr int BM = BM_, BN = BN_, RB = RB_, CPR = RB_ / 16, BK = RB_ / ESZ;
     static constexpr int WAVES_M = WM_, WAVES_N = WN_, WAVES_K = WK_;
-    static constexpr int NW = WM_ * WN_, NT = NW * WK_ * 64;
+    static constexpr int PLACES = WM_ * WN_, NW = PLACES * WK_, NT = NW * 64;
     static constexpr int WTM = BM / WM_, WTN = BN / WN_, MB = WTM / 16, NB = WTN / 16;
     static constexpr int KROUND = 4 * EPC;                  // k per round of fragment reads: 4 chunks of 16 bytes
     static constexpr int ROUNDS = BK / KROUND / WK_;        // per stage and wave
-    static constexpr int PF = PF_, EU = EU_;
+    static constexpr int PF = PF_, EU = EU_, RING = RING_, STAGES = RING_ ? RING_ : 2;
     static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
-    static constexpr int EPI_BYTES = 32 * (WTN * 4 + 16) * NW, RED_BYTES = NW * (WK_ - 1) * MB * NB * 1024;
-    static constexpr int LDS_BYTES = 2 * STAGE > EPI_BYTES ? (2 * STAGE > RED_BYTES ? 2 * STAGE : RED_BYTES)
-                                                           : (EPI_BYTES > RED_BYTES ? EPI_BYTES : RED_BYTES);
+    static constexpr int RED_BYTES = PLACES * (WK_ - 1) * MB * NB * 1024;
+    static constexpr int LDS_BYTES = STAGES * STAGE > RED_BYTES ? STAGES * STAGE : RED_BYTES;
     static_assert(RB_ == 128 || RB_ == 256, "swizzles below");
     static_assert(ROUNDS * WK_ * KROUND == BK && ROUNDS >= 1, "whole rounds per wave");
     static_assert(WTM % 32 == 0 && WTN % 16 == 0, "epilogue slabs of 32 rows");
@@ -72,6 +72,13 @@ struct CfgAny {
             if constexpr (ROWB >= 256) return k * ROWB + ((c ^ (4 * (k & 3)) ^ (2 * hi)) << 4);
             else return k * ROWB + ((c ^ (2 * ((k >> 1) & 1)) ^ (4 * hi)) << 4);
         }
+    }
+    // ... and the other way round: the k-row and chunk whose place is position `pos` of row `slot`
+    template <int X>
+    static __device__ __forceinline__ void kx_at(int slot, int pos, int &k, int &c)
+    {
+        k = DT_ == DT_F32 && X * ESZ < 256 ? (slot & ~5) | ((slot >> 2) & 1) | ((slot & 1) << 2) : slot;
+        c = pos ^ ((kx_offset<X>(k, 0) >> 4) & (X * ESZ / 16 - 1));
     }
     // fp32: offset of k-row k + e from k-row k, k a multiple of 4
     template <int X>
@@ -214,6 +221,43 @@ struct AnyX {
     }
 };
 
+// Direct copies of [k][x] rows for the ring form: a wave instruction fills 1024 contiguous LDS bytes, which chunk a
+// lane fetches makes the placement.  X a whole number of chunks; one at or past the matrix edge fetches the row's last.
+template <class C, int COLS>
+struct RingX {
+    static constexpr int ROWB = COLS * C::ESZ, CPX = ROWB / 16, PER_WAVE = C::BK * ROWB / 1024 / C::NW;
+    static_assert(C::BK * ROWB % (1024 * C::NW) == 0 && 64 % CPX == 0, "every wave issues the same number of loads");
+    __amdgpu_buffer_rsrc_t rsrc;
+    int voff[PER_WAVE], voff_tail[PER_WAVE], step;
+
+    PEAK_DEVM void init(const void *base, int64_t ld, int64_t x0, int64_t nx, int64_t k0, int64_t K, int tail_k, int wave, int lane)
+    {
+        const uint64_t panel = (uint64_t)((const char *)base + (k0 * ld + x0) * C::ESZ);
+        const int64_t bytes = ((K - k0 - 1) * ld + (nx - x0)) * C::ESZ;          // < 2^31, checked when the plan is made
+        const uint64_t panel_u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(panel >> 32)) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)panel);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)panel_u, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+        step = __builtin_amdgcn_readfirstlane((int)(C::BK * ld * C::ESZ));
+        const int last = (int)((nx - x0) / C::EPC) - 1;
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int at = (wave + C::NW * i) * 64 + lane;
+            int k, c;
+            C::template kx_at<COLS>(at / CPX, at % CPX, k, c);
+            if (c > last) c = last;
+            voff[i] = (int)((k * ld + (int64_t)c * C::EPC) * C::ESZ);
+            voff_tail[i] = k >= tail_k ? OOB_VOFFSET : voff[i];
+        }
+    }
+    PEAK_DEVM void issue(char *tile, int ktile, bool tail, int wave) const
+    {
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)(tile + (wave + C::NW * i) * 1024),
+                                                     16, tail ? voff_tail[i] : voff[i], ktile * step, 0, 0);
+    }
+};
+
 template <class C>
 __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p)
 {
@@ -221,7 +265,7 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
     __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave = wave_all % C::NW, kpar = wave_all / C::NW;
+    const int wave = wave_all % C::PLACES, kpar = wave_all / C::PLACES;
     const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
     const int r16 = lane & 15, q = lane >> 4;
 
@@ -295,93 +339,185 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         else return *(const u32x4 *)(st + b_k[r] + i * 16 * C::RB);
     };
 
-    AnyK<C, C::BM> kA;
-    AnyX<C, C::BM> xA;
-    AnyK<C, C::BN> kB;
-    AnyX<C, C::BN> xB;
-    if constexpr (C::A_KM) xA.init(p.A, p.lda, m0, p.M, p.K, tid);
-    else kA.init(p.A, p.lda, m0, p.M, p.K, tid);
-    if constexpr (C::B_KN) xB.init(p.B, p.ldb, n0, p.N, p.K, tid);
-    else kB.init(p.B, p.ldb, n0, p.N, p.K, tid);
-    constexpr int CA = AnyK<C, C::BM>::NCH, CB = AnyK<C, C::BN>::NCH;
-    u32x4 va[C::PF][CA], vb[C::PF][CB];
-    auto load = [&](int kt, u32x4 (&a)[CA], u32x4 (&b)[CB]) {   // kt relative to the slice
-        const int64_t k0 = kbase + (int64_t)kt * C::BK;
-        if constexpr (C::A_KM) xA.load(a, k0, tid);
-        else kA.load(a, k0, tid);
-        if constexpr (C::B_KN) xB.load(b, k0, tid);
-        else kB.load(b, k0, tid);
-    };
-    auto store = [&](int kt, int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
-        char *st = lds + stage * C::STAGE;
-        const int64_t k0 = kbase + (int64_t)kt * C::BK;
-        if constexpr (C::A_KM) xA.store(st, a, k0, tid);
-        else kA.store(st, a, k0, tid);
-        if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, k0, tid);
-        else kB.store(st + C::A_BYTES, b, k0, tid);
+    auto multiply = [&](const u32x4 (&af)[C::MB], const u32x4 (&bf)[C::NB]) {
+                            // (B's rows feed the instruction's row operand: a lane ends with 4 consecutive n of one m)
+                            if constexpr (C::DT == DT_F32) {
+        #pragma unroll
+                                for (int e = 0; e < 4; ++e)
+        #pragma unroll
+                                    for (int nb = 0; nb < C::NB; ++nb)
+        #pragma unroll
+                                        for (int mb = 0; mb < C::MB; ++mb) {
+                                            const f32x4 b = __builtin_bit_cast(f32x4, bf[nb]), a = __builtin_bit_cast(f32x4, af[mb]);
+                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
+                                        }
+                            } else {
+        #pragma unroll
+                                for (int nb = 0; nb < C::NB; ++nb)
+        #pragma unroll
+                                    for (int mb = 0; mb < C::MB; ++mb) {
+                                        if constexpr (C::DT == DT_BF16)
+                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf[nb]),
+                                                                                                  __builtin_bit_cast(bf16x8, af[mb]), acc[mb][nb], 0, 0, 0);
+                                        else
+                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, bf[nb]),
+                                                                                                 __builtin_bit_cast(f16x8, af[mb]), acc[mb][nb], 0, 0, 0);
+                                    }
+                            }
     };
 
-    // One barrier per tile: while tile kt is multiplied out of one stage, tile kt + 1 goes from registers into the
-    // other (everybody left it at the last barrier) and the loads of tile kt + 1 + PF go out.
-    static_for<C::PF>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-        if (t < KT) load(t, va[t], vb[t]);
-    });
-    store(0, 0, va[0], vb[0]);
-    if (C::PF < KT) load(C::PF, va[0], vb[0]);
-    lds_barrier();
-    constexpr int U = C::PF % 2 == 0 ? C::PF : 2 * C::PF;   // tiles per trip: stage and register set static
-    for (int kt0 = 0; kt0 < KT; kt0 += U) {
-        static_for<U>([&](auto uc) {
-            constexpr int u = decltype(uc)::value, s = u % 2, set = (u + 1) % C::PF;
-            const int kt = kt0 + u;
-            if (kt < KT) {
-                const char *st = lds + s * C::STAGE;
-                u32x4 af[2][C::MB], bf[2][C::NB];
-#pragma unroll
-                for (int i = 0; i < C::NB; ++i) bf[0][i] = frag_b(st, i, 0);
-#pragma unroll
-                for (int i = 0; i < C::MB; ++i) af[0][i] = frag_a(st, i, 0);
-                __builtin_amdgcn_sched_barrier(0);          // (the compiler would sink the reads to their first use)
-                if (kt + 1 < KT) store(kt + 1, 1 - s, va[set], vb[set]);
-                if (kt + 1 + C::PF < KT) load(kt + 1 + C::PF, va[set], vb[set]);
-                static_for<C::ROUNDS>([&](auto rc) {
-                    constexpr int r = decltype(rc)::value, cur = r & 1, nxt = cur ^ 1;
-                    if constexpr (r + 1 < C::ROUNDS) {
-#pragma unroll
-                        for (int i = 0; i < C::NB; ++i) bf[nxt][i] = frag_b(st, i, r + 1);
-#pragma unroll
-                        for (int i = 0; i < C::MB; ++i) af[nxt][i] = frag_a(st, i, r + 1);
-                        __builtin_amdgcn_sched_barrier(0);
+    // Ring form: direct copies, RING - 1 K tiles ahead.  For small tiles the loads' latency is the cost (a 64 x 64 x 64
+    // tile's MFMAs take 128 cycles, a trip to the L2 some 500 and to memory over 1500), so most of the CU's LDS holds
+    // tiles on their way.
+    if constexpr (C::RING > 0) {
+        LoaderDirect<C, C::BM> dA;
+        LoaderDirect<C, C::BN> dB;
+        RingX<C, C::BM> nA;
+        RingX<C, C::BN> nB;
+        constexpr int L = (C::A_BYTES + C::B_BYTES) / 1024 / C::NW;      // loads per wave and tile
+        static_assert(C::A_BYTES % (1024 * C::NW) == 0 && C::B_BYTES % (1024 * C::NW) == 0, "every wave issues the same number of loads");
+        constexpr int P = C::RING - 1;
+        static_assert((P - 1) * L < 64, "fits the wait's counter");
+        const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
+        const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
+        if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
+        else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
+        if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
+        else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
+        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
+        auto issue = [&](int kt, int stage) {
+            int kr = (kt < KT ? kt : KT - 1) + rot;         // past the end: the last tile again, into a free stage
+            if (kr >= KT) kr -= KT;
+            char *st = lds + stage * C::STAGE;
+            const bool tail = kr == tail_tile;
+            if constexpr (C::A_KM) nA.issue(st, kr, tail, wave_all);
+            else dA.template issue<0, 1>(st, kr, tail, wave_all);
+            if constexpr (C::B_KN) nB.issue(st + C::A_BYTES, kr, tail, wave_all);
+            else dB.template issue<0, 1>(st + C::A_BYTES, kr, tail, wave_all);
+        };
+        // (the compiler would put a wait for every direct copy in front of a transposing read: assembly, handed over
+        // after a wait for everything asked of LDS)
+        const uint32_t lds_b0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+        auto tr_read = [&](int addr, auto offc, u32x2 &lo, u32x2 &hi, auto rowbc) {
+            constexpr int off = decltype(offc)::value, rowb = decltype(rowbc)::value;
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(addr), "n"(off) : "memory");
+            asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(off + 4 * rowb) : "memory");
+        };
+        static_for<P>([&](auto tc) { issue(decltype(tc)::value, decltype(tc)::value); });
+        for (int kt0 = 0; kt0 < KT; kt0 += C::RING) {
+            static_for<C::RING>([&](auto sc) {
+                constexpr int s = decltype(sc)::value;
+                const int kt = kt0 + s;
+                if (kt < KT) {
+                    wait_vmcnt<(P - 1) * L>();              // own copies of tile kt
+                    lds_barrier();                          // everybody's; nobody reads the stage before this one any more
+                    issue(kt + P, (s + P) % C::RING);
+                    const char *st = lds + s * C::STAGE;
+                    u32x4 af[C::ROUNDS][C::MB], bf[C::ROUNDS][C::NB];
+                    u32x2 al[C::ROUNDS][C::MB], ah[C::ROUNDS][C::MB], bl[C::ROUNDS][C::NB], bh[C::ROUNDS][C::NB];
+                    constexpr bool TRA = C::A_KM && C::DT != DT_F32, TRB = C::B_KN && C::DT != DT_F32;
+                    static_for<C::ROUNDS>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value;
+                        static_for<C::NB>([&](auto ic) {
+                            constexpr int i = decltype(ic)::value;
+                            if constexpr (TRB) tr_read(lds_b0 + s * C::STAGE + b_x[i], IC<r * C::WAVES_K * C::KROUND * C::BN * C::ESZ>{}, bl[r][i], bh[r][i], IC<C::BN * C::ESZ>{});
+                            else bf[r][i] = frag_b(st, i, r);
+                        });
+                        static_for<C::MB>([&](auto ic) {
+                            constexpr int i = decltype(ic)::value;
+                            if constexpr (TRA) tr_read(lds_b0 + s * C::STAGE + a_x[i], IC<r * C::WAVES_K * C::KROUND * C::BM * C::ESZ>{}, al[r][i], ah[r][i], IC<C::BM * C::ESZ>{});
+                            else af[r][i] = frag_a(st, i, r);
+                        });
+                    });
+                    if constexpr (TRA || TRB) {
+                        __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+                        static_for<C::ROUNDS>([&](auto rc) {
+                            constexpr int r = decltype(rc)::value;
+                            if constexpr (TRB) static_for<C::NB>([&](auto ic) {
+                                u32x2 &lo = bl[r][decltype(ic)::value], &hi = bh[r][decltype(ic)::value];
+                                asm volatile("" : "+v"(lo), "+v"(hi));
+                                bf[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                            });
+                            if constexpr (TRA) static_for<C::MB>([&](auto ic) {
+                                u32x2 &lo = al[r][decltype(ic)::value], &hi = ah[r][decltype(ic)::value];
+                                asm volatile("" : "+v"(lo), "+v"(hi));
+                                af[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                            });
+                        });
                     }
-                    // (B's rows feed the instruction's row operand: a lane ends with 4 consecutive n of one m)
-                    if constexpr (C::DT == DT_F32) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-#pragma unroll
-                            for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                                for (int mb = 0; mb < C::MB; ++mb) {
-                                    const f32x4 b = __builtin_bit_cast(f32x4, bf[cur][nb]), a = __builtin_bit_cast(f32x4, af[cur][mb]);
-                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
-                                }
-                    } else {
-#pragma unroll
-                        for (int nb = 0; nb < C::NB; ++nb)
-#pragma unroll
-                            for (int mb = 0; mb < C::MB; ++mb) {
-                                if constexpr (C::DT == DT_BF16)
-                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf[cur][nb]),
-                                                                                          __builtin_bit_cast(bf16x8, af[cur][mb]), acc[mb][nb], 0, 0, 0);
-                                else
-                                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, bf[cur][nb]),
-                                                                                         __builtin_bit_cast(f16x8, af[cur][mb]), acc[mb][nb], 0, 0, 0);
-                            }
-                    }
-                });
-                lds_barrier();                              // (loads stay under way across it)
-            }
+                    __builtin_amdgcn_sched_barrier(0);
+                    static_for<C::ROUNDS>([&](auto rc) { multiply(af[decltype(rc)::value], bf[decltype(rc)::value]); });
+                }
+            });
+        }
+        wait_vmcnt<0>();    // copies past the end must land before this workgroup's LDS is given away
+        if constexpr (C::WAVES_K > 1) lds_barrier();        // everybody's, before the sums over waves go through LDS
+    } else {
+        AnyK<C, C::BM> kA;
+        AnyX<C, C::BM> xA;
+        AnyK<C, C::BN> kB;
+        AnyX<C, C::BN> xB;
+        if constexpr (C::A_KM) xA.init(p.A, p.lda, m0, p.M, p.K, tid);
+        else kA.init(p.A, p.lda, m0, p.M, p.K, tid);
+        if constexpr (C::B_KN) xB.init(p.B, p.ldb, n0, p.N, p.K, tid);
+        else kB.init(p.B, p.ldb, n0, p.N, p.K, tid);
+        constexpr int CA = AnyK<C, C::BM>::NCH, CB = AnyK<C, C::BN>::NCH;
+        u32x4 va[C::PF][CA], vb[C::PF][CB];
+        auto load = [&](int kt, u32x4 (&a)[CA], u32x4 (&b)[CB]) {   // kt relative to the slice
+            const int64_t k0 = kbase + (int64_t)kt * C::BK;
+            if constexpr (C::A_KM) xA.load(a, k0, tid);
+            else kA.load(a, k0, tid);
+            if constexpr (C::B_KN) xB.load(b, k0, tid);
+            else kB.load(b, k0, tid);
+        };
+        auto store = [&](int kt, int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
+            char *st = lds + stage * C::STAGE;
+            const int64_t k0 = kbase + (int64_t)kt * C::BK;
+            if constexpr (C::A_KM) xA.store(st, a, k0, tid);
+            else kA.store(st, a, k0, tid);
+            if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, k0, tid);
+            else kB.store(st + C::A_BYTES, b, k0, tid);
+        };
+
+        // One barrier per tile: while tile kt is multiplied out of one stage, tile kt + 1 goes from registers into the
+        // other (everybody left it at the last barrier) and the loads of tile kt + 1 + PF go out.
+        static_for<C::PF>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if (t < KT) load(t, va[t], vb[t]);
         });
+        store(0, 0, va[0], vb[0]);
+        if (C::PF < KT) load(C::PF, va[0], vb[0]);
+        lds_barrier();
+        constexpr int U = C::PF % 2 == 0 ? C::PF : 2 * C::PF;   // tiles per trip: stage and register set static
+        for (int kt0 = 0; kt0 < KT; kt0 += U) {
+            static_for<U>([&](auto uc) {
+                constexpr int u = decltype(uc)::value, s = u % 2, set = (u + 1) % C::PF;
+                const int kt = kt0 + u;
+                if (kt < KT) {
+                    const char *st = lds + s * C::STAGE;
+                    u32x4 af[2][C::MB], bf[2][C::NB];
+    #pragma unroll
+                    for (int i = 0; i < C::NB; ++i) bf[0][i] = frag_b(st, i, 0);
+    #pragma unroll
+                    for (int i = 0; i < C::MB; ++i) af[0][i] = frag_a(st, i, 0);
+                    __builtin_amdgcn_sched_barrier(0);          // (the compiler would sink the reads to their first use)
+                    if (kt + 1 < KT) store(kt + 1, 1 - s, va[set], vb[set]);
+                    if (kt + 1 + C::PF < KT) load(kt + 1 + C::PF, va[set], vb[set]);
+                    static_for<C::ROUNDS>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value, cur = r & 1, nxt = cur ^ 1;
+                        if constexpr (r + 1 < C::ROUNDS) {
+    #pragma unroll
+                            for (int i = 0; i < C::NB; ++i) bf[nxt][i] = frag_b(st, i, r + 1);
+    #pragma unroll
+                            for (int i = 0; i < C::MB; ++i) af[nxt][i] = frag_a(st, i, r + 1);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        multiply(af[cur], bf[cur]);
+                    });
+                    lds_barrier();                              // (loads stay under way across it)
+                }
+            });
+        }
     }
 
     if constexpr (C::WAVES_K > 1) {
@@ -390,7 +526,7 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
 #pragma unroll
             for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < C::NB; ++nb) red[((kpar - 1) * C::NW + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64] = acc[mb][nb];
+                for (int nb = 0; nb < C::NB; ++nb) red[((kpar - 1) * C::PLACES + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64] = acc[mb][nb];
         }
         lds_barrier();
         if (kpar > 0) return;
@@ -399,7 +535,7 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
 #pragma unroll
             for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] += red[(k * C::NW + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64];
+                for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] += red[(k * C::PLACES + wave) * (C::MB * C::NB * 64) + (mb * C::NB + nb) * 64];
     }
 
     // acc[mb][nb][v] <-> m = 16 mb + lane % 16, n = 16 nb + 4 (lane / 16) + v; slab s = blocks 2 s and 2 s + 1

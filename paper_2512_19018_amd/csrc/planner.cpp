@@ -93,6 +93,11 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
 // bf16 4095^3 (saturated) 0.26 with 128x128 tiles, 0.19 with 128x64, 0.14 with 64x64; 1023x2047x3001 0.13, 0.11 and
 // (two workgroups of eight waves) 0.13 with one to two workgroups per CU.  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
 // 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.43, with four 0.52.
+// (Measured in microseconds.  tiled_cost's units are rates of full rounds under the power limit: about 2.7e6 of them
+// to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4e6 in fp32.)
+static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.0e6 : 2.7e6); }
+constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-adds per CU at the full rate
+
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
@@ -108,7 +113,28 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     const double full = (double)(per_cu / fit) * fit * work / eff;
     const int64_t rest = per_cu % fit;
     const double part = rest ? (double)rest * work / (eff * (fit > 1 ? one + (1.0 - one) * (double)(rest - 1) / (fit - 1) : 1.0)) : 0.0;
-    return full + part + 12.0e6 * (double)cdiv(per_cu, fit) + reduce_cost(d, split);
+    return units_of_us(v, (full + part + reduce_cost(d, split)) / MFMA_PER_US + 2.5 * (double)cdiv(per_cu, fit));
+}
+
+// The ring kernels: small tiles, bound by the way into the LDS (16 bits) or by the MFMAs (fp32).  16 bits, bytes per ns
+// and CU, however many workgroups share it: 72 with 64 k per stage (bf16 300x3072x2048, 240 tiles of 64x64: 9.6 us;
+// f16 2048x1024x4096 TN, 256 tiles of 128x64 25.6, 512 of 64x64 31.9) and 85 with 128 (100x4096x4096, 256 tiles of
+// 32x64: 11.4 us).  fp32, share of the MFMA rate alone and with several
+// workgroups: 64x64 0.72 and 0.81 (1024^3 22.2 us, 2048^3 139), 64x32 0.60 and 0.70, 32x32 0.52 and 0.63 (512^3 6.7 us).
+static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
+{
+    const int64_t per_cu = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
+    const double ktiles = (double)per_cu * (double)cdiv(cdiv(d.K, v.bk), split);
+    double us;
+    if (v.dt == PEAK_DT_F32) {
+        const double alone = v.bm * v.bn >= 64 * 64 ? 0.72 : v.bm * v.bn >= 64 * 32 ? 0.60 : 0.52;
+        us = ktiles * v.bm * v.bn * v.bk * 16.0 / MFMA_PER_US / (per_cu > 1 ? alone + 0.1 : alone);
+    } else {
+        us = ktiles * (v.bm + v.bn) * v.bk * 2.0 / 1000.0 / (v.bk >= 128 ? 85.0 : 72.0);
+    }
+    // (a K split costs these short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 tiles 13.3 us in two
+    // slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads)
+    return units_of_us(v, us + 2.5 + (split > 1 ? 2.0 + reduce_cost(d, split) / MFMA_PER_US : 0.0));
 }
 
 // Estimated time of a tiled variant, in units of "one 32x32xBK-row MFMA group":
@@ -117,6 +143,7 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
 static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     if (!v.direct) return staged_cost(v, d, split);
+    if (v.ring) return ring_cost(v, d, split);
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
     const int64_t rounds = cdiv(tiles, num_cu());
     const double ktiles = (double)cdiv(cdiv(d.K, v.bk), split);
@@ -278,6 +305,16 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     }
 }
 
+// A streaming kernel wins wherever one applies, but for an A taller than 32 rows against a small streamed operand: the
+// K split that then fills the chip costs more than the rows the ring kernels read twice (bf16 64x4096x8192 NT, 67 MB,
+// 16.8 us against 18.1 at best; f16 64x8192x2048 8.0 against 11.6; 64x8192x8192, 134 MB, 35.3 against 33.1).
+static bool streams(const Variant &v, const peak_gemm_desc_t &d)
+{
+    const int64_t bytes = d.N * d.K * esize_of(d.dtype);
+    if (stages_a(v, d.transA)) return bytes >= (int64_t)8 << 20;    // the transposition of A is one more launch
+    return d.M <= 32 || d.dtype == PEAK_DT_F32 || bytes > (int64_t)72 << 20;
+}
+
 // The selector's own choice among the variants that fit (cost model); with
 // `staged_only`, among those that take any operand alignment.
 static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
@@ -289,7 +326,7 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     for (int i = 0; i < NUM_VARIANTS; ++i) {
         const Variant &v = g_variants[i];
         if (v.kind == KIND_TILED || v.sweep_only || (staged_only && v.direct) || !variant_fits(v, d)) continue;
-        if (stages_a(v, d.transA) && d.N * d.K * esize_of(d.dtype) < ((int64_t)8 << 20)) continue;
+        if (!streams(v, d)) continue;
         if (stream_bm == 0 || v.bm < stream_bm) stream_bm = v.bm;
     }
     for (int i = 0; i < NUM_VARIANTS; ++i) {
@@ -297,12 +334,13 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
         if (v.sweep_only || (staged_only && v.direct) || !variant_fits(v, d)) continue;
         if (v.kind != KIND_TILED) {
             if (v.bm != stream_bm) continue;
-            // the transposition of A is one more launch: worth it once the streamed operand has some MB
-            if (stages_a(v, d.transA) && d.N * d.K * esize_of(d.dtype) < ((int64_t)8 << 20)) continue;
+            if (!streams(v, d)) continue;
             // rank 3 only where one workgroup per tile of its (larger) BN fills four fifths of the chip, or where
             // the M x K operand is tall enough for its re-reads to matter (every workgroup reads its K slice of
             // all of it: bf16 64x8192x28672 takes 101.9 us with 128 rows per workgroup, 126.4 us with 64)
-            if (v.stream_rank == 3 && v.bm < 64 && cdiv(d.N, v.bn) * 5 < (int64_t)num_cu() * 4) continue;
+            // (but not where tiles of half the columns fill it without a K split: 64x16384x8192 50.1 us against 56.9)
+            const int64_t fill = (int64_t)num_cu() * 4;
+            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || cdiv(d.N, v.bn / 2) * 5 >= fill)) continue;
             if (stream[v.stream_rank] < 0) stream[v.stream_rank] = i;
             continue;
         }

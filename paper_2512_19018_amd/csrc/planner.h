@@ -33,6 +33,7 @@ struct Variant {
     int stream_rank;     // streaming (skinny) kernels: 3 = taken when its workgroups fill the chip without a K split,
                          // 2 = the usual choice, 1 = the fallback for other K, 0 = sweeps only
     int mf16;            // built on the 16x16x32 MFMA (holds a higher clock under the chip's power limit)
+    int ring;            // small tile with most of the LDS as a ring of K tiles on their way (`ns` stages)
 };
 
 struct VariantGroup {

@@ -25,6 +25,9 @@ VariantGroup variants_mf16s();
 VariantGroup variants_mf16d();
 VariantGroup variants_mf16r();
 VariantGroup variants_mf16k();
+VariantGroup variants_ring_bf16();
+VariantGroup variants_ring_f16();
+VariantGroup variants_ring_f32();
 VariantGroup variants_any_bf16();
 VariantGroup variants_any_f16();
 VariantGroup variants_any_f32();

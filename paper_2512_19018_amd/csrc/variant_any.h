@@ -24,4 +24,17 @@ static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
     TILED_ANY(NAME "_tt", DT, 1, 0, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
     TILED_ANY(NAME "_tn", DT, 1, 1, BM, BN, WMW, WNW, WKW, RB, PF, EU)
 
+// aligned operands straight to LDS, STAGES K tiles in a ring
+#define TILED_RING(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                          \
+    {NAME, KIND_TILED, DT, AKM, BKN, 1, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, STAGES,         \
+     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, 1, EU, STAGES>::LDS_BYTES, 0,           \
+     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, 1, EU, STAGES>>,       \
+     BKN, AKM, 0, 0, 0, 1}
+
+#define TILED_RING_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                            \
+    TILED_RING(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                           \
+    TILED_RING(NAME "_nn", DT, 0, 1, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                           \
+    TILED_RING(NAME "_tt", DT, 1, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                           \
+    TILED_RING(NAME "_tn", DT, 1, 1, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)
+
 }  // namespace peak
