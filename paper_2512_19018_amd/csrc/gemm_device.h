@@ -658,7 +658,10 @@ PEAK_DEV PartialOut splitk_out(const GemmArgs &p, int slice)
 // per-row bias) is asked for before the run before it is stored, so that its way from memory overlaps a turnaround, and
 // every choice (beta, bias, activation) is made once per run, not once per row group: fp32 C with beta = 1, taken row group
 // by row group with a load and a wait in each, made bf16 4096x4096x2000 TN 88 us against 52 for a plain bf16 C.
-template <class C, int SLABS, int OES, class WriteSlab>
+// RAGGED: C ends inside a lane's columns.  That lane takes the last EPL columns instead, some of them a second time (the
+// same values, from the same wave's scratch): masked loops on the tiles of the right edge, which all others wait for,
+// cost bf16 4095^3 40 us of 167.
+template <class C, int SLABS, int OES, bool RAGGED, class WriteSlab>
 PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, int wn, int64_t m0, int64_t n0, bool interior,
                               const PartialOut &po, WriteSlab &&write_slab)
 {
@@ -668,7 +671,12 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
     constexpr int RPI = 64 / LPR, G = 32 / RPI;                    // rows per store instruction, row groups per slab
     static_assert(C::WTN % EPL == 0 && 64 % LPR == 0 && 32 % RPI == 0, "wave tile rows split into 16-byte pieces");
     constexpr int ODT = OES == 4 ? DT_F32 : C::DT;
-    const int orow = lane / LPR, ocol = (lane % LPR) * EPL;
+    const int orow = lane / LPR;
+    int ocol = (lane % LPR) * EPL;
+    if constexpr (RAGGED) {
+        const int64_t left = p.N - (n0 + wn * C::WTN);             // columns of the wave tile that C has, EPL at least
+        if (ocol < left && ocol + EPL > left) ocol = (int)left - EPL;
+    }
     const bool partial = po.base != nullptr;
     const float alpha = partial ? 1.0f : p.alpha, beta = partial ? 0.0f : p.beta;
     const int act = partial ? ACT_NONE : p.hook.act, bias_kind = partial ? BIAS_NONE : p.hook.bias_kind;
@@ -717,7 +725,8 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
         for (int g = 0; g < GR; ++g)
 #pragma unroll
             for (int h = 0; h < EPL / 4; ++h) {
-                const f32x4 t = *(const f32x4 *)(scr + ((run % RUNS * GR + g) * RPI + orow) * SROW + ocol * 4 + 16 * h);
+                const char *src = scr + ((run % RUNS * GR + g) * RPI + orow) * SROW + ocol * 4 + 16 * h;
+                const f32x4 t = RAGGED ? load_loose<f32x4, 4>(src) : *(const f32x4 *)src;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[g][4 * h + e] = t[e];
             }
@@ -772,8 +781,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     const bool interior = m0 + C::BM <= p.M && n0 + C::BN <= p.N;      // whole tile inside C: no masks
     // Each wave turns its 32-row slabs around in LDS (fp32, padded rows) so that a
     // store instruction writes whole row segments of the wave tile (16 bytes per
-    // lane) instead of 32 scattered 8-byte pieces, whatever the alignment of C's rows; tiles on a
-    // ragged right edge leave through the same turnaround with masked stores, so the
+    // lane) instead of 32 scattered 8-byte pieces, whatever the alignment of C's rows, so the
     // accumulators have one way out and never wait in ordinary registers.
     constexpr int SROW = C::WTN * 4 + 16;                              // scratch row stride, bytes
     static_assert(32 * SROW * C::NW <= C::LDS_BYTES, "the staging buffers are large enough for the turnaround");
@@ -813,42 +821,44 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             return;
         }
     }
-    // 16-byte stores need, on edge tiles, that no lane's column group straddles N (then a group is either stored whole
-    // or not at all)
     const bool out32 = C::DT == DT_F32 || c_f32 || po.base;
-    if (interior || p.N % (out32 ? 4 : 8) == 0) {
+    const int epl = out32 ? 4 : 8;
+    const int64_t left = p.N - (n0 + wn * C::WTN);                     // columns of C in the wave tile and beyond
+    if (interior || p.N % epl == 0) {
         if (out32) {
-            epilogue_vector<C, SLABS, 4>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+            epilogue_vector<C, SLABS, 4, false>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
         } else if constexpr (C::DT != DT_F32) {
-            epilogue_vector<C, SLABS, 2>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+            epilogue_vector<C, SLABS, 2, false>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
         }
-        return;
-    }
-    // ragged right edge: four columns per lane, masked
-    constexpr int LPR = C::WTN / 4, RPI = 64 / LPR;
-    const int orow = lane / LPR, ocol = (lane % LPR) * 4;
-    const int64_t n = n0 + wn * C::WTN + ocol, left = p.N - n;
-    const int nvalid = left >= 4 ? 4 : (int)left;
-    write_slab(0, scr);
+    } else if (left >= epl) {
+        if (out32) {
+            epilogue_vector<C, SLABS, 4, true>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+        } else if constexpr (C::DT != DT_F32) {
+            epilogue_vector<C, SLABS, 2, true>(p, scr, lane, wm, wn, m0, n0, interior, po, write_slab);
+        }
+    } else if (left > 0) {
+        // fewer columns than a lane stores: one row and every other of the columns per lane
+        write_slab(0, scr);
 #pragma unroll
-    for (int mi = 0; mi < SLABS; ++mi) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
+        for (int mi = 0; mi < SLABS; ++mi) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            const int64_t m = m0 + wm * C::WTM + mi * 32 + (lane & 31);
 #pragma unroll 1
-        for (int g = 0; g < 32 / RPI; ++g) {
-            const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
-            if (m < p.M && left > 0) {
-                const f32x4 t = *(const f32x4 *)(scr + (g * RPI + orow) * SROW + ocol * 4);
-                const float x[4] = {t[0], t[1], t[2], t[3]};
-                if (po.base) store4<DT_F32>(po.base, (m - po.m_org) * po.ld + (n - po.n_org), x, 1.0f, 0.0f, nvalid);
-                else if (out32) store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
-                else store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, nvalid, p.hook, m, n);
+            for (int c = lane >> 5; c < left; c += 2) {
+                const int64_t n = n0 + wn * C::WTN + c;
+                const float x[4] = {*(const float *)(scr + (lane & 31) * SROW + c * 4), 0.0f, 0.0f, 0.0f};
+                if (m < p.M) {
+                    if (po.base) store4<DT_F32>(po.base, (m - po.m_org) * po.ld + (n - po.n_org), x, 1.0f, 0.0f, 1);
+                    else if (out32) store4<DT_F32>(p.C, m * p.ldc + n, x, p.alpha, p.beta, 1, p.hook, m, n);
+                    else store4<C::DT>(p.C, m * p.ldc + n, x, p.alpha, p.beta, 1, p.hook, m, n);
+                }
             }
+            asm volatile("" ::: "memory");
+            if (mi + 1 < SLABS) write_slab(mi + 1, scr);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
         }
-        asm volatile("" ::: "memory");
-        if (mi + 1 < SLABS) write_slab(mi + 1, scr);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
     }
 }
 

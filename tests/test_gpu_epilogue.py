@@ -47,3 +47,36 @@ def test_vector_epilogue_exact(gu, oracle, dtype, transA, transB):
                                          cdtype=cdtype)
             assert np.array_equal(got, ref), (name, case, info)
             assert np.array_equal(raw[:, N:].view(np.uint8), C[:, N:].view(np.uint8)), (name, case)
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.F16, pi.BF16])
+@pytest.mark.parametrize("transA,transB", list(itertools.product([0, 1], [0, 1])))
+def test_ragged_right_edge_exact(gu, oracle, dtype, transA, transB):
+    """N that ends one to seven columns into a lane's piece, a wave tile or a tile: the last lane's overlapping store,
+    and the columns that are fewer than a lane stores."""
+    pg = gu.pg
+    K = 64
+    data = {}
+    for vid, name in gu.variants_for(dtype, transA, transB):
+        if "skinny" in name:
+            continue
+        for case, (M, N, split, c_f32) in enumerate([(72, 257, None, False), (40, 391, None, False), (264, 331, None, True),
+                                                     (72, 133, 2, False), (33, 66, None, False)]):
+            cdtype = pi.F32 if c_f32 else dtype
+            if case not in data:
+                A = pi.store(pi.small_int_matrix(80 + case, 0, M, K, -1, 1, dtype), bool(transA))
+                B = pi.store(pi.small_int_matrix(80 + case, 1, K, N, -1, 1, dtype), bool(transB))
+                C = pi.store(pi.small_int_matrix(80 + case, 2, M, N, -9, 9, cdtype), False, N + case % 3)
+                bias = (np.arange(N) % 13 - 6).astype(np.float32)
+                ref = oracle.gemm(dtype, transA, transB, M, N, K, 1.0, A, B, -1.0, C, cdtype=cdtype)
+                data[case] = A, B, C, bias, oracle.bias_act(ref, M, pg.PEAK_BIAS_PER_COLUMN, bias, pg.PEAK_ACT_RELU)
+            A, B, C, bias, ref = data[case]
+            try:
+                got, raw, info = gu.run_gemm(dtype, transA, transB, M, N, K, 1.0, -1.0, A, B, C,
+                                             flags=pg.force_flags(vid, split),
+                                             fused=(pg.PEAK_BIAS_PER_COLUMN, bias, pg.PEAK_ACT_RELU), cdtype=cdtype)
+            except pg.PeakError as e:
+                assert e.status == pg.PEAK_ERR_UNSUPPORTED        # rows that the direct copies do not take
+                continue
+            assert np.array_equal(got, ref), (name, case, info)
+            assert np.array_equal(raw[:, N:].view(np.uint8), C[:, N:].view(np.uint8)), (name, case)
