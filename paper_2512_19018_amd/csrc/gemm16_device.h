@@ -298,9 +298,9 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
                   "every wave issues the same number of loads");
     const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
     const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
-    if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
+    if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave, lane);
     else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
-    if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
+    if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave, lane);
     else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
     auto a_stage = [&](int s) { return lds + s * C::A_BYTES; };
     auto b_stage = [&](int s) { return lds + C::NSA * C::A_BYTES + s * C::B_BYTES; };

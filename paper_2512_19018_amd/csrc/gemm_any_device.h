@@ -380,9 +380,9 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         static_assert((P - 1) * L < 64, "fits the wait's counter");
         const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
         const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
-        if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
+        if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave_all, lane);
         else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
-        if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
+        if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave_all, lane);
         else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
         const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
         auto issue = [&](int kt, int stage) {

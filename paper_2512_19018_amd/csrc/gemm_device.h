@@ -51,6 +51,7 @@ struct GemmArgs {
     float *ws;                // split > 1: fp32 partials [split][M][N]
     int64_t M, N, K;
     int64_t lda, ldb, ldc;    // elements
+    int64_t a_cols, b_cols;   // columns of an operand stored K x M (K x N): M (N), or more in an aligned copy
     float alpha, beta;
     int32_t tiles_m, tiles_n;
     int32_t split;            // number of K slices
@@ -1003,9 +1004,9 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
     const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
     if (A_DIRECT && !C::A_TR) dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
-    if (A_DIRECT && C::A_TR) nA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
+    if (A_DIRECT && C::A_TR) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && !C::B_TR) dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
-    if (B_DIRECT && C::B_TR) nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
+    if (B_DIRECT && C::B_TR) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave, lane);
     if (!B_DIRECT) tB.init(p.B, p.ldb, n0, p.N, tid);
 
     auto a_stage = [&](int s) { return lds + s * C::A_BYTES; };

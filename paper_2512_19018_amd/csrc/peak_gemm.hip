@@ -8,7 +8,7 @@
 #include <mutex>
 #include <vector>
 
-#include "gemm_device.h"
+#include "gemm_any_device.h"
 #include "skinny_device.h"
 #include "variant.h"
 
@@ -69,6 +69,44 @@ __global__ __launch_bounds__(256) void stage_a_kernel(const T *A, int64_t lda, T
     }
 }
 
+// Aligned copies of one or two operands: `rows` rows of `cols` elements at any alignment, written out as `rows_to` rows
+// of `ld_to` elements (whole 16-byte chunks, 128-byte lines) with zeros beyond the matrix.  One 16-byte chunk per thread
+// and step; A's chunks come first.  Bound by memory: read once, written once.
+struct PackOperand {
+    const void *src;
+    void *dst;
+    int64_t rows, cols, ld, rows_to, ld_to;
+};
+constexpr int PACK_STEPS = 4;
+template <int DT>
+__global__ __launch_bounds__(256) void pack_kernel(const PackOperand a, const PackOperand b, int64_t blocks_a)
+{
+    constexpr int EPC = DT == DT_F32 ? 4 : 8, ESZ = 16 / EPC;
+    const bool second = blockIdx.x >= blocks_a;
+    const PackOperand &o = second ? b : a;
+    const uint32_t per_row = (uint32_t)(o.ld_to / EPC);
+    const int64_t total = o.rows_to * per_row;
+    const int64_t first = ((int64_t)blockIdx.x - (second ? blocks_a : 0)) * (256 * PACK_STEPS);
+    const int64_t r0 = first / per_row;                     // (the workgroup's: the only division in 64 bits)
+    const uint32_t c0 = (uint32_t)(first - r0 * per_row) + threadIdx.x;
+    u32x4 v[PACK_STEPS];
+#pragma unroll
+    for (int s = 0; s < PACK_STEPS; ++s) {
+        const uint32_t down = (c0 + 256 * s) / per_row;
+        const int64_t r = r0 + down, c = (int64_t)(c0 + 256 * s - down * per_row) * EPC;
+        v[s] = u32x4{0u, 0u, 0u, 0u};
+        if (r >= o.rows || c >= o.cols) continue;
+        const char *row = (const char *)o.src + r * o.ld * ESZ;
+        if (c + EPC <= o.cols) v[s] = load_loose<u32x4, ESZ>(row + c * ESZ);
+        else v[s] = load_elems<DT>(row + c * ESZ, (int)(o.cols - c));
+    }
+#pragma unroll
+    for (int s = 0; s < PACK_STEPS; ++s) {
+        const int64_t at = first + threadIdx.x + 256 * s;
+        if (at < total) *(u32x4 *)((char *)o.dst + at * 16) = v[s];
+    }
+}
+
 static int esize_of(int dt) { return dt == PEAK_DT_F32 ? 4 : 2; }
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -118,17 +156,42 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
     const bool b_al = (uintptr_t)B % 16 == 0 && (d.ldb * es) % 16 == 0;
     // the selected variant, or its stand-in when it copies 16-byte chunks and a base is off that alignment
     const Geometry *g = &p->g;
-    if (g_variants[g->variant].direct && !((a_al || g->a_copy) && b_al)) {
+    if (g_variants[g->variant].direct && !((a_al || g->a_copy || (g->pack & 1)) && (b_al || (g->pack & 2)))) {
         if (p->alt.variant < 0) return PEAK_ERR_UNSUPPORTED;
         g = &p->alt;
     }
+    // (a workspace too small for aligned copies, such as the fixed array of peak_gemm_run_static, does for the stand-in)
+    if (g->pack && (!workspace || workspace_bytes < g->ws_bytes)) g = &p->alt;
     const Variant &v = g_variants[g->variant];
 
-    if (g->split > 1 || g->a_copy) {
+    if (g->split > 1 || g->a_copy || g->pack) {
         if (!workspace || workspace_bytes < g->ws_bytes) return PEAK_ERR_WORKSPACE;
         if ((uintptr_t)workspace % 256) return PEAK_ERR_INVALID_ARG;
     }
     if (g->split > 1) a.ws = (float *)workspace;
+    a.a_cols = d.M; a.b_cols = d.N;
+    if (g->pack) {
+        PackOperand ops[2] = {};
+        const int64_t k_to = g->pack_k;
+        if (g->pack & 1) {
+            ops[0] = PackOperand{A, (char *)workspace + g->pack_off[0], d.transA ? d.K : d.M, d.transA ? d.M : d.K, d.lda,
+                                 d.transA ? k_to : d.M, g->pack_ld[0]};
+            a.A = ops[0].dst; a.lda = g->pack_ld[0]; a.a_cols = g->pack_m;
+        }
+        if (g->pack & 2) {
+            ops[1] = PackOperand{B, (char *)workspace + g->pack_off[1], d.transB ? d.N : d.K, d.transB ? d.K : d.N, d.ldb,
+                                 d.transB ? d.N : k_to, g->pack_ld[1]};
+            a.B = ops[1].dst; a.ldb = g->pack_ld[1]; a.b_cols = g->pack_n;
+        }
+        a.K = k_to;
+        int64_t blocks[2];
+        for (int i = 0; i < 2; ++i) blocks[i] = (g->pack >> i) & 1 ? cdiv(ops[i].rows_to * ops[i].ld_to * es / 16, 256 * PACK_STEPS) : 0;
+        if (blocks[0] + blocks[1] > 0x7FFFFFFF) return PEAK_ERR_UNSUPPORTED;
+        dim3 pgrid((unsigned)(blocks[0] + blocks[1]));
+        if (es == 4) hipLaunchKernelGGL(pack_kernel<DT_F32>, pgrid, dim3(256), 0, stream, ops[0], ops[1], blocks[0]);
+        else hipLaunchKernelGGL(pack_kernel<DT_F16>, pgrid, dim3(256), 0, stream, ops[0], ops[1], blocks[0]);
+        if (hipGetLastError() != hipSuccess) return PEAK_ERR_HIP;
+    }
     if (g->a_copy) {
         if (d.M > 64) return PEAK_ERR_UNSUPPORTED;          // (the planner admits no such plan)
         void *copy = (char *)workspace + g->a_copy_off;
@@ -214,7 +277,9 @@ peak_status_t peak_gemm_run_static(peak_gemm_plan_t *plan, float alpha, const vo
                                    void *C, void *hip_stream)
 {
     if (!plan) return PEAK_ERR_INVALID_ARG;
-    if (plan->ws_bytes > (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES) return PEAK_ERR_WORKSPACE;
+    // (a plan that would make aligned copies runs its stand-in where the copies do not fit)
+    if (plan->ws_bytes > (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES &&
+        !(plan->g.pack && plan->alt.ws_bytes <= (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES)) return PEAK_ERR_WORKSPACE;
     void *ws = nullptr;
     if (plan->ws_bytes > 0) {
         int dev = -1;

@@ -90,13 +90,17 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
 
 // The register-staged kernels: the loads bound them, not the MFMAs, and how well the loads overlap depends on the
 // workgroups that share a CU.  Measured as a share of the MFMA rate, with as many workgroups as fit and with one:
-// bf16 4095^3 (saturated) 0.26 with 128x128 tiles, 0.19 with 128x64, 0.14 with 64x64; 1023x2047x3001 0.13, 0.11 and
-// (two workgroups of eight waves) 0.13 with one to two workgroups per CU.  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
+// bf16 128x128 tiles 0.24 (4095^3), 0.19 (1023x2047x3001 in four slices), 0.20 (8191x8191x1023), 128x64 0.19 to 0.23
+// (1500x1501x4000, two and three workgroups per CU) and 0.10 alone, 64x64 0.15 (1111x1003x1500).  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
 // 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.43, with four 0.52.
 // (Measured in microseconds.  tiled_cost's units are rates of full rounds under the power limit: about 2.7e6 of them
 // to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4e6 in fp32.)
 static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.0e6 : 2.7e6); }
 constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-adds per CU at the full rate
+
+// A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in two
+// slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads.
+static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
 
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
@@ -109,11 +113,11 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     if (fit < 1) fit = 1;
     double eff, one;                                        // saturated; one workgroup's share of it
     if (v.dt == PEAK_DT_F32) { eff = area >= 128 * 128 ? 0.65 : area >= 64 * 64 ? 0.66 : area >= 64 * 32 ? 0.60 : 0.50; one = 0.6; }
-    else { eff = area >= 128 * 128 ? 0.25 : area >= 128 * 64 ? 0.19 : 0.145; one = area >= 128 * 64 ? 0.55 : 0.8; }
+    else { eff = area >= 128 * 128 ? 0.22 : area >= 128 * 64 ? 0.20 : 0.15; one = area >= 128 * 64 ? 0.55 : 0.8; }
     const double full = (double)(per_cu / fit) * fit * work / eff;
     const int64_t rest = per_cu % fit;
     const double part = rest ? (double)rest * work / (eff * (fit > 1 ? one + (1.0 - one) * (double)(rest - 1) / (fit - 1) : 1.0)) : 0.0;
-    return units_of_us(v, (full + part + reduce_cost(d, split)) / MFMA_PER_US + 2.5 * (double)cdiv(per_cu, fit));
+    return units_of_us(v, (full + part) / MFMA_PER_US + 2.5 * (double)cdiv(per_cu, fit) + 1.3 * split_us(d, split));
 }
 
 // The ring kernels: small tiles, bound by the way into the LDS (16 bits) or by the MFMAs (fp32).  16 bits, bytes per ns
@@ -132,9 +136,7 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     } else {
         us = ktiles * (v.bm + v.bn) * v.bk * 2.0 / 1000.0 / (v.bk >= 128 ? 85.0 : 72.0);
     }
-    // (a K split costs these short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 tiles 13.3 us in two
-    // slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads)
-    return units_of_us(v, us + 2.5 + (split > 1 ? 2.0 + reduce_cost(d, split) / MFMA_PER_US : 0.0));
+    return units_of_us(v, us + 2.5 + split_us(d, split));
 }
 
 // Estimated time of a tiled variant, in units of "one 32x32xBK-row MFMA group":
@@ -205,6 +207,8 @@ static int choose_split(const Variant &v, const peak_gemm_desc_t &d)
 {
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn);
     const int64_t ktiles = cdiv(d.K, v.bk);
+    // (partials of these kernels stay within the array of peak_gemm_run_static)
+    const bool cap = !v.direct || v.ring;
     // (the register-staged kernels gain from several workgroups per CU: bf16 1023x2047x3001 in 256 tiles of 128x64
     // 48.9 us unsplit, 40.2 in two slices)
     if (tiles > (v.direct ? num_cu() / 2 : 2 * num_cu()) || ktiles < 4) return 1;
@@ -212,6 +216,7 @@ static int choose_split(const Variant &v, const peak_gemm_desc_t &d)
     double best_cost = tiled_cost(v, d, 1);
     for (int s = 2; s <= 16; ++s) {
         if (ktiles / s < 2) break;
+        if (cap && 4.0 * s * (double)d.M * (double)d.N > (double)PEAK_GEMM_STATIC_WORKSPACE_BYTES) break;
         const double c = tiled_cost(v, d, s);
         if (c < best_cost * 0.95) { best_cost = c; best = s; }
     }
@@ -254,6 +259,7 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     const Variant &v = g_variants[variant];
     p->variant = variant;
     p->sk_tiles = 0;
+    p->pack = 0;
     p->tiles_m = (int)cdiv(d.M, v.bm);
     p->tiles_n = (int)cdiv(d.N, v.bn);
     p->ktiles_total = (int)cdiv(d.K, v.bk);
@@ -362,6 +368,48 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     for (int r = 3; r >= 1; --r)
         if (stream[r] >= 0) return stream[r];
     return pick;
+}
+
+// Products whose rows do not suit the 16-byte copies, by the direct kernels on aligned copies of the operands that the
+// run writes first.  The copies cost a pass over the operands (about 4 TB/s with the write, 4.5 us at least), the
+// register-staged kernels a third to three quarters of the rate, so this pays for large products: bf16 4095^3 143 us
+// against 230, 1500x1501x4000 NN 38 against 55, 1023x2047x3001 29 against 40; fp32 1023x2047x3001 TN 116 against 133; level
+// at 2049x2047x1031 NN and 1111x1003x1500.  Fills *g and
+// returns true if the cost model has it ahead of `staged` (the register-staged choice).
+static int64_t round_up(int64_t x, int64_t m) { return cdiv(x, m) * m; }
+static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int streamk)
+{
+    const int64_t es = esize_of(d.dtype), chunk = 16 / es, line = 128 / es;
+    if (d.M <= 64) return false;                            // streamed once: a copy would double the traffic
+    peak_gemm_desc_t e = d;
+    e.K = round_up(d.K, chunk);
+    const bool tail = e.K != d.K;                           // both operands then need zeros up to the chunk
+    int pack = 0;
+    if (tail || d.lda % chunk || (d.transA && d.M % chunk)) {
+        pack |= 1;
+        if (d.transA) e.M = round_up(d.M, chunk);
+        e.lda = round_up(d.transA ? e.M : e.K, line);
+    }
+    if (tail || d.ldb % chunk || (!d.transB && d.N % chunk)) {
+        pack |= 2;
+        if (!d.transB) e.N = round_up(d.N, chunk);
+        e.ldb = round_up(d.transB ? e.K : e.N, line);
+    }
+    const int v = pack ? select_variant(e, false) : -1;
+    if (v < 0 || !g_variants[v].direct || g_variants[v].kind != KIND_TILED) return false;
+    const size_t bytes_a = (pack & 1) ? (size_t)((d.transA ? e.K : d.M) * e.lda * es) : 0;
+    const size_t bytes_b = (pack & 2) ? (size_t)((d.transB ? d.N : e.K) * e.ldb * es) : 0;
+    const double copy_us = 4.5 + 2.0 * (double)(bytes_a + bytes_b) / 4.0e6;
+    const double direct = tiled_cost(g_variants[v], e, choose_split(g_variants[v], e)) + units_of_us(g_variants[v], copy_us);
+    if (direct >= 0.93 * tiled_cost(g_variants[staged], d, choose_split(g_variants[staged], d))) return false;
+    plan_geometry(g, e, v, 0, streamk);
+    g->pack = pack;
+    g->pack_k = e.K; g->pack_m = e.M; g->pack_n = e.N;
+    g->pack_ld[0] = e.lda; g->pack_ld[1] = e.ldb;
+    g->pack_off[0] = (g->ws_bytes + 255) & ~(size_t)255;    // behind the partials, on 256-byte boundaries
+    g->pack_off[1] = (g->pack_off[0] + bytes_a + 255) & ~(size_t)255;
+    g->ws_bytes = (g->pack_off[1] + bytes_b + 255) & ~(size_t)255;
+    return true;
 }
 
 // Selector table from an offline sweep: exact shape -> variant and K split.
@@ -560,6 +608,14 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     plan_geometry(&p->g, d, pick, forced_split > 0 ? forced_split : (table_split > 0 ? table_split : 0), streamk);
     // Leading dimensions are known here, base addresses only at run time: a variant that copies
     // 16-byte chunks gets a register-staged stand-in for runs whose A or B base is off that alignment
+    // A register-staged choice of the cost model's is the stand-in itself where aligned copies are worth making
+    if (forced < 0 && forced_split <= 0 && !g_variants[pick].direct) {
+        Geometry packed = Geometry();
+        if (pack_plan(d, pick, &packed, streamk)) {
+            p->alt = p->g;
+            p->g = packed;
+        }
+    }
     if (g_variants[pick].direct) {
         const int alt = select_variant(d, true);
         if (alt >= 0) plan_geometry(&p->alt, d, alt, forced_split);
@@ -587,10 +643,10 @@ int peak_gemm_plan_info(const peak_gemm_plan_t *p, char *buf, size_t n)
     const Variant &v = g_variants[g.variant];
     return snprintf(buf, n,
                     "variant=%d:%s tile=%dx%dx%d threads=%d stages=%d lds=%d split=%d ktiles/slice=%d "
-                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s streamk=%d rot=%d,%d acopy=%d",
+                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s streamk=%d rot=%d,%d pack=%d acopy=%d",
                     g.variant, v.name, v.bm, v.bn, v.bk, v.nt, v.ns, v.lds, g.split, g.ktiles_per_slice,
                     (long long)grid_blocks(g), g.tiles_m, g.tiles_n, g.group_m, p->ws_bytes,
-                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same", g.sk_tiles, g.rot_m, g.rot_n, g.a_copy);
+                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same", g.sk_tiles, g.rot_m, g.rot_n, g.pack, g.a_copy);
 }
 
 peak_status_t peak_gemm_destroy(peak_gemm_plan_t *plan)

@@ -54,6 +54,12 @@ struct Geometry {
     int a_copy;           // streaming kernel on an A stored K x M: A is first written out along K (M rows of K
                           // elements) at a_copy_off of the workspace, and the kernel reads that
     size_t a_copy_off;
+    // Operands that the run first writes out with aligned rows (bit 0: A, bit 1: B), at pack_off of the workspace, and
+    // the product's sizes over the copies: K and the columns of an operand stored K x M or K x N rounded up to whole
+    // 16-byte chunks, zeros beyond the matrix; leading dimensions of the copies a multiple of 128 bytes.
+    int pack;
+    size_t pack_off[2];
+    int64_t pack_k, pack_m, pack_n, pack_ld[2];
     size_t ws_bytes;
 };
 

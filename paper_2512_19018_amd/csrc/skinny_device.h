@@ -455,7 +455,7 @@ __global__ __launch_bounds__(C::NT) void skinny_kn_kernel(const GemmArgs p)
         ja[i] = j;
     }
     LoaderDirectKN<C, C::BN, true> nB;
-    nB.init(p.B, p.ldb, n0, p.N, kbase, p.K, C::BK, wave, lane);
+    nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, C::BK, wave, lane);
     constexpr int LB = LoaderDirectKN<C, C::BN, true>::PER_WAVE;
     static_assert(LoaderDirectKN<C, C::BN, true>::NINST % C::NW == 0, "every wave issues the same number of loads");
     constexpr int DLOADS = C::A_PER_WAVE + LB;
