@@ -92,7 +92,7 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
 // workgroups that share a CU.  Measured as a share of the MFMA rate, with as many workgroups as fit and with one:
 // bf16 128x128 tiles 0.24 (4095^3), 0.19 (1023x2047x3001 in four slices), 0.20 (8191x8191x1023), 128x64 0.19 to 0.23
 // (1500x1501x4000, two and three workgroups per CU) and 0.10 alone, 64x64 0.15 (1111x1003x1500).  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
-// 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.43, with four 0.52.
+// 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.50, with four 0.56.
 // (Measured in microseconds.  tiled_cost's units are rates of full rounds under the power limit: about 2.7e6 of them
 // to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4e6 in fp32.)
 static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.0e6 : 2.7e6); }
@@ -100,7 +100,8 @@ constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-a
 
 // A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in two
 // slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads.
-static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
+// (and 0.15 us a slice where the partials are too few to matter: fp32 131x167x1069 14.1 us in four slices, 15.4 in twelve)
+static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + 0.15 * split + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
 
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
