@@ -94,8 +94,9 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
 // (1500x1501x4000, two and three workgroups per CU) and 0.10 alone, 64x64 0.15 (1111x1003x1500).  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
 // 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.50, with four 0.56.
 // (Measured in microseconds.  tiled_cost's units are rates of full rounds under the power limit: about 2.7e6 of them
-// to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4e6 in fp32.)
-static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.0e6 : 2.7e6); }
+// to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4.4e6 in
+// fp32: 2300x1700x4096 NT 260 and 246.)
+static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.4e6 : 2.7e6); }
 constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-adds per CU at the full rate
 
 // A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in two
@@ -103,15 +104,21 @@ constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-a
 // (and 0.15 us a slice where the partials are too few to matter: fp32 131x167x1069 14.1 us in four slices, 15.4 in twelve)
 static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + 0.15 * split + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
 
+// workgroups that share a CU: LDS, four waves per SIMD
+static int resident(const Variant &v)
+{
+    int fit = LDS_LIMIT / v.lds;
+    if (fit > 1024 / v.nt) fit = 1024 / v.nt;
+    return fit < 1 ? 1 : fit;
+}
+
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
     const int64_t per_cu = cdiv(tiles, num_cu());
     const double work = (double)v.bm * v.bn * v.bk * (double)cdiv(cdiv(d.K, v.bk), split) * (v.dt == PEAK_DT_F32 ? 16.0 : 1.0);
     const int area = v.bm * v.bn;
-    int fit = LDS_LIMIT / v.lds, by_waves = 1024 / v.nt;    // workgroups that share a CU: LDS, four waves per SIMD
-    if (fit > by_waves) fit = by_waves;
-    if (fit < 1) fit = 1;
+    const int fit = resident(v);
     double eff, one;                                        // saturated; one workgroup's share of it
     if (v.dt == PEAK_DT_F32) { eff = area >= 128 * 128 ? 0.65 : area >= 64 * 64 ? 0.66 : area >= 64 * 32 ? 0.60 : 0.50; one = 0.6; }
     else { eff = area >= 128 * 128 ? 0.22 : area >= 128 * 64 ? 0.20 : 0.15; one = area >= 128 * 64 ? 0.55 : 0.8; }
@@ -126,6 +133,8 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
 // f16 2048x1024x4096 TN, 256 tiles of 128x64 25.6, 512 of 64x64 31.9) and 85 with 128 (100x4096x4096, 256 tiles of
 // 32x64: 11.4 us).  fp32, share of the MFMA rate alone and with several
 // workgroups: 64x64 0.72 and 0.81 (1024^3 22.2 us, 2048^3 139), 64x32 0.60 and 0.70, 32x32 0.52 and 0.63 (512^3 6.7 us).
+// Each round of workgroups fills its rings and stores C anew: bf16 4096x4096x64 NN, eight 128x64 tiles per CU, 15.7 us
+// against 12.4 in one round of 256x256 tiles.
 static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t per_cu = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
@@ -137,7 +146,7 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     } else {
         us = ktiles * (v.bm + v.bn) * v.bk * 2.0 / 1000.0 / (v.bk >= 128 ? 85.0 : 72.0);
     }
-    return units_of_us(v, us + 2.5 + split_us(d, split));
+    return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v)) + split_us(d, split));
 }
 
 // Estimated time of a tiled variant, in units of "one 32x32xBK-row MFMA group":
@@ -326,8 +335,8 @@ static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 // `staged_only`, among those that take any operand alignment.
 static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 {
-    double best = 0.0;
-    int pick = -1, stream[4] = {-1, -1, -1, -1};            // first fitting streaming kernel of each rank
+    double best = 0.0, best_ring = 0.0;
+    int pick = -1, ring = -1, pick_split = 1, stream[4] = {-1, -1, -1, -1};            // first fitting streaming kernel of each rank
     // streaming kernels: only those with the fewest rows of the M x K operand that hold M
     int stream_bm = 0;
     for (int i = 0; i < NUM_VARIANTS; ++i) {
@@ -363,12 +372,19 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
                 c -= per_round * (1.0 - 1.0 / S) * 0.8;              // four fifths of the saving that round counting predicts
             }
         }
-        if (pick < 0 || c < best) { pick = i; best = c; }
+        if (v.ring) { if (ring < 0 || c < best_ring) { ring = i; best_ring = c; } }
+        else if (pick < 0 || c < best) { pick = i; best = c; pick_split = split; }
     }
     // a streaming kernel wins whenever one applies
     for (int r = 3; r >= 1; --r)
         if (stream[r] >= 0) return stream[r];
-    return pick;
+    // A K split of an fp32 launch costs some microseconds more than the model has for it: 504x1396x2380 NT in five slices
+    // of 128x128 tiles 42.1 us, 36.1 in ring tiles unsplit; 112x208x816 NN 10.0 in 13 slices, 8.2 in ring tiles.
+    // (2560x1340x2164 TT, unsplit in both, 134 us with the 128 x 128 tile and 147 in ring tiles.)  It counts against the
+    // ring kernels only: among the others tile and split, and with them the workspace, are as they would be without.
+    if (ring >= 0 && pick >= 0 && g_variants[pick].direct && d.dtype == PEAK_DT_F32 && pick_split > 1)
+        best += units_of_us(g_variants[pick], 4.0 + 0.3 * pick_split);
+    return ring >= 0 && (pick < 0 || best_ring < best) ? ring : pick;
 }
 
 // Products whose rows do not suit the 16-byte copies, by the direct kernels on aligned copies of the operands that the
