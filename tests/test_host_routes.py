@@ -1,0 +1,65 @@
+"""Which route a plan takes: aligned copies, any-alignment kernels, ring kernels (no GPU needed)."""
+import itertools
+
+import pytest
+
+import paper_2512_19018_amd as pg
+
+DTYPES = {"f32": (pg.PEAK_DT_F32, 4), "f16": (pg.PEAK_DT_F16, 2), "bf16": (pg.PEAK_DT_BF16, 2)}
+
+
+def plan(dt, ta, tb, M, N, K, pad=(0, 0, 0), flags=0):
+    p = pg.Plan(M, N, K, DTYPES[dt][0], ta, tb, (M if ta else K) + pad[0], (K if tb else N) + pad[1], N + pad[2],
+                flags=flags)
+    info = p.info()
+    fields = dict(w.split("=", 1) for w in info.split() if "=" in w)
+    return p, fields["variant"].split(":")[1], int(fields["split"]), int(fields["pack"]), fields["unaligned"]
+
+
+@pytest.mark.parametrize("dt,ta,tb", list(itertools.product(DTYPES, (0, 1), (0, 1))))
+def test_every_form_takes_a_kernel_that_can_read_it(dt, ta, tb):
+    """Rows that do not fill 16-byte chunks go to a kernel for any alignment or through copies of just those operands."""
+    chunk = 16 // DTYPES[dt][1]
+    for M, N, K, pa, pb in itertools.product((100, 1024, 2049), (96, 1000, 2051), (512, 1031), (0, 1, chunk), (0, 1, chunk)):
+        p, name, _, pack, alt = plan(dt, ta, tb, M, N, K, (pa, pb, 0))
+        tail = K % chunk != 0
+        odd_a = tail or ((M if ta else K) + pa) % chunk != 0 or (ta and M % chunk != 0)
+        odd_b = tail or ((K if tb else N) + pb) % chunk != 0 or (not tb and N % chunk != 0)
+        any_alignment = name.startswith(dt + "_r") or "skinny" in name
+        if pack:
+            assert M > 64 and pack == (1 if odd_a else 0) | (2 if odd_b else 0)
+            rows = (pack & 1) * M * K + (pack >> 1) * N * K
+            assert p.workspace_bytes >= rows * DTYPES[dt][1]
+            assert not any_alignment and alt.startswith(dt + "_r")
+        elif odd_a or odd_b:
+            # (the "_d..._nn" kernels mask the columns of B themselves; with K along no row the direct copies end with K)
+            masked = name.endswith("_nn") and "_d" in name and not odd_a and (N + pb) % chunk == 0
+            rows_of_k = ta and not tb and (M + pa) % chunk == M % chunk == 0 and (N + pb) % chunk == N % chunk == 0
+            assert any_alignment or masked or rows_of_k, (M, N, K, pa, pb, name)
+        # whatever the operands' addresses, a kernel without alignment conditions stands by
+        assert any_alignment or alt.startswith(dt + "_r"), (name, alt)
+
+
+@pytest.mark.parametrize("dt", DTYPES)
+def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
+    for M, N, K, odd in itertools.product((33, 100, 700, 1700), (40, 512, 3072, 8192), (256, 3000, 16384), (0, 1)):
+        p, name, split, pack, _ = plan(dt, 0, 1, M, N, K, (odd, odd, 0))
+        if not pack and (name.startswith(dt + "_r") or "q" in name):
+            assert split * M * N * 4 <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES or split == 1
+            assert p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES
+
+
+@pytest.mark.parametrize("dt,ta,tb,M,N,K,ring", [
+    ("f32", 0, 1, 504, 1396, 2380, True),        # the large tile only with a K split
+    ("f32", 0, 0, 112, 208, 816, True),
+    ("f32", 1, 1, 2560, 1340, 2164, False),      # the large tile unsplit
+    ("f32", 0, 0, 2048, 4096, 32, False),        # K too short for many rounds of small tiles
+    ("bf16", 0, 0, 4096, 4096, 64, False),
+    ("bf16", 0, 1, 100, 4096, 4096, True),
+    ("f16", 0, 1, 64, 4096, 8192, True),         # 33 to 64 rows against a small streamed operand
+    ("f16", 0, 1, 32, 4096, 8192, False),
+    ("bf16", 0, 1, 8192, 8192, 8192, False),
+])
+def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
+    _, name, _, _, _ = plan(dt, ta, tb, M, N, K)
+    assert ("q" in name.split("_")[1]) == ring, name
