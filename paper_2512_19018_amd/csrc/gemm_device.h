@@ -822,6 +822,36 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             return;
         }
     }
+    // Plain runs of the fp32 kernels on interior tiles, K slices among them: straight through, without the choices below
+    // (652x4536x16 TN 7.8 us without them, 8.9 with; 4096x4096x64 NT 31.0 and 32.7; 256^3 4.3 and 4.8).
+    if constexpr (C::DT == DT_F32) {
+        if (interior && (po.base || (p.beta == 0.0f && !hooked))) {
+            constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
+            constexpr int GR = G < 8 ? G : 8;                          // ... of which at most eight in registers
+            const int orow = lane / LPR, ocol = (lane % LPR) * 4;
+            const float alpha = po.base ? 1.0f : p.alpha;
+            const int64_t ld = po.base ? po.ld : p.ldc, m = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
+            float *out = po.base ? po.base + (m - po.m_org) * ld + (n - po.n_org) : (float *)p.C + m * ld + n;
+            write_slab(0, scr);
+#pragma unroll
+            for (int run = 0; run < SLABS * (G / GR); ++run) {
+                const int first = run % (G / GR) * GR;
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
+                f32x4 v[GR];
+#pragma unroll
+                for (int g = 0; g < GR; ++g) v[g] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4);
+                if (first + GR == G && run + 1 < SLABS * (G / GR)) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
+#pragma unroll
+                for (int g = 0; g < GR; ++g) {
+                    union { u32x4 u; f32x4 f; } o;
+                    o.f = v[g] * alpha;
+                    store_loose<u32x4, 4>((char *)out + (int64_t)(run * GR + g) * RPI * ld * 4, o.u);
+                }
+            }
+            return;
+        }
+    }
     const bool out32 = C::DT == DT_F32 || c_f32 || po.base;
     const int epl = out32 ? 4 : 8;
     const int64_t left = p.N - (n0 + wn * C::WTN);                     // columns of C in the wave tile and beyond
