@@ -354,9 +354,10 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             // rank 3 only where one workgroup per tile of its (larger) BN fills four fifths of the chip, or where
             // the M x K operand is tall enough for its re-reads to matter (every workgroup reads its K slice of
             // all of it: bf16 64x8192x28672 takes 101.9 us with 128 rows per workgroup, 126.4 us with 64)
-            // (but not where tiles of half the columns fill it without a K split: 64x16384x8192 50.1 us against 56.9)
+            // (but not where tiles of half the columns fill it in one round without a K split: 64x16384x8192 50.1 us
+            // against 56.9; a second round, nearly empty or not, costs more: 64x25664x14080 164 against 135)
             const int64_t fill = (int64_t)num_cu() * 4;
-            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || cdiv(d.N, v.bn / 2) * 5 >= fill)) continue;
+            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || (cdiv(d.N, v.bn / 2) * 5 >= fill && cdiv(d.N, v.bn / 2) <= num_cu()))) continue;
             if (stream[v.stream_rank] < 0) stream[v.stream_rank] = i;
             continue;
         }

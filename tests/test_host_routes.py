@@ -63,3 +63,9 @@ def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
 def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
     _, name, _, _, _ = plan(dt, ta, tb, M, N, K)
     assert ("q" in name.split("_")[1]) == ring, name
+
+
+@pytest.mark.parametrize("N,columns", [(13312, 64), (16384, 64), (16448, 128), (25664, 128), (26624, 128)])
+def test_streaming_tiles_of_64_columns_only_in_one_round(N, columns):
+    _, name, _, _, _ = plan("bf16", 0, 1, 64, N, 14080)
+    assert name == "bf16_skinny_m64n%dk128s3_nt" % columns
