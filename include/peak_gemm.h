@@ -127,6 +127,11 @@ size_t peak_gemm_workspace_bytes(const peak_gemm_plan_t *plan);
  *                a larger matrix), the run uses the plan's register-staged
  *                stand-in variant (named after "unaligned=" by
  *                peak_gemm_plan_info): same result within the tolerance, slower.
+ *                Plans of large products whose leading dimensions or sizes do not
+ *                suit them ("pack=" in peak_gemm_plan_info) write aligned copies of
+ *                those operands into the workspace on every run; a run whose
+ *                workspace holds the stand-in's partials but not the copies takes
+ *                the stand-in.
  *   A, B, C      device pointers, aligned to the element size; C must not
  *                overlap A or B.  With beta == 0 C is write-only: whatever it
  *                holds, NaN included, does not reach the result.  With
@@ -192,12 +197,13 @@ peak_status_t peak_gemm_run_fused(peak_gemm_plan_t *plan, float alpha,
 /*
  * peak_gemm_run for callers that cannot allocate device memory or pass a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same plan, same kernels, same result bits as peak_gemm_run;
+ * forbid hipMalloc.  Same plan, same kernels, same result bits as peak_gemm_run
+ * (a plan whose aligned copies do not fit the array runs its stand-in variant instead);
  * what the workspace would hold goes to an array of PEAK_GEMM_STATIC_WORKSPACE_BYTES that
  * is part of the library's device code (every GPU the library runs on holds
  * its own copy until the process ends).  The call allocates nothing.
  *
- *   PEAK_ERR_WORKSPACE  the plan needs more than PEAK_GEMM_STATIC_WORKSPACE_BYTES
+ *   PEAK_ERR_WORKSPACE  the plan, aligned copies aside, needs more than PEAK_GEMM_STATIC_WORKSPACE_BYTES
  *                       (peak_gemm_workspace_bytes() tells beforehand); nothing is launched.
  *   PEAK_ERR_HIP        no current device, or the array's address could not be obtained.
  *
