@@ -160,8 +160,8 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
         if (p->alt.variant < 0) return PEAK_ERR_UNSUPPORTED;
         g = &p->alt;
     }
-    // (a workspace too small for aligned copies, such as the fixed array of peak_gemm_run_static, does for the stand-in)
-    if (g->pack && (!workspace || workspace_bytes < g->ws_bytes)) g = &p->alt;
+    // (a workspace that does not suit aligned copies, such as the fixed array of peak_gemm_run_static, does for the stand-in)
+    if (g->pack && (!workspace || workspace_bytes < g->ws_bytes || (uintptr_t)workspace % 256)) g = &p->alt;
     const Variant &v = g_variants[g->variant];
 
     if (g->split > 1 || g->a_copy || g->pack) {

@@ -58,3 +58,55 @@ def test_aligned_copies(gu, oracle, dtype, transA, transB, sizes, blocks):
             torch.cuda.synchronize()
             got = pi.to_f64(gu.from_dev(dC, dtype), dtype)
             gu.check_against_oracle(oracle, got, dtype, transA, transB, M, N, K, 0.5, A, B, 2.0, lc, rows=rows, what=(info, nbytes))
+
+
+def test_workspace_off_256_bytes_takes_the_stand_in(gu):
+    import torch
+    pg = gu.pg
+    M, N, K = 4097, 4099, 515                                   # more tiles than the stand-in ever splits K for
+    A, B = (torch.randn(r, K, device="cuda", dtype=torch.bfloat16) for r in (M, N))
+    stream = torch.cuda.current_stream().cuda_stream
+    with pg.Plan(M, N, K, pi.BF16, 0, 1, K, K, N) as plan:
+        assert "pack=3" in plan.info(), plan.info()
+        ws = torch.empty(plan.workspace_bytes + 16, dtype=torch.uint8, device="cuda")
+        out = []
+        for ptr, nbytes in ((ws.data_ptr() + 16, plan.workspace_bytes), (0, 0)):
+            C = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+            plan.run(1.0, A.data_ptr(), B.data_ptr(), 0.0, C.data_ptr(), ptr, nbytes, stream)
+            torch.cuda.synchronize()
+            out.append(C)
+    assert torch.equal(out[0], out[1])                           # (NaN would not compare equal)
+
+
+@pytest.mark.parametrize("static", [0, 1])
+def test_aligned_copies_under_capture(gu, static):
+    """Replays copy what the operands hold then, not what they held at capture."""
+    import torch
+    pg = gu.pg
+    M, N, K = 2049, 2047, 1031
+    A, B = (torch.randn(r, K, device="cuda", dtype=torch.bfloat16) for r in (M, N))
+    C, E = (torch.zeros(M, N, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    with pg.Plan(M, N, K, pi.BF16, 0, 1, K, K, N) as plan:
+        assert "pack=3" in plan.info(), plan.info()
+        ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+
+        def run(out):
+            stream = torch.cuda.current_stream().cuda_stream
+            if static:
+                assert pg.peak_gemm_run_static(plan.handle, 1.0, A.data_ptr(), B.data_ptr(), 0.0, out.data_ptr(), stream) == pg.PEAK_OK
+            else:
+                plan.run(1.0, A.data_ptr(), B.data_ptr(), 0.0, out.data_ptr(), ws.data_ptr(), ws.numel(), stream)
+
+        run(E)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run(C)
+        for _ in range(3):
+            A.copy_(torch.randn(M, K, device="cuda"))
+            run(E)
+            torch.cuda.synchronize()
+            C.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(C, E)
