@@ -78,9 +78,10 @@ static bool variant_fits(const Variant &v, const peak_gemm_desc_t &d)
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The K split's part of a variant's cost (units of tiled_cost): slices write and re-read fp32 partials, about 9 units per element and slice when
-// they go through HBM, half of that while the workspace stays in the last-level cache, plus the launch of the
-// reduction kernel (about 2 us).
+// The K split's part of a variant's cost (units of tiled_cost): slices write and re-read fp32 partials, 4.5 units per element and
+// slice (4.8 TB/s), plus the launch of the reduction kernel (about 2 us).  Beyond 64 MB the time is the same, but plans
+// that need none of it would come to ask for that much workspace, more than peak_gemm_run_static has: the double price
+// keeps them (bf16 1536x3584x11584 NN 154 us in two slices; 135 in three, with 66 MB).
 static double reduce_cost(const peak_gemm_desc_t &d, int split)
 {
     if (split <= 1) return 0.0;
