@@ -605,6 +605,7 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
 
     int pick = -1;
     int table_split = 0;
+    bool own_choice = false;                          // neither forced nor from the selector table
     if (forced >= 0) {
         if (forced >= NUM_VARIANTS || !variant_fits(g_variants[forced], d)) {
             delete p;
@@ -616,6 +617,7 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
         table_split = t->split > 0 ? t->split : -1;
     } else {
         pick = select_variant(d, false);
+        own_choice = true;
         if (pick < 0) {
             delete p;
             return PEAK_ERR_UNSUPPORTED;
@@ -626,9 +628,10 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     if (forced_split <= 0 && streamk == 0 && table_split < 0) streamk = 1;
     plan_geometry(&p->g, d, pick, forced_split > 0 ? forced_split : (table_split > 0 ? table_split : 0), streamk);
     // Leading dimensions are known here, base addresses only at run time: a variant that copies
-    // 16-byte chunks gets a register-staged stand-in for runs whose A or B base is off that alignment
+    // 16-byte chunks gets a register-staged stand-in for runs whose A or B base is off that alignment.
     // A register-staged choice of the cost model's is the stand-in itself where aligned copies are worth making
-    if (forced < 0 && forced_split <= 0 && !g_variants[pick].direct) {
+    // (a table row's variant and split are taken as they are)
+    if (own_choice && forced_split <= 0 && !g_variants[pick].direct) {
         Geometry packed = Geometry();
         if (pack_plan(d, pick, &packed, streamk)) {
             p->alt = p->g;

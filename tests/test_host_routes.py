@@ -1,10 +1,12 @@
 """Which route a plan takes: aligned copies, any-alignment kernels, ring kernels (no GPU needed)."""
 import itertools
+import os
 
 import pytest
 
 import paper_2512_19018_amd as pg
 
+SHIPPED_TABLE = os.path.join(os.path.dirname(pg.__file__), "peak_gemm_tuning.txt")
 DTYPES = {"f32": (pg.PEAK_DT_F32, 4), "f16": (pg.PEAK_DT_F16, 2), "bf16": (pg.PEAK_DT_BF16, 2)}
 
 
@@ -69,3 +71,26 @@ def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
 def test_streaming_tiles_of_64_columns_only_in_one_round(N, columns):
     _, name, _, _, _ = plan("bf16", 0, 1, 64, N, 14080)
     assert name == "bf16_skinny_m64n%dk128s3_nt" % columns
+
+
+@pytest.mark.parametrize("row,sizes", [
+    ("bf16 0 1 4095 4095 4095 bf16_r128x128_nt 1", (4095, 4095, 4095)),
+    ("bf16 0 1 1023 2047 3001 bf16_r128x64_nt 4", (1023, 2047, 3001)),
+    ("f32 1 0 2049 3001 1023 f32_r64x64_tn 1", (2049, 3001, 1023)),
+])
+def test_table_rows_of_unaligned_products_are_the_plan(tmp_path, row, sizes):
+    """Variant and split of the row, without copies that the row does not name; other shapes still get them."""
+    dt, ta, tb, _, _, _, variant, split = row.split()
+    args = (dt, int(ta), int(tb))
+    assert plan(*args, *sizes)[3] == 3                           # the cost model's choice: aligned copies of both operands
+    table = tmp_path / "table.txt"
+    table.write_text(row + "\n")
+    try:
+        assert pg.peak_gemm_load_tuning(str(table)) == 1
+        p, name, s, pack, _ = plan(*args, *sizes)
+        assert (name, s, pack) == (variant, int(split), 0)
+        assert p.workspace_bytes == (s * sizes[0] * sizes[1] * 4 if s > 1 else 0)
+        M, N, K = sizes
+        assert plan(*args, M + 2, N, K)[3] == 3
+    finally:
+        pg.peak_gemm_load_tuning(SHIPPED_TABLE)
