@@ -322,14 +322,35 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     }
 }
 
-// A streaming kernel wins wherever one applies, but for an A taller than 32 rows against a small streamed operand: the
-// K split that then fills the chip costs more than the rows the ring kernels read twice (bf16 64x4096x8192 NT, 67 MB,
-// 16.8 us against 18.1 at best; f16 64x8192x2048 8.0 against 11.6; 64x8192x8192, 134 MB, 35.3 against 33.1).
+// A streaming kernel wins wherever one applies, but for an A stored K x M against a small streamed operand: the
+// transposition of A is one more launch.
 static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 {
-    const int64_t bytes = d.N * d.K * esize_of(d.dtype);
-    if (stages_a(v, d.transA)) return bytes >= (int64_t)8 << 20;    // the transposition of A is one more launch
-    return d.M <= 32 || d.dtype == PEAK_DT_F32 || bytes > (int64_t)72 << 20;
+    return !stages_a(v, d.transA) || d.N * d.K * esize_of(d.dtype) >= (int64_t)8 << 20;
+}
+
+// ... and for an A taller than 32 rows against a small streamed operand in 16 bits: the K split that fills the chip with
+// the streaming kernel costs more than the rows of A that the ring kernels read twice.  Times with the operand cold in
+// the caches: bf16 64x15360x1536 NT (47 MB) 13.1 us against 16.4 in two slices, f16 64x10752x2048 (44 MB) 14.4 and 16.2;
+// NN bf16 51x14016x2432 (68 MB) 16.0 and 21.3.  Where the slices of the streaming kernel spill into a second round they
+// cost more yet (36x11008x2304 NT, 258 workgroups, 23.3 us, 16.1 in ring tiles; 33x6592x4864 23.3 and 20.3, but
+// 62x5632x6272 23.6 and 27.7).  Not where
+//  - the streaming kernel needs no split (bf16 50x23232x1152 NT 14.4 us, 16.6 in ring tiles);
+//  - a slice of the ring kernel is deep, few workgroups then reading at one CU's rate (bf16 50x6144x4992 NT in two slices
+//    22.5 us, streamed 19.6; f16 42x10112x3200 21.9 and 19.9; NN, whose rows of B the streaming kernel reads at a lower
+//    rate, 63x8576x4224 25.9 and 23.7);
+//  - B is stored K x N and the 64-column tiles begin a second round, unless K is short (46x18368x2048 23.1 and 21.2,
+//    41x20736x1536 21.5 and 20.1, 43x26432x1408 19.3 and 20.9).
+// And for the ring kernels only: the other tiled kernels, priced for full tiles, lose either way (50x23232x1152 18.3 us;
+// f16 37x10112x3200 NN 18.2 in ring tiles, 19.9 streamed, 22.7 in 64x128 tiles).
+static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const peak_gemm_desc_t &d)
+{
+    if (d.M <= 32 || d.dtype == PEAK_DT_F32 || stages_a(v, d.transA) || d.N * d.K * esize_of(d.dtype) > (int64_t)72 << 20) return false;
+    const int split = skinny_split(d.N, d.K, v.bn, v.bk);
+    if (split == 1) return false;
+    const bool spills = cdiv(d.N, v.bn) * split > num_cu();
+    if (v.tr && !spills && cdiv(d.N, 64) > num_cu() && d.K > 1408) return false;
+    return cdiv(d.K, choose_split(ring, d)) <= (v.tr ? 3840 : 2560) * (spills ? 2 : 1);
 }
 
 // The selector's own choice among the variants that fit (cost model); with
@@ -377,9 +398,8 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
         if (v.ring) { if (ring < 0 || c < best_ring) { ring = i; best_ring = c; } }
         else if (pick < 0 || c < best) { pick = i; best = c; pick_split = split; }
     }
-    // a streaming kernel wins whenever one applies
     for (int r = 3; r >= 1; --r)
-        if (stream[r] >= 0) return stream[r];
+        if (stream[r] >= 0) return ring >= 0 && ring_ahead_of_streaming(g_variants[ring], g_variants[stream[r]], d) ? ring : stream[r];
     // A K split of an fp32 launch costs some microseconds more than the model has for it: 504x1396x2380 NT in five slices
     // of 128x128 tiles 42.1 us, 36.1 in ring tiles unsplit; 112x208x816 NN 10.0 in 13 slices, 8.2 in ring tiles.
     // (2560x1340x2164 TT, unsplit in both, 134 us with the 128 x 128 tile and 147 in ring tiles.)  It counts against the

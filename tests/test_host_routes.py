@@ -60,6 +60,14 @@ def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
     ("bf16", 0, 1, 100, 4096, 4096, True),
     ("f16", 0, 1, 64, 4096, 8192, True),         # 33 to 64 rows against a small streamed operand
     ("f16", 0, 1, 32, 4096, 8192, False),
+    ("bf16", 0, 1, 50, 23232, 1152, False),      # ... but not where the streaming kernel needs no K split
+    ("bf16", 0, 1, 50, 6144, 4992, False),       # nor where a slice of the ring kernel is deep
+    ("bf16", 0, 1, 40, 4800, 7552, True),
+    ("f16", 0, 1, 36, 11008, 2304, True),        # the streaming kernel's slices spill into a second round
+    ("bf16", 0, 1, 62, 5632, 6272, False),
+    ("bf16", 0, 0, 46, 18368, 2048, False),      # B stored K x N: a second round of ring tiles on a long K
+    ("f16", 0, 0, 37, 10112, 3200, True),        # ring tiles, not the 64x128 ones
+    ("bf16", 0, 0, 43, 26432, 1408, True),
     ("bf16", 0, 1, 8192, 8192, 8192, False),
 ])
 def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
