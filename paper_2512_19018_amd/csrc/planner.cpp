@@ -377,9 +377,14 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             // the M x K operand is tall enough for its re-reads to matter (every workgroup reads its K slice of
             // all of it: bf16 64x8192x28672 takes 101.9 us with 128 rows per workgroup, 126.4 us with 64)
             // (but not where tiles of half the columns fill it in one round without a K split: 64x16384x8192 50.1 us
-            // against 56.9; a second round, nearly empty or not, costs more: 64x25664x14080 164 against 135)
-            const int64_t fill = (int64_t)num_cu() * 4;
-            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || (cdiv(d.N, v.bn / 2) * 5 >= fill && cdiv(d.N, v.bn / 2) <= num_cu()))) continue;
+            // against 56.9; a second round, nearly empty or not, costs more: 64x25664x14080 164 against 135.  A workgroup
+            // of 64 columns reads as much of A as one of 128, and over a long K that outweighs the reduction, the
+            // sooner the fewer CUs share it: up to K = 14336 with 15/16 of the CUs at work, up to 6656 with fewer -
+            // 59x16320x13952 87.5 us against 90.2, 64x16384x15488 103 and 97; 56x13184x6784 40.8 and 40.7,
+            // 48x13824x11136 67.3 and 60.9, 64x14080x12928 80.0 and 77.9, the operand cold in the caches)
+            const int64_t fill = (int64_t)num_cu() * 4, halves = cdiv(d.N, v.bn / 2);
+            const bool halves_fill = halves <= num_cu() && (halves * 16 >= (int64_t)num_cu() * 15 ? d.K <= 14336 : halves * 5 >= fill && d.K <= 6656);
+            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || halves_fill)) continue;
             if (stream[v.stream_rank] < 0) stream[v.stream_rank] = i;
             continue;
         }

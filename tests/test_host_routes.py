@@ -75,9 +75,14 @@ def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
     assert ("q" in name.split("_")[1]) == ring, name
 
 
-@pytest.mark.parametrize("N,columns", [(13312, 64), (16384, 64), (16448, 128), (25664, 128), (26624, 128)])
-def test_streaming_tiles_of_64_columns_only_in_one_round(N, columns):
-    _, name, _, _, _ = plan("bf16", 0, 1, 64, N, 14080)
+# 64 rows, unsplit with 64 columns per tile against 128 and a K split (bf16, us, the operand cold in the caches):
+# 16384x8192 50.1 / 56.9, 13312x4096 26.1 / 27.4, 14080x12928 80.0 / 77.9, 13312x10624 62.4 / 57.9, 16320x13952 87.5 / 90.2,
+# 16384x15488 103 / 97
+@pytest.mark.parametrize("N,K,columns", [(13312, 4096, 64), (13312, 10624, 128), (14080, 12928, 128), (16384, 8192, 64),
+                                         (16320, 13952, 64), (16384, 15488, 128), (16448, 14080, 128), (25664, 14080, 128),
+                                         (26624, 14080, 128)])
+def test_streaming_tiles_of_64_columns_only_in_one_round(N, K, columns):
+    _, name, _, _, _ = plan("bf16", 0, 1, 64, N, K)
     assert name == "bf16_skinny_m64n%dk128s3_nt" % columns
 
 
