@@ -687,30 +687,46 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
                          : (char *)p.C + (m_first * ld + n) * OES);
     const int rows_left = interior ? 32 * SLABS : (int)(p.M - m_first < 32 * SLABS ? p.M - m_first : 32 * SLABS);
     const int rows_ok = interior || n + EPL <= p.N ? rows_left : 0;     // rows of this lane's columns that C has
+    // Which parts of the step the launch has (1 C_in, 2 bias per column, 4 bias per row, 8 and up the activation), branched
+    // on once per run.  Hidden from the compiler, which would otherwise write the rest of the epilogue out once for every
+    // combination.
+    int kinds = __builtin_amdgcn_readfirstlane((beta != 0.0f ? 1 : 0) | (bias_kind == BIAS_PER_COLUMN ? 2 : 0) |
+                                               (bias_kind == BIAS_PER_ROW ? 4 : 0) | act << 3);
+    asm volatile("" : "+s"(kinds));
     float bcol[EPL];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) bcol[e] = bias_kind == BIAS_PER_COLUMN && n + e < p.N ? p.hook.bias[n + e] : 0.0f;
+    for (int e = 0; e < EPL; ++e) bcol[e] = 0.0f;
+    if ((kinds & 2) && rows_ok > 0) {                              // (then all of the lane's columns are C's)
+#pragma unroll
+        for (int h = 0; h < EPL / 4; ++h) {
+            const f32x4 b = load_loose<f32x4, 4>(p.hook.bias + n + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bcol[4 * h + e] = b[e];
+        }
+    }
     // a slab's row groups go in runs of at most eight (what a run holds in registers: 8 x 16 bytes of C_in on their way,
     // the values, their successors' C_in)
     constexpr int GR = G < 8 ? G : 8, RUNS = G / GR;
-    u32x4 cin[GR];
-    float brow[GR];
+    // (a run's own set, written only where the launch has that part: with masked loads of no rows instead, launches
+    // without C_in and per-row bias lost 0.3 us and more, f16 2402x1288x752 NT with bias and ReLU 12.4 us against 11.6; one
+    // set for all runs, kept over the branches, holds every load up until it has left for the registers it is kept in)
+    u32x4 cin[SLABS * RUNS][GR];
+    float brow[SLABS * RUNS][GR];
     auto fetch = [&](int run) {                                    // run: 32 rows x RUNS per slab, counted through
-        // (the choices are hidden from the compiler, which would otherwise write the rest of the epilogue out once for
-        // every combination of them)
-        int rows_c = beta != 0.0f ? rows_ok : 0, rows_b = bias_kind == BIAS_PER_ROW ? rows_left : 0;
+        if ((kinds & 5) == 0) return;
+        int rows_c = kinds & 1 ? rows_ok : 0, rows_b = kinds & 4 ? rows_ok : 0;
         asm volatile("" : "+v"(rows_c), "+v"(rows_b));
 #pragma unroll
         for (int g = 0; g < GR; ++g) {
             const int r = (run * GR + g) * RPI;
-            cin[g] = u32x4{0u, 0u, 0u, 0u};
-            if (r < rows_c) cin[g] = load_loose<u32x4, OES>(out + r * ld * OES);
+            cin[run][g] = u32x4{0u, 0u, 0u, 0u};
+            if (r < rows_c) cin[run][g] = load_loose<u32x4, OES>(out + r * ld * OES);
         }
 #pragma unroll
         for (int g = 0; g < GR; ++g) {
             const int r = (run * GR + g) * RPI;
-            brow[g] = 0.0f;
-            if (r < rows_b) brow[g] = p.hook.bias[m_first + r];
+            brow[run][g] = 0.0f;
+            if (r < rows_b) brow[run][g] = p.hook.bias[m_first + r];
         }
     };
     fetch(0);
@@ -736,13 +752,12 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
         for (int g = 0; g < GR; ++g)
 #pragma unroll
             for (int e = 0; e < EPL; ++e) x[g][e] *= alpha;
-        int kinds = __builtin_amdgcn_readfirstlane((beta != 0.0f ? 1 : 0) | (bias_kind != BIAS_NONE ? 2 : 0) | act << 2);
         asm volatile("" : "+s"(kinds));
         if (kinds & 1) {
 #pragma unroll
             for (int g = 0; g < GR; ++g) {
                 union { u32x4 u; float f[4]; _Float16 h[8]; __bf16 b[8]; } c;
-                c.u = cin[g];
+                c.u = cin[run][g];
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) x[g][e] += beta * (ODT == DT_F32 ? c.f[e & 3] : ODT == DT_F16 ? (float)c.h[e] : (float)c.b[e]);
             }
@@ -751,11 +766,17 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
 #pragma unroll
             for (int g = 0; g < GR; ++g)
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) x[g][e] += bcol[e] + brow[g];      // (one of the two is zero)
+                for (int e = 0; e < EPL; ++e) x[g][e] += bcol[e];
         }
-        if (kinds >> 2) {
+        if (kinds & 4) {
 #pragma unroll
-            for (int g = 0; g < GR; ++g) hook_apply(kinds >> 2, false, x[g], x[g]);
+            for (int g = 0; g < GR; ++g)
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) x[g][e] += brow[run][g];
+        }
+        if (kinds >> 3) {
+#pragma unroll
+            for (int g = 0; g < GR; ++g) hook_apply(kinds >> 3, false, x[g], x[g]);
         }
         if (run + 1 < SLABS * RUNS) fetch(run + 1);
 #pragma unroll
@@ -790,35 +811,44 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     char *scr = lds + wave * (32 * SROW);
     const bool hooked = !po.base && hook_active(p.hook);
     const bool c_f32 = C::DT != DT_F32 && (p.flags & GF_C_F32);        // fp32 C of a 16-bit kernel
-    // Plain runs of the 16-bit kernels on interior tiles (beta == 0, no fused step): the slab
+    // Plain runs of the 16-bit kernels (beta == 0, no fused step) on interior tiles, and on edge tiles that C ends in at a
+    // whole 16-byte piece (short launches wait for those: bf16 3648x896x448 TN 7.6 us, 8.6 with the edge tiles going through
+    // epilogue_vector; f16 2176x1344x768 NT 9.1 and 10.3): the slab
     // goes through LDS already scaled and rounded, 8 bytes per lane and 4-column group, which
     // halves the LDS traffic of the turnaround; the way back is a 16-byte read and the store.
     // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
     // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
     if constexpr (C::DT != DT_F32) {
-        if (interior && !po.base && !c_f32 && p.beta == 0.0f && !hooked) {
+        if ((interior || p.N % 8 == 0) && !po.base && !c_f32 && p.beta == 0.0f && !hooked) {
             constexpr int LPR = C::WTN * 2 / 16, RPI = 64 / LPR;       // lanes per row, rows per store instruction
             constexpr int SROW16 = C::WTN * 2 + 16;
             constexpr int G = 32 / RPI;
             const int orow = lane / LPR, ocol = (lane % LPR) * 8;
             char *scr16 = lds + wave * (32 * SROW16);
-            write16(0, scr16);
+            const int64_t m_first = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
+            uint16_t *out = (uint16_t *)p.C + m_first * p.ldc + n;
+            auto plain = [&](auto edge_c) {
+                constexpr bool EDGE = decltype(edge_c)::value != 0;
+                const int rows_ok = n < p.N ? (int)(p.M - m_first < C::WTM ? p.M - m_first : C::WTM) : 0;   // ... that C has (EDGE)
+                write16(0, scr16);
 #pragma unroll
-            for (int mi = 0; mi < SLABS; ++mi) {
-                u32x4 v[G];
+                for (int mi = 0; mi < SLABS; ++mi) {
+                    u32x4 v[G];
 #pragma unroll
-                for (int g = 0; g < G; ++g)
-                    v[g] = *(const u32x4 *)(scr16 + (g * RPI + orow) * SROW16 + ocol * 2);
-                if (mi + 1 < SLABS) write16(mi + 1, scr16);          // in-order LDS: lands after the reads above
+                    for (int g = 0; g < G; ++g)
+                        v[g] = *(const u32x4 *)(scr16 + (g * RPI + orow) * SROW16 + ocol * 2);
+                    if (mi + 1 < SLABS) write16(mi + 1, scr16);      // in-order LDS: lands after the reads above
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const int64_t m = m0 + wm * C::WTM + mi * 32 + g * RPI + orow;
-                    const int64_t n = n0 + wn * C::WTN + ocol;
-                    const bool upper = RPI >= 32 ? orow >= 16 : RPI == 16 ? (g & 1) : ((g * RPI) >> 4) & 1;   // rows 16..31
-                    const u32x4 o = upper ? u32x4{v[g][2], v[g][3], v[g][0], v[g][1]} : v[g];
-                    store_loose<u32x4, 2>((uint16_t *)p.C + m * p.ldc + n, o);
+                    for (int g = 0; g < G; ++g) {
+                        const int r = mi * 32 + g * RPI;
+                        const bool upper = RPI >= 32 ? orow >= 16 : RPI == 16 ? (g & 1) : ((g * RPI) >> 4) & 1;   // rows 16..31
+                        const u32x4 o = upper ? u32x4{v[g][2], v[g][3], v[g][0], v[g][1]} : v[g];
+                        if (!EDGE || r < rows_ok) store_loose<u32x4, 2>(out + (int64_t)r * p.ldc, o);
+                    }
                 }
-            }
+            };
+            if (interior) plain(IC<0>{});
+            else plain(IC<1>{});
             return;
         }
     }
