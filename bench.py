@@ -18,7 +18,9 @@ load, and the calibration loop is a different load; the count is in the line as
 torch.matmul on the same buffers as context; the CPU oracle on a bounded sample
 of rows; then the other workloads the same way with shorter CPU samples.
 
-Prints ONE JSON line.
+Prints ONE JSON line, short enough to survive where only the end of the output is
+kept: of the other workloads the figures that the headline has, rounded.  Their
+full records go to the file named by --records.
 """
 from __future__ import annotations
 
@@ -93,6 +95,51 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+LINE_LIMIT = 8192                                         # bytes of the JSON line
+
+
+def rounded(v, digits=6):
+    """v with every float in it at `digits` significant digits."""
+    if isinstance(v, float):
+        return float("%.*g" % (digits, v))
+    if isinstance(v, dict):
+        return {k: rounded(x, digits) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x, digits) for x in v]
+    return v
+
+
+def short_record(r):
+    """What the JSON line says of a workload beside the headline's: shape and type are those of its name."""
+    plan = dict(w.split("=", 1) for w in r["plan"].split() if "=" in w)
+    s = {"name": r["workload"], "ms_per_step": r["ms_per_step"], "tflops": r["tflops"], "gbs": r["gbs_events"],
+         "bound": r["roofline"]["bound"], "frac": r["roofline"]["frac"],
+         "plan": "%s/%s" % (plan.get("variant", "?").split(":")[-1], plan.get("split", "?"))}
+    for k in ("torch_tflops", "pct_of_library"):
+        if r.get(k) is not None:
+            s[k] = r[k]
+    if r.get("cpu_baseline"):
+        s["cpu_tflops"] = r["cpu_baseline"]["value"]
+    return s
+
+
+def result_line(out, records):
+    """The JSON line: the headline's fields and a short record of each other workload; the fields that the contract does
+    not name go first where it would be too long."""
+    out = dict(out)
+    value, ms = out["value"], out["ms_per_step"]
+    if records:
+        out["workloads"] = rounded([short_record(r) for r in records], 4)
+    out = rounded(out)
+    out["value"], out["ms_per_step"] = value, ms
+    for drop in (None, "rocm_smi", "per_launch_ms", "workloads"):
+        out.pop(drop, None)
+        line = json.dumps(out)
+        if len(line) <= LINE_LIMIT:
+            break
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -106,6 +153,7 @@ def main():
                          "short warmup does not time the power management's reaction to the change of load")
     ap.add_argument("--workload", default="C3")
     ap.add_argument("--only", action="store_true", help="time only the headline workload")
+    ap.add_argument("--records", default=None, metavar="FILE", help="write the workloads' full records (JSON) to FILE")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU-oracle baseline leg")
     ap.add_argument("--no-torch", action="store_true", help="skip the torch.matmul context rows")
     ap.add_argument("--variant", default=None, help="force a kernel variant, by id or name (sweeps)")
@@ -499,8 +547,8 @@ def main():
         out["cpu_baseline"] = cpu_leg(w, host, 15.0)
     del host
 
+    others = []
     if not args.only:
-        others = []
         for name in ["C1", "C2", "C3b", "C4", "C5", "P2k_f32", "P4k_f32", "P2k_f16", "P4k_f16", "T4k_bf16_tn", "T4k_bf16_tt", "SK_bf16",
                      "S32_bf16", "S64_f16", "S16_f32", "S16_bf16_kn", "S16_f32_kn", "S64_f32", "S32_f16_tn", "S16_bf16_tt", "D128_bf16"]:
             if name == args.workload:
@@ -511,10 +559,11 @@ def main():
             log("[bench] %s: %.3f ms  %.1f TFLOP/s  %.0f GB/s  (%s)" % (name, r["event_ms_per_step"], r["tflops_events"],
                                                                         r["gbs_events"], r["plan"]))
             others.append(r)
-        out["workloads"] = others
     out["rocm_smi"] = {"before": smi_before, "after": smi_snapshot()}
-
-    print(json.dumps(out))
+    if args.records:
+        with open(args.records, "w") as f:
+            json.dump(dict(out, headline=head, workloads=others), f)
+    print(result_line(out, others), flush=True)
 
 
 if __name__ == "__main__":
