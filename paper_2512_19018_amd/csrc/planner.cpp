@@ -334,7 +334,9 @@ static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 // the caches: bf16 64x15360x1536 NT (47 MB) 13.1 us against 16.4 in two slices, f16 64x10752x2048 (44 MB) 14.4 and 16.2;
 // NN bf16 51x14016x2432 (68 MB) 16.0 and 21.3.  Where the slices of the streaming kernel spill into a second round they
 // cost more yet (36x11008x2304 NT, 258 workgroups, 23.3 us, 16.1 in ring tiles; 33x6592x4864 23.3 and 20.3, but
-// 62x5632x6272 23.6 and 27.7).  Not where
+// 62x5632x6272 23.6 and 27.7).  With A stored K x M, which the ring kernels read as it lies, the streaming kernel has the
+// transposition as well: 120 of 120 shapes of 9 to 76 MB ahead in ring tiles (bf16 40x12800x1024 TN 10.3 us and 20.9, f16
+// 56x24128x1536 TT 21.1 and 26.3, 40x4608x8192 TN 23.3 and 28.8).  Else not where
 //  - the streaming kernel needs no split (bf16 50x23232x1152 NT 14.4 us, 16.6 in ring tiles);
 //  - a slice of the ring kernel is deep, few workgroups then reading at one CU's rate (bf16 50x6144x4992 NT in two slices
 //    22.5 us, streamed 19.6; f16 42x10112x3200 21.9 and 19.9; NN, whose rows of B the streaming kernel reads at a lower
@@ -345,7 +347,8 @@ static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 // f16 37x10112x3200 NN 18.2 in ring tiles, 19.9 streamed, 22.7 in 64x128 tiles).
 static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const peak_gemm_desc_t &d)
 {
-    if (d.M <= 32 || d.dtype == PEAK_DT_F32 || stages_a(v, d.transA) || d.N * d.K * esize_of(d.dtype) > (int64_t)72 << 20) return false;
+    if (d.M <= 32 || d.dtype == PEAK_DT_F32 || d.N * d.K * esize_of(d.dtype) > (int64_t)72 << 20) return false;
+    if (stages_a(v, d.transA)) return true;
     const int split = skinny_split(d.N, d.K, v.bn, v.bk);
     if (split == 1) return false;
     const bool spills = cdiv(d.N, v.bn) * split > num_cu();

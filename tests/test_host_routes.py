@@ -68,6 +68,11 @@ def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
     ("bf16", 0, 0, 46, 18368, 2048, False),      # B stored K x N: a second round of ring tiles on a long K
     ("f16", 0, 0, 37, 10112, 3200, True),        # ring tiles, not the 64x128 ones
     ("bf16", 0, 0, 43, 26432, 1408, True),
+    ("bf16", 1, 0, 40, 12800, 1024, True),       # A stored K x M: no transposition first
+    ("f16", 1, 1, 56, 24128, 1536, True),
+    ("f16", 1, 0, 32, 4096, 8192, False),
+    ("bf16", 1, 1, 64, 8192, 8192, False),       # too large an operand to be read by small tiles
+    ("bf16", 1, 1, 33, 8192, 2048, False),       # rows of A that the ring kernels cannot copy
     ("bf16", 0, 1, 8192, 8192, 8192, False),
 ])
 def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
