@@ -1,6 +1,7 @@
 """Plans that write aligned copies of their operands first ("pack=" in the plan description): odd sizes and leading
 dimensions, blocks of NaN-filled larger matrices at odd addresses, one operand aligned and the other not, all layouts;
-a run without room for the copies takes the register-staged stand-in, and so does the entry point with the fixed array."""
+copies behind the partials of a K split and of a cut last round; a run without room for the copies, and the entry point
+with the fixed array where they outgrow it, takes the register-staged stand-in."""
 import itertools
 import re
 
@@ -29,7 +30,7 @@ def _block(gu, values, pad, off, dtype):
 
 @pytest.mark.parametrize("dtype,transA,transB,sizes,blocks", [
     (dt, ta, tb, s, b) for dt in (pi.F32, pi.BF16, pi.F16) for ta, tb in itertools.product([0, 1], [0, 1])
-    for s, b in [((2049, 2047, 1031), (1, 1)), ((2056, 2048, 1024), (3, 0))]])
+    for s, b in [((2049, 2047, 1031), (1, 1)), ((2056, 2048, 1024), (3, 0)), ((2056, 2048, 1024), (0, 3))]])
 def test_aligned_copies(gu, oracle, dtype, transA, transB, sizes, blocks):
     import torch
     pg = gu.pg
@@ -46,7 +47,7 @@ def test_aligned_copies(gu, oracle, dtype, transA, transB, sizes, blocks):
     with pg.Plan(M, N, K, dtype, transA, transB, lda, ldb, N) as plan:
         info = plan.info()
         pack = int(re.search(r"pack=(\d)", info).group(1))
-        assert pack == (3 if blocks[1] else 1) and "_r" in re.search(r"unaligned=(\S+)", info).group(1), info
+        assert pack == (3 if K % 8 else (1 if blocks[0] else 0) | (2 if blocks[1] else 0)) and "_r" in re.search(r"unaligned=(\S+)", info).group(1), info
         args = (0.5, dA.data_ptr() + blocks[0] * es, dB.data_ptr() + blocks[1] * es, 2.0)
         for nbytes in (plan.workspace_bytes, pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, None):
             dC = gu.to_dev(lc)
@@ -60,22 +61,64 @@ def test_aligned_copies(gu, oracle, dtype, transA, transB, sizes, blocks):
             gu.check_against_oracle(oracle, got, dtype, transA, transB, M, N, K, 0.5, A, B, 2.0, lc, rows=rows, what=(info, nbytes))
 
 
-def test_workspace_off_256_bytes_takes_the_stand_in(gu):
+def _product(gu, dtype, transA, transB, M, N, K, seed):
+    """Stored whole matrices of a product on the host, their device copies, and C full of NaN."""
+    A, B = (pi.store(pi.logical_matrix(seed, i, *s, "uniform", 1.0, dtype), bool(t)) for i, (s, t) in enumerate((((M, K), transA), ((K, N), transB))))
+    return A, B, gu.to_dev(A), gu.to_dev(B), gu.to_dev(gu.nan_fill(M, N, dtype))
+
+
+def _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, what):
     import torch
-    pg = gu.pg
-    M, N, K = 4097, 4099, 515                                   # more tiles than the stand-in ever splits K for
-    A, B = (torch.randn(r, K, device="cuda", dtype=torch.bfloat16) for r in (M, N))
+    torch.cuda.synchronize()
+    rows = sorted({0, 1, 127, 128, 255, 256, 511, M // 2, M - 130, M - 9, M - 2, M - 1} & set(range(M)))
+    got = pi.to_f64(gu.from_dev(dC, dtype), dtype)
+    gu.check_against_oracle(oracle, got, dtype, transA, transB, M, N, K, 1.0, A, B, 0.0, None, rows=rows, what=what)
+
+
+@pytest.mark.parametrize("dtype,transA,transB,M,N,K,streamk", [
+    (pi.F32, 1, 0, 759, 1437, 853, False), (pi.F16, 0, 0, 1353, 747, 3209, False), (pi.BF16, 1, 1, 811, 1383, 3221, False),
+    (pi.F16, 0, 1, 3497, 4657, 611, True), (pi.BF16, 1, 1, 4263, 3875, 801, True)])
+def test_copies_behind_partials(gu, oracle, dtype, transA, transB, M, N, K, streamk):
+    import torch
+    A, B, dA, dB, dC = _product(gu, dtype, transA, transB, M, N, K, 41)
+    with gu.pg.Plan(M, N, K, dtype, transA, transB) as plan:
+        info = plan.info()
+        fields = dict(w.split("=", 1) for w in info.split() if "=" in w)
+        assert fields["pack"] == "3" and int(fields["split"]) > 1 and (fields["streamk"] != "0") == streamk, info
+        ws = torch.full((plan.workspace_bytes,), 0xFF, dtype=torch.uint8, device="cuda")       # NaN wherever nothing is written
+        plan.run(1.0, dA.data_ptr(), dB.data_ptr(), 0.0, dC.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, info)
+
+
+# (products of more tiles than the stand-in splits K for: it needs no workspace and writes nothing to the one it is given)
+@pytest.mark.parametrize("dtype,transA,transB,M,N,K", [
+    (dt, ta, tb, 2049, 2047, 1031) for dt in (pi.F32, pi.BF16) for ta, tb in itertools.product([0, 1], [0, 1])] + [(pi.F16, 0, 1, 4097, 4099, 515)])
+def test_workspace_without_room_for_the_copies_takes_the_stand_in(gu, oracle, dtype, transA, transB, M, N, K):
+    import torch
+    A, B, dA, dB, dC = _product(gu, dtype, transA, transB, M, N, K, 42)
     stream = torch.cuda.current_stream().cuda_stream
-    with pg.Plan(M, N, K, pi.BF16, 0, 1, K, K, N) as plan:
-        assert "pack=3" in plan.info(), plan.info()
-        ws = torch.empty(plan.workspace_bytes + 16, dtype=torch.uint8, device="cuda")
-        out = []
-        for ptr, nbytes in ((ws.data_ptr() + 16, plan.workspace_bytes), (0, 0)):
-            C = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
-            plan.run(1.0, A.data_ptr(), B.data_ptr(), 0.0, C.data_ptr(), ptr, nbytes, stream)
-            torch.cuda.synchronize()
-            out.append(C)
-    assert torch.equal(out[0], out[1])                           # (NaN would not compare equal)
+    with gu.pg.Plan(M, N, K, dtype, transA, transB) as plan:
+        assert "pack=3" in plan.info() and plan.workspace_bytes > 0, plan.info()
+        ws = torch.full((plan.workspace_bytes + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+        # one byte short, off 256 bytes, none at all
+        for ptr, nbytes in ((ws.data_ptr(), plan.workspace_bytes - 1), (ws.data_ptr() + 16, plan.workspace_bytes), (0, 0)):
+            dC.copy_(gu.to_dev(gu.nan_fill(M, N, dtype)))
+            plan.run(1.0, dA.data_ptr(), dB.data_ptr(), 0.0, dC.data_ptr(), ptr, nbytes, stream)
+            _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, (plan.info(), nbytes))
+        assert bool((ws == 0xA5).all())                          # no copies were made
+        plan.run(1.0, dA.data_ptr(), dB.data_ptr(), 0.0, dC.data_ptr(), ws.data_ptr(), plan.workspace_bytes, stream)
+        assert not bool((ws == 0xA5).all())
+
+
+@pytest.mark.parametrize("dtype,transA,transB,M,N,K", [(pi.BF16, 0, 1, 4097, 4099, 2051), (pi.F32, 1, 0, 2049, 3001, 2051)])
+def test_copies_larger_than_the_fixed_array_take_the_stand_in(gu, oracle, dtype, transA, transB, M, N, K):
+    import torch
+    A, B, dA, dB, dC = _product(gu, dtype, transA, transB, M, N, K, 43)
+    with gu.pg.Plan(M, N, K, dtype, transA, transB) as plan:
+        assert "pack=3" in plan.info() and plan.workspace_bytes > gu.pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, plan.info()
+        assert gu.pg.peak_gemm_run_static(plan.handle, 1.0, dA.data_ptr(), dB.data_ptr(), 0.0, dC.data_ptr(),
+                                          torch.cuda.current_stream().cuda_stream) == gu.pg.PEAK_OK
+        _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, plan.info())
 
 
 @pytest.mark.parametrize("static", [0, 1])
