@@ -112,3 +112,12 @@ def test_table_rows_of_unaligned_products_are_the_plan(tmp_path, row, sizes):
         assert plan(*args, M + 2, N, K)[3] == 3
     finally:
         pg.peak_gemm_load_tuning(SHIPPED_TABLE)
+
+
+def test_tuner_leaves_plans_that_no_row_can_ask_for():
+    """A row is taken as it is: one for a product whose own plan makes aligned copies or cuts its last round would lose that."""
+    from paper_2512_19018_amd import tune
+    assert tune.beyond_rows(plan("bf16", 0, 1, 4095, 4095, 4095)[0].info()) == "aligned copies"
+    assert tune.beyond_rows(plan("bf16", 0, 1, 4096, 5120, 5120, flags=pg.force_flags(streamk=True))[0].info()) == "stream-K"
+    assert tune.beyond_rows(plan("bf16", 0, 1, 8192, 8192, 8192)[0].info()) is None
+    assert tune.beyond_rows(plan("bf16", 0, 1, 101, 103, 107)[0].info()) is None
