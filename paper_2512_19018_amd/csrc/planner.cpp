@@ -337,12 +337,13 @@ static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 // 62x5632x6272 23.6 and 27.7).  With A stored K x M, which the ring kernels read as it lies, the streaming kernel has the
 // transposition as well: 120 of 120 shapes of 9 to 76 MB ahead in ring tiles (bf16 40x12800x1024 TN 10.3 us and 20.9, f16
 // 56x24128x1536 TT 21.1 and 26.3, 40x4608x8192 TN 23.3 and 28.8).  Else not where
-//  - the streaming kernel needs no split (bf16 50x23232x1152 NT 14.4 us, 16.6 in ring tiles);
-//  - a slice of the ring kernel is deep, few workgroups then reading at one CU's rate (bf16 50x6144x4992 NT in two slices
-//    22.5 us, streamed 19.6; f16 42x10112x3200 21.9 and 19.9; NN, whose rows of B the streaming kernel reads at a lower
-//    rate, 63x8576x4224 25.9 and 23.7);
-//  - B is stored K x N and the 64-column tiles begin a second round, unless K is short (46x18368x2048 23.1 and 21.2,
-//    41x20736x1536 21.5 and 20.1, 43x26432x1408 19.3 and 20.9).
+//  - the streaming kernel needs no split (bf16 50x23232x1152 NT 14.4 us, 16.6 in ring tiles; with tiles of 64 columns, one
+//    round of either, the ring kernels are level or ahead: f16 48x13888x1152 10.5 and 11.0);
+//  - a slice of the ring kernel is deep, few workgroups then reading at one CU's rate.  Streaming over ring time at 3968 to
+//    5120 k per slice: NT 0.90 in the mean, the operand cold, and 1.18 with it in the last-level cache; NN 0.96 and 1.32;
+//    at 2688 to 3840 k 1.02 and 1.25, 1.12 and 1.45 (f16 36x6016x5120 NT 0.85, bf16 59x4416x4224 NT 0.86);
+//  - B is stored K x N and the 64-column tiles begin a second round, unless K is short (46x18368x2048 23.1 us and 21.2,
+//    46x20672x1664 20.4 and 20.9, 43x26432x1408 19.3 and 20.9).
 // And for the ring kernels only: the other tiled kernels, priced for full tiles, lose either way (50x23232x1152 18.3 us;
 // f16 37x10112x3200 NN 18.2 in ring tiles, 19.9 streamed, 22.7 in 64x128 tiles).
 static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const peak_gemm_desc_t &d)
@@ -350,10 +351,10 @@ static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const
     if (d.M <= 32 || d.dtype == PEAK_DT_F32 || d.N * d.K * esize_of(d.dtype) > (int64_t)72 << 20) return false;
     if (stages_a(v, d.transA)) return true;
     const int split = skinny_split(d.N, d.K, v.bn, v.bk);
-    if (split == 1) return false;
+    if (split == 1) return v.bn < 128;
     const bool spills = cdiv(d.N, v.bn) * split > num_cu();
-    if (v.tr && !spills && cdiv(d.N, 64) > num_cu() && d.K > 1408) return false;
-    return cdiv(d.K, choose_split(ring, d)) <= (v.tr ? 3840 : 2560) * (spills ? 2 : 1);
+    if (v.tr && !spills && cdiv(d.N, 64) > num_cu() && d.K > 1664) return false;
+    return cdiv(d.K, choose_split(ring, d)) <= (v.tr || spills ? 5120 : 3840);
 }
 
 // The selector's own choice among the variants that fit (cost model); with

@@ -63,6 +63,9 @@ def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
     ("bf16", 0, 1, 50, 23232, 1152, False),      # ... but not where the streaming kernel needs no K split
     ("bf16", 0, 1, 50, 6144, 4992, False),       # nor where a slice of the ring kernel is deep
     ("bf16", 0, 1, 40, 4800, 7552, True),
+    ("bf16", 0, 1, 64, 8192, 2688, True),
+    ("f16", 0, 0, 64, 6848, 4160, True),
+    ("f16", 0, 1, 48, 13888, 1152, True),        # unsplit in 64-column tiles: level cold, ring ahead warm
     ("f16", 0, 1, 36, 11008, 2304, True),        # the streaming kernel's slices spill into a second round
     ("bf16", 0, 1, 62, 5632, 6272, False),
     ("bf16", 0, 0, 46, 18368, 2048, False),      # B stored K x N: a second round of ring tiles on a long K
