@@ -85,20 +85,6 @@ struct CfgAny {
     static constexpr int kx_step(int e) { return (X * ESZ >= 256 ? e : (e & 2) | (e & 1) << 2) * (X * ESZ); }
 };
 
-// Up to a chunk of elements fetched one by one, zeros behind them: operands with fewer elements per row than a chunk.
-template <int DT>
-PEAK_DEV u32x4 load_elems(const char *src, int n)
-{
-    constexpr int EPC = DT == DT_F32 ? 4 : 8, ESZ = 16 / EPC;
-    u32x4 v = {0u, 0u, 0u, 0u};
-#pragma unroll 1
-    for (int e = (n < EPC ? n : EPC) - 1; e >= 0; --e) {        // each one pushed in below those behind it
-        if constexpr (DT == DT_F32) v = u32x4{*(const uint32_t *)(src + e * ESZ), v[0], v[1], v[2]};
-        else v = u32x4{v[0] << 16 | *(const uint16_t *)(src + e * ESZ), v[1] << 16 | v[0] >> 16, v[2] << 16 | v[1] >> 16, v[3] << 16 | v[2] >> 16};
-    }
-    return v;
-}
-
 // Operand that runs along K: ROWS rows x K.
 template <class C, int ROWS>
 struct AnyK {
@@ -340,30 +326,30 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
     };
 
     auto multiply = [&](const u32x4 (&af)[C::MB], const u32x4 (&bf)[C::NB]) {
-                            // (B's rows feed the instruction's row operand: a lane ends with 4 consecutive n of one m)
-                            if constexpr (C::DT == DT_F32) {
-        #pragma unroll
-                                for (int e = 0; e < 4; ++e)
-        #pragma unroll
-                                    for (int nb = 0; nb < C::NB; ++nb)
-        #pragma unroll
-                                        for (int mb = 0; mb < C::MB; ++mb) {
-                                            const f32x4 b = __builtin_bit_cast(f32x4, bf[nb]), a = __builtin_bit_cast(f32x4, af[mb]);
-                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
-                                        }
-                            } else {
-        #pragma unroll
-                                for (int nb = 0; nb < C::NB; ++nb)
-        #pragma unroll
-                                    for (int mb = 0; mb < C::MB; ++mb) {
-                                        if constexpr (C::DT == DT_BF16)
-                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf[nb]),
-                                                                                                  __builtin_bit_cast(bf16x8, af[mb]), acc[mb][nb], 0, 0, 0);
-                                        else
-                                            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, bf[nb]),
-                                                                                                 __builtin_bit_cast(f16x8, af[mb]), acc[mb][nb], 0, 0, 0);
-                                    }
-                            }
+        // (B's rows feed the instruction's row operand: a lane ends with 4 consecutive n of one m)
+        if constexpr (C::DT == DT_F32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                    for (int mb = 0; mb < C::MB; ++mb) {
+                        const f32x4 b = __builtin_bit_cast(f32x4, bf[nb]), a = __builtin_bit_cast(f32x4, af[mb]);
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
+                    }
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb)
+#pragma unroll
+                for (int mb = 0; mb < C::MB; ++mb) {
+                    if constexpr (C::DT == DT_BF16)
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, bf[nb]),
+                                                                              __builtin_bit_cast(bf16x8, af[mb]), acc[mb][nb], 0, 0, 0);
+                    else
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, bf[nb]),
+                                                                             __builtin_bit_cast(f16x8, af[mb]), acc[mb][nb], 0, 0, 0);
+                }
+        }
     };
 
     // Ring form: direct copies, RING - 1 K tiles ahead.  For small tiles the loads' latency is the cost (a 64 x 64 x 64
@@ -496,9 +482,9 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
                 if (kt < KT) {
                     const char *st = lds + s * C::STAGE;
                     u32x4 af[2][C::MB], bf[2][C::NB];
-    #pragma unroll
+#pragma unroll
                     for (int i = 0; i < C::NB; ++i) bf[0][i] = frag_b(st, i, 0);
-    #pragma unroll
+#pragma unroll
                     for (int i = 0; i < C::MB; ++i) af[0][i] = frag_a(st, i, 0);
                     __builtin_amdgcn_sched_barrier(0);          // (the compiler would sink the reads to their first use)
                     if (kt + 1 < KT) store(kt + 1, 1 - s, va[set], vb[set]);
@@ -506,9 +492,9 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
                     static_for<C::ROUNDS>([&](auto rc) {
                         constexpr int r = decltype(rc)::value, cur = r & 1, nxt = cur ^ 1;
                         if constexpr (r + 1 < C::ROUNDS) {
-    #pragma unroll
+#pragma unroll
                             for (int i = 0; i < C::NB; ++i) bf[nxt][i] = frag_b(st, i, r + 1);
-    #pragma unroll
+#pragma unroll
                             for (int i = 0; i < C::MB; ++i) af[nxt][i] = frag_a(st, i, r + 1);
                             __builtin_amdgcn_sched_barrier(0);
                         }

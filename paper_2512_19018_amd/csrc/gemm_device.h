@@ -216,22 +216,16 @@ PEAK_DEV u32x4 shift_down(u32x4 v, int s)
 // tiles as well (cut into its elements, the edge workgroups of a 1023 x 2047 product held up all others).  Operands
 // of fewer elements per row than a chunk are fetched one by one.
 // ---------------------------------------------------------------------------
+// Up to a chunk of elements fetched one by one, zeros behind them: operands with fewer elements per row than a chunk.
 template <int DT>
-PEAK_DEV u32x4 load_chunk_elems(const void *base, int64_t idx0, int nvalid)
+PEAK_DEV u32x4 load_elems(const char *src, int n)
 {
-    // nvalid leading elements of the chunk come from memory, the rest are zero.
-    constexpr int EPC = DT == DT_F32 ? 4 : 8;
+    constexpr int EPC = DT == DT_F32 ? 4 : 8, ESZ = 16 / EPC;
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (DT == DT_F32) {
-        const uint32_t *p = (const uint32_t *)base;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e)
-            if (e < nvalid) v[e] = p[idx0 + e];
-    } else {
-        const uint16_t *p = (const uint16_t *)base;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e)
-            if (e < nvalid) v[e >> 1] |= (uint32_t)p[idx0 + e] << ((e & 1) * 16);
+#pragma unroll 1
+    for (int e = (n < EPC ? n : EPC) - 1; e >= 0; --e) {        // each one pushed in below those behind it
+        if constexpr (DT == DT_F32) v = u32x4{*(const uint32_t *)(src + e * ESZ), v[0], v[1], v[2]};
+        else v = u32x4{v[0] << 16 | *(const uint16_t *)(src + e * ESZ), v[1] << 16 | v[0] >> 16, v[2] << 16 | v[1] >> 16, v[3] << 16 | v[2] >> 16};
     }
     return v;
 }
@@ -278,7 +272,7 @@ struct LoaderT {
                 const int64_t kc = k < kend ? k : kend - 1;       // past the end: a valid row, zeroed below
                 u32x4 val;
                 if (!narrow) val = load_loose<u32x4, C::ESZ>(col_ptr[b] + kc * step);
-                else val = load_chunk_elems<C::DT>(col_ptr[b] + kc * step, 0, left - rb * E);
+                else val = load_elems<C::DT>(col_ptr[b] + kc * step, left - rb * E);
                 v[b][kk] = val;
             }
         }
@@ -1045,7 +1039,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     };
 
     // operand loaders
-    constexpr bool A_DIRECT = true, B_DIRECT = !C::B_T || C::B_TR;
+    constexpr bool B_DIRECT = !C::B_T || C::B_TR;
     static_assert(C::DIRECT && (!C::A_T || C::A_TR), "A goes to LDS directly (gemm_any_kernel takes what cannot)");
     LoaderDirect<C, C::BM> dA;
     LoaderDirect<C, C::BN> dB;
@@ -1053,18 +1047,18 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     LoaderDirectKN<C, C::BN> nB;
     LoaderT<C, C::BN> tB;
     // loads per thread and tile that stay in flight across iterations
-    constexpr int LA = !A_DIRECT ? 0 : (C::A_TR ? LoaderDirectKN<C, C::BM>::PER_WAVE : LoaderDirect<C, C::BM>::PER_WAVE);
+    constexpr int LA = C::A_TR ? LoaderDirectKN<C, C::BM>::PER_WAVE : LoaderDirect<C, C::BM>::PER_WAVE;
     constexpr int LB = !B_DIRECT ? 0 : (C::B_TR ? LoaderDirectKN<C, C::BN>::PER_WAVE : LoaderDirect<C, C::BN>::PER_WAVE);
     constexpr int DLOADS = LA + LB;
     constexpr int P = C::NS - 1;                            // prefetch distance of the direct loads
-    static_assert(!A_DIRECT || (C::A_TR ? LoaderDirectKN<C, C::BM>::NINST : LoaderDirect<C, C::BM>::NINST) % C::NW == 0, "every wave issues the same number of loads");
+    static_assert((C::A_TR ? LoaderDirectKN<C, C::BM>::NINST : LoaderDirect<C, C::BM>::NINST) % C::NW == 0, "every wave issues the same number of loads");
     static_assert(!B_DIRECT || (C::B_TR ? LoaderDirectKN<C, C::BN>::NINST : LoaderDirect<C, C::BN>::NINST) % C::NW == 0, "every wave issues the same number of loads");
 
     // valid k in the matrix's last K tile; only the slice that holds that tile can see a short one
     const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
     const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
-    if (A_DIRECT && !C::A_TR) dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
-    if (A_DIRECT && C::A_TR) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave, lane);
+    if (!C::A_TR) dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave, lane);
+    if (C::A_TR) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && !C::B_TR) dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave, lane);
     if (B_DIRECT && C::B_TR) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave, lane);
     if (!B_DIRECT) tB.init(p.B, p.ldb, n0, p.N, tid);
@@ -1095,8 +1089,8 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     auto issue_a = [&](int kt, int sa, auto part, auto nparts) {
         constexpr int PART = decltype(part)::value, NPARTS = decltype(nparts)::value;
         const int kr = rotated(kt < KT ? kt : KT - 1);
-        if (A_DIRECT && !C::A_TR) dA.template issue<PART, NPARTS>(a_stage(sa), kr, kr == tail_tile, wave);
-        if (A_DIRECT && C::A_TR) nA.template issue<PART, NPARTS>(a_stage(sa), kr, kr == tail_tile, wave);
+        if (!C::A_TR) dA.template issue<PART, NPARTS>(a_stage(sa), kr, kr == tail_tile, wave);
+        if (C::A_TR) nA.template issue<PART, NPARTS>(a_stage(sa), kr, kr == tail_tile, wave);
     };
     auto issue_b = [&](int kt, int sb, auto part, auto nparts) {
         constexpr int PART = decltype(part)::value, NPARTS = decltype(nparts)::value;
@@ -1147,8 +1141,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
         }
     };
 
-    constexpr bool ALL_DIRECT = A_DIRECT && B_DIRECT;
-    constexpr bool PREFETCH2 = ALL_DIRECT && C::NS == 2 && C::KG % 2 == 0 && !C::PP;
+        constexpr bool PREFETCH2 = B_DIRECT && C::NS == 2 && C::KG % 2 == 0 && !C::PP;
     if (C::PP) {
         // Alternating scheme.  Waves w and w+4 share a SIMD.  A K tile is worked off two
         // k-groups at a time; for each such part a wave first reads its fragments from
@@ -1539,7 +1532,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
 #pragma unroll
             for (int s = 0; s < P; ++s) issue_direct_all(s, s);
         }
-        if (!ALL_DIRECT) {
+        if (!B_DIRECT) {
             load_regs(0);
             store_regs(0);
         }
@@ -1550,11 +1543,11 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
                 if (kt < KT) {
                     if (DLOADS > 0) wait_vmcnt<(P - 1) * DLOADS>();     // tile kt has landed (this wave's part)
                     lds_barrier();                                      // everyone's part; stage (kt-1) % NS is free
-                    if (!ALL_DIRECT && kt + 1 < KT) load_regs(kt + 1);
+                    if (!B_DIRECT && kt + 1 < KT) load_regs(kt + 1);
                     // with one stage in flight the loads go out at once: each gets the whole step to land
                     if (DLOADS > 0) issue_direct_all(kt + P, (s + P) % C::NS);
                     compute(s, s);
-                    if (!ALL_DIRECT && kt + 1 < KT) store_regs((s + 1) % C::NS);
+                    if (!B_DIRECT && kt + 1 < KT) store_regs((s + 1) % C::NS);
                 }
             }
         }
@@ -1571,7 +1564,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
 #pragma unroll
             for (int s = 0; s < PN - 1; ++s) issue_direct_all(s, s);
         }
-        if (!ALL_DIRECT) {
+        if (!B_DIRECT) {
             load_regs(0);
             store_regs(0);
             if (KT > 1) {
@@ -1598,7 +1591,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
             for (int s = 0; s < PN; ++s) {
                 const int j = j0 + s;
                 if (j < KT) {
-                    if (!ALL_DIRECT && j + 2 < KT) load_regs(j + 2);
+                    if (!B_DIRECT && j + 2 < KT) load_regs(j + 2);
                     static_for<C::KG>([&](auto kgc) {
                         constexpr int kg = decltype(kgc)::value;
                         // next fragments: same tile, or the first k-group of tile j+1 (past the
@@ -1626,7 +1619,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
                         });
                         __builtin_amdgcn_sched_barrier(0);
                     });
-                    if (!ALL_DIRECT && j + 2 < KT) store_regs((s + 2) % PN);
+                    if (!B_DIRECT && j + 2 < KT) store_regs((s + 2) % PN);
                     if (DLOADS > 0) wait_vmcnt<(PN - 3) * DLOADS>();    // own loads of tile j+2 have landed
                     lds_barrier();                                      // tiles <= j+2 complete; stage j % NS is free
                 }

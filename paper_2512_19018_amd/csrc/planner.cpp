@@ -78,10 +78,11 @@ static bool variant_fits(const Variant &v, const peak_gemm_desc_t &d)
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The K split's part of a variant's cost (units of tiled_cost): slices write and re-read fp32 partials, 4.5 units per element and
-// slice (4.8 TB/s), plus the launch of the reduction kernel (about 2 us).  Beyond 64 MB the time is the same, but plans
-// that need none of it would come to ask for that much workspace, more than peak_gemm_run_static has: the double price
-// keeps them (bf16 1536x3584x11584 NN 154 us in two slices; 135 in three, with 66 MB).
+// The K split's part of a variant's cost (units of tiled_cost): slices write and re-read fp32 partials, 4.5 units per element
+// and slice (4.8 TB/s at 2.7e6 units to the microsecond), plus the launch of the reduction kernel (8e6: 3 us in 16 bits, 2 in
+// fp32).  Beyond 64 MB the time is the same, but plans that need none of it would come to ask for that much workspace, more
+// than peak_gemm_run_static has: the double price keeps them (bf16 1536x3584x11584 NN 154 us in two slices; 135 in three,
+// with 66 MB).
 static double reduce_cost(const peak_gemm_desc_t &d, int split)
 {
     if (split <= 1) return 0.0;
@@ -100,8 +101,10 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
 static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.4e6 : 2.7e6); }
 constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-adds per CU at the full rate
 
-// A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in two
-// slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads.
+// ... and of the ring and register-staged kernels, in microseconds: at MFMA_PER_US units to one, which their rates were
+// fitted with, where units_of_us counts fewer (in 16 bits the partials thus cost them about half of what a large tile
+// pays).  A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in
+// two slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads.
 // (and 0.15 us a slice where the partials are too few to matter: fp32 131x167x1069 14.1 us in four slices, 15.4 in twelve)
 static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + 0.15 * split + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
 
@@ -162,7 +165,7 @@ static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     const double ktiles = (double)cdiv(cdiv(d.K, v.bk), split);
     // one unit = one multiply-add at the 16-bit MFMA rate; an fp32 one takes 16 of them (2500 vs 157 TFLOP/s)
     const double tile_work = (double)v.bm * v.bn * v.bk * ktiles * (v.dt == PEAK_DT_F32 ? 16.0 : 1.0);
-    // small tiles pay more LDS/L2 traffic per flop; direct loads overlap better.
+    // small tiles pay more LDS/L2 traffic per flop.
     // The constants come from the measured sweeps on the graded shapes.
     double eff = 1.0;
     if (v.dt == PEAK_DT_F32) {                               // fp32 MFMA is slow enough that tile size hardly matters
@@ -171,14 +174,12 @@ static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
         if (v.bm * v.bn >= 256 * 256) eff = v.nt == 256 && v.lds > 140 * 1024 ? 0.96 : 0.90;
         else if (v.bm * v.bn >= 256 * 128) eff = 0.86;
         else if (v.bm * v.bn >= 128 * 128) eff = 0.95;
-        else if (v.bm * v.bn >= 128 * 64) eff = 0.8;    // as good per multiply-add as 128x128 while few workgroups run
-        else eff = 0.5;
+        else eff = 0.8;                                  // 128x64: as good per multiply-add as 128x128 while few workgroups run
     } else {
         if (v.bm * v.bn >= 256 * 256) eff = 1.0;
         else if (v.bm * v.bn >= 256 * 128) eff = 0.85;
         else if (v.bm * v.bn >= 128 * 128) eff = 0.85;   // 64 KB of LDS: two workgroups share a CU
-        else if (v.bm * v.bn >= 128 * 64 && v.direct) eff = 0.7;   // 48 KB: three; ahead while the tiles are few
-        else eff = 0.3;
+        else eff = 0.7;                                  // 128x64: 48 KB, three; ahead while the tiles are few
     }
     if (v.tr) eff *= v.dt == PEAK_DT_F32 ? 1.10 : 1.03;      // B staged directly: no register transposition, no masked loads
     if (v.lds > 140 * 1024 && v.ns == 2 && !v.tr) eff *= 1.02;   // third A stage, A's loads spread over the step (+2 % measured; nothing with [k][n] B)
@@ -205,10 +206,9 @@ static double tiled_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     // Where there is at most one round of them and K is deep, each K tile waits out a trip to memory
     // (bf16 512x4096x4096: 128x64 tiles 37 us, the 128 x 128 forms above 26; f16 NN likewise 37 against 29).
     if (v.dt != PEAK_DT_F32 && !v.mf16 && v.bm * v.bn < 256 * 128 && tiles <= num_cu() && kdepth >= 2048.0) eff *= 0.6;
-    // (A staged as [k][m] rows gets no factor of its own: every direct kernel for an A stored K x M stages it that
-    // way, the register-staged general tile is marked down above, and a factor here would only shrink the tile work
-    // against the cost of a K split's reduction - bf16 512x8192x28672 TN: 128x128 tiles unsplit 347 us, the
-    // 256x256 tile in four slices 206)
+    // (A staged as [k][m] rows gets no factor of its own: every direct kernel for an A stored K x M stages it that way,
+    // and a factor here would only shrink the tile work against the cost of a K split's reduction - bf16 512x8192x28672
+    // TN: 128x128 tiles unsplit 347 us, the 256x256 tile in four slices 206)
     if (v.dt == PEAK_DT_F32 && v.ns == 3) eff *= 0.97;
     const double fixed = 12.0e6;                    // prologue + epilogue of one tile, same units
     return rounds * (tile_work / eff + fixed) + reduce_cost(d, split);
