@@ -159,6 +159,10 @@ struct Cfg {
     // another full stage of both (asymmetric ring, prefetch loops only).
     static constexpr int NSA = NS_ + AX_, NSB = NS_;
     static constexpr int LDS_BYTES = A_BYTES * NSA + B_BYTES * NSB;
+    // 64x128 tiles with B as [k][n] rows: two workgroups per CU, not the three that fit.  The selector takes them for one to
+    // two tiles per CU, where that makes no difference, and for three to four, which two and two share evenly: bf16
+    // 264x22016x4232 99.5 us against 117.9, 555x13504x4800 110 and 133, f16 319x26048x3904 104 and 108.
+    static constexpr int LDS_ALLOC = ESZ == 2 && TR_ && BM_ == 64 && BN_ == 128 && LDS_BYTES < 56 * 1024 ? 56 * 1024 : LDS_BYTES;
     static constexpr bool PIPE = NS_ >= 4 && AX_ == 0 && !PP_;   // run-ahead main loop (see gemm_kernel); with 3 stages the
                                                          // two-phase loop keeps loads two steps ahead instead
     // Alternating main loop: the two waves of a SIMD take turns, one reading
@@ -841,7 +845,9 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                     }
                 }
             };
-            if (interior) plain(IC<0>{});
+            // interior tiles without the masks where the launches are short enough for them to show (0.1 us of 3.4); the
+            // large wave tiles take one form, two drove the 8-wave 256x256 kernels 9 to 47 registers past the register file
+            if (C::WTM * C::WTN < 128 * 64 && interior) plain(IC<0>{});
             else plain(IC<1>{});
             return;
         }
@@ -924,7 +930,7 @@ template <class C>
 __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's symbol; the body uses device-only builtins
-    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_ALLOC];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
