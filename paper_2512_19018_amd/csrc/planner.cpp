@@ -337,8 +337,10 @@ static bool streams(const Variant &v, const peak_gemm_desc_t &d)
 // 62x5632x6272 23.6 and 27.7).  With A stored K x M, which the ring kernels read as it lies, the streaming kernel has the
 // transposition as well: 120 of 120 shapes of 9 to 76 MB ahead in ring tiles (bf16 40x12800x1024 TN 10.3 us and 20.9, f16
 // 56x24128x1536 TT 21.1 and 26.3, 40x4608x8192 TN 23.3 and 28.8).  Else not where
-//  - the streaming kernel needs no split (bf16 50x23232x1152 NT 14.4 us, 16.6 in ring tiles; with tiles of 64 columns, one
-//    round of either, the ring kernels are level or ahead: f16 48x13888x1152 10.5 and 11.0);
+//  - the streaming kernel fills one round, from half of the chip on, without a split (bf16 50x23232x1152 NT 14.4 us, 16.6
+//    in ring tiles; over ring time, 130 to 253 tiles of 128 columns, the operand cold and warm, 0.90 and 1.01 in the mean;
+//    fewer tiles, K too short for slices, 1.36 and 1.42, NN 1.36 and 1.48; more 1.17 and 1.24.  With tiles of 64
+//    columns, one round of either, the ring kernels are level or ahead: f16 48x13888x1152 10.5 us and 11.0);
 //  - a slice of the ring kernel is deep, few workgroups then reading at one CU's rate.  Streaming over ring time at 3968 to
 //    5120 k per slice: NT 0.90 in the mean, the operand cold, and 1.18 with it in the last-level cache; NN 0.96 and 1.32;
 //    at 2688 to 3840 k 1.02 and 1.25, 1.12 and 1.45 (f16 36x6016x5120 NT 0.85, bf16 59x4416x4224 NT 0.86);
@@ -351,8 +353,9 @@ static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const
     if (d.M <= 32 || d.dtype == PEAK_DT_F32 || d.N * d.K * esize_of(d.dtype) > (int64_t)72 << 20) return false;
     if (stages_a(v, d.transA)) return true;
     const int split = skinny_split(d.N, d.K, v.bn, v.bk);
-    if (split == 1) return v.bn < 128;
-    const bool spills = cdiv(d.N, v.bn) * split > num_cu();
+    const int64_t tiles = cdiv(d.N, v.bn);
+    if (split == 1) return v.bn < 128 || tiles * 2 <= num_cu() || tiles > num_cu();
+    const bool spills = tiles * split > num_cu();
     if (v.tr && !spills && cdiv(d.N, 64) > num_cu() && d.K > 1664) return false;
     return cdiv(d.K, choose_split(ring, d)) <= (v.tr || spills ? 5120 : 3840);
 }
@@ -383,11 +386,11 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             // (but not where tiles of half the columns fill it in one round without a K split: 64x16384x8192 50.1 us
             // against 56.9; a second round, nearly empty or not, costs more: 64x25664x14080 164 against 135.  A workgroup
             // of 64 columns reads as much of A as one of 128, and over a long K that outweighs the reduction, the
-            // sooner the fewer CUs share it: up to K = 14336 with 15/16 of the CUs at work, up to 6656 with fewer -
-            // 59x16320x13952 87.5 us against 90.2, 64x16384x15488 103 and 97; 56x13184x6784 40.8 and 40.7,
+            // sooner the fewer CUs share it: up to K = 14336 with 15/16 of the CUs at work, up to 9344 with fewer -
+            // 59x16320x13952 87.5 us against 90.2, 64x16384x15488 103 and 97; 35x13504x8320 44.2 and 49.9,
             // 48x13824x11136 67.3 and 60.9, 64x14080x12928 80.0 and 77.9, the operand cold in the caches)
             const int64_t fill = (int64_t)num_cu() * 4, halves = cdiv(d.N, v.bn / 2);
-            const bool halves_fill = halves <= num_cu() && (halves * 16 >= (int64_t)num_cu() * 15 ? d.K <= 14336 : halves * 5 >= fill && d.K <= 6656);
+            const bool halves_fill = halves <= num_cu() && (halves * 16 >= (int64_t)num_cu() * 15 ? d.K <= 14336 : halves * 5 >= fill && d.K <= 9344);
             if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || halves_fill)) continue;
             if (stream[v.stream_rank] < 0) stream[v.stream_rank] = i;
             continue;

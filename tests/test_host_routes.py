@@ -66,6 +66,9 @@ def test_partials_of_ring_and_any_alignment_kernels_fit_the_fixed_array(dt):
     ("bf16", 0, 1, 64, 8192, 2688, True),
     ("f16", 0, 0, 64, 6848, 4160, True),
     ("f16", 0, 1, 48, 13888, 1152, True),        # unsplit in 64-column tiles: level cold, ring ahead warm
+    ("bf16", 0, 0, 64, 384, 256, True),          # ... or because K is too short for slices
+    ("bf16", 0, 1, 64, 1728, 768, True),
+    ("bf16", 0, 1, 59, 33088, 768, True),        # unsplit in more than a round
     ("f16", 0, 1, 36, 11008, 2304, True),        # the streaming kernel's slices spill into a second round
     ("bf16", 0, 1, 62, 5632, 6272, False),
     ("bf16", 0, 0, 46, 18368, 2048, False),      # B stored K x N: a second round of ring tiles on a long K
@@ -84,9 +87,9 @@ def test_ring_kernels_where_they_pay(dt, ta, tb, M, N, K, ring):
 
 
 # 64 rows, unsplit with 64 columns per tile against 128 and a K split (bf16, us, the operand cold in the caches):
-# 16384x8192 50.1 / 56.9, 13312x4096 26.1 / 27.4, 14080x12928 80.0 / 77.9, 13312x10624 62.4 / 57.9, 16320x13952 87.5 / 90.2,
+# 16384x8192 50.1 / 56.9, 13312x4096 26.1 / 27.4, 13504x8320 44.2 / 49.9, 14080x12928 80.0 / 77.9, 13312x10624 62.4 / 57.9, 16320x13952 87.5 / 90.2,
 # 16384x15488 103 / 97
-@pytest.mark.parametrize("N,K,columns", [(13312, 4096, 64), (13312, 10624, 128), (14080, 12928, 128), (16384, 8192, 64),
+@pytest.mark.parametrize("N,K,columns", [(13312, 4096, 64), (13504, 8320, 64), (13312, 10624, 128), (14080, 12928, 128), (16384, 8192, 64),
                                          (16320, 13952, 64), (16384, 15488, 128), (16448, 14080, 128), (25664, 14080, 128),
                                          (26624, 14080, 128)])
 def test_streaming_tiles_of_64_columns_only_in_one_round(N, K, columns):
