@@ -1,0 +1,50 @@
+"""The launches around the product: the ordered sum of the K slices where N ends inside a group of four columns, and the
+transposition of an A stored K x M for the streaming kernels."""
+import numpy as np
+import pytest
+
+import peak_inputs as pi
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from tests import gpu_util
+    return gpu_util
+
+
+def _check(gu, oracle, dtype, ta, tb, M, N, K, flags, want):
+    A, B = (pi.store(pi.logical_matrix(70, i, *s, "uniform", 1.0, dtype), bool(t))
+            for i, (s, t) in enumerate((((M, K), ta), ((K, N), tb))))
+    C = pi.store(pi.logical_matrix(70, 2, M, N, "uniform", 1.0, dtype), False)
+    got, raw, info = gu.run_gemm(dtype, ta, tb, M, N, K, 0.5, 2.0, A, B, C, flags=flags)
+    assert want in info, info
+    gu.check_against_oracle(oracle, got, dtype, ta, tb, M, N, K, 0.5, A, B, 2.0, C, what=info)
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 127, 129, 130, 131, 132])
+def test_sum_of_slices_ragged_columns(gu, oracle, dtype, N):
+    for M, split in ((9, 2), (70, 7)):                        # fewer slices than are loaded at a time, and a remainder
+        vid = next(i for i, n in gu.variants_for(dtype, 0, 1) if "_r64x64" in n)
+        _check(gu, oracle, dtype, 0, 1, M, N, 7 * 128, gu.pg.force_flags(vid, split), "split=%d " % split)
+
+
+@pytest.mark.parametrize("dtype,tb,M,K", [(pi.BF16, 1, 1, 4096), (pi.F16, 1, 64, 2048 + 128), (pi.BF16, 0, 37, 4096 + 64),
+                                          (pi.F32, 0, 17, 2048 + 32), (pi.F32, 1, 63, 2048), (pi.F32, 0, 4, 2048), (pi.BF16, 1, 5, 2048), (pi.F16, 0, 16, 2048)])
+def test_transposed_copy_of_a(gu, oracle, dtype, tb, M, K):
+    pre, suf = {pi.F32: "f32", pi.F16: "f16", pi.BF16: "bf16"}[dtype], "_nt" if tb else "_nn"
+    pg = gu.pg
+    for i in range(pg.peak_gemm_variant_count()):             # every streaming kernel that takes the shape
+        n = pg.peak_gemm_variant_name(i)
+        if not (n.startswith(pre + "_skinny") and n.endswith(suf)):
+            continue
+        try:
+            pg.Plan(M, 264, K, dtype, 1, tb, flags=pg.force_flags(i)).close()
+        except pg.PeakError:
+            continue
+        print(n, flush=True)
+        _check(gu, oracle, dtype, 1, tb, M, 264, K, pg.force_flags(i), "acopy=1")
