@@ -124,7 +124,7 @@ size_t peak_gemm_workspace_bytes(const peak_gemm_plan_t *plan);
  *   A, B         need element alignment only.  Plans are made from the leading
  *                dimensions; when those suit the 16-byte copies of the fast
  *                kernels but a base address does not (a view one element into
- *                a larger matrix), the run uses the plan's register-staged
+ *                a larger matrix), the run uses the plan's any-alignment
  *                stand-in variant (named after "unaligned=" by
  *                peak_gemm_plan_info): same result within the tolerance, slower.
  *                Plans of large products whose leading dimensions or sizes do not

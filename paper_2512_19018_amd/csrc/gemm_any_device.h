@@ -1,22 +1,20 @@
-// Tiled kernel for operands of any alignment (odd leading dimensions, blocks of larger matrices that start
-// anywhere, K that is no whole number of 16-byte chunks), every storage type, all four layouts, on the 16x16 MFMA
-// (16x16x32 for 16-bit operands, 16x16x4 for fp32).
+// Tiled kernel with a ring of K tiles on their way into the LDS, every storage type, all four layouts, on the 16x16
+// MFMA (16x16x32 for 16-bit operands, 16x16x4 for fp32), in two forms:
+//   aligned operands, small tiles ("_m...q<stages>"): for grids that would leave the large tiles' chip idle;
+//   operands of any alignment ("_r"): odd leading dimensions, blocks of larger matrices that start anywhere, K that is
+//   no whole number of 16-byte chunks.
 //
-// The direct-to-LDS copies of the other tiled kernels need 16-byte aligned rows.  Here a tile goes through
-// registers: 16-byte loads at element alignment (the hardware takes them; see load_loose), then 16-byte LDS
-// stores to the very places the direct copies would fill, so that the fragment reads are theirs: rows along K as
-// they lie, [k][x] rows as they lie with the transposing read for 16-bit operands - no transposition in registers.
-// Chunks that K or a matrix edge cuts are fetched so that they end on the last element, and shifted into place
-// (shift_down): every chunk is one load inside the matrix, also on edge tiles (cut into elements, the edge workgroups
-// hold up all others).
+// Both copy global -> LDS directly, 16 bytes per lane: the copies take addresses of any 2-byte alignment (the
+// LDS side is always aligned; checked over all of them, rows 16 bytes to 4 KB apart).  Rows along K lie as they do in
+// memory, [k][x] rows too, with the transposing read for 16-bit operands.  For operands of any alignment that holds for
+// whole K tiles; the tile that K ends in goes through registers, shifted into place (shift_down), and is asked for before the loop.
 //
-// Bound: the way of unaligned rows into the CU.  One CU takes 110 bytes per ns from the L2 where rows start on
-// 128-byte lines, 69 where they only start on 16-byte boundaries (a K tile of a row then lies in two lines), 54 with
-// half of the rows on odd 2-byte addresses; the MFMAs of a 128 x 128 tile could take 130.  So the tile is large where
-// the problem has the tiles for it; small problems take small tiles, several workgroups per CU covering each other's
-// waits.  Measured against register staging with a transposition in registers and element-wise edges: bf16
-// 1023x2047x3001 NT (block, odd rows) 46.6 -> 40.5 us, fp32 777x1234x1555 TT 60.9 -> 44.7, fp32 256^3 (one launch
-// instead of a K split and its sum) 8.2 -> 5.1.
+// Bound, 16 bits: the way of the rows into the CU.  72 to 85 bytes per ns and CU where rows start on 128-byte lines, 48 to 60
+// where they start anywhere (each piece of a row then lies in one line more than it fills; on odd 2-byte addresses a
+// tenth less again).  fp32: the MFMAs, at 0.75 to 0.9 of their rate.  The any-alignment form went through registers before: 16-byte
+// loads, one tile on its way, LDS stores, two barriers' worth of LDS traffic in a chain per tile; more tiles on their way changed nothing.
+// Through the ring: fp32 777x1234x1555 TT 42.5 -> 31 us, 4095^3 NT 1054 -> 947, 219x1105x1177 NN 16.6 -> 11.0; bf16 704x640x1331 NT 12.0 -> 8.6,
+// 407x705x977 TN 11.0 -> 8.6, 1931x1587x1251 TT 28 -> 23.5, 1023x2047x3001 NT 40.8 -> 28.5.
 #pragma once
 
 #include "gemm_device.h"
@@ -24,10 +22,9 @@
 namespace peak {
 
 // WM x WN waves share the tile, WK waves each of its places (the rounds of a stage dealt out over them, their sums
-// added in LDS at the end, in wave order); RB: bytes of K per row and stage; PF: tiles that are on their way in
-// registers; EU: waves per SIMD that the register budget is cut for.
-// RING: 0, or the number of LDS stages of the form that copies aligned operands to LDS directly (see the loop).
-template <int DT_, bool A_KM_, bool B_KN_, int BM_, int BN_, int WM_, int WN_, int WK_, int RB_, int PF_, int EU_, int RING_ = 0>
+// added in LDS at the end, in wave order); RB: bytes of K per row and stage; EU: waves per SIMD that the register
+// budget is cut for; RING: stages in LDS; LOOSE: operands of any alignment.
+template <int DT_, bool A_KM_, bool B_KN_, int BM_, int BN_, int WM_, int WN_, int WK_, int RB_, int EU_, int RING_, bool LOOSE_>
 struct CfgAny {
     static constexpr int DT = DT_;
     static constexpr bool A_KM = A_KM_, B_KN = B_KN_;
@@ -38,10 +35,15 @@ struct CfgAny {
     static constexpr int WTM = BM / WM_, WTN = BN / WN_, MB = WTM / 16, NB = WTN / 16;
     static constexpr int KROUND = 4 * EPC;                  // k per round of fragment reads: 4 chunks of 16 bytes
     static constexpr int ROUNDS = BK / KROUND / WK_;        // per stage and wave
-    static constexpr int PF = PF_, EU = EU_, RING = RING_, STAGES = RING_ ? RING_ : 2;
+    static constexpr int EU = EU_, RING = RING_;
+    // fp32, any alignment: a sum of its own for every fourth k, where the registers hold them, so that a tile with few waves
+    // along K is no further from the exact sum than those of four waves that it stands in for (777x1234x1555 TT, relative error: one
+    // sum per wave 5.0e-7 in 64x32 tiles, 3.6e-7 in 32x32 ones; four 2.6e-7 and 1.9e-7; level in time)
+    static constexpr int SETS = DT_ == DT_F32 && LOOSE_ && MB * NB <= 4 ? 4 : 1;
+    static constexpr bool LOOSE = LOOSE_;
     static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
     static constexpr int RED_BYTES = PLACES * (WK_ - 1) * MB * NB * 1024;
-    static constexpr int LDS_BYTES = STAGES * STAGE > RED_BYTES ? STAGES * STAGE : RED_BYTES;
+    static constexpr int LDS_BYTES = RING_ * STAGE > RED_BYTES ? RING_ * STAGE : RED_BYTES;
     static_assert(RB_ == 128 || RB_ == 256, "swizzles below");
     static_assert(ROUNDS * WK_ * KROUND == BK && ROUNDS >= 1, "whole rounds per wave");
     static_assert(WTM % 32 == 0 && WTN % 16 == 0, "epilogue slabs of 32 rows");
@@ -85,7 +87,10 @@ struct CfgAny {
     static constexpr int kx_step(int e) { return (X * ESZ >= 256 ? e : (e & 2) | (e & 1) << 2) * (X * ESZ); }
 };
 
-// Operand that runs along K: ROWS rows x K.
+// Operand of any alignment through registers, one K tile: load asks for it, fix (once it has arrived) shifts the chunks that K
+// cuts into place, store writes it where the direct copies would.  Chunks that K or a matrix edge cuts are fetched so that they
+// end on the last element: every chunk is one load inside the matrix, also on edge tiles.
+// Rows along K: ROWS rows x K.
 template <class C, int ROWS>
 struct AnyK {
     static constexpr int NCH = ROWS * C::CPR / C::NT;
@@ -117,24 +122,21 @@ struct AnyK {
     PEAK_DEVM void load(u32x4 (&v)[NCH], int64_t k0, int tid) const
     {
         const char *p = panel + k0 * C::ESZ;
-        if (K - k0 >= C::BK) {
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) v[i] = load_loose<u32x4, C::ESZ>(p + voff[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                if (K >= C::EPC) v[i] = load_loose<u32x4, C::ESZ>(p + (voff[i] - back(k0, i, tid) * C::ESZ));
-                else v[i] = load_elems<C::DT>(p + voff[i], (int)K - (tid + C::NT * i) % C::CPR * C::EPC);
-            }
+        for (int i = 0; i < NCH; ++i) {
+            if (K >= C::EPC) v[i] = load_loose<u32x4, C::ESZ>(p + (voff[i] - back(k0, i, tid) * C::ESZ));
+            else v[i] = load_elems<C::DT>(p + voff[i], (int)K - (tid + C::NT * i) % C::CPR * C::EPC);
         }
     }
-    // (the shift waits until the tile is stored, when the loads have arrived)
-    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int64_t k0, int tid) const
+    PEAK_DEVM void fix(u32x4 (&v)[NCH], int64_t k0, int tid) const
     {
-        if (K - k0 < C::BK && K >= C::EPC) {
+        if (K >= C::EPC) {
 #pragma unroll
             for (int i = 0; i < NCH; ++i) v[i] = shift_down<C::DT>(v[i], back(k0, i, tid));
         }
+    }
+    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int tid) const
+    {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int idx = tid + C::NT * i, row = idx / C::CPR;
@@ -174,30 +176,28 @@ struct AnyX {
     PEAK_DEVM void load(u32x4 (&v)[NCH], int64_t k0, int tid) const
     {
         const char *p = base + k0 * ld * C::ESZ;
-        if (K - k0 >= C::BK && !narrow) {
+        // k-rows past the end: fetched from the last one, zeroed by fix
+        const int last = K - k0 < C::BK ? (int)(K - k0) - 1 : C::BK - 1;
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) v[i] = load_loose<u32x4, C::ESZ>(p + voff[i]);
-        } else {                                            // k-rows past the end: fetched from the last one, zeroed below
-            const int last = K - k0 < C::BK ? (int)(K - k0) - 1 : C::BK - 1;
-#pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                const int k = (tid + C::NT * i) / CPX, over = k > last ? k - last : 0;
-                const char *src = p + (voff[i] - over * ld * C::ESZ);
-                if (!narrow) v[i] = load_loose<u32x4, C::ESZ>(src);
-                else v[i] = load_elems<C::DT>(src, narrow - (tid + C::NT * i) % CPX * C::EPC);
-            }
+        for (int i = 0; i < NCH; ++i) {
+            const int k = (tid + C::NT * i) / CPX, over = k > last ? k - last : 0;
+            const char *src = p + (voff[i] - over * ld * C::ESZ);
+            if (!narrow) v[i] = load_loose<u32x4, C::ESZ>(src);
+            else v[i] = load_elems<C::DT>(src, narrow - (tid + C::NT * i) % CPX * C::EPC);
         }
     }
-    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int64_t k0, int tid) const
+    PEAK_DEVM void fix(u32x4 (&v)[NCH], int64_t k0, int tid) const
+    {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i)
+            if (K - k0 < C::BK && (tid + C::NT * i) / CPX >= (int)(K - k0)) v[i] = u32x4{0u, 0u, 0u, 0u};
+    }
+    // (the shift waits until the tile is stored, when the loads have arrived)
+    PEAK_DEVM void store(char *tile, u32x4 (&v)[NCH], int tid) const
     {
         if (edge) {
 #pragma unroll
             for (int i = 0; i < NCH; ++i) v[i] = shift_down<C::DT>(v[i], shift[i]);
-        }
-        if (K - k0 < C::BK) {
-#pragma unroll
-            for (int i = 0; i < NCH; ++i)
-                if ((tid + C::NT * i) / CPX >= (int)(K - k0)) v[i] = u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
@@ -244,6 +244,51 @@ struct RingX {
     }
 };
 
+// Direct copies of operands of any (dword) alignment: whole K tiles only, so rows along K need no care.  KX: [k][x] rows.
+// A chunk that the matrix edge cuts is copied whole, what lies behind it in memory with it (it feeds columns of C that
+// are never stored), so the k-row after it must be the matrix's as well.  The descriptor moves along K with the tiles:
+// no limit on the operand's size, but one on its leading dimension.
+template <class C, int ROWS, bool KX>
+struct RingLoose {
+    static constexpr int ROWB = KX ? ROWS * C::ESZ : C::RB, CPX = ROWB / 16;
+    static constexpr int PER_WAVE = (KX ? C::BK : ROWS) * ROWB / 1024 / C::NW;
+    static_assert((KX ? C::BK : ROWS) * ROWB % (1024 * C::NW) == 0 && 64 % CPX == 0, "every wave issues the same number of loads");
+    uint64_t base;
+    int64_t step;
+    int voff[PER_WAVE];
+
+    static PEAK_DEVM bool fits(int64_t ld) { return ld < ((int64_t)1 << 31) / ((KX ? C::BK : ROWS) * C::ESZ) - ROWB; }
+    PEAK_DEVM void init(const void *src, int64_t ld, int64_t x0, int64_t nx, int64_t k0, int wave, int lane)
+    {
+        const uint64_t first = (uint64_t)((const char *)src + (KX ? k0 * ld + x0 : x0 * ld + k0) * C::ESZ);
+        base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(first >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)first);
+        step = KX ? C::BK * ld * C::ESZ : C::RB;
+        const int left = nx - x0 < ROWS ? (int)(nx - x0) : ROWS;       // rows or columns of the tile inside the matrix
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int at = (wave + C::NW * i) * 64 + lane;
+            int r = at / CPX, c = at % CPX;
+            if constexpr (KX) {
+                C::template kx_at<ROWS>(at / CPX, at % CPX, r, c);
+                if (c * C::EPC >= left) c = (left - 1) / C::EPC;
+            } else {
+                c ^= C::swizzle(r);
+                if (r > left - 1) r = left - 1;             // duplicate of a valid row; its results are never stored
+            }
+            voff[i] = (int)((r * ld + (int64_t)c * C::EPC) * C::ESZ);
+        }
+    }
+    PEAK_DEVM void issue(char *tile, int ktile, int wave) const
+    {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(base + ktile * step), 0, 0x7FFFFFFF, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)(tile + (wave + C::NW * i) * 1024),
+                                                     16, voff[i], 0, 0, 0);
+    }
+};
+
 template <class C>
 __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p)
 {
@@ -267,11 +312,13 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
     const int KT = __builtin_amdgcn_readfirstlane(kt_end - kt_begin);   // >= 1 by construction of the plan
     const int64_t kbase = (int64_t)kt_begin * C::BK;
 
-    f32x4 acc[C::MB][C::NB];
+    f32x4 sums[C::SETS][C::MB][C::NB], (&acc)[C::MB][C::NB] = sums[0];
 #pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
+    for (int e = 0; e < C::SETS; ++e)
 #pragma unroll
-        for (int nb = 0; nb < C::NB; ++nb) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb) sums[e][mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     // Fragment addresses of round kpar; round kpar + WAVES_K * i lies a constant on, but for rows along K, whose
     // swizzle does not commute with the chunk number: one address per round of a stage.
@@ -335,7 +382,8 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
 #pragma unroll
                     for (int mb = 0; mb < C::MB; ++mb) {
                         const f32x4 b = __builtin_bit_cast(f32x4, bf[nb]), a = __builtin_bit_cast(f32x4, af[mb]);
-                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], acc[mb][nb], 0, 0, 0);
+                        f32x4 &c = sums[e % C::SETS][mb][nb];
+                        c = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[e], c, 0, 0, 0);
                     }
         } else {
 #pragma unroll
@@ -354,33 +402,12 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
 
     // Ring form: direct copies, RING - 1 K tiles ahead.  For small tiles the loads' latency is the cost (a 64 x 64 x 64
     // tile's MFMAs take 128 cycles, a trip to the L2 some 500 and to memory over 1500), so most of the CU's LDS holds
-    // tiles on their way.
-    if constexpr (C::RING > 0) {
-        LoaderDirect<C, C::BM> dA;
-        LoaderDirect<C, C::BN> dB;
-        RingX<C, C::BM> nA;
-        RingX<C, C::BN> nB;
+    // tiles on their way.  n: K tiles, one at least; issue(kt, stage): the copies of tile kt.
+    auto ring_loop = [&](int n, auto &&issue) {
         constexpr int L = (C::A_BYTES + C::B_BYTES) / 1024 / C::NW;      // loads per wave and tile
         static_assert(C::A_BYTES % (1024 * C::NW) == 0 && C::B_BYTES % (1024 * C::NW) == 0, "every wave issues the same number of loads");
         constexpr int P = C::RING - 1;
         static_assert((P - 1) * L < 64, "fits the wait's counter");
-        const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
-        const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
-        if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave_all, lane);
-        else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
-        if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave_all, lane);
-        else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
-        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
-        auto issue = [&](int kt, int stage) {
-            int kr = (kt < KT ? kt : KT - 1) + rot;         // past the end: the last tile again, into a free stage
-            if (kr >= KT) kr -= KT;
-            char *st = lds + stage * C::STAGE;
-            const bool tail = kr == tail_tile;
-            if constexpr (C::A_KM) nA.issue(st, kr, tail, wave_all);
-            else dA.template issue<0, 1>(st, kr, tail, wave_all);
-            if constexpr (C::B_KN) nB.issue(st + C::A_BYTES, kr, tail, wave_all);
-            else dB.template issue<0, 1>(st + C::A_BYTES, kr, tail, wave_all);
-        };
         // (the compiler would put a wait for every direct copy in front of a transposing read: assembly, handed over
         // after a wait for everything asked of LDS)
         const uint32_t lds_b0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
@@ -389,55 +416,97 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
             asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(addr), "n"(off) : "memory");
             asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(off + 4 * rowb) : "memory");
         };
-        static_for<P>([&](auto tc) { issue(decltype(tc)::value, decltype(tc)::value); });
-        for (int kt0 = 0; kt0 < KT; kt0 += C::RING) {
+        auto multiply_stage = [&](int so) {                     // so: the stage's offset in LDS
+            const char *st = lds + so;
+            u32x4 af[C::ROUNDS][C::MB], bf[C::ROUNDS][C::NB];
+            u32x2 al[C::ROUNDS][C::MB], ah[C::ROUNDS][C::MB], bl[C::ROUNDS][C::NB], bh[C::ROUNDS][C::NB];
+            constexpr bool TRA = C::A_KM && C::DT != DT_F32, TRB = C::B_KN && C::DT != DT_F32;
+            static_for<C::ROUNDS>([&](auto rc) {
+                constexpr int r = decltype(rc)::value;
+                static_for<C::NB>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    if constexpr (TRB) tr_read(lds_b0 + so + b_x[i], IC<r * C::WAVES_K * C::KROUND * C::BN * C::ESZ>{}, bl[r][i], bh[r][i], IC<C::BN * C::ESZ>{});
+                    else bf[r][i] = frag_b(st, i, r);
+                });
+                static_for<C::MB>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    if constexpr (TRA) tr_read(lds_b0 + so + a_x[i], IC<r * C::WAVES_K * C::KROUND * C::BM * C::ESZ>{}, al[r][i], ah[r][i], IC<C::BM * C::ESZ>{});
+                    else af[r][i] = frag_a(st, i, r);
+                });
+            });
+            if constexpr (TRA || TRB) {
+                __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
+                static_for<C::ROUNDS>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    if constexpr (TRB) static_for<C::NB>([&](auto ic) {
+                        u32x2 &lo = bl[r][decltype(ic)::value], &hi = bh[r][decltype(ic)::value];
+                        asm volatile("" : "+v"(lo), "+v"(hi));
+                        bf[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                    });
+                    if constexpr (TRA) static_for<C::MB>([&](auto ic) {
+                        u32x2 &lo = al[r][decltype(ic)::value], &hi = ah[r][decltype(ic)::value];
+                        asm volatile("" : "+v"(lo), "+v"(hi));
+                        af[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                    });
+                });
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<C::ROUNDS>([&](auto rc) { multiply(af[decltype(rc)::value], bf[decltype(rc)::value]); });
+        };
+        static_for<P>([&](auto tc) {
+            if (decltype(tc)::value < n) issue(decltype(tc)::value, decltype(tc)::value);
+        });
+        // own copies of tile kt; everybody's, and nobody reads the stage before this one any more; the next copies into that
+        int kt = 0;
+        for (; kt + C::RING + P <= n; kt += C::RING)
             static_for<C::RING>([&](auto sc) {
                 constexpr int s = decltype(sc)::value;
-                const int kt = kt0 + s;
-                if (kt < KT) {
-                    wait_vmcnt<(P - 1) * L>();              // own copies of tile kt
-                    lds_barrier();                          // everybody's; nobody reads the stage before this one any more
-                    issue(kt + P, (s + P) % C::RING);
-                    const char *st = lds + s * C::STAGE;
-                    u32x4 af[C::ROUNDS][C::MB], bf[C::ROUNDS][C::NB];
-                    u32x2 al[C::ROUNDS][C::MB], ah[C::ROUNDS][C::MB], bl[C::ROUNDS][C::NB], bh[C::ROUNDS][C::NB];
-                    constexpr bool TRA = C::A_KM && C::DT != DT_F32, TRB = C::B_KN && C::DT != DT_F32;
-                    static_for<C::ROUNDS>([&](auto rc) {
-                        constexpr int r = decltype(rc)::value;
-                        static_for<C::NB>([&](auto ic) {
-                            constexpr int i = decltype(ic)::value;
-                            if constexpr (TRB) tr_read(lds_b0 + s * C::STAGE + b_x[i], IC<r * C::WAVES_K * C::KROUND * C::BN * C::ESZ>{}, bl[r][i], bh[r][i], IC<C::BN * C::ESZ>{});
-                            else bf[r][i] = frag_b(st, i, r);
-                        });
-                        static_for<C::MB>([&](auto ic) {
-                            constexpr int i = decltype(ic)::value;
-                            if constexpr (TRA) tr_read(lds_b0 + s * C::STAGE + a_x[i], IC<r * C::WAVES_K * C::KROUND * C::BM * C::ESZ>{}, al[r][i], ah[r][i], IC<C::BM * C::ESZ>{});
-                            else af[r][i] = frag_a(st, i, r);
-                        });
-                    });
-                    if constexpr (TRA || TRB) {
-                        __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));
-                        static_for<C::ROUNDS>([&](auto rc) {
-                            constexpr int r = decltype(rc)::value;
-                            if constexpr (TRB) static_for<C::NB>([&](auto ic) {
-                                u32x2 &lo = bl[r][decltype(ic)::value], &hi = bh[r][decltype(ic)::value];
-                                asm volatile("" : "+v"(lo), "+v"(hi));
-                                bf[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                            });
-                            if constexpr (TRA) static_for<C::MB>([&](auto ic) {
-                                u32x2 &lo = al[r][decltype(ic)::value], &hi = ah[r][decltype(ic)::value];
-                                asm volatile("" : "+v"(lo), "+v"(hi));
-                                af[r][decltype(ic)::value] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                            });
-                        });
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    static_for<C::ROUNDS>([&](auto rc) { multiply(af[decltype(rc)::value], bf[decltype(rc)::value]); });
-                }
+                wait_vmcnt<(P - 1) * L>();
+                lds_barrier();
+                issue(kt + s + P, (s + P) % C::RING);
+                multiply_stage(s * C::STAGE);
             });
-        }
-        wait_vmcnt<0>();    // copies past the end must land before this workgroup's LDS is given away
-        if constexpr (C::WAVES_K > 1) lds_barrier();        // everybody's, before the sums over waves go through LDS
+        // The last tiles, all of a short K: no copies past the end, fewer behind the one that is waited for.  (Conditions in the
+        // loop above cost it 1 to 12 %; the last tile copied again in place of those past it, with one count for all, doubled
+        // the copies of a short K: bf16 439x375x131 NN 5.7 us against 4.8.)
+        static_for<C::RING + P - 1>([&](auto uc) {
+            constexpr int u = decltype(uc)::value, s = u % C::RING;
+            if (kt + u < n) {
+                const int behind_here = n - 1 - kt - u;
+                static_for<P>([&](auto rc) {
+                    constexpr int behind = P - 1 - decltype(rc)::value;
+                    if (decltype(rc)::value == 0 ? behind_here >= behind : behind_here == behind) wait_vmcnt<behind * L>();
+                });
+                lds_barrier();
+                if (behind_here >= P) issue(kt + u + P, (s + P) % C::RING);
+                multiply_stage(s * C::STAGE);
+            }
+        });
+    };
+    if constexpr (!C::LOOSE) {
+        LoaderDirect<C, C::BM> dA;
+        LoaderDirect<C, C::BN> dB;
+        RingX<C, C::BM> nA;
+        RingX<C, C::BN> nB;
+        const int tail_k = __builtin_amdgcn_readfirstlane((int)(p.K - (int64_t)(p.ktiles_total - 1) * C::BK));
+        const int tail_tile = tail_k < C::BK ? p.ktiles_total - 1 - kt_begin : -1;   // relative to the slice
+        if constexpr (C::A_KM) nA.init(p.A, p.lda, m0, p.a_cols, kbase, p.K, tail_k, wave_all, lane);
+        else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
+        if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave_all, lane);
+        else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
+        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
+        auto issue = [&](int kt, int stage) {
+            int kr = kt + rot;
+            if (kr >= KT) kr -= KT;
+            char *st = lds + stage * C::STAGE;
+            const bool tail = kr == tail_tile;
+            if constexpr (C::A_KM) nA.issue(st, kr, tail, wave_all);
+            else dA.template issue<0, 1>(st, kr, tail, wave_all);
+            if constexpr (C::B_KN) nB.issue(st + C::A_BYTES, kr, tail, wave_all);
+            else dB.template issue<0, 1>(st + C::A_BYTES, kr, tail, wave_all);
+        };
+        ring_loop(KT, issue);
+        if constexpr (C::WAVES_K > 1) lds_barrier();        // everybody's copies, before the sums over waves go through LDS
     } else {
         AnyK<C, C::BM> kA;
         AnyX<C, C::BM> xA;
@@ -448,63 +517,76 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         if constexpr (C::B_KN) xB.init(p.B, p.ldb, n0, p.N, p.K, tid);
         else kB.init(p.B, p.ldb, n0, p.N, p.K, tid);
         constexpr int CA = AnyK<C, C::BM>::NCH, CB = AnyK<C, C::BN>::NCH;
-        u32x4 va[C::PF][CA], vb[C::PF][CB];
-        auto load = [&](int kt, u32x4 (&a)[CA], u32x4 (&b)[CB]) {   // kt relative to the slice
+        auto load = [&](int kt, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
             const int64_t k0 = kbase + (int64_t)kt * C::BK;
             if constexpr (C::A_KM) xA.load(a, k0, tid);
             else kA.load(a, k0, tid);
             if constexpr (C::B_KN) xB.load(b, k0, tid);
             else kB.load(b, k0, tid);
         };
-        auto store = [&](int kt, int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
+        auto store = [&](int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
             char *st = lds + stage * C::STAGE;
-            const int64_t k0 = kbase + (int64_t)kt * C::BK;
-            if constexpr (C::A_KM) xA.store(st, a, k0, tid);
-            else kA.store(st, a, k0, tid);
-            if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, k0, tid);
-            else kB.store(st + C::A_BYTES, b, k0, tid);
+            if constexpr (C::A_KM) xA.store(st, a, tid);
+            else kA.store(st, a, tid);
+            if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, tid);
+            else kB.store(st + C::A_BYTES, b, tid);
+        };
+        auto fragments = [&](const char *st, int r, u32x4 (&af)[C::MB], u32x4 (&bf)[C::NB]) {
+    #pragma unroll
+            for (int i = 0; i < C::NB; ++i) bf[i] = frag_b(st, i, r);
+    #pragma unroll
+            for (int i = 0; i < C::MB; ++i) af[i] = frag_a(st, i, r);
+            __builtin_amdgcn_sched_barrier(0);              // (the compiler would sink the reads to their first use)
         };
 
-        // One barrier per tile: while tile kt is multiplied out of one stage, tile kt + 1 goes from registers into the
-        // other (everybody left it at the last barrier) and the loads of tile kt + 1 + PF go out.
-        static_for<C::PF>([&](auto tc) {
-            constexpr int t = decltype(tc)::value;
-            if (t < KT) load(t, va[t], vb[t]);
-        });
-        store(0, 0, va[0], vb[0]);
-        if (C::PF < KT) load(C::PF, va[0], vb[0]);
-        lds_barrier();
-        constexpr int U = C::PF % 2 == 0 ? C::PF : 2 * C::PF;   // tiles per trip: stage and register set static
-        for (int kt0 = 0; kt0 < KT; kt0 += U) {
-            static_for<U>([&](auto uc) {
-                constexpr int u = decltype(uc)::value, s = u % 2, set = (u + 1) % C::PF;
-                const int kt = kt0 + u;
-                if (kt < KT) {
-                    const char *st = lds + s * C::STAGE;
-                    u32x4 af[2][C::MB], bf[2][C::NB];
-#pragma unroll
-                    for (int i = 0; i < C::NB; ++i) bf[0][i] = frag_b(st, i, 0);
-#pragma unroll
-                    for (int i = 0; i < C::MB; ++i) af[0][i] = frag_a(st, i, 0);
-                    __builtin_amdgcn_sched_barrier(0);          // (the compiler would sink the reads to their first use)
-                    if (kt + 1 < KT) store(kt + 1, 1 - s, va[set], vb[set]);
-                    if (kt + 1 + C::PF < KT) load(kt + 1 + C::PF, va[set], vb[set]);
-                    static_for<C::ROUNDS>([&](auto rc) {
-                        constexpr int r = decltype(rc)::value, cur = r & 1, nxt = cur ^ 1;
-                        if constexpr (r + 1 < C::ROUNDS) {
-#pragma unroll
-                            for (int i = 0; i < C::NB; ++i) bf[nxt][i] = frag_b(st, i, r + 1);
-#pragma unroll
-                            for (int i = 0; i < C::MB; ++i) af[nxt][i] = frag_a(st, i, r + 1);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                        multiply(af[cur], bf[cur]);
-                    });
-                    lds_barrier();                              // (loads stay under way across it)
-                }
+        // The tile that K ends in (and all tiles of a narrow operand) comes last, through registers; it is asked for first,
+        // so that it costs no round trip of its own at the end.
+        bool slow = false, cut = false;
+        if constexpr (C::A_KM) { slow |= xA.narrow != 0; cut |= xA.edge && p.M % C::EPC != 0; }
+        if constexpr (C::B_KN) { slow |= xB.narrow != 0; cut |= xB.edge && p.N % C::EPC != 0; }
+        slow |= !(RingLoose<C, C::BM, C::A_KM>::fits(p.lda) && RingLoose<C, C::BN, C::B_KN>::fits(p.ldb));
+        // (the direct copies of a cut chunk read on into the next k-row: not on the matrix's last)
+        const int64_t whole = slow ? 0 : (p.K - kbase - (cut ? 1 : 0)) / C::BK;
+        const int KF = __builtin_amdgcn_readfirstlane((int)(whole < KT ? whole : KT));
+        u32x4 ta[CA], tb[CB];
+        if (KF < KT) load(KF, ta, tb);
+        if (KF > 0) {
+            RingLoose<C, C::BM, C::A_KM> rA;
+            RingLoose<C, C::BN, C::B_KN> rB;
+            rA.init(p.A, p.lda, m0, p.M, kbase, wave_all, lane);
+            rB.init(p.B, p.ldb, n0, p.N, kbase, wave_all, lane);
+            ring_loop(KF, [&](int kt, int stage) {
+                rA.issue(lds + stage * C::STAGE, kt, wave_all);
+                rB.issue(lds + stage * C::STAGE + C::A_BYTES, kt, wave_all);
             });
+            lds_barrier();                                  // everybody's copies, before the stages are written again
+        }
+        for (int kt = KF; kt < KT; ++kt) {
+            const int64_t k0 = kbase + (int64_t)kt * C::BK;
+            if constexpr (C::A_KM) xA.fix(ta, k0, tid);
+            else kA.fix(ta, k0, tid);
+            if constexpr (C::B_KN) xB.fix(tb, k0, tid);
+            else kB.fix(tb, k0, tid);
+            store(0, ta, tb);
+            if (kt + 1 < KT) load(kt + 1, ta, tb);
+            lds_barrier();
+            u32x4 af[C::MB], bf[C::NB];
+            static_for<C::ROUNDS>([&](auto rc) {
+                fragments(lds, decltype(rc)::value, af, bf);
+                multiply(af, bf);
+            });
+            lds_barrier();
         }
     }
+
+#pragma unroll
+    for (int h = 1; h < C::SETS; h *= 2)                       // pairs, then pairs of pairs
+#pragma unroll
+        for (int e = 0; e + h < C::SETS; e += 2 * h)
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < C::NB; ++nb) sums[e][mb][nb] += sums[e + h][mb][nb];
 
     if constexpr (C::WAVES_K > 1) {
         f32x4 *red = (f32x4 *)lds + lane;

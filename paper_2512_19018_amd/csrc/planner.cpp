@@ -90,18 +90,13 @@ static double reduce_cost(const peak_gemm_desc_t &d, int split)
     return (4.0 * partials <= 64.0e6 ? 4.5 : 9.0) * partials + 8.0e6;
 }
 
-// The register-staged kernels: the loads bound them, not the MFMAs, and how well the loads overlap depends on the
-// workgroups that share a CU.  Measured as a share of the MFMA rate, with as many workgroups as fit and with one:
-// bf16 128x128 tiles 0.24 (4095^3), 0.19 (1023x2047x3001 in four slices), 0.20 (8191x8191x1023), 128x64 0.19 to 0.23
-// (1500x1501x4000, two and three workgroups per CU) and 0.10 alone, 64x64 0.15 (1111x1003x1500).  fp32 2049x3001x1023: 0.70 (0.58 at 777x1234x1555 in seven slices), 0.66 (64x64),
-// 0.60 (64x32), 0.50 (32x32); 777x1234x1555 with two 64x32 workgroups per CU 0.50, with four 0.56.
-// (Measured in microseconds.  tiled_cost's units are rates of full rounds under the power limit: about 2.7e6 of them
-// to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5 measured, 1024^3 9.6 and 9.8 - and 4.4e6 in
-// fp32: 2300x1700x4096 NT 260 and 246.)
+// The kernels for any alignment and the ring kernels are priced in microseconds.  tiled_cost's units are rates of full
+// rounds under the power limit: about 2.7e6 of them to the microsecond in 16 bits - bf16 2048^3 14.9 by the model, 17.5
+// measured, 1024^3 9.6 and 9.8 - and 4.4e6 in fp32: 2300x1700x4096 NT 260 and 246.
 static double units_of_us(const Variant &v, double us) { return us * (v.dt == PEAK_DT_F32 ? 4.4e6 : 2.7e6); }
 constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-adds per CU at the full rate
 
-// ... and of the ring and register-staged kernels, in microseconds: at MFMA_PER_US units to one, which their rates were
+// reduce_cost of the ring kernels, in microseconds: at MFMA_PER_US units to one, which their rates were
 // fitted with, where units_of_us counts fewer (in 16 bits the partials thus cost them about half of what a large tile
 // pays).  A K split costs short launches 2 us more than the sum itself: bf16 100x4096x4096 in 64x64 ring tiles 13.3 us in
 // two slices, 7.3 + 2.5 by the loads; 768x768x3072 in three slices of 128x64 14.4, 8.0 by the loads.
@@ -116,20 +111,35 @@ static int resident(const Variant &v)
     return fit < 1 ? 1 : fit;
 }
 
+// The kernels that take any alignment.  Times of all their tiles and K splits over 160 random unaligned products of
+// 65 to 8192 rows and columns, fitted as a launch and a round of workgroups (their first tiles' trip to memory and the store of C) and
+// the way into the LDS in 16 bits (bytes per ns and CU; rows on odd 2-byte addresses a tenth less), the MFMAs in fp32 (share
+// of their rate): within 12 % in 16 bits and 6 % in fp32 (root mean square); the pick by it is 1.7 and 0.8 % off the best on average.
+// alone: what one workgroup on a CU gets of the rate that as many as fit get together.  (The fp32 128x128 tile reaches 0.95, but as
+// much of that is lost to few tiles as the 64x64 one loses to its loads - 4095^3 953 us and 947 -, and it holds one sum for all k.)
+struct StagedRate { int bm, bn; double rate, alone, launch, round; };
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
-    const int64_t tiles = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
-    const int64_t per_cu = cdiv(tiles, num_cu());
-    const double work = (double)v.bm * v.bn * v.bk * (double)cdiv(cdiv(d.K, v.bk), split) * (v.dt == PEAK_DT_F32 ? 16.0 : 1.0);
-    const int area = v.bm * v.bn;
+    static const StagedRate rate16[] = {{128, 128, 46.6, 0.96, 2.3, 3.25}, {128, 64, 62.0, 1.0, 2.15, 2.65}, {64, 64, 60.3, 1.0, 2.6, 1.3},
+                                        {0, 0, 65.0, 0.95, 2.0, 1.9}};
+    static const StagedRate rate32[] = {{128, 128, 0.78, 0.9, 3.7, 2.3}, {64, 64, 0.816, 1.0, 2.9, 1.4}, {64, 32, 0.754, 1.0, 1.6, 2.6},
+                                        {0, 0, 0.767, 0.93, 1.5, 3.0}};
+    const bool f32 = v.dt == PEAK_DT_F32;
+    const StagedRate *r = f32 ? rate32 : rate16;
+    while (r->bm && (r->bm != v.bm || r->bn != v.bn)) ++r;
+    const int64_t per_cu = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
     const int fit = resident(v);
-    double eff, one;                                        // saturated; one workgroup's share of it
-    if (v.dt == PEAK_DT_F32) { eff = area >= 128 * 128 ? 0.65 : area >= 64 * 64 ? 0.66 : area >= 64 * 32 ? 0.60 : 0.50; one = 0.6; }
-    else { eff = area >= 128 * 128 ? 0.22 : area >= 128 * 64 ? 0.20 : 0.15; one = area >= 128 * 64 ? 0.55 : 0.8; }
-    const double full = (double)(per_cu / fit) * fit * work / eff;
+    const double k = (double)v.bk * (double)cdiv(cdiv(d.K, v.bk), split);
+    const double us = f32 ? k * v.bm * v.bn * 16.0 / MFMA_PER_US
+                          : k * 2.0 * (v.bm * (d.lda % 2 ? 1.1 : 1.0) + v.bn * (d.ldb % 2 ? 1.1 : 1.0)) / 1000.0;    // of one workgroup at rate 1
     const int64_t rest = per_cu % fit;
-    const double part = rest ? (double)rest * work / (eff * (fit > 1 ? one + (1.0 - one) * (double)(rest - 1) / (fit - 1) : 1.0)) : 0.0;
-    return units_of_us(v, (full + part) / MFMA_PER_US + 2.5 * (double)cdiv(per_cu, fit) + 1.3 * split_us(d, split));
+    double t = (double)(per_cu / fit) * fit * us / r->rate + r->launch + r->round * (double)cdiv(per_cu, fit);
+    if (rest) t += (double)rest * us / (r->rate * (fit > 1 ? r->alone + (1.0 - r->alone) * (double)(rest - 1) / (fit - 1) : 1.0));
+    if (split > 1) {                                        // the partials out and back (3.8 and 3.2 TB/s) and the second launch
+        const double mb = 4.0e-6 * split * (double)d.M * (double)d.N;
+        t += f32 ? 2.2 + 0.08 * split + 0.313 * mb : 2.8 + 0.11 * split + 0.26 * mb;
+    }
+    return units_of_us(v, t);
 }
 
 // The ring kernels: small tiles, bound by the way into the LDS (16 bits) or by the MFMAs (fp32).  16 bits, bytes per ns
@@ -220,8 +230,8 @@ static int choose_split(const Variant &v, const peak_gemm_desc_t &d)
     const int64_t ktiles = cdiv(d.K, v.bk);
     // (partials of these kernels stay within the array of peak_gemm_run_static)
     const bool cap = !v.direct || v.ring;
-    // (the register-staged kernels gain from several workgroups per CU: bf16 1023x2047x3001 in 256 tiles of 128x64
-    // 48.9 us unsplit, 40.2 in two slices)
+    // (the kernels for any alignment gain from several workgroups per CU: fp32 1472x263x6248 TN in 414 tiles of 32x32 and
+    // three slices 57 us)
     if (tiles > (v.direct ? num_cu() / 2 : 2 * num_cu()) || ktiles < 4) return 1;
     int best = 1;
     double best_cost = tiled_cost(v, d, 1);
@@ -364,8 +374,8 @@ static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const
 // `staged_only`, among those that take any operand alignment.
 static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 {
-    double best = 0.0, best_ring = 0.0;
-    int pick = -1, ring = -1, pick_split = 1, stream[4] = {-1, -1, -1, -1};            // first fitting streaming kernel of each rank
+    double best = 0.0, best_ring = 0.0, best_any = 0.0;
+    int pick = -1, ring = -1, any = -1, pick_split = 1, stream[4] = {-1, -1, -1, -1};            // first fitting streaming kernel of each rank
     // streaming kernels: only those with the fewest rows of the M x K operand that hold M
     int stream_bm = 0;
     for (int i = 0; i < NUM_VARIANTS; ++i) {
@@ -408,25 +418,44 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             }
         }
         if (v.ring) { if (ring < 0 || c < best_ring) { ring = i; best_ring = c; } }
+        else if (!v.direct) { if (any < 0 || c < best_any) { any = i; best_any = c; } }
         else if (pick < 0 || c < best) { pick = i; best = c; pick_split = split; }
     }
     for (int r = 3; r >= 1; --r)
         if (stream[r] >= 0) return ring >= 0 && ring_ahead_of_streaming(g_variants[ring], g_variants[stream[r]], d) ? ring : stream[r];
+    if (pick < 0 && ring < 0) return any;                   // (operands that suit the 16-byte copies always take a kernel made of them)
     // A K split of an fp32 launch costs some microseconds more than the model has for it: 504x1396x2380 NT in five slices
     // of 128x128 tiles 42.1 us, 36.1 in ring tiles unsplit; 112x208x816 NN 10.0 in 13 slices, 8.2 in ring tiles.
     // (2560x1340x2164 TT, unsplit in both, 134 us with the 128 x 128 tile and 147 in ring tiles.)  It counts against the
     // ring kernels only: among the others tile and split, and with them the workspace, are as they would be without.
-    if (ring >= 0 && pick >= 0 && g_variants[pick].direct && d.dtype == PEAK_DT_F32 && pick_split > 1)
+    if (ring >= 0 && pick >= 0 && d.dtype == PEAK_DT_F32 && pick_split > 1)
         best += units_of_us(g_variants[pick], 4.0 + 0.3 * pick_split);
     return ring >= 0 && (pick < 0 || best_ring < best) ? ring : pick;
 }
 
-// Products whose rows do not suit the 16-byte copies, by the direct kernels on aligned copies of the operands that the
-// run writes first.  The copies cost a pass over the operands (about 4 TB/s with the write, 4.5 us at least), the
-// register-staged kernels a third to three quarters of the rate, so this pays for large products: bf16 4095^3 143 us
-// against 230, 1500x1501x4000 NN 38 against 55, 1023x2047x3001 29 against 40; fp32 1023x2047x3001 TN 116 against 133; level
-// at 2049x2047x1031 NN and 1111x1003x1500.  Fills *g and
-// returns true if the cost model has it ahead of `staged` (the register-staged choice).
+// Products whose rows do not suit the 16-byte copies of the other tiled kernels, by those on aligned copies of the operands
+// that the run writes first.  The copies cost a pass over the operands (about 4 TB/s with the write, 6 us at least with the
+// launch); what they save is that rows which start anywhere lie in a line more than they fill, so that small tiles reach
+// 48 to 60 bytes per ns and CU where aligned ones reach 72, and that the tiles may be large.
+// 16 bits: by the cost model from K = 512 on (bf16 6369x1352x5784 TN 126 us with copies, 197 without, 3195x1471x3771 NT 60 and
+// 90, 401x5608x759 NN 22 and 17; shorter, the store of C outweighs the loads: f16 3904x5358x192 39 and 27, bf16 4496x2239x448 31 and 25).
+// Products of 3.2e9 multiply-adds and more with a deep K and no narrow side take them also where the model is undecided (within an
+// eighth; two fifths from K = 3000 on, where the loose tiles fall behind their rates): 2239x1507x2255 NN 33 and 40, 3301x1557x3749 TT
+// 63.5 and 84, level at 2049x2047x1031 TT 32.6 and 30.2, f16 1353x747x3209 28.9 and 28.3, bf16 1023x2047x3001 NT 29.8 and 29.2; behind at
+// 1038x1136x3136, 35 %.  Over 142 random products the pick is 1.2 % off the better route on average.
+// fp32: the MFMAs bound both, the copies come on top (47 random products: never with them 0.5 % off the better route; 1203x1419x999
+// 48 and 38, 863x1795x2139 81 and 70, 2049x3001x2051 TN 258 and 257).  Kept for products wide on both sides, where the two differ
+// least, and for TN from half of that width on, whose loose tiles are a tenth slower than the other layouts'.
+static bool pack_pays(const peak_gemm_desc_t &d, double direct, double staged)
+{
+    const double M = (double)d.M, N = (double)d.N, width = M * N / (M + N), work = M * N * (double)d.K;
+    if (d.K < 512) return false;
+    if (d.dtype == PEAK_DT_F32) return width >= 1000.0 || (width >= 480.0 && d.transA && !d.transB);
+    if (direct < 0.93 * staged) return true;
+    return width >= 480.0 && work >= 3.2e9 && (d.K >= 1000 || work >= 8.0e9) && direct < (d.K >= 3000 ? 1.4 : 1.12) * staged;
+}
+
+// Fills *g and returns true if copies pay against `staged` (the choice among the kernels that take any alignment).
 static int64_t round_up(int64_t x, int64_t m) { return cdiv(x, m) * m; }
 static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int streamk)
 {
@@ -450,9 +479,9 @@ static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int st
     if (v < 0 || !g_variants[v].direct || g_variants[v].kind != KIND_TILED) return false;
     const size_t bytes_a = (pack & 1) ? (size_t)((d.transA ? e.K : d.M) * e.lda * es) : 0;
     const size_t bytes_b = (pack & 2) ? (size_t)((d.transB ? d.N : e.K) * e.ldb * es) : 0;
-    const double copy_us = 4.5 + 2.0 * (double)(bytes_a + bytes_b) / 4.0e6;
+    const double copy_us = 6.0 + 2.0 * (double)(bytes_a + bytes_b) / 4.0e6;
     const double direct = tiled_cost(g_variants[v], e, choose_split(g_variants[v], e)) + units_of_us(g_variants[v], copy_us);
-    if (direct >= 0.93 * tiled_cost(g_variants[staged], d, choose_split(g_variants[staged], d))) return false;
+    if (!pack_pays(d, direct, tiled_cost(g_variants[staged], d, choose_split(g_variants[staged], d)))) return false;
     plan_geometry(g, e, v, 0, streamk);
     g->pack = pack;
     g->pack_k = e.K; g->pack_m = e.M; g->pack_n = e.N;
@@ -660,8 +689,8 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     if (forced_split <= 0 && streamk == 0 && table_split < 0) streamk = 1;
     plan_geometry(&p->g, d, pick, forced_split > 0 ? forced_split : (table_split > 0 ? table_split : 0), streamk);
     // Leading dimensions are known here, base addresses only at run time: a variant that copies
-    // 16-byte chunks gets a register-staged stand-in for runs whose A or B base is off that alignment.
-    // A register-staged choice of the cost model's is the stand-in itself where aligned copies are worth making
+    // 16-byte chunks gets a stand-in that takes any alignment for runs whose A or B base is off that alignment.
+    // Such a choice of the cost model's is the stand-in itself where aligned copies are worth making
     // (a table row's variant and split are taken as they are)
     if (own_choice && forced_split <= 0 && !g_variants[pick].direct) {
         Geometry packed = Geometry();

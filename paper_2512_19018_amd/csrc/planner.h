@@ -102,7 +102,7 @@ static inline int skinny_reg_split(int64_t N, int64_t K)
 struct peak_gemm_plan {
     peak_gemm_desc_t d;
     peak::Geometry g;           // the selected variant
-    peak::Geometry alt;         // register-staged stand-in for runs whose A or B base is not 16-byte aligned
+    peak::Geometry alt;         // stand-in of any alignment for runs whose A or B base is not 16-byte aligned
                           // (variant -1 when the selected variant has no alignment needs)
     size_t ws_bytes;      // the larger of the two workspaces
 };

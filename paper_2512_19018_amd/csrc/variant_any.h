@@ -1,4 +1,4 @@
-// Launch of the any-alignment kernels ("_r": through registers) and the macro for their rows of the variant table.
+// Launch of the ring kernels and the macros for their rows of the variant table.
 #pragma once
 
 #include "variant.h"
@@ -13,22 +13,23 @@ static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-#define TILED_ANY(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, PF, EU)                               \
-    {NAME, KIND_TILED, DT, AKM, BKN, 0, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, 2,                \
-     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, PF, EU>::LDS_BYTES, 0,                  \
-     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, PF, EU>>, 0, 0, 0, 0, 0}
+// operands of any alignment straight to LDS, STAGES K tiles in a ring
+#define TILED_LOOSE(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                         \
+    {NAME, KIND_TILED, DT, AKM, BKN, 0, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, STAGES,         \
+     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>::LDS_BYTES, 0,     \
+     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>>, 0, 0, 0, 0, 0}
 
-#define TILED_ANY_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, PF, EU)                                 \
-    TILED_ANY(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
-    TILED_ANY(NAME "_nn", DT, 0, 1, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
-    TILED_ANY(NAME "_tt", DT, 1, 0, BM, BN, WMW, WNW, WKW, RB, PF, EU),                                \
-    TILED_ANY(NAME "_tn", DT, 1, 1, BM, BN, WMW, WNW, WKW, RB, PF, EU)
+#define TILED_LOOSE_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                           \
+    TILED_LOOSE(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                          \
+    TILED_LOOSE(NAME "_nn", DT, 0, 1, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                          \
+    TILED_LOOSE(NAME "_tt", DT, 1, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                          \
+    TILED_LOOSE(NAME "_tn", DT, 1, 1, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)
 
 // aligned operands straight to LDS, STAGES K tiles in a ring
 #define TILED_RING(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                          \
     {NAME, KIND_TILED, DT, AKM, BKN, 1, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, STAGES,         \
-     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, 1, EU, STAGES>::LDS_BYTES, 0,           \
-     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, 1, EU, STAGES>>,       \
+     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, false>::LDS_BYTES, 0,           \
+     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, false>>,       \
      BKN, AKM, 0, 0, 0, 1}
 
 #define TILED_RING_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                            \

@@ -51,8 +51,8 @@ def sample_settings(cands, samples, seed=0):
 
 
 def reference_setting(cands):
-    """The plainest accepted setting: register-staged 64x64 tiles if present, else
-    the first register-staged one, else the first of all; always without a K split."""
+    """The plainest accepted setting: any-alignment 64x64 tiles if present, else
+    the first any-alignment one, else the first of all; always without a K split."""
     unsplit = [c for c in cands if c[2] == 1] or list(cands)
     for key in ("_r64x64_", "_r128x128_"):
         for c in unsplit:
