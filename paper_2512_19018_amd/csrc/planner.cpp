@@ -160,6 +160,10 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     } else {
         us = ktiles * (v.bm + v.bn) * v.bk * 2.0 / 1000.0 / (v.bk >= 128 ? 85.0 : 72.0);
     }
+    // 64x64 in 16 bits: three stages and three workgroups per CU up to 28 K tiles per slice (192x2816x1088 NN 6.3 us against 6.9 with
+    // five, f16 195x3088x472 NT 4.2 and 4.9), five beyond (1024x1024x4480 NT 19.9 and 17.4).  60 plans, time with three over that with
+    // five: 0.93 in the mean up to 28 tiles, 1.02 beyond, 1.17 at most.
+    if (v.dt != PEAK_DT_F32 && v.bm == 64 && v.bn == 64 && (v.ns < 5) != (cdiv(cdiv(d.K, v.bk), split) <= 28)) us *= 1.05;
     return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v)) + split_us(d, split));
 }
 

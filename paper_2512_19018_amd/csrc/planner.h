@@ -70,10 +70,8 @@ static inline bool stages_a(const Variant &v, int transA) { return v.kind == KIN
 // workgroups of the GEMM launch
 int64_t grid_blocks(const Geometry &g);
 
-// Number of K slices: one workgroup per CU is enough once it streams (measured:
-// splitting further only adds the reduction pass), at least 4 stages each.  Workgroups on
-// four fifths of the CUs already count as enough (bf16 16x28672x8192 with 128 rows per
-// workgroup: 224 workgroups unsplit 74.9 us, 448 in two slices 87.1 us).
+// K slices with which a streaming kernel's workgroups fill the chip once, rounded up from four fifths, at least 4 stages
+// each: what the choice between streaming and ring kernels goes by (its limits were measured with it).
 static inline int skinny_split(int64_t N, int64_t K, int bn, int kstep)
 {
     const int64_t tiles_n = (N + bn - 1) / bn;
