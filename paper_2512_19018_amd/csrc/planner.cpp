@@ -5,6 +5,7 @@
 #include <dlfcn.h>
 
 #include <cerrno>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -278,6 +279,45 @@ static bool streamk_pays(const Variant &v, const peak_gemm_desc_t &d, int S, int
     return cut < 0.9 * (tile + fixed);
 }
 
+// The streaming kernels, in microseconds: the operand's bytes at the chip's rate and the busiest CU's share of them (with the rows
+// of the M x K operand its workgroups read again) at one CU's rate - in fp32 with M > 16 its MFMAs' -, as a root of squares
+// since neither overlaps the other fully; rounds of workgroups; slices out, back and a launch.  Fitted over 77 random decode
+// shapes (M 1 to 64, 2048 to 32768 x 2048 to 16384) with 15 splits each, within 3 to 7 % for each kernel.
+static double stream_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
+{
+    const int64_t ktiles = cdiv(d.K, v.bk), per_slice = cdiv(ktiles, split), slices = cdiv(ktiles, per_slice);
+    const int64_t groups = cdiv(d.N, v.bn) * slices, fit = LDS_LIMIT / v.lds > 1 ? LDS_LIMIT / v.lds : 1;
+    const double es = (double)esize_of(d.dtype);
+    double cu = 57.0, chip = 7000.0;                        // bytes per ns
+    if (d.dtype == PEAK_DT_F32) {
+        cu = v.bm <= 16 ? 52.0 : v.bm <= 32 ? 41.0 : v.tr ? 25.0 : 30.0;
+        chip = v.bm <= 16 ? 7000.0 : v.bm <= 32 ? 6500.0 : 5000.0;
+    }
+    const double busiest = (double)cdiv(groups, num_cu()) * (double)(v.bm + v.bn) * (double)(v.bk * per_slice) * es / 1000.0 / cu;
+    const double all = (double)d.N * (double)d.K * es / 1000.0 / chip;
+    const double us = sqrt(busiest * busiest + all * all) + 1.5 * (double)cdiv(groups, num_cu() * fit) + 1.5;
+    return slices > 1 ? us + 2.5 + 0.1 * (double)slices + 0.5 * 4.0e-6 * (double)(slices * d.M * d.N) : us;
+}
+
+// ... and the K split by it, where it sees 7 % over as many slices as fill the chip once, rounded up (skinny_split): slices that
+// spill into a second, nearly empty round cost most (f16 16x8960x7680 NT, 140 tiles, 38.9 us in two slices, 33.1 in three; fp32
+// 37x6592x16128 NN 238 in five, 145 in fourteen; 35x11840x2560 NN 70 in three, 50 in five; 30x23296x9344 NN 107 in three, 81 in two).
+// Of 73 shapes 1.1 % off the best split on average, 7 % without, none behind.  At least four stages per slice; partials within
+// the array of peak_gemm_run_static.
+static int stream_split(const Variant &v, const peak_gemm_desc_t &d)
+{
+    const size_t copy = stages_a(v, d.transA) ? (size_t)d.M * (size_t)d.K * esize_of(d.dtype) + 512 : 0;
+    const int64_t most = cdiv(d.K, v.bk) / 4;
+    int best = skinny_split(d.N, d.K, v.bn, v.bk);
+    double best_us = 0.93 * stream_cost(v, d, best);
+    for (int s = 1; s <= 64 && (s == 1 || s <= most); ++s) {
+        if (s > 1 && 4 * (size_t)s * (size_t)d.M * (size_t)d.N + copy > (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES) break;
+        const double us = stream_cost(v, d, s);
+        if (us < best_us) { best_us = us; best = s; }
+    }
+    return best;
+}
+
 // streamk: 1 take hybrid stream-K wherever it applies, -1 never, 0 let the cost model decide
 static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, int forced_split, int streamk = 0)
 {
@@ -289,7 +329,7 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     p->tiles_n = (int)cdiv(d.N, v.bn);
     p->ktiles_total = (int)cdiv(d.K, v.bk);
     int split = forced_split > 0 ? forced_split
-              : v.kind == KIND_SKINNY     ? skinny_split(d.N, d.K, v.bn, v.bk)
+              : v.kind == KIND_SKINNY     ? stream_split(v, d)
               : v.kind == KIND_SKINNY_REG ? skinny_reg_split(d.N, d.K)
                                           : choose_split(v, d);
     if (split > p->ktiles_total) split = p->ktiles_total;
@@ -405,7 +445,11 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             // 48x13824x11136 67.3 and 60.9, 64x14080x12928 80.0 and 77.9, the operand cold in the caches)
             const int64_t fill = (int64_t)num_cu() * 4, halves = cdiv(d.N, v.bn / 2);
             const bool halves_fill = halves <= num_cu() && (halves * 16 >= (int64_t)num_cu() * 15 ? d.K <= 14336 : halves * 5 >= fill && d.K <= 9344);
-            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 || halves_fill)) continue;
+            if (v.stream_rank == 3 && cdiv(d.N, v.bn) * 5 < fill && (v.bm < 64 ? v.bm < 32 || d.dtype == PEAK_DT_F32 : halves_fill)) continue;
+            // 17 to 32 rows in 16 bits: 128 columns also where the cost has them a tenth ahead of 64 (25x19968x7552 68.5 us with 64, 58.7
+            // with 128; 29x17792x13568 119 and 93)
+            if (v.stream_rank == 3 && v.bm == 32 && cdiv(d.N, v.bn) * 5 < fill && stream[2] >= 0 &&
+                stream_cost(v, d, stream_split(v, d)) >= 0.9 * stream_cost(g_variants[stream[2]], d, stream_split(g_variants[stream[2]], d))) continue;
             if (stream[v.stream_rank] < 0) stream[v.stream_rank] = i;
             continue;
         }
