@@ -162,8 +162,9 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     const int whole = tiles - p.sk_tiles;                   // stream-K: tiles that are not cut
     int slice, tile, sk_pos = -1;
     if (p.sk_tiles == 0) {
-        slice = __builtin_amdgcn_readfirstlane(bid / tiles);
-        tile = bid - slice * tiles;
+        const int pos = order_of_block(bid, tiles * p.split);
+        slice = __builtin_amdgcn_readfirstlane(pos / tiles);
+        tile = pos - slice * tiles;
     } else if (bid < whole) {
         slice = -1;                                         // the whole of K
         tile = bid;
@@ -173,7 +174,8 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
         tile = whole + sk_pos;
     }
     int tm, tn;
-    tile_of_block(tile, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    if (p.sk_tiles != 0) tile = order_of_block(tile, tiles);
+    tile_in_order(tile, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
 
     const int kt_begin = slice < 0 ? 0 : slice * p.ktiles_per_slice;

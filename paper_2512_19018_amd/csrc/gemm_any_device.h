@@ -301,10 +301,10 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
     const int r16 = lane & 15, q = lane >> 4;
 
     const int tiles = p.tiles_m * p.tiles_n;
-    const int bid = blockIdx.x;
-    const int slice = __builtin_amdgcn_readfirstlane(bid / tiles);
+    const int pos = order_of_block(blockIdx.x, tiles * p.split);
+    const int slice = __builtin_amdgcn_readfirstlane(pos / tiles);
     int tm, tn;
-    tile_of_block(bid - slice * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    tile_in_order(pos - slice * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int kt_begin = slice * p.ktiles_per_slice;
     int kt_end = kt_begin + p.ktiles_per_slice;

@@ -48,3 +48,13 @@ def test_transposed_copy_of_a(gu, oracle, dtype, tb, M, K):
             continue
         print(n, flush=True)
         _check(gu, oracle, dtype, 1, tb, M, 264, K, pg.force_flags(i), "acopy=1")
+
+
+@pytest.mark.parametrize("dtype,name", [(pi.BF16, "_m256x128w4a3_nn"), (pi.BF16, "_m64x64q3_nn"), (pi.F16, "_t128x128w4_nn"),
+                                        (pi.F32, "_r32x32_nn"), (pi.F32, "_m64x64q3_nn")])
+@pytest.mark.parametrize("tiles_n,split", [(1, 2), (1, 7), (3, 3), (5, 2), (7, 9)])
+def test_order_of_tiles_and_slices(gu, oracle, dtype, name, tiles_n, split):
+    """Tiles x slices below, at odd distances from and above the 8 XCDs that share them out."""
+    vid, full = next((i, n) for i, n in gu.variants_for(dtype, 0, 0) if n.endswith(name))
+    N = {"m256x128w4a3": 128, "t128x128w4": 128, "r32x32": 32, "m64x64q3": 64}[name.split("_")[1]] * tiles_n - 8
+    _check(gu, oracle, dtype, 0, 0, 24, N, split * 128, gu.pg.force_flags(vid, split), "split=%d " % split)
