@@ -301,7 +301,7 @@ static double stream_cost(const Variant &v, const peak_gemm_desc_t &d, int split
 
 // ... and the K split by it, where it sees 7 % over as many slices as fill the chip once, rounded up (skinny_split): slices that
 // spill into a second, nearly empty round cost most (f16 16x8960x7680 NT, 140 tiles, 38.9 us in two slices, 33.1 in three; fp32
-// 37x6592x16128 NN 238 in five, 145 in fourteen; 35x11840x2560 NN 70 in three, 50 in five; 30x23296x9344 NN 107 in three, 81 in two).
+// 37x6592x16128 TN 238 in five, 147 in nine; 35x11840x2560 NN 70 in three, 50 in five; bf16 30x23296x9344 NN 107 in three, 81 in two).
 // Of 73 shapes 1.1 % off the best split on average, 7 % without, none behind.  At least four stages per slice; partials within
 // the array of peak_gemm_run_static.
 static int stream_split(const Variant &v, const peak_gemm_desc_t &d)

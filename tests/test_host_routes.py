@@ -127,3 +127,27 @@ def test_tuner_leaves_plans_that_no_row_can_ask_for():
     assert tune.beyond_rows(plan("bf16", 0, 1, 4096, 5120, 5120, flags=pg.force_flags(streamk=True))[0].info()) == "stream-K"
     assert tune.beyond_rows(plan("bf16", 0, 1, 8192, 8192, 8192)[0].info()) is None
     assert tune.beyond_rows(plan("bf16", 0, 1, 101, 103, 107)[0].info()) is None
+
+
+# (as many slices as fill the chip once, rounded up, were 2, 5, 3 and 3: a second round with few workgroups in it)
+@pytest.mark.parametrize("dt,ta,tb,M,N,K,splits", [("f16", 0, 1, 16, 8960, 7680, 3), ("f32", 1, 0, 37, 6592, 16128, 9),
+                                                   ("f32", 0, 0, 35, 11840, 2560, 5), ("bf16", 0, 0, 30, 23296, 9344, 2)])
+def test_streaming_slices_do_not_spill_into_a_thin_round(dt, ta, tb, M, N, K, splits):
+    _, name, split, _, _ = plan(dt, ta, tb, M, N, K)
+    assert "skinny" in name and split == splits
+
+
+@pytest.mark.parametrize("dt,ta,tb", list(itertools.product(DTYPES, (0, 1), (0, 1))))
+def test_streaming_slices_and_copy_fit_the_fixed_array(dt, ta, tb):
+    for M, N, K in itertools.product((1, 16, 17, 32, 33, 48, 64), (2048, 8960, 13312, 28672, 40960), (2048, 7680, 16384, 28672)):
+        p, name, split, _, _ = plan(dt, ta, tb, M, N, K)
+        if "skinny" in name:
+            assert p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, (M, N, K, split)
+
+
+@pytest.mark.parametrize("dt", ("f16", "bf16"))
+@pytest.mark.parametrize("tb,M,N,K,stages", [(0, 192, 2816, 1088, 3), (1, 195, 3088, 472, 3), (0, 192, 2816, 28 * 64, 3), (0, 192, 2816, 29 * 64, 5),
+                                             (0, 320, 2688, 28 * 64, 3), (0, 320, 2688, 29 * 64, 5), (1, 1024, 1024, 4480, 5)])
+def test_ring_stages_by_the_depth_of_a_slice(dt, tb, M, N, K, stages):
+    _, name, split, _, _ = plan(dt, 0, tb, M, N, K)
+    assert "_m64x64q%d_" % stages in name and split == 1
