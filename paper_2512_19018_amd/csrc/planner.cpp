@@ -163,8 +163,15 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
     }
     // 64x64 in 16 bits: three stages and three workgroups per CU up to 28 K tiles per slice (192x2816x1088 NN 6.3 us against 6.9 with
     // five, f16 195x3088x472 NT 4.2 and 4.9), five beyond (1024x1024x4480 NT 19.9 and 17.4).  60 plans, time with three over that with
-    // five: 0.93 in the mean up to 28 tiles, 1.02 beyond, 1.17 at most.
-    if (v.dt != PEAK_DT_F32 && v.bm == 64 && v.bn == 64 && (v.ns < 5) != (cdiv(cdiv(d.K, v.bk), split) <= 28)) us *= 1.05;
+    // five: 0.93 in the mean up to 28 tiles, 1.02 beyond, 1.17 at most.  One workgroup on most of the CUs: nothing else
+    // there covers a stage's way through loaded caches, and three do up to 20 tiles: 20 plans of 21 to 27 tiles, five over three, 0.95
+    // of the time with operands from HBM (192x4432x1536 TT 10.5 us and 11.7), 1.04 where each run finds its own in the L2 (7.8 and 7.5);
+    // with the L2 cold and the rest in the last-level cache bf16 462x1984x1728 NN 8.7 and 9.4.
+    if (v.dt != PEAK_DT_F32 && v.bm == 64 && v.bn == 64) {
+        const int64_t groups = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split;
+        const int64_t most = per_cu == 1 && 8 * groups > 5 * num_cu() ? 20 : 28;
+        if ((v.ns < 5) != (cdiv(cdiv(d.K, v.bk), split) <= most)) us *= 1.05;
+    }
     return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v)) + split_us(d, split));
 }
 

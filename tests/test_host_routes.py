@@ -147,7 +147,7 @@ def test_streaming_slices_and_copy_fit_the_fixed_array(dt, ta, tb):
 
 @pytest.mark.parametrize("dt", ("f16", "bf16"))
 @pytest.mark.parametrize("tb,M,N,K,stages", [(0, 192, 2816, 1088, 3), (1, 195, 3088, 472, 3), (0, 192, 2816, 28 * 64, 3), (0, 192, 2816, 29 * 64, 5),
-                                             (0, 320, 2688, 28 * 64, 3), (0, 320, 2688, 29 * 64, 5), (1, 1024, 1024, 4480, 5)])
+                                             (0, 320, 2688, 20 * 64, 3), (0, 320, 2688, 21 * 64, 5), (1, 1024, 1024, 4480, 5)])
 def test_ring_stages_by_the_depth_of_a_slice(dt, tb, M, N, K, stages):
     _, name, split, _, _ = plan(dt, 0, tb, M, N, K)
     assert "_m64x64q%d_" % stages in name and split == 1
