@@ -516,6 +516,7 @@ static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int st
 {
     const int64_t es = esize_of(d.dtype), chunk = 16 / es, line = 128 / es;
     if (d.M <= 64) return false;                            // streamed once: a copy would double the traffic
+    if (d.N < chunk || d.K < chunk) return false;           // pack_kernel loads whole chunks of a row
     peak_gemm_desc_t e = d;
     e.K = round_up(d.K, chunk);
     const bool tail = e.K != d.K;                           // both operands then need zeros up to the chunk

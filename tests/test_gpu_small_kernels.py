@@ -58,3 +58,16 @@ def test_order_of_tiles_and_slices(gu, oracle, dtype, name, tiles_n, split):
     vid, full = next((i, n) for i, n in gu.variants_for(dtype, 0, 0) if n.endswith(name))
     N = {"m256x128w4a3": 128, "t128x128w4": 128, "r32x32": 32, "m64x64q3": 64}[name.split("_")[1]] * tiles_n - 8
     _check(gu, oracle, dtype, 0, 0, 24, N, split * 128, gu.pg.force_flags(vid, split), "split=%d " % split)
+
+
+@pytest.mark.parametrize("dtype,rem", [(pi.F32, r) for r in (1, 2, 3)] + [(pi.BF16, r) for r in range(1, 8)])
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0)])
+def test_aligned_copies_of_rows_that_end_inside_a_chunk(gu, oracle, dtype, rem, ta, tb):
+    """Every number of elements over, along K and along the matrices' other sides."""
+    M, N, K = 2048 + rem, 2040 + rem, 1024 + rem
+    A, B = (pi.store(pi.logical_matrix(71, i, *s, "uniform", 1.0, dtype), bool(t))
+            for i, (s, t) in enumerate((((M, K), ta), ((K, N), tb))))
+    C = pi.store(pi.logical_matrix(71, 2, M, N, "uniform", 1.0, dtype), False)
+    got, raw, info = gu.run_gemm(dtype, ta, tb, M, N, K, 0.5, 2.0, A, B, C)
+    assert "pack=3" in info, info
+    gu.check_against_oracle(oracle, got, dtype, ta, tb, M, N, K, 0.5, A, B, 2.0, C, rows=[0, 1, 255, 1000, M - 9, M - 2, M - 1], what=info)
