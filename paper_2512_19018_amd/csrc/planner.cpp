@@ -136,6 +136,9 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     const int64_t rest = per_cu % fit;
     double t = (double)(per_cu / fit) * fit * us / r->rate + r->launch + r->round * (double)cdiv(per_cu, fit);
     if (rest) t += (double)rest * us / (r->rate * (fit > 1 ? r->alone + (1.0 - r->alone) * (double)(rest - 1) / (fit - 1) : 1.0));
+    // fp32, one round of a few K tiles: 32x32 with its 64 k per tile 0.2 to 0.5 us ahead of 64x32 with 32 (345x79x33 NT 3.76 us and
+    // 4.21, 171x1321x77 TN 4.76 and 5.05, 1261x89x95 NN 4.78 and 4.90; with at most 32 k 0.1 to 0.2 behind)
+    if (f32 && v.bm == 32 && per_cu == 1 && split == 1 && d.K > 32 && d.K <= 128) t -= 0.5;
     if (split > 1) {                                        // the partials out and back (3.8 and 3.2 TB/s) and the second launch
         const double mb = 4.0e-6 * split * (double)d.M * (double)d.N;
         t += f32 ? 2.2 + 0.08 * split + 0.313 * mb : 2.8 + 0.11 * split + 0.26 * mb;
@@ -507,7 +510,10 @@ static bool pack_pays(const peak_gemm_desc_t &d, double direct, double staged)
     if (d.K < 512) return false;
     if (d.dtype == PEAK_DT_F32) return width >= 1000.0 || (width >= 480.0 && d.transA && !d.transB);
     if (direct < 0.93 * staged) return true;
-    return width >= 480.0 && work >= 3.2e9 && (d.K >= 1000 || work >= 8.0e9) && direct < (d.K >= 3000 ? 1.4 : 1.12) * staged;
+    // (long and narrow: 15 products of 3600 to 5800 by 400 to 535 at most, 1.11 in the mean - f16 531x3745x3655 TN 41.3 us and 37.3,
+    // bf16 413x5725x2967 NN 46.4 and 35.8 -, none below 1.00; 26 squarer ones of that width 0.98)
+    const bool wide = width >= 480.0 || (width >= 360.0 && (d.M > d.N ? d.M : d.N) >= 3600);
+    return wide && work >= 3.2e9 && (d.K >= 1000 || work >= 8.0e9) && direct < (d.K >= 3000 ? 1.4 : 1.12) * staged;
 }
 
 // Fills *g and returns true if copies pay against `staged` (the choice among the kernels that take any alignment).
