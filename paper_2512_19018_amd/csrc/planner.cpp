@@ -481,7 +481,12 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     }
     for (int r = 3; r >= 1; --r)
         if (stream[r] >= 0) return ring >= 0 && ring_ahead_of_streaming(g_variants[ring], g_variants[stream[r]], d) ? ring : stream[r];
-    if (pick < 0 && ring < 0) return any;                   // (operands that suit the 16-byte copies always take a kernel made of them)
+    // Operands that suit the 16-byte copies take a kernel made of them.  Where the ring kernels do not fit, only large tiles
+    // that copy directly are left - B stored K x N in padded rows, N of no whole chunks, whose edge they mask -, and the kernels
+    // for any alignment stand against those by price, aligned copies of B then against both: 69 such products, 0.44 of the masked
+    // tiles' time in the mean (f16 272x2514x416 5.6 us and 17.8, f32 7403x579x372 37.6 and 60.7, 2592x6294x76 42.9 and 47.2), and
+    // without their partials (fp32 524x3826x3752, five slices of 256x128, 40 MB).
+    if (ring < 0 && any >= 0 && (pick < 0 || best_any < best)) return any;
     // A K split of an fp32 launch costs some microseconds more than the model has for it: 504x1396x2380 NT in five slices
     // of 128x128 tiles 42.1 us, 36.1 in ring tiles unsplit; 112x208x816 NN 10.0 in 13 slices, 8.2 in ring tiles.
     // (2560x1340x2164 TT, unsplit in both, 134 us with the 128 x 128 tile and 147 in ring tiles.)  It counts against the

@@ -151,3 +151,25 @@ def test_streaming_slices_and_copy_fit_the_fixed_array(dt, ta, tb):
 def test_ring_stages_by_the_depth_of_a_slice(dt, tb, M, N, K, stages):
     _, name, split, _, _ = plan(dt, 0, tb, M, N, K)
     assert "_m64x64q%d_" % stages in name and split == 1
+
+
+# B stored K x N in whole-chunk rows with an N of no whole chunks: the ring kernels cannot read it, the large tiles that mask the edge can
+PADDED_B = [("f32", 112, 109, 72), ("f32", 614, 359, 84), ("f32", 384, 105, 5844), ("bf16", 512, 1001, 1024), ("f16", 1328, 204, 384),
+            ("f16", 272, 2514, 416), ("bf16", 1753, 157, 544), ("f32", 524, 3826, 3752), ("f32", 345, 5647, 4848), ("f32", 324, 5531, 3416)]
+
+
+@pytest.mark.parametrize("dt,M,N,K", PADDED_B)
+def test_masked_large_tiles_stand_against_the_kernels_for_any_alignment(dt, M, N, K):
+    chunk = 16 // DTYPES[dt][1]
+    p, name, split, pack, _ = plan(dt, 0, 0, M, N, K, (0, -N % chunk, 0))
+    assert name.startswith(dt + "_r") and not pack, (name, pack)
+    assert p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES
+
+
+def test_partials_with_a_padded_b_fit_the_fixed_array():
+    """fp32, where the masked tiles' own split would ask for more: peak_gemm_run_static takes every one."""
+    for M, N, K in itertools.product((345, 524, 858, 1060), (1509, 2809, 3183, 3826, 5647), (1032, 3264, 4848, 6336)):
+        p, name, _, pack, _ = plan("f32", 0, 0, M, N, K, (0, -N % 4, 0))
+        if not pack:
+            assert p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, (M, N, K, name)
+        assert pg.peak_gemm_run_static(p.handle, 1.0, 0, 0, 0.0, 0, 0) != pg.PEAK_ERR_WORKSPACE, (M, N, K, name)
