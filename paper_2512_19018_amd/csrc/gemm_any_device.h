@@ -41,9 +41,19 @@ struct CfgAny {
     // sum per wave 5.0e-7 in 64x32 tiles, 3.6e-7 in 32x32 ones; four 2.6e-7 and 1.9e-7; level in time)
     static constexpr int SETS = DT_ == DT_F32 && LOOSE_ && MB * NB <= 4 ? 4 : 1;
     static constexpr bool LOOSE = LOOSE_;
+    // fragments of one round at a time, where those of a whole stage do not fit the registers beside the sums (fp32 64x64: 128
+    // registers and four workgroups per CU, 148 and three; level with a deep K, K = 59 11.3 us against 13.0 for 8031x467 TT)
+    static constexpr bool BY_ROUND = SETS == 4 && EU == 4 && ROUNDS > 1;
     static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB, STAGE = A_BYTES + B_BYTES;
     static constexpr int RED_BYTES = PLACES * (WK_ - 1) * MB * NB * 1024;
-    static constexpr int LDS_BYTES = RING_ * STAGE > RED_BYTES ? RING_ * STAGE : RED_BYTES;
+    static constexpr int OUT_BYTES = 32 * (WTN * 4 + 16) * PLACES;        // the turnaround on the way out
+    // The least a launch needs, the ring in full, and a launch's own: no more stages than it has K tiles, since with a short K it is
+    // the workgroups that share a CU which cover its trips to memory (the whole ring whatever K, and a ring of its K tiles: bf16
+    // 5839x5535x43 NT in 128x64 tiles 29.7 us and 24.4, 7795x2115x80 TN 24.8 and 20.3; f16 3848x4144x48 TT in 128x64 ring tiles 14.5
+    // and 11.4, 40 aligned products with K to 128 0.875 of the time)
+    static constexpr int LDS_LEAST = OUT_BYTES > RED_BYTES ? OUT_BYTES : RED_BYTES;
+    static constexpr int LDS_BYTES = RING_ * STAGE > LDS_LEAST ? RING_ * STAGE : LDS_LEAST;
+    static int lds_of(int ktiles) { return ktiles >= RING_ ? LDS_BYTES : ktiles * STAGE > LDS_LEAST ? ktiles * STAGE : LDS_LEAST; }
     static_assert(RB_ == 128 || RB_ == 256, "swizzles below");
     static_assert(ROUNDS * WK_ * KROUND == BK && ROUNDS >= 1, "whole rounds per wave");
     static_assert(WTM % 32 == 0 && WTN % 16 == 0, "epilogue slabs of 32 rows");
@@ -293,7 +303,7 @@ template <class C>
 __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's symbol
-    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
+    extern __shared__ __attribute__((aligned(1024))) char lds[];            // C::lds_of(K tiles of a slice) bytes
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave_all % C::PLACES, kpar = wave_all / C::PLACES;
@@ -418,6 +428,20 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         };
         auto multiply_stage = [&](int so) {                     // so: the stage's offset in LDS
             const char *st = lds + so;
+            if constexpr (C::BY_ROUND) {
+                static_for<C::ROUNDS>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    u32x4 af[C::MB], bf[C::NB];
+#pragma unroll
+                    for (int i = 0; i < C::NB; ++i) bf[i] = frag_b(st, i, r);
+#pragma unroll
+                    for (int i = 0; i < C::MB; ++i) af[i] = frag_a(st, i, r);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(af, bf);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                return;
+            }
             u32x4 af[C::ROUNDS][C::MB], bf[C::ROUNDS][C::NB];
             u32x2 al[C::ROUNDS][C::MB], ah[C::ROUNDS][C::MB], bl[C::ROUNDS][C::NB], bh[C::ROUNDS][C::NB];
             constexpr bool TRA = C::A_KM && C::DT != DT_F32, TRB = C::B_KN && C::DT != DT_F32;
@@ -524,8 +548,7 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
             if constexpr (C::B_KN) xB.load(b, k0, tid);
             else kB.load(b, k0, tid);
         };
-        auto store = [&](int stage, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
-            char *st = lds + stage * C::STAGE;
+        auto store = [&](char *st, u32x4 (&a)[CA], u32x4 (&b)[CB]) {
             if constexpr (C::A_KM) xA.store(st, a, tid);
             else kA.store(st, a, tid);
             if constexpr (C::B_KN) xB.store(st + C::A_BYTES, b, tid);
@@ -559,24 +582,26 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
                 rA.issue(lds + stage * C::STAGE, kt, wave_all);
                 rB.issue(lds + stage * C::STAGE + C::A_BYTES, kt, wave_all);
             });
-            lds_barrier();                                  // everybody's copies, before the stages are written again
         }
+        // After the ring's last barrier every copy has landed and nobody reads the stage after the last tile's any more.
+        const int st = (KF % C::RING) * C::STAGE;
         for (int kt = KF; kt < KT; ++kt) {
             const int64_t k0 = kbase + (int64_t)kt * C::BK;
             if constexpr (C::A_KM) xA.fix(ta, k0, tid);
             else kA.fix(ta, k0, tid);
             if constexpr (C::B_KN) xB.fix(tb, k0, tid);
             else kB.fix(tb, k0, tid);
-            store(0, ta, tb);
+            if (kt > KF) lds_barrier();
+            store(lds + st, ta, tb);
             if (kt + 1 < KT) load(kt + 1, ta, tb);
             lds_barrier();
             u32x4 af[C::MB], bf[C::NB];
             static_for<C::ROUNDS>([&](auto rc) {
-                fragments(lds, decltype(rc)::value, af, bf);
+                fragments(lds + st, decltype(rc)::value, af, bf);
                 multiply(af, bf);
             });
-            lds_barrier();
         }
+        if constexpr (C::WAVES_K > 1) lds_barrier();        // the stages are read, before the sums over waves go through LDS
     }
 
 #pragma unroll

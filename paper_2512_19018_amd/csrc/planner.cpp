@@ -104,12 +104,15 @@ constexpr double MFMA_PER_US = 4.88e6;                      // 16-bit multiply-a
 // (and 0.15 us a slice where the partials are too few to matter: fp32 131x167x1069 14.1 us in four slices, 15.4 in twelve)
 static double split_us(const peak_gemm_desc_t &d, int split) { return split > 1 ? 2.0 + 0.15 * split + reduce_cost(d, split) / MFMA_PER_US : 0.0; }
 
-// workgroups that share a CU: LDS, four waves per SIMD
-static int resident(const Variant &v)
+// workgroups that share a CU at `ktiles` K tiles per slice: LDS (a ring has no more stages than that), registers
+static int resident(const Variant &v, int64_t ktiles)
 {
-    int fit = LDS_LIMIT / v.lds;
-    if (fit > 1024 / v.nt) fit = 1024 / v.nt;
-    return fit < 1 ? 1 : fit;
+    int64_t lds = v.lds;
+    if (v.lds_least > 0 && ktiles < v.ns) lds = v.lds / v.ns * ktiles > v.lds_least ? v.lds / v.ns * ktiles : v.lds_least;
+    int64_t fit = LDS_LIMIT / lds;
+    const int64_t waves = 256 * (v.eu > 0 ? v.eu : 4) / v.nt;
+    if (fit > waves) fit = waves;
+    return fit < 1 ? 1 : (int)fit;
 }
 
 // The kernels that take any alignment.  Times of all their tiles and K splits over 160 random unaligned products of
@@ -129,8 +132,9 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     const StagedRate *r = f32 ? rate32 : rate16;
     while (r->bm && (r->bm != v.bm || r->bn != v.bn)) ++r;
     const int64_t per_cu = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
-    const int fit = resident(v);
-    const double k = (double)v.bk * (double)cdiv(cdiv(d.K, v.bk), split);
+    const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split);
+    const int fit = resident(v, ktiles);
+    const double k = (double)v.bk * (double)ktiles;
     const double us = f32 ? k * v.bm * v.bn * 16.0 / MFMA_PER_US
                           : k * 2.0 * (v.bm * (d.lda % 2 ? 1.1 : 1.0) + v.bn * (d.ldb % 2 ? 1.1 : 1.0)) / 1000.0;    // of one workgroup at rate 1
     const int64_t rest = per_cu % fit;
@@ -175,7 +179,7 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
         const int64_t most = per_cu == 1 && 8 * groups > 5 * num_cu() ? 20 : 28;
         if ((v.ns < 5) != (cdiv(cdiv(d.K, v.bk), split) <= most)) us *= 1.05;
     }
-    return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v)) + split_us(d, split));
+    return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v, cdiv(cdiv(d.K, v.bk), split))) + split_us(d, split));
 }
 
 // Estimated time of a tiled variant, in units of "one 32x32xBK-row MFMA group":

@@ -34,6 +34,8 @@ struct Variant {
                          // 2 = the usual choice, 1 = the fallback for other K, 0 = sweeps only
     int mf16;            // built on the 16x16x32 MFMA (holds a higher clock under the chip's power limit)
     int ring;            // small tile with most of the LDS as a ring of K tiles on their way (`ns` stages)
+    int lds_least;       // kernels that take no more stages than a slice has K tiles: bytes of LDS below which none goes; 0: always `lds`
+    int eu;              // ... and waves per SIMD that their registers leave room for
 };
 
 struct VariantGroup {

@@ -9,7 +9,7 @@ namespace peak {
 template <class C>
 static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
 {
-    hipLaunchKernelGGL((gemm_any_kernel<C>), dim3(grid), dim3(C::NT), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL((gemm_any_kernel<C>), dim3(grid), dim3(C::NT), C::lds_of(a.ktiles_per_slice), (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -17,7 +17,8 @@ static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
 #define TILED_LOOSE(NAME, DT, AKM, BKN, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                         \
     {NAME, KIND_TILED, DT, AKM, BKN, 0, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, STAGES,         \
      CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>::LDS_BYTES, 0,     \
-     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>>, 0, 0, 0, 0, 0}
+     &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>>, 0, 0, 0, 0, 0, 0, \
+     CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, true>::LDS_LEAST, EU}
 
 #define TILED_LOOSE_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                           \
     TILED_LOOSE(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                          \
@@ -30,7 +31,7 @@ static int launch_gemm_any(const GemmArgs &a, unsigned grid, void *stream)
     {NAME, KIND_TILED, DT, AKM, BKN, 1, BM, BN, PEAK_BK(DT, RB), WMW * WNW * WKW * 64, STAGES,         \
      CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, false>::LDS_BYTES, 0,           \
      &launch_gemm_any<CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, false>>,       \
-     BKN, AKM, 0, 0, 0, 1}
+     BKN, AKM, 0, 0, 0, 1, CfgAny<DT, AKM != 0, BKN != 0, BM, BN, WMW, WNW, WKW, RB, EU, STAGES, false>::LDS_LEAST, EU}
 
 #define TILED_RING_LAYOUTS(NAME, DT, BM, BN, WMW, WNW, WKW, RB, STAGES, EU)                            \
     TILED_RING(NAME "_nt", DT, 0, 0, BM, BN, WMW, WNW, WKW, RB, STAGES, EU),                           \

@@ -70,3 +70,27 @@ def test_leading_dimension_beyond_32_bit_offsets(gu, oracle, dtype, transA, tran
     ld = 17_000_001                                           # 64 rows of it are over 2^31 bytes in 16 bits, 32 in fp32
     M, N, K = (3, 70, 66) if not transA else (70, 70, 3)
     _run(gu, oracle, dtype, transA, transB, M, N, K, vid, None, (ld - (M if transA else K), 1), (1, 1), "far rows")
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.F16, pi.BF16])
+@pytest.mark.parametrize("transA,transB", list(itertools.product([0, 1], [0, 1])))
+def test_no_more_stages_than_k_tiles(gu, oracle, dtype, transA, transB):
+    """Fewer K tiles than the ring has stages: a launch's LDS ends with the last of them, the one that K ends in among them."""
+    epc = 16 // pi.DTYPE_SIZE[dtype]
+    seen = 0
+    for vid, name in gu.variants_for(dtype, transA, transB):
+        ring = "_m" in name and "q" in name.split("_")[1]
+        if not ring and "_r" not in name:
+            continue
+        seen += 1
+        with gu.pg.Plan(64, 64, 4096, dtype, transA, transB, flags=gu.pg.force_flags(vid)) as p:
+            info = dict(w.split("=", 1) for w in p.info().split() if "=" in w)
+        bm, bn, bk = (int(x) for x in info["tile"].split("x"))
+        for tiles in range(1, int(info["stages"]) + 1):
+            if ring:                                          # K a whole number of chunks, at and off a tile's end
+                _run(gu, oracle, dtype, transA, transB, bm + 2 * epc, 2 * bn, tiles * bk - (tiles % 2) * epc, vid, None, (0, 0), (0, 0), name)
+            else:
+                _run(gu, oracle, dtype, transA, transB, bm + epc + 1, 2 * bn - 3, tiles * bk - (tiles % 2) * (bk // 2 + 1), vid, None,
+                     (tiles % 3, 1), (1, tiles % 2), name)
+        _run(gu, oracle, dtype, transA, transB, bm, bn, 3 * bk, vid, 3, (0, 0), (0, 0), name)      # slices of one tile
+    assert seen >= 5
