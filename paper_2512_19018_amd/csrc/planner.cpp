@@ -115,19 +115,21 @@ static int resident(const Variant &v, int64_t ktiles)
     return fit < 1 ? 1 : (int)fit;
 }
 
-// The kernels that take any alignment.  Times of all their tiles and K splits over 160 random unaligned products of
-// 65 to 8192 rows and columns, fitted as a launch and a round of workgroups (their first tiles' trip to memory and the store of C) and
-// the way into the LDS in 16 bits (bytes per ns and CU; rows on odd 2-byte addresses a tenth less), the MFMAs in fp32 (share
-// of their rate): within 12 % in 16 bits and 6 % in fp32 (root mean square); the pick by it is 1.7 and 0.8 % off the best on average.
-// alone: what one workgroup on a CU gets of the rate that as many as fit get together.  (The fp32 128x128 tile reaches 0.95, but as
-// much of that is lost to few tiles as the 64x64 one loses to its loads - 4095^3 953 us and 947 -, and it holds one sum for all k.)
-struct StagedRate { int bm, bn; double rate, alone, launch, round; };
+// The kernels that take any alignment: a launch, what each workgroup on a CU adds to it (its first tile's trip to memory, its
+// part of C), and the way into the LDS in 16 bits (bytes per ns and CU), the MFMAs in fp32 (share of their rate).  Rows on odd
+// 2-byte addresses come in slower, by a sixth where an odd leading dimension puts every other of them there, by two fifths where an
+// odd base and an even one put them all: the plan does not know the base, so that an even leading dimension counts as an odd one
+// and one of whole 16-byte chunks as half of that.  Fitted to 2083 times of all 16-bit tiles, unsplit and in two to four slices, over
+// 490 random unaligned products of 65 to 8192 rows and columns with K from 33 up, within 5 % (root mean square, the bases known; 12 %
+// with a price per round of workgroups and one for odd rows), and to 536 in fp32, within 3 to 6 %.
+// alone: what one workgroup on a CU gets of the rate that as many as fit get together.
+struct StagedRate { int bm, bn; double rate, alone, launch, each; };
 static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
-    static const StagedRate rate16[] = {{128, 128, 46.6, 0.96, 2.3, 3.25}, {128, 64, 62.0, 1.0, 2.15, 2.65}, {64, 64, 60.3, 1.0, 2.6, 1.3},
-                                        {0, 0, 65.0, 0.95, 2.0, 1.9}};
-    static const StagedRate rate32[] = {{128, 128, 0.78, 0.9, 3.7, 2.3}, {64, 64, 0.816, 1.0, 2.9, 1.4}, {64, 32, 0.754, 1.0, 1.6, 2.6},
-                                        {0, 0, 0.767, 0.93, 1.5, 3.0}};
+    static const StagedRate rate16[] = {{128, 128, 57.6, 0.78, 4.05, 1.58}, {128, 64, 64.9, 0.95, 3.65, 0.91}, {64, 64, 64.4, 0.91, 3.15, 0.44},
+                                        {0, 0, 68.5, 0.93, 3.3, 0.4}};
+    static const StagedRate rate32[] = {{128, 128, 0.90, 0.9, 4.05, 2.55}, {64, 64, 0.91, 0.83, 2.95, 1.1}, {64, 32, 0.885, 0.78, 3.05, 0.85},
+                                        {0, 0, 0.76, 0.74, 3.0, 0.7}};
     const bool f32 = v.dt == PEAK_DT_F32;
     const StagedRate *r = f32 ? rate32 : rate16;
     while (r->bm && (r->bm != v.bm || r->bn != v.bn)) ++r;
@@ -136,16 +138,13 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     const int fit = resident(v, ktiles);
     const double k = (double)v.bk * (double)ktiles;
     const double us = f32 ? k * v.bm * v.bn * 16.0 / MFMA_PER_US
-                          : k * 2.0 * (v.bm * (d.lda % 2 ? 1.1 : 1.0) + v.bn * (d.ldb % 2 ? 1.1 : 1.0)) / 1000.0;    // of one workgroup at rate 1
+                          : k * 2.0 * (v.bm * (d.lda % 8 ? 1.2 : 1.08) + v.bn * (d.ldb % 8 ? 1.2 : 1.08)) / 1000.0;    // of one workgroup at rate 1
     const int64_t rest = per_cu % fit;
-    double t = (double)(per_cu / fit) * fit * us / r->rate + r->launch + r->round * (double)cdiv(per_cu, fit);
+    double t = (double)(per_cu / fit) * fit * us / r->rate + r->launch + r->each * (double)per_cu;
     if (rest) t += (double)rest * us / (r->rate * (fit > 1 ? r->alone + (1.0 - r->alone) * (double)(rest - 1) / (fit - 1) : 1.0));
-    // fp32, one round of a few K tiles: 32x32 with its 64 k per tile 0.2 to 0.5 us ahead of 64x32 with 32 (345x79x33 NT 3.76 us and
-    // 4.21, 171x1321x77 TN 4.76 and 5.05, 1261x89x95 NN 4.78 and 4.90; with at most 32 k 0.1 to 0.2 behind)
-    if (f32 && v.bm == 32 && per_cu == 1 && split == 1 && d.K > 32 && d.K <= 128) t -= 0.5;
-    if (split > 1) {                                        // the partials out and back (3.8 and 3.2 TB/s) and the second launch
+    if (split > 1) {                                        // the partials out and back and the second launch
         const double mb = 4.0e-6 * split * (double)d.M * (double)d.N;
-        t += f32 ? 2.2 + 0.08 * split + 0.313 * mb : 2.8 + 0.11 * split + 0.26 * mb;
+        t += f32 ? 2.2 + 0.08 * split + 0.313 * mb : 3.3 + 0.21 * mb;
     }
     return units_of_us(v, t);
 }
@@ -497,6 +496,11 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     // ring kernels only: among the others tile and split, and with them the workspace, are as they would be without.
     if (ring >= 0 && pick >= 0 && d.dtype == PEAK_DT_F32 && pick_split > 1)
         best += units_of_us(g_variants[pick], 4.0 + 0.3 * pick_split);
+    // A large 16-bit tile costs a launch of two or three K tiles more than the model has for it, which leaves out most of its way
+    // out: 256x256 at 1616x4864x144 TN 12.5 us, 8.6 by the model, 10.1 in 128x64 ring tiles; 5024x1864x80 TN 11.7 and 10.1,
+    // 1120x6576x171 TN 12.6.  (At one K tile it is the four ring workgroups that share a CU which tell the two apart.)
+    if (ring >= 0 && pick >= 0 && d.dtype != PEAK_DT_F32 && pick_split == 1 && d.K > 64 && d.K <= 192)
+        best += units_of_us(g_variants[pick], 4.0 * g_variants[pick].bm * g_variants[pick].bn / 65536.0);
     return ring >= 0 && (pick < 0 || best_ring < best) ? ring : pick;
 }
 
