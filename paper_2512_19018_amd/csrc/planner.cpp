@@ -505,28 +505,23 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 }
 
 // Products whose rows do not suit the 16-byte copies of the other tiled kernels, by those on aligned copies of the operands
-// that the run writes first.  The copies cost a pass over the operands (about 4 TB/s with the write, 6 us at least with the
-// launch); what they save is that rows which start anywhere lie in a line more than they fill, so that small tiles reach
-// 48 to 60 bytes per ns and CU where aligned ones reach 72, and that the tiles may be large.
-// 16 bits: by the cost model from K = 512 on (bf16 6369x1352x5784 TN 126 us with copies, 197 without, 3195x1471x3771 NT 60 and
-// 90, 401x5608x759 NN 22 and 17; shorter, the store of C outweighs the loads: f16 3904x5358x192 39 and 27, bf16 4496x2239x448 31 and 25).
-// Products of 3.2e9 multiply-adds and more with a deep K and no narrow side take them also where the model is undecided (within an
-// eighth; two fifths from K = 3000 on, where the loose tiles fall behind their rates): 2239x1507x2255 NN 33 and 40, 3301x1557x3749 TT
-// 63.5 and 84, level at 2049x2047x1031 TT 32.6 and 30.2, f16 1353x747x3209 28.9 and 28.3, bf16 1023x2047x3001 NT 29.8 and 29.2; behind at
-// 1038x1136x3136, 35 %.  Over 142 random products the pick is 1.2 % off the better route on average.
-// fp32: the MFMAs bound both, the copies come on top (47 random products: never with them 0.5 % off the better route; 1203x1419x999
-// 48 and 38, 863x1795x2139 81 and 70, 2049x3001x2051 TN 258 and 257).  Kept for products wide on both sides, where the two differ
-// least, and for TN from half of that width on, whose loose tiles are a tenth slower than the other layouts'.
+// that the run writes first.  The copies cost a pass over the operands and a launch; what they save is that rows which start
+// anywhere lie in a line more than they fill, and that the tiles may be large.
+// 16 bits: by price, with a limit that K moves, since the price leaves out part of the way out of the large tiles and of what
+// rows at any address cost the caches.  Over 297 random products of 100 to 8192 rows and columns with K from 300 the pick is 1.2 %
+// off the better route with operands in the last-level cache and with B from HBM (all with copies 12.6 and 9.9 %, none 10.9 and
+// 14.5): 1647x8173x2121 NT 70 us with copies, 109 without; 316x1147x1735 TT 16 and 9; 1023x2047 NT level at
+// K = 2300 from HBM and 3000 in the cache.  Below K = 384 they won four of 50 products.
+// fp32: the MFMAs bound both and the copies come on top, 2 to 26 % behind in each of 86 products.  Kept for products wide on both
+// sides, where they are least behind (6539x2247x665 TN 174 us and 167, 2049x2047x1031 NT 94 and 81), and for TN from half of that
+// width on, by a price that is closest there.
 static bool pack_pays(const peak_gemm_desc_t &d, double direct, double staged)
 {
-    const double M = (double)d.M, N = (double)d.N, width = M * N / (M + N), work = M * N * (double)d.K;
-    if (d.K < 512) return false;
-    if (d.dtype == PEAK_DT_F32) return width >= 1000.0 || (width >= 480.0 && d.transA && !d.transB);
-    if (direct < 0.93 * staged) return true;
-    // (long and narrow: 15 products of 3600 to 5800 by 400 to 535 at most, 1.11 in the mean - f16 531x3745x3655 TN 41.3 us and 37.3,
-    // bf16 413x5725x2967 NN 46.4 and 35.8 -, none below 1.00; 26 squarer ones of that width 0.98)
-    const bool wide = width >= 480.0 || (width >= 360.0 && (d.M > d.N ? d.M : d.N) >= 3600);
-    return wide && work >= 3.2e9 && (d.K >= 1000 || work >= 8.0e9) && direct < (d.K >= 3000 ? 1.4 : 1.12) * staged;
+    if (d.dtype == PEAK_DT_F32) {
+        const double width = (double)d.M * (double)d.N / (double)(d.M + d.N);
+        return d.K >= 512 && (width >= 1000.0 || (width >= 480.0 && d.transA && !d.transB)) && direct < 1.22 * staged;
+    }
+    return d.K >= 384 && direct < 1.01 * pow((double)d.K / 1000.0, 0.09) * staged;
 }
 
 // Fills *g and returns true if copies pay against `staged` (the choice among the kernels that take any alignment).
@@ -554,7 +549,7 @@ static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int st
     if (v < 0 || !g_variants[v].direct || g_variants[v].kind != KIND_TILED) return false;
     const size_t bytes_a = (pack & 1) ? (size_t)((d.transA ? e.K : d.M) * e.lda * es) : 0;
     const size_t bytes_b = (pack & 2) ? (size_t)((d.transB ? d.N : e.K) * e.ldb * es) : 0;
-    const double copy_us = 6.0 + 2.0 * (double)(bytes_a + bytes_b) / 4.0e6;
+    const double copy_us = 6.0 + 0.3 * (double)(bytes_a + bytes_b) / 1.0e6;
     const double direct = tiled_cost(g_variants[v], e, choose_split(g_variants[v], e)) + units_of_us(g_variants[v], copy_us);
     if (!pack_pays(d, direct, tiled_cost(g_variants[staged], d, choose_split(g_variants[staged], d)))) return false;
     plan_geometry(g, e, v, 0, streamk);

@@ -191,3 +191,20 @@ def test_few_k_tiles_go_to_ring_tiles(dt, ta, tb, M, N, K):
     ("bf16", 1, 0, 1616, 4864, 144, "bf16_m128x64q3_tn"), ("f16", 1, 0, 1120, 6576, 176, "f16_m128x64q3_tn")])
 def test_tiles_of_a_short_k(dt, ta, tb, M, N, K, variant):
     assert plan(dt, ta, tb, M, N, K)[1] == variant
+
+
+def test_copies_by_price_without_steps_in_k():
+    """Blocks of 1023 x 2047: copies from one K on, wherever rows of the larger matrices end."""
+    packed = [plan("bf16", 0, 1, 1023, 2047, K, (6, 6, 6))[3] == 3 for K in range(515, 4100, 24)]
+    assert packed == sorted(packed) and not packed[0] and packed[-1]
+    for K in (999, 1001, 2999, 3001):
+        assert plan("bf16", 0, 1, 1023, 2047, K, (6, 6, 6))[3] == plan("bf16", 0, 1, 1023, 2047, K + 2, (6, 6, 6))[3]
+
+
+# us with copies and without: 28 and 32, 70 and 109; 37 and 30, 116 and 94, 114 and 102, 94 and 78, 72 and 59
+@pytest.mark.parametrize("dt,ta,tb,M,N,K,copies", [
+    ("bf16", 0, 1, 563, 5571, 1817, True), ("f16", 0, 1, 1647, 8173, 2121, True), ("f32", 1, 0, 797, 2311, 673, False),
+    ("f32", 1, 0, 685, 2997, 2121, False), ("f32", 1, 1, 1753, 3463, 907, False), ("f32", 1, 0, 629, 2419, 2833, False),
+    ("f32", 1, 0, 1547, 843, 2115, False)])
+def test_copies_where_they_pay(dt, ta, tb, M, N, K, copies):
+    assert (plan(dt, ta, tb, M, N, K)[3] != 0) == copies
