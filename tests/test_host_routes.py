@@ -208,3 +208,11 @@ def test_copies_by_price_without_steps_in_k():
     ("f32", 1, 0, 1547, 843, 2115, False)])
 def test_copies_where_they_pay(dt, ta, tb, M, N, K, copies):
     assert (plan(dt, ta, tb, M, N, K)[3] != 0) == copies
+
+
+# relative error of one sum for all k in ring tiles, then of these: 1.6e-6, 3.5e-7; 6.4e-7, 2.7e-7; 1.2e-6, 2.8e-7; 7.9e-7, 3.3e-7; 7.1e-7, 3.6e-7
+@pytest.mark.parametrize("ta,tb,M,N,K", [(0, 1, 192, 4304, 7576), (0, 1, 3336, 168, 4976), (1, 0, 4120, 192, 4464), (1, 1, 172, 3592, 7824),
+                                         (1, 1, 5912, 168, 6364)])
+def test_deep_fp32_products_in_tiles_of_several_sums(ta, tb, M, N, K):
+    _, name, split, _, _ = plan("f32", ta, tb, M, N, K)
+    assert name.startswith("f32_r64x") and split >= 3
