@@ -254,7 +254,7 @@ struct RingX {
     }
 };
 
-// Direct copies of operands of any (dword) alignment: whole K tiles only, so rows along K need no care.  KX: [k][x] rows.
+// Direct copies of operands of any (2-byte) alignment: whole K tiles only, so rows along K need no care.  KX: [k][x] rows.
 // A chunk that the matrix edge cuts is copied whole, what lies behind it in memory with it (it feeds columns of C that
 // are never stored), so the k-row after it must be the matrix's as well.  The descriptor moves along K with the tiles:
 // no limit on the operand's size, but one on its leading dimension.
@@ -267,7 +267,9 @@ struct RingLoose {
     int64_t step;
     int voff[PER_WAVE];
 
-    static PEAK_DEVM bool fits(int64_t ld) { return ld < ((int64_t)1 << 31) / ((KX ? C::BK : ROWS) * C::ESZ) - ROWB; }
+    static constexpr int64_t LD_LIMIT = ((int64_t)1 << 31) / ((KX ? C::BK : ROWS) * C::ESZ) - ROWB;
+    static_assert(((KX ? C::BK : ROWS) - 1) * (LD_LIMIT - 1) * C::ESZ + ROWB < 0x7FFFFFFF, "the last chunk of a tile within 32 bits and the descriptor");
+    static PEAK_DEVM bool fits(int64_t ld) { return ld < LD_LIMIT; }
     PEAK_DEVM void init(const void *src, int64_t ld, int64_t x0, int64_t nx, int64_t k0, int wave, int lane)
     {
         const uint64_t first = (uint64_t)((const char *)src + (KX ? k0 * ld + x0 : x0 * ld + k0) * C::ESZ);

@@ -64,10 +64,45 @@ def test_ring_of_loose_tiles(gu, oracle, dtype, transA, transB):
 
 
 @pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
-@pytest.mark.parametrize("transA,transB", [(0, 1), (1, 0)])
-def test_leading_dimension_beyond_32_bit_offsets(gu, oracle, dtype, transA, transB):
+@pytest.mark.parametrize("operand", ["A", "B"])
+@pytest.mark.parametrize("along_k", [True, False])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_leading_dimension_at_the_limit_of_the_copies(gu, oracle, dtype, operand, along_k, beyond):
+    """A 64x64 tile with a whole K tile and a tail; its last row (along K) or k-row ends just within 2^31 bytes of its first, by direct
+    copies, or beyond them, where 32-bit offsets would overflow, through registers."""
+    import torch
+    es = pi.DTYPE_SIZE[dtype]
+    bk = 128 // es
+    strides = 64 if along_k else bk                           # rows of the tile that lie one leading dimension apart
+    ld = (2 ** 31 + 2 ** 23) // ((strides - 1) * es) | 1 if beyond else 2 ** 31 // (strides * es) - 129 - 128 * (not along_k)
+    assert ((strides - 1) * ld * es > 2 ** 31) == beyond
+    M, N, K = 64 + 5, 64 + 7, bk + 3
+    transA, transB = (int(not along_k), 1) if operand == "A" else (0, int(along_k))
     vid = next(i for i, n in gu.variants_for(dtype, transA, transB) if "_r64x64" in n)
-    ld = 17_000_001                                           # 64 rows of it are over 2^31 bytes in 16 bits, 32 in fp32
+    la, lb = (pi.logical_matrix(61, i, *s, "uniform", 1.0, dtype) for i, s in enumerate(((M, K), (K, N))))
+    A, B = pi.store(la, bool(transA)), pi.store(lb, bool(transB))
+    far = A if operand == "A" else B
+    rows, cols = far.shape
+    buf = torch.full((1 + (rows - 1) * ld + cols,), float("nan"), dtype=torch.float32 if es == 4 else torch.bfloat16, device="cuda")
+    torch.as_strided(buf, (rows, cols), (ld, 1), 1).copy_(gu.to_dev(far).view(buf.dtype))
+    dA, dB = (buf if m is far else gu.to_dev(m) for m in (A, B))
+    dC = gu.to_dev(gu.nan_fill(M, N, dtype))
+    lda, ldb = (ld if m is far else m.shape[1] for m in (A, B))
+    off = [es if m is far else 0 for m in (A, B)]
+    print(operand, along_k, M, N, K, lda, ldb, flush=True)
+    with gu.pg.Plan(M, N, K, dtype, transA, transB, lda, ldb, N, gu.pg.force_flags(vid, 1)) as plan:
+        plan.run(1.0, dA.data_ptr() + off[0], dB.data_ptr() + off[1], 0.0, dC.data_ptr(), 0, 0, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    got = pi.to_f64(np.ascontiguousarray(gu.from_dev(dC, dtype)), dtype)
+    gu.check_against_oracle(oracle, got, dtype, transA, transB, M, N, K, 1.0, A, B, 0.0, None, what=(operand, along_k, ld))
+
+
+@pytest.mark.parametrize("dtype", [pi.F32, pi.BF16])
+@pytest.mark.parametrize("transA,transB", [(0, 1), (1, 0)])
+def test_few_rows_far_apart(gu, oracle, dtype, transA, transB):
+    """Three rows of A, or three k, a leading dimension apart that is too large for 64 of them."""
+    vid = next(i for i, n in gu.variants_for(dtype, transA, transB) if "_r64x64" in n)
+    ld = 17_000_001
     M, N, K = (3, 70, 66) if not transA else (70, 70, 3)
     _run(gu, oracle, dtype, transA, transB, M, N, K, vid, None, (ld - (M if transA else K), 1), (1, 1), "far rows")
 
