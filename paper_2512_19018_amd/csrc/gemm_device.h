@@ -1714,7 +1714,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs p)
     float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     const float *w = p.ws + m * p.N + n;
     const int64_t plane = p.M * p.N;
-    if (nvalid == 4 || p.N >= 4) {
+    if (p.N >= 4) {
         // A group that N cuts adds up the row's last four columns and keeps those that are its own (added element by element,
         // every load waited for, it held up all others: fp32 149x135x3595 TN in ten slices 8.8 us against 4.0)
         const int back = 4 - nvalid;

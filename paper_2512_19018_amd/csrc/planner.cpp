@@ -292,6 +292,31 @@ static bool streamk_pays(const Variant &v, const peak_gemm_desc_t &d, int S, int
     return cut < 0.9 * (tile + fixed);
 }
 
+// K slices with which a streaming kernel's workgroups fill the chip once, rounded up from four fifths, at least 4 stages
+// each: what the choice between streaming and ring kernels goes by (its limits were measured with it).
+static int skinny_split(int64_t N, int64_t K, int bn, int kstep)
+{
+    const int64_t tiles_n = (N + bn - 1) / bn;
+    const int64_t ktiles = (K + kstep - 1) / kstep;
+    int64_t s = (num_cu() + tiles_n / 4) / tiles_n;
+    if (s > ktiles / 4) s = ktiles / 4;
+    if (s < 1) s = 1;
+    if (s > 64) s = 64;
+    return (int)s;
+}
+
+// K slices for the register-streaming kernel: aim at >= 8 waves per CU
+static int skinny_reg_split(int64_t N, int64_t K)
+{
+    const int64_t groups = (N + 15) / 16;
+    const int64_t iters = K / 64;
+    int64_t s = (8 * (int64_t)num_cu() + groups - 1) / groups;
+    if (s > iters / 16) s = iters / 16;
+    if (s < 1) s = 1;
+    if (s > 64) s = 64;
+    return (int)s;
+}
+
 // The streaming kernels, in microseconds: the operand's bytes at the chip's rate and the busiest CU's share of them (with the rows
 // of the M x K operand its workgroups read again) at one CU's rate - in fp32 with M > 16 its MFMAs' -, as a root of squares
 // since neither overlaps the other fully; rounds of workgroups; slices out, back and a launch.  Fitted over 77 random decode
@@ -315,8 +340,9 @@ static double stream_cost(const Variant &v, const peak_gemm_desc_t &d, int split
 // ... and the K split by it, where it sees 7 % over as many slices as fill the chip once, rounded up (skinny_split): slices that
 // spill into a second, nearly empty round cost most (f16 16x8960x7680 NT, 140 tiles, 38.9 us in two slices, 33.1 in three; fp32
 // 37x6592x16128 TN 238 in five, 147 in nine; 35x11840x2560 NN 70 in three, 50 in five; bf16 30x23296x9344 NN 107 in three, 81 in two).
-// Of 73 shapes 1.1 % off the best split on average, 7 % without, none behind.  At least four stages per slice; partials within
-// the array of peak_gemm_run_static.
+// Of 73 shapes 1.1 % off the best split on average, 7 % without, none behind.  At least four stages per slice.  No
+// other number of slices than those asks for more than the array of peak_gemm_run_static, the copy of A included; those may, with a
+// K beyond 100000 (fp32 64x2048x131072 TN 40 MB).
 static int stream_split(const Variant &v, const peak_gemm_desc_t &d)
 {
     const size_t copy = stages_a(v, d.transA) ? (size_t)d.M * (size_t)d.K * esize_of(d.dtype) + 512 : 0;

@@ -72,31 +72,6 @@ static inline bool stages_a(const Variant &v, int transA) { return v.kind == KIN
 // workgroups of the GEMM launch
 int64_t grid_blocks(const Geometry &g);
 
-// K slices with which a streaming kernel's workgroups fill the chip once, rounded up from four fifths, at least 4 stages
-// each: what the choice between streaming and ring kernels goes by (its limits were measured with it).
-static inline int skinny_split(int64_t N, int64_t K, int bn, int kstep)
-{
-    const int64_t tiles_n = (N + bn - 1) / bn;
-    const int64_t ktiles = (K + kstep - 1) / kstep;
-    int64_t s = (256 + tiles_n / 4) / tiles_n;
-    if (s > ktiles / 4) s = ktiles / 4;
-    if (s < 1) s = 1;
-    if (s > 64) s = 64;
-    return (int)s;
-}
-
-// K slices for the register-streaming kernel: aim at >= 8 waves per CU
-static inline int skinny_reg_split(int64_t N, int64_t K)
-{
-    const int64_t groups = (N + 15) / 16;
-    const int64_t iters = K / 64;
-    int64_t s = (2048 + groups - 1) / groups;
-    if (s > iters / 16) s = iters / 16;
-    if (s < 1) s = 1;
-    if (s > 64) s = 64;
-    return (int)s;
-}
-
 }  // namespace peak
 
 struct peak_gemm_plan {

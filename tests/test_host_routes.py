@@ -1,6 +1,8 @@
 """Which route a plan takes: aligned copies, any-alignment kernels, ring kernels (no GPU needed)."""
 import itertools
 import os
+import subprocess
+import sys
 
 import pytest
 
@@ -139,10 +141,29 @@ def test_streaming_slices_do_not_spill_into_a_thin_round(dt, ta, tb, M, N, K, sp
 
 @pytest.mark.parametrize("dt,ta,tb", list(itertools.product(DTYPES, (0, 1), (0, 1))))
 def test_streaming_slices_and_copy_fit_the_fixed_array(dt, ta, tb):
-    for M, N, K in itertools.product((1, 16, 17, 32, 33, 48, 64), (2048, 8960, 13312, 28672, 40960), (2048, 7680, 16384, 28672)):
+    """... unless already the slices that fill the chip once ask for more, which only a K beyond 100000 does."""
+    streaming = beyond = 0
+    for M, N, K in itertools.product((1, 16, 17, 32, 33, 48, 64), (2048, 8960, 13312, 28672, 40960), (2048, 7680, 16384, 28672, 131072)):
         p, name, split, _, _ = plan(dt, ta, tb, M, N, K)
-        if "skinny" in name:
-            assert p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, (M, N, K, split)
+        if "skinny" not in name:
+            continue
+        streaming += 1
+        if p.workspace_bytes > pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES:
+            columns = int(p.info().split("tile=")[1].split()[0].split("x")[1])
+            tiles = -(-N // columns)
+            assert K == 131072 and split == max(1, (256 + tiles // 4) // tiles), (M, N, K, split)
+            beyond += 1
+    assert streaming > 100 and beyond < 20
+
+
+def test_streaming_slices_fill_the_compute_units_there_are():
+    code = ("import paper_2512_19018_amd as pg\n"
+            "for N in (2048, 4096, 8192):\n"
+            "    print(pg.Plan(16, N, 16384, pg.PEAK_DT_BF16, 0, 1).info().split('grid=')[1].split()[0])")
+    for cu in (64, 128, 256):
+        env = dict(os.environ, PEAK_GEMM_NUM_CU=str(cu), PYTHONPATH=os.path.dirname(os.path.dirname(pg.__file__)))
+        out = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, check=True).stdout.split()
+        assert all(cu * 3 // 4 <= int(g) <= cu * 5 // 4 for g in out), (cu, out)
 
 
 @pytest.mark.parametrize("dt", ("f16", "bf16"))
