@@ -198,6 +198,9 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
         if (p->alt.variant < 0) return PEAK_ERR_UNSUPPORTED;
         g = &p->alt;
     }
+    // copies that pay only against rows on odd 2-byte addresses, and none there
+    auto odd_rows = [](const void *base, int64_t ld) { return ld % 2 == 0 && (uintptr_t)base % 4 != 0; };
+    if (g->pack_odd && !((g->pack & 1) && odd_rows(A, d.lda)) && !((g->pack & 2) && odd_rows(B, d.ldb))) g = &p->alt;
     // (a workspace that does not suit aligned copies, such as the fixed array of peak_gemm_run_static, does for the stand-in)
     if (g->pack && (!workspace || workspace_bytes < g->ws_bytes || (uintptr_t)workspace % 256)) g = &p->alt;
     const Variant &v = g_variants[g->variant];

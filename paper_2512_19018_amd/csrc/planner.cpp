@@ -117,14 +117,13 @@ static int resident(const Variant &v, int64_t ktiles)
 
 // The kernels that take any alignment: a launch, what each workgroup on a CU adds to it (its first tile's trip to memory, its
 // part of C), and the way into the LDS in 16 bits (bytes per ns and CU), the MFMAs in fp32 (share of their rate).  Rows on odd
-// 2-byte addresses come in slower, by a sixth where an odd leading dimension puts every other of them there, by two fifths where an
-// odd base and an even one put them all: the plan does not know the base, so that an even leading dimension counts as an odd one
-// and one of whole 16-byte chunks as half of that.  Fitted to 2083 times of all 16-bit tiles, unsplit and in two to four slices, over
+// 2-byte addresses come in slower: by a sixth where an odd leading dimension puts every other of them there, by two fifths where an
+// odd base and an even one put them all (even_a, even_b: 1.67 for that, which the plan does not know).  Fitted to 2083 times of all 16-bit tiles, unsplit and in two to four slices, over
 // 490 random unaligned products of 65 to 8192 rows and columns with K from 33 up, within 5 % (root mean square, the bases known; 12 %
 // with a price per round of workgroups and one for odd rows), and to 536 in fp32, within 3 to 6 %.
 // alone: what one workgroup on a CU gets of the rate that as many as fit get together.
 struct StagedRate { int bm, bn; double rate, alone, launch, each; };
-static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
+static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split, double even_a = 1.0, double even_b = 1.0)
 {
     static const StagedRate rate16[] = {{128, 128, 57.6, 0.78, 4.05, 1.58}, {128, 64, 64.9, 0.95, 3.65, 0.91}, {64, 64, 64.4, 0.91, 3.15, 0.44},
                                         {0, 0, 68.5, 0.93, 3.3, 0.4}};
@@ -138,7 +137,7 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
     const int fit = resident(v, ktiles);
     const double k = (double)v.bk * (double)ktiles;
     const double us = f32 ? k * v.bm * v.bn * 16.0 / MFMA_PER_US
-                          : k * 2.0 * (v.bm * (d.lda % 8 ? 1.2 : 1.08) + v.bn * (d.ldb % 8 ? 1.2 : 1.08)) / 1000.0;    // of one workgroup at rate 1
+                          : k * 2.0 * (v.bm * (d.lda % 2 ? 1.2 : even_a) + v.bn * (d.ldb % 2 ? 1.2 : even_b)) / 1000.0;    // of one workgroup at rate 1
     const int64_t rest = per_cu % fit;
     double t = (double)(per_cu / fit) * fit * us / r->rate + r->launch + r->each * (double)per_cu;
     if (rest) t += (double)rest * us / (r->rate * (fit > 1 ? r->alone + (1.0 - r->alone) * (double)(rest - 1) / (fit - 1) : 1.0));
@@ -363,7 +362,7 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     const Variant &v = g_variants[variant];
     p->variant = variant;
     p->sk_tiles = 0;
-    p->pack = 0;
+    p->pack = p->pack_odd = 0;
     p->tiles_m = (int)cdiv(d.M, v.bm);
     p->tiles_n = (int)cdiv(d.N, v.bn);
     p->ktiles_total = (int)cdiv(d.K, v.bk);
@@ -538,21 +537,22 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 // Products whose rows do not suit the 16-byte copies of the other tiled kernels, by those on aligned copies of the operands
 // that the run writes first.  The copies cost a pass over the operands and a launch; what they save is that rows which start
 // anywhere lie in a line more than they fill, and that the tiles may be large.
-// 16 bits: by price, with a limit that K moves, since the price leaves out part of the way out of the large tiles and of what
-// rows at any address cost the caches.  Over 297 random products of 100 to 8192 rows and columns with K from 300 the pick is 1.2 %
-// off the better route with operands in the last-level cache and with B from HBM (all with copies 12.6 and 9.9 %, none 10.9 and
-// 14.5): 1647x8173x2121 NT 70 us with copies, 109 without; 316x1147x1735 TT 16 and 9; 1023x2047 NT level at
-// K = 2300 from HBM and 3000 in the cache.  Below K = 384 they won four of 50 products.
+// 16 bits: by price, with a limit that rises with K and the work, since the price leaves out part of the way out of the large tiles
+// and of what rows at any address cost the caches.  Over 697 random products of 65 to 8192 rows and columns with K from 300, blocks
+// of larger matrices among them, the pick is 0.9 % off the better route with operands in the last-level cache and with B from HBM
+// (none with copies 7.8 and 9.8 %): 1647x8173x2121 NT 70 us with copies, 109 without; 316x1147x1735 TT 16 and 9; 1023x2047 NT level
+// at K = 2300 from HBM and 3000 in the cache.  Below K = 384 they won four of 50 products.
 // fp32: the MFMAs bound both and the copies come on top, 2 to 26 % behind in each of 86 products.  Kept for products wide on both
 // sides, where they are least behind (6539x2247x665 TN 174 us and 167, 2049x2047x1031 NT 94 and 81), and for TN from half of that
 // width on, by a price that is closest there.
 static bool pack_pays(const peak_gemm_desc_t &d, double direct, double staged)
 {
+    const double M = (double)d.M, N = (double)d.N, K = (double)d.K;
     if (d.dtype == PEAK_DT_F32) {
-        const double width = (double)d.M * (double)d.N / (double)(d.M + d.N);
+        const double width = M * N / (M + N);
         return d.K >= 512 && (width >= 1000.0 || (width >= 480.0 && d.transA && !d.transB)) && direct < 1.22 * staged;
     }
-    return d.K >= 384 && direct < 1.01 * pow((double)d.K / 1000.0, 0.09) * staged;
+    return d.K >= 384 && direct < 0.995 * pow(K / 1000.0, 0.09) * pow(M * N * K / 4.0e9, 0.05) * staged;
 }
 
 // Fills *g and returns true if copies pay against `staged` (the choice among the kernels that take any alignment).
@@ -582,9 +582,14 @@ static bool pack_plan(const peak_gemm_desc_t &d, int staged, Geometry *g, int st
     const size_t bytes_b = (pack & 2) ? (size_t)((d.transB ? d.N : e.K) * e.ldb * es) : 0;
     const double copy_us = 6.0 + 0.3 * (double)(bytes_a + bytes_b) / 1.0e6;
     const double direct = tiled_cost(g_variants[v], e, choose_split(g_variants[v], e)) + units_of_us(g_variants[v], copy_us);
-    if (!pack_pays(d, direct, tiled_cost(g_variants[staged], d, choose_split(g_variants[staged], d)))) return false;
+    const Variant &sv = g_variants[staged];
+    const int ss = choose_split(sv, d);
+    const bool pays = pack_pays(d, direct, staged_cost(sv, d, ss));
+    // in 16 bits also where they pay only against rows that all lie on odd addresses: whether they do is known to the run
+    if (!pays && (d.dtype == PEAK_DT_F32 || !pack_pays(d, direct, staged_cost(sv, d, ss, pack & 1 ? 1.67 : 1.0, pack & 2 ? 1.67 : 1.0)))) return false;
     plan_geometry(g, e, v, 0, streamk);
     g->pack = pack;
+    g->pack_odd = !pays;
     g->pack_k = e.K; g->pack_m = e.M; g->pack_n = e.N;
     g->pack_ld[0] = e.lda; g->pack_ld[1] = e.ldb;
     g->pack_off[0] = (g->ws_bytes + 255) & ~(size_t)255;    // behind the partials, on 256-byte boundaries
@@ -827,10 +832,10 @@ int peak_gemm_plan_info(const peak_gemm_plan_t *p, char *buf, size_t n)
     const Variant &v = g_variants[g.variant];
     return snprintf(buf, n,
                     "variant=%d:%s tile=%dx%dx%d threads=%d stages=%d lds=%d split=%d ktiles/slice=%d "
-                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s streamk=%d rot=%d,%d pack=%d acopy=%d",
+                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s streamk=%d rot=%d,%d pack=%d oddbase=%d acopy=%d",
                     g.variant, v.name, v.bm, v.bn, v.bk, v.nt, v.ns, v.lds, g.split, g.ktiles_per_slice,
                     (long long)grid_blocks(g), g.tiles_m, g.tiles_n, g.group_m, p->ws_bytes,
-                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same", g.sk_tiles, g.rot_m, g.rot_n, g.pack, g.a_copy);
+                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same", g.sk_tiles, g.rot_m, g.rot_n, g.pack, g.pack_odd, g.a_copy);
 }
 
 peak_status_t peak_gemm_destroy(peak_gemm_plan_t *plan)

@@ -60,6 +60,7 @@ struct Geometry {
     // the product's sizes over the copies: K and the columns of an operand stored K x M or K x N rounded up to whole
     // 16-byte chunks, zeros beyond the matrix; leading dimensions of the copies a multiple of 128 bytes.
     int pack;
+    int pack_odd;         // 1: the copies pay only against rows on odd 2-byte addresses (a base there, an even leading dimension)
     size_t pack_off[2];
     int64_t pack_k, pack_m, pack_n, pack_ld[2];
     size_t ws_bytes;

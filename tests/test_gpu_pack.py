@@ -121,6 +121,26 @@ def test_copies_larger_than_the_fixed_array_take_the_stand_in(gu, oracle, dtype,
         _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, plan.info())
 
 
+@pytest.mark.parametrize("dtype", [pi.F16, pi.BF16])
+@pytest.mark.parametrize("transA,transB", list(itertools.product([0, 1], [0, 1])))
+@pytest.mark.parametrize("rem", [2, 4, 6])
+def test_copies_only_against_rows_on_odd_addresses(gu, oracle, dtype, transA, transB, rem):
+    """Even leading dimensions: copies where a base puts every row on odd 2-byte addresses, none where both are even."""
+    import torch
+    M, N, K = 2048 + rem, 2040 + rem, 1024 + rem
+    A, B = (pi.store(pi.logical_matrix(44, i, *s, "uniform", 1.0, dtype), bool(t)) for i, (s, t) in enumerate((((M, K), transA), ((K, N), transB))))
+    stream = torch.cuda.current_stream().cuda_stream
+    with gu.pg.Plan(M, N, K, dtype, transA, transB) as plan:
+        assert "pack=3" in plan.info() and "oddbase=1" in plan.info(), plan.info()
+        for offs in ((0, 0), (1, 0), (0, 1), (1, 1), (2, 2)):
+            dA, dB = (gu.to_dev(_block(gu, x, 0, o, dtype)[0]) for x, o in zip((A, B), offs))
+            dC = gu.to_dev(gu.nan_fill(M, N, dtype))
+            ws = torch.full((plan.workspace_bytes,), 0xA5, dtype=torch.uint8, device="cuda")
+            plan.run(1.0, dA.data_ptr() + 2 * offs[0], dB.data_ptr() + 2 * offs[1], 0.0, dC.data_ptr(), ws.data_ptr(), ws.numel(), stream)
+            _check(gu, oracle, dC, dtype, transA, transB, M, N, K, A, B, (plan.info(), offs))
+            assert bool((ws == 0xA5).all()) == (offs[0] % 2 == 0 and offs[1] % 2 == 0), offs
+
+
 @pytest.mark.parametrize("static", [0, 1])
 def test_aligned_copies_under_capture(gu, static):
     """Replays copy what the operands hold then, not what they held at capture."""

@@ -222,6 +222,14 @@ def test_copies_by_price_without_steps_in_k():
         assert plan("bf16", 0, 1, 1023, 2047, K, (6, 6, 6))[3] == plan("bf16", 0, 1, 1023, 2047, K + 2, (6, 6, 6))[3]
 
 
+def test_copies_of_even_leading_dimensions_wait_for_the_base():
+    """16 bits: 2050x2042x1026 takes 24 us without copies where both bases are even, 37 where they are odd, and 29 with copies."""
+    for dt, M, N, K, pad, odd in (("bf16", 2050, 2042, 1026, 0, 1), ("f16", 2049, 2047, 1031, 1, 1), ("bf16", 2049, 2047, 1031, 0, 0),
+                                  ("bf16", 4096, 4096, 4095, 1, 0)):
+        p = plan(dt, 0, 1, M, N, K, (pad, pad, 0))[0]
+        assert "pack=3 oddbase=%d " % odd in p.info(), p.info()
+
+
 # us with copies and without: 28 and 32, 70 and 109; 37 and 30, 116 and 94, 114 and 102, 94 and 78, 72 and 59
 @pytest.mark.parametrize("dt,ta,tb,M,N,K,copies", [
     ("bf16", 0, 1, 563, 5571, 1817, True), ("f16", 0, 1, 1647, 8173, 2121, True), ("f32", 1, 0, 797, 2311, 673, False),
