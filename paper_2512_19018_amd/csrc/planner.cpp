@@ -526,7 +526,12 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     // 1120x6576x171 TN 12.6.  (At one K tile it is the four ring workgroups that share a CU which tell the two apart.)
     if (ring >= 0 && pick >= 0 && d.dtype != PEAK_DT_F32 && pick_split == 1 && d.K > 64 && d.K <= 192)
         best += units_of_us(g_variants[pick], 4.0 * g_variants[pick].bm * g_variants[pick].bn / 65536.0);
-    if (ring < 0 || (pick >= 0 && best <= best_ring)) return pick;
+    if (ring < 0 || (pick >= 0 && best <= best_ring)) {
+        // (... and against a large tile whose partials are beyond the array of peak_gemm_run_static: 192x5908x7808 NT, 43 MB in ten
+        // slices, by the same margin)
+        const bool beyond = pick >= 0 && 4.0 * pick_split * (double)d.M * (double)d.N > (double)PEAK_GEMM_STATIC_WORKSPACE_BYTES;
+        return d.dtype == PEAK_DT_F32 && any >= 0 && beyond && pick_split > 1 && best_any < 0.85 * best ? any : pick;
+    }
     // In fp32 the kernels for any alignment stand against the ring kernels as well, 15 % ahead by price: theirs knows what several
     // workgroups on a CU gain, that of the ring kernels does not.  60 aligned products that this decides: 0.92 of the ring kernels'
     // time in the mean, 1.02 at most (192x4304x7576 NT 109 us in five slices of 64x64, 134 unsplit; 3336x168x4976 NT 59 and 67), and

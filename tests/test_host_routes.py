@@ -239,6 +239,12 @@ def test_copies_where_they_pay(dt, ta, tb, M, N, K, copies):
     assert (plan(dt, ta, tb, M, N, K)[3] != 0) == copies
 
 
+def test_partials_beyond_the_fixed_array_stand_against_the_kernels_for_any_alignment():
+    """fp32: ten slices of 256x256 tiles ask for 43 MB, the kernels for any alignment are 20 % ahead by price and within the array."""
+    p, name, _, _, _ = plan("f32", 0, 1, 192, 5908, 7808, (0, 8, 0))
+    assert name.startswith("f32_r") and p.workspace_bytes <= pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES
+
+
 # relative error of one sum for all k in ring tiles, then of these: 1.6e-6, 3.5e-7; 6.4e-7, 2.7e-7; 1.2e-6, 2.8e-7; 7.9e-7, 3.3e-7; 7.1e-7, 3.6e-7
 @pytest.mark.parametrize("ta,tb,M,N,K", [(0, 1, 192, 4304, 7576), (0, 1, 3336, 168, 4976), (1, 0, 4120, 192, 4464), (1, 1, 172, 3592, 7824),
                                          (1, 1, 5912, 168, 6364)])
