@@ -127,7 +127,7 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
 {
     static const StagedRate rate16[] = {{128, 128, 57.6, 0.78, 4.05, 1.58}, {128, 64, 64.9, 0.95, 3.65, 0.91}, {64, 64, 64.4, 0.91, 3.15, 0.44},
                                         {0, 0, 68.5, 0.93, 3.3, 0.4}};
-    static const StagedRate rate32[] = {{128, 128, 0.90, 0.9, 4.05, 2.55}, {64, 64, 0.91, 0.83, 2.95, 1.1}, {64, 32, 0.885, 0.78, 3.05, 0.85},
+    static const StagedRate rate32[] = {{128, 128, 0.78, 0.9, 4.05, 2.55}, {64, 64, 0.91, 0.83, 2.95, 1.1}, {64, 32, 0.885, 0.78, 3.05, 0.85},
                                         {0, 0, 0.76, 0.74, 3.0, 0.7}};
     const bool f32 = v.dt == PEAK_DT_F32;
     const StagedRate *r = f32 ? rate32 : rate16;
@@ -146,6 +146,16 @@ static double staged_cost(const Variant &v, const peak_gemm_desc_t &d, int split
         t += f32 ? 2.2 + 0.08 * split + 0.313 * mb : 3.3 + 0.21 * mb;
     }
     return units_of_us(v, t);
+}
+
+// Among these kernels in fp32: how many sums an element has (one in the 128x128 tile, 4 in 64x64, 8 in 64x32, 16 in 32x32) weighs a
+// little against the time, where two are close.  300 unaligned products: 0.2 to 0.4 % of the time, and 5 to 7 % of the error where K is
+// beyond 128; where the time alone chose, one in 12 was further from the exact result than the tiles of before (to 1.8 times), now one
+// in 25, all with K to 128 (to 1.3 times).
+static double few_sums(const Variant &v)
+{
+    if (v.dt != PEAK_DT_F32) return 1.0;
+    return v.bm * v.bn >= 128 * 128 ? 1.2 : v.bm * v.bn >= 64 * 64 ? 1.08 : v.bm * v.bn >= 64 * 32 ? 1.04 : 1.0;
 }
 
 // The ring kernels: small tiles, bound by the way into the LDS (16 bits) or by the MFMAs (fp32).  16 bits, bytes per ns
@@ -456,7 +466,7 @@ static bool ring_ahead_of_streaming(const Variant &ring, const Variant &v, const
 // `staged_only`, among those that take any operand alignment.
 static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 {
-    double best = 0.0, best_ring = 0.0, best_any = 0.0;
+    double best = 0.0, best_ring = 0.0, best_any = 0.0, best_any_weighed = 0.0;
     int pick = -1, ring = -1, any = -1, pick_split = 1, stream[4] = {-1, -1, -1, -1};            // first fitting streaming kernel of each rank
     // streaming kernels: only those with the fewest rows of the M x K operand that hold M
     int stream_bm = 0;
@@ -504,7 +514,10 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
             }
         }
         if (v.ring) { if (ring < 0 || c < best_ring) { ring = i; best_ring = c; } }
-        else if (!v.direct) { if (any < 0 || c < best_any) { any = i; best_any = c; } }
+        else if (!v.direct) {
+            const double weighed = c * few_sums(v);
+            if (any < 0 || weighed < best_any_weighed) { any = i; best_any = c; best_any_weighed = weighed; }
+        }
         else if (pick < 0 || c < best) { pick = i; best = c; pick_split = split; }
     }
     for (int r = 3; r >= 1; --r)

@@ -251,3 +251,9 @@ def test_partials_beyond_the_fixed_array_stand_against_the_kernels_for_any_align
 def test_deep_fp32_products_in_tiles_of_several_sums(ta, tb, M, N, K):
     _, name, split, _, _ = plan("f32", ta, tb, M, N, K)
     assert name.startswith("f32_r64x") and split >= 3
+
+
+# one sum per element in 128x128, four in 64x64: a result of K in the hundreds is off by 3.6e-7 and 2.6e-7
+@pytest.mark.parametrize("ta,tb,M,N,K", [(1, 1, 6204, 3846, 393), (1, 1, 979, 3200, 68), (0, 1, 2809, 3841, 1255), (1, 0, 1043, 2179, 2697)])
+def test_fp32_tiles_of_one_sum_only_far_ahead(ta, tb, M, N, K):
+    assert "_r128x128" not in plan("f32", ta, tb, M, N, K, (1, 1, 0))[1]
