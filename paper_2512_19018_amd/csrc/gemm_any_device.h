@@ -53,6 +53,10 @@ struct CfgAny {
     // and 11.4, 40 aligned products with K to 128 0.875 of the time)
     static constexpr int LDS_LEAST = OUT_BYTES > RED_BYTES ? OUT_BYTES : RED_BYTES;
     static constexpr int LDS_BYTES = RING_ * STAGE > LDS_LEAST ? RING_ * STAGE : LDS_LEAST;
+    // Aligned 16-bit tiles below 128x64 keep the whole ring whatever K, as an array of their own: two or three workgroups of them share
+    // a CU anyway, and sized by the launch they were 1 % slower (100x4096x4096 11.36 us and 11.25; 60 products of 64x64 tiles 1.3 %).
+    static constexpr bool OWN_LDS = !LOOSE_ && DT_ != DT_F32 && BM_ < 128;
+    static constexpr int LDS_SHORTEST = OWN_LDS ? 0 : LDS_LEAST;    // 0: the whole ring whatever K
     static int lds_of(int ktiles) { return ktiles >= RING_ ? LDS_BYTES : ktiles * STAGE > LDS_LEAST ? ktiles * STAGE : LDS_LEAST; }
     static_assert(RB_ == 128 || RB_ == 256, "swizzles below");
     static_assert(ROUNDS * WK_ * KROUND == BK && ROUNDS >= 1, "whole rounds per wave");
@@ -305,7 +309,12 @@ template <class C>
 __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the kernel's symbol
-    extern __shared__ __attribute__((aligned(1024))) char lds[];            // C::lds_of(K tiles of a slice) bytes
+    // The launch's C::lds_of(K tiles of a slice) bytes, from address 0 on: the kernel has no other LDS, and in that address space 0 is
+    // an address like any other, a null pointer is -1 (hence the bit cast: a cast of the constant 0 would be one).  An extern
+    // array's address is known to the assembler only: extra additions, another order of loads and MFMAs, and fp32 64x64 tiles
+    // with K of 150 and more 2 % slower.
+    __shared__ __attribute__((aligned(1024))) char own[C::OWN_LDS ? C::LDS_BYTES : 1];
+    char *const lds = C::OWN_LDS ? own : (char *)__builtin_bit_cast(__attribute__((address_space(3))) char *, 0u);
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave_all % C::PLACES, kpar = wave_all / C::PLACES;
