@@ -187,6 +187,9 @@ static double ring_cost(const Variant &v, const peak_gemm_desc_t &d, int split)
         const int64_t most = per_cu == 1 && 8 * groups > 5 * num_cu() ? 20 : 28;
         if ((v.ns < 5) != (cdiv(cdiv(d.K, v.bk), split) <= most)) us *= 1.05;
     }
+    // fp32, a third workgroup of 64x32 on a CU where two of 64x64 do: with one or two K tiles its launch and way out cost more than its
+    // MFMAs save (110 products of 261 to 1045 tiles of 64x64: with K to 32 0.93 of the speed, to 64 0.97, to 96 1.01, to 128 1.05)
+    if (v.dt == PEAK_DT_F32 && v.bm * v.bn == 64 * 32 && per_cu > 2 && cdiv(cdiv(d.K, v.bk), split) <= 2) us += 0.32;
     return units_of_us(v, us + 2.5 * (double)cdiv(per_cu, resident(v, cdiv(cdiv(d.K, v.bk), split))) + split_us(d, split));
 }
 

@@ -257,3 +257,9 @@ def test_deep_fp32_products_in_tiles_of_several_sums(ta, tb, M, N, K):
 @pytest.mark.parametrize("ta,tb,M,N,K", [(1, 1, 6204, 3846, 393), (1, 1, 979, 3200, 68), (0, 1, 2809, 3841, 1255), (1, 0, 1043, 2179, 2697)])
 def test_fp32_tiles_of_one_sum_only_far_ahead(ta, tb, M, N, K):
     assert "_r128x128" not in plan("f32", ta, tb, M, N, K, (1, 1, 0))[1]
+
+
+# 64x32 tiles in place of 64x64 with one or two K tiles: a third workgroup per CU to start (748x1752x32 NN 5.11 us and 4.76)
+@pytest.mark.parametrize("ta,tb,M,N,K", [(0, 0, 748, 1752, 32), (1, 0, 2348, 492, 12), (0, 1, 240, 4740, 16), (0, 1, 968, 1268, 64)])
+def test_fp32_64x64_rings_at_short_k(ta, tb, M, N, K):
+    assert "_m64x64q3" in plan("f32", ta, tb, M, N, K)[1]
