@@ -131,7 +131,9 @@ size_t peak_gemm_workspace_bytes(const peak_gemm_plan_t *plan);
  *                suit them ("pack=" in peak_gemm_plan_info) write aligned copies of
  *                those operands into the workspace on every run; a run whose
  *                workspace holds the stand-in's partials but not the copies takes
- *                the stand-in.
+ *                the stand-in.  Where the copies pay only against rows that all
+ *                lie on odd 2-byte addresses ("oddbase=1"), so does a run of
+ *                operands without such rows.
  *   A, B, C      device pointers, aligned to the element size; C must not
  *                overlap A or B.  With beta == 0 C is write-only: whatever it
  *                holds, NaN included, does not reach the result.  With

@@ -9,11 +9,11 @@
 // memory, [k][x] rows too, with the transposing read for 16-bit operands.  For operands of any alignment that holds for
 // whole K tiles; the tile that K ends in goes through registers, shifted into place (shift_down), and is asked for before the loop.
 //
-// Bound, 16 bits: the way of the rows into the CU.  72 to 85 bytes per ns and CU where rows start on 128-byte lines, 48 to 60
-// where they start anywhere (each piece of a row then lies in one line more than it fills; on odd 2-byte addresses a
-// tenth less again).  fp32: the MFMAs, at 0.75 to 0.9 of their rate.  The any-alignment form went through registers before: 16-byte
+// Bound, 16 bits: the way of the rows into the CU.  72 to 85 bytes per ns and CU where rows start on 128-byte lines, 58 to 68
+// where they start anywhere (each piece of a row then lies in one line more than it fills; a sixth less where every other row
+// lies on an odd 2-byte address, two fifths less where all do).  fp32: the MFMAs, at 0.75 to 0.9 of their rate.  The any-alignment form went through registers before: 16-byte
 // loads, one tile on its way, LDS stores, two barriers' worth of LDS traffic in a chain per tile; more tiles on their way changed nothing.
-// Through the ring: fp32 777x1234x1555 TT 42.5 -> 31 us, 4095^3 NT 1054 -> 947, 219x1105x1177 NN 16.6 -> 11.0; bf16 704x640x1331 NT 12.0 -> 8.6,
+// Through the ring: fp32 777x1234x1555 TT 42.5 -> 29.5 us, 4095^3 NT 1054 -> 947, 219x1105x1177 NN 16.6 -> 11.0; bf16 704x640x1331 NT 12.0 -> 8.6,
 // 407x705x977 TN 11.0 -> 8.6, 1931x1587x1251 TT 28 -> 23.5, 1023x2047x3001 NT 40.8 -> 28.5.
 #pragma once
 

@@ -1,7 +1,7 @@
 """Plans that write aligned copies of their operands first ("pack=" in the plan description): odd sizes and leading
 dimensions, blocks of NaN-filled larger matrices at odd addresses, one operand aligned and the other not, all layouts;
 copies behind the partials of a K split and of a cut last round; a run without room for the copies, and the entry point
-with the fixed array where they outgrow it, takes the register-staged stand-in."""
+with the fixed array where they outgrow it, takes the stand-in for any alignment."""
 import itertools
 import re
 
