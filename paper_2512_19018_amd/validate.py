@@ -5,7 +5,7 @@ budget of execution-parameter settings to sample; the portable task compares
 outputs against a trusted reference within a tolerance, and the extended tasks
 look for what output comparison misses: memory-safety violations and
 nondeterminism.  This module is that task for the library's own kernels, for
-use on a GPU machine where no sanitizer is at hand:
+use on a machine where no sanitizer is at hand:
 
   * reference: the plainest kernel variant that accepts the problem (register
     staging, 64x64 tiles, no K split) plays the paper's "simple trusted kernel";
