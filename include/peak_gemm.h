@@ -104,8 +104,11 @@ typedef struct {
  */
 peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **out_plan);
 
-/* Bytes of device workspace peak_gemm_run needs for this plan (0 for most
- * plans that do not split K).  The workspace holds fp32 partial tiles of the
+/* Bytes of device workspace peak_gemm_run takes for this plan (0 for most
+ * plans that do not split K).  Plans of large products with few tiles and a deep
+ * K ("small=" in peak_gemm_plan_info) take up to 96 MB for partials; given less, or
+ * none where that plan needs none, a run takes the plan with fewer K slices that
+ * the description names.  The workspace holds fp32 partial tiles of the
  * Split-K step (Section 4.1, Table 2) and, for a streaming plan on an A stored
  * K x M, the copy of A with rows along K that the run writes first (Section
  * 4.1, Table 2, Transpose). */
@@ -200,12 +203,12 @@ peak_status_t peak_gemm_run_fused(peak_gemm_plan_t *plan, float alpha,
  * peak_gemm_run for callers that cannot allocate device memory or pass a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same plan, same kernels, same result bits as peak_gemm_run
- * (a plan whose aligned copies do not fit the array runs its stand-in variant instead);
+ * (a plan whose aligned copies or deep K split do not fit the array runs its stand-in instead);
  * what the workspace would hold goes to an array of PEAK_GEMM_STATIC_WORKSPACE_BYTES that
  * is part of the library's device code (every GPU the library runs on holds
  * its own copy until the process ends).  The call allocates nothing.
  *
- *   PEAK_ERR_WORKSPACE  the plan, aligned copies aside, needs more than PEAK_GEMM_STATIC_WORKSPACE_BYTES
+ *   PEAK_ERR_WORKSPACE  the plan, or its stand-in where it has one for small workspaces, needs more than PEAK_GEMM_STATIC_WORKSPACE_BYTES
  *                       (peak_gemm_workspace_bytes() tells beforehand); nothing is launched.
  *   PEAK_ERR_HIP        no current device, or the array's address could not be obtained.
  *

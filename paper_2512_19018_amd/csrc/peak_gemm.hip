@@ -198,6 +198,8 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
         if (p->alt.variant < 0) return PEAK_ERR_UNSUPPORTED;
         g = &p->alt;
     }
+    // (a workspace too small for a deep K split's partials does for the plan with fewer)
+    if (g == &p->g && p->small.variant >= 0 && (!workspace || workspace_bytes < g->ws_bytes || (uintptr_t)workspace % 256)) g = &p->small;
     // copies that pay only against rows on odd 2-byte addresses, and none there
     auto odd_rows = [](const void *base, int64_t ld) { return ld % 2 == 0 && (uintptr_t)base % 4 != 0; };
     if (g->pack_odd && !((g->pack & 1) && odd_rows(A, d.lda)) && !((g->pack & 2) && odd_rows(B, d.ldb))) g = &p->alt;
@@ -318,9 +320,10 @@ peak_status_t peak_gemm_run_static(peak_gemm_plan_t *plan, float alpha, const vo
                                    void *C, void *hip_stream)
 {
     if (!plan) return PEAK_ERR_INVALID_ARG;
-    // (a plan that would make aligned copies runs its stand-in where the copies do not fit)
-    if (plan->ws_bytes > (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES &&
-        !(plan->g.pack && plan->alt.ws_bytes <= (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES)) return PEAK_ERR_WORKSPACE;
+    // (a plan that would make aligned copies runs its stand-in where the copies do not fit, one with a deep K split that with fewer partials)
+    const bool other = plan->g.pack || plan->small.variant >= 0;
+    const size_t least = !other ? plan->ws_bytes : plan->alt.ws_bytes > plan->small.ws_bytes ? plan->alt.ws_bytes : plan->small.ws_bytes;
+    if (least > (size_t)PEAK_GEMM_STATIC_WORKSPACE_BYTES) return PEAK_ERR_WORKSPACE;
     void *ws = nullptr;
     if (plan->ws_bytes > 0) {
         int dev = -1;

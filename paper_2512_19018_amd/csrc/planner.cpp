@@ -555,6 +555,48 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
     return d.dtype == PEAK_DT_F32 && any >= 0 && best_any < 0.85 * best_ring ? any : ring;
 }
 
+// Few tiles and a deep K in 16 bits, in microseconds: the 256x256 tile by its K tiles (1.25 each), smaller ones, which ask for
+// about twice the bytes per multiply-add, by their way into the CU, 58 bytes per ns with the operands from HBM (54 to 65 in 14
+// products, 62 with 128 k per stage, 61 to 64 in 9), 90 from the last-level cache (80 to 101), where operands up to 100 MB are taken
+// to be; none sooner than the operands come from HBM (a single row of 256x256 tiles 4.6 TB/s); all with what the partials cost out and back.
+static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
+{
+    const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split), rounds = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
+    const double partials = split > 1 ? 2.0 + 0.33 * 4.0e-6 * split * (double)d.M * (double)d.N : 0.0;
+    const double bytes = 2.0 * ((double)d.M + (double)d.N) * (double)d.K, rate = bytes <= 100.0e6 ? 90.0 : v.bk >= 128 ? 62.0 : 58.0;
+    double us = 6.0 + 1.25 * (double)ktiles;
+    if (v.bm * v.bn < 256 * 256) us = 6.0 + (double)(ktiles * v.bk) * 2.0 * (v.bm + v.bn) / 1000.0 / rate;
+    us *= (double)rounds;
+    if (us < 8.0 + bytes / 4.6e6) us = 8.0 + bytes / 4.6e6;
+    return us + partials;
+}
+
+// The 256x256 tile in as many K slices as fill the chip in place of the choice by tiled_cost, which keeps to few partials and
+// does not know where the operands come from, where that is 13 % ahead by these prices.
+// Times of the choice by tiled_cost over those of the slices: 38 drawn products of 152 to 4480 rows that this decides 1.06 to 1.47, 1.22 in
+// the mean, each run with other operands than the last (512x4096x14336 NN, two slices of 128x128, 78.7 us, in eight of 256x256 64.9;
+// 391x5504x11392 NN unsplit 102.0, in five 69.3); 40 others with one set of operands over and over, in the last-level cache, 0.90 to
+// 1.12, 1.00 in the mean.  Where it sees less than 13 % the slices lost up to 4 %, with operands that fit the cache up to 16 %.
+// Partials to 96 MB: the run has the choice by tiled_cost as its stand-in where the workspace holds less.
+static bool deep_split(const peak_gemm_desc_t &d, int present, int present_split, int *variant, int *split)
+{
+    const Variant &pv = g_variants[present];
+    if (pv.kind != KIND_TILED || !pv.mf16) return false;
+    double best = 0.87 * deep_us(pv, d, present_split);
+    bool found = false;
+    for (int i = 0; i < NUM_VARIANTS; ++i) {
+        const Variant &v = g_variants[i];
+        if (v.sweep_only || v.kind != KIND_TILED || !v.mf16 || v.bm != 256 || v.bn != 256 || !variant_fits(v, d)) continue;
+        for (int s = 2; s <= 16; ++s) {
+            if (cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * s > num_cu() || cdiv(d.K, v.bk) / s < 12) break;
+            if (4.0 * s * (double)d.M * (double)d.N > 96.0e6) break;
+            const double us = deep_us(v, d, s);
+            if (us < best) { best = us; *variant = i; *split = s; found = true; }
+        }
+    }
+    return found;
+}
+
 // Products whose rows do not suit the 16-byte copies of the other tiled kernels, by those on aligned copies of the operands
 // that the run writes first.  The copies cost a pass over the operands and a launch; what they save is that rows which start
 // anywhere lie in a line more than they fill, and that the tiles may be large.
@@ -776,8 +818,8 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     if (!p) return PEAK_ERR_ALLOC;
     memset(p, 0, sizeof *p);
     p->d = d;
-    p->g.variant = p->alt.variant = -1;
-    p->g.split = p->alt.split = 1;
+    p->g.variant = p->alt.variant = p->small.variant = -1;
+    p->g.split = p->alt.split = p->small.split = 1;
 
     const int forced = (int)(d.flags & 0xFF) - 1;
     const int forced_split = (int)((d.flags >> 8) & 0xFF);
@@ -815,6 +857,11 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     int streamk = (d.flags & PEAK_GEMM_STREAMK_ON) ? 1 : (d.flags & PEAK_GEMM_STREAMK_OFF) ? -1 : 0;
     if (forced_split <= 0 && streamk == 0 && table_split < 0) streamk = 1;
     plan_geometry(&p->g, d, pick, forced_split > 0 ? forced_split : (table_split > 0 ? table_split : 0), streamk);
+    int deep = -1, slices = 0;
+    if (own_choice && forced_split <= 0 && streamk == 0 && p->g.sk_tiles == 0 && deep_split(d, pick, p->g.split, &deep, &slices)) {
+        p->small = p->g;
+        plan_geometry(&p->g, d, deep, slices);
+    }
     // Leading dimensions are known here, base addresses only at run time: a variant that copies
     // 16-byte chunks gets a stand-in that takes any alignment for runs whose A or B base is off that alignment.
     // Such a choice of the cost model's is the stand-in itself where aligned copies are worth making
@@ -831,6 +878,7 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
         if (alt >= 0) plan_geometry(&p->alt, d, alt, forced_split);
     }
     p->ws_bytes = p->g.ws_bytes > p->alt.ws_bytes ? p->g.ws_bytes : p->alt.ws_bytes;
+    if (p->small.ws_bytes > p->ws_bytes) p->ws_bytes = p->small.ws_bytes;
     const int64_t grid = (int64_t)p->g.tiles_m * p->g.tiles_n * p->g.split;   // (an upper bound for a stream-K plan)
     const int64_t grid_alt = p->alt.variant < 0 ? 0 : (int64_t)p->alt.tiles_m * p->alt.tiles_n * p->alt.split;
     if (grid > 0x7FFFFFFF || grid_alt > 0x7FFFFFFF) {
@@ -853,10 +901,11 @@ int peak_gemm_plan_info(const peak_gemm_plan_t *p, char *buf, size_t n)
     const Variant &v = g_variants[g.variant];
     return snprintf(buf, n,
                     "variant=%d:%s tile=%dx%dx%d threads=%d stages=%d lds=%d split=%d ktiles/slice=%d "
-                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s streamk=%d rot=%d,%d pack=%d oddbase=%d acopy=%d",
+                    "grid=%lld (tiles %dx%d) group_m=%d workspace=%zu unaligned=%s small=%s streamk=%d rot=%d,%d pack=%d oddbase=%d acopy=%d",
                     g.variant, v.name, v.bm, v.bn, v.bk, v.nt, v.ns, v.lds, g.split, g.ktiles_per_slice,
                     (long long)grid_blocks(g), g.tiles_m, g.tiles_n, g.group_m, p->ws_bytes,
-                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same", g.sk_tiles, g.rot_m, g.rot_n, g.pack, g.pack_odd, g.a_copy);
+                    p->alt.variant >= 0 ? g_variants[p->alt.variant].name : "same",
+                    p->small.variant >= 0 ? g_variants[p->small.variant].name : "none", g.sk_tiles, g.rot_m, g.rot_n, g.pack, g.pack_odd, g.a_copy);
 }
 
 peak_status_t peak_gemm_destroy(peak_gemm_plan_t *plan)

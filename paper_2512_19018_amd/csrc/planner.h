@@ -80,5 +80,7 @@ struct peak_gemm_plan {
     peak::Geometry g;           // the selected variant
     peak::Geometry alt;         // stand-in of any alignment for runs whose A or B base is not 16-byte aligned
                           // (variant -1 when the selected variant has no alignment needs)
-    size_t ws_bytes;      // the larger of the two workspaces
+    peak::Geometry small;       // ... and for runs whose workspace does not hold the selected variant's partials, where those are
+                          // a deep K split's (variant -1: none, such a run is refused)
+    size_t ws_bytes;      // the largest of their workspaces
 };
