@@ -315,7 +315,8 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     // K rotation: this workgroup walks its K tiles starting at tile `rot` and wraps round (only the order
     // of the sum over k changes).  Off (0) unless the plan asks for it: where every tile streams rows of its
     // own from HBM, workgroups that all read the same k range at once load few memory channels at a time.
-    const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
+    const int xcd = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
+    const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + xcd) % KT));
     auto next_offsets = [&](int kt) {
         int kr = (kt < KT ? kt : KT - 1) + rot;
         if (kr >= KT) kr -= KT;

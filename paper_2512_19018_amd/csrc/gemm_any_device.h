@@ -529,7 +529,8 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
         if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave_all, lane);
         else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
-        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m) % KT));
+        const int xcd = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
+        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + xcd) % KT));
         auto issue = [&](int kt, int stage) {
             int kr = kt + rot;
             if (kr >= KT) kr -= KT;

@@ -59,6 +59,7 @@ struct GemmArgs {
     int32_t ktiles_total;     // ceil(K / BK)
     int32_t group_m;          // tile rows per band of the tile order
     int32_t rot_m, rot_n;     // K rotation per tile row / tile column within an XCD's patch of tiles
+    int32_t rot_x;            // 1: the XCDs start an eighth of the K tiles apart
     int32_t sk_tiles;         // hybrid stream-K: the last sk_tiles tiles of the tile order are cut into `split` K slices
                               // (fp32 partials [slice][tile][BM][BN] in ws), all others take the whole of K; 0: off
     uint32_t flags;

@@ -256,6 +256,7 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
     a.group_m = g->group_m;
     a.rot_m = g->rot_m;
     a.rot_n = g->rot_n;
+    a.rot_x = g->rot_x;
     a.sk_tiles = g->sk_tiles;
 
     int64_t nblocks = grid_blocks(*g);

@@ -399,13 +399,19 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     // ... except where a single row of tiles has every workgroup stream rows of B that no other reads: started one
     // K tile apart they spread over the memory channels (16x16x32 kernels; bf16 128x28672x8192 109 -> 103 us)
     if (v.mf16 && p->tiles_m == 1 && p->tiles_n > 1) p->rot_n = 1;
+    // ... and by XCD, an eighth of the K tiles apart, where B's rows run along K and K is deep: workgroups that all read the same k of
+    // rows a power of two apart load few memory channels at a time, those of an XCD keep in step for its L2.  16 bits, time over that
+    // without, from HBM: 512x8192x8192 NT 76.5 us -> 74.6, TT 77.1 -> 74.6, 700x4096x8192 TT 69.3 -> 62.5, 512x4096x4096 NT 30.8 ->
+    // 29.9, 1000x14336x4096 97.4 -> 96.3; in the last-level cache level to 1 % (4096^3 98.2 -> 97.7).  Not with B stored K x N, whose
+    // k-rows are contiguous (256x14336x4096 NN 45.0 and 46.2), nor with a short K (512x4096x1024 NT 8.43 and 8.56).
+    p->rot_x = (v.mf16 || (v.ring && d.dtype != PEAK_DT_F32)) && !v.tr && p->rot_n == 0 && (int64_t)p->ktiles_per_slice * v.bk >= 4096 ? 1 : 0;
     if (const char *e = getenv("PEAK_GEMM_GROUP_M")) {      // tuning knob: tile rows per band
         const int g = atoi(e);
         if (g >= 1 && g <= 64) p->group_m = g < p->tiles_m ? g : (p->tiles_m > 0 ? p->tiles_m : 1);
     }
     if (const char *e = getenv("PEAK_GEMM_ROT")) {          // tuning knob: "rot_m,rot_n"
         int a = 0, b = 0;
-        if (sscanf(e, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 0) { p->rot_m = a; p->rot_n = b; }
+        if (sscanf(e, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 0) { p->rot_m = a; p->rot_n = b; p->rot_x = 0; }
     }
     p->ws_bytes = p->split > 1 ? (size_t)p->split * (size_t)d.M * (size_t)d.N * sizeof(float) : 0;
     p->a_copy = stages_a(v, d.transA) ? 1 : 0;

@@ -51,7 +51,7 @@ int planner_device_cu_count();
 // Grid and K split of one variant for the plan's problem.
 struct Geometry {
     int variant;          // index into the variant table, -1: nothing to launch
-    int tiles_m, tiles_n, split, ktiles_total, ktiles_per_slice, group_m, rot_m, rot_n;
+    int tiles_m, tiles_n, split, ktiles_total, ktiles_per_slice, group_m, rot_m, rot_n, rot_x;
     int sk_tiles;         // hybrid stream-K: tiles of the last, partial round that are cut into `split` K slices; 0: off
     int a_copy;           // streaming kernel on an A stored K x M: A is first written out along K (M rows of K
                           // elements) at a_copy_off of the workspace, and the kernel reads that
