@@ -46,6 +46,7 @@ struct Cfg16 {
     static constexpr bool A_KM = A_KM_;                      // A stored K x M: staged as [k][m] rows
     static constexpr bool B_KN = B_KN_;                      // B stored K x N: staged as [k][n] rows
     static constexpr int ESZ = 2, EPC = 8;
+    static constexpr bool FUSED16 = true;
     static_assert(BK_ == 64 || BK_ == 128, "k per stage");
     static constexpr int BM = TILE_, BN = TILE_N_, RB = BK_ * 2, CPR = RB / 16, BK = BK_;
     static constexpr int WAVES_M = 2, WAVES_N = 2, NW = 4, NT = 256;
@@ -564,29 +565,33 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
             for (int nb = 0; nb < C::NB; ++nb)
                 *(f32x4v *)(scr + (16 * h + r16) * SROW + (nb * 16 + 4 * q) * 4) = acc[2 * sl + h][nb];
     };
-    auto write16 = [&](int sl, char *scr16) {
+    auto write16 = [&](int sl, char *scr16, const auto &step) {
         constexpr int SROW16 = C::WTN * 2 + 16;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            float x[4 * C::NB];
 #pragma unroll
-            for (int nb = 0; nb < C::NB; ++nb) {
-                float x[4];
+            for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     // out of the accumulation registers here, group by group
                     const float aj = acc[2 * sl + h][nb][j];
-                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[j]) : "a"(aj));
-                    x[j] *= p.alpha;
+                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[4 * nb + j]) : "a"(aj));
+                    x[4 * nb + j] *= p.alpha;
                 }
+            if constexpr (!std::is_same_v<std::decay_t<decltype(step)>, NoStep>) step.apply(2 * sl + h, x);
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb) {
                 union { u32x2 u; _Float16 hh[4]; __bf16 bb[4]; } pk;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    if (C::DT == DT_F16) pk.hh[j] = (_Float16)x[j];
-                    else pk.bb[j] = (__bf16)x[j];
+                    if (C::DT == DT_F16) pk.hh[j] = (_Float16)x[4 * nb + j];
+                    else pk.bb[j] = (__bf16)x[4 * nb + j];
                 }
                 const int grp = (nb * 4 + q) ^ h;            // 4-column group, swapped pairwise in rows 16..31
                 *(u32x2 *)(scr16 + (16 * h + r16) * SROW16 + grp * 8) = pk.u;
             }
+        }
     };
     PartialOut po = splitk_out(p, slice < 0 ? 0 : slice);
     if (p.sk_tiles != 0) {

@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace peak {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -125,6 +127,7 @@ struct Cfg {
     static constexpr int DT = DT_;
     static constexpr int ESZ = DT_ == DT_F32 ? 4 : 2;
     static constexpr int EPC = 16 / ESZ;              // elements per 16-byte chunk
+    static constexpr bool FUSED16 = false;            // (see FusedStep)
     static constexpr int BM = BM_, BN = BN_, RB = RB_;
     static constexpr int CPR = RB_ / 16;              // chunks per tile row
     static constexpr int BK = RB_ / ESZ;              // t_k
@@ -806,6 +809,53 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
     }
 }
 
+// The fused step where a slab of 16-bit C goes through LDS already rounded (the 16x16x32 kernels, FUSED16), on the accumulators'
+// way out: half the LDS traffic of epilogue_vector, which took any launch with a step before.  Written out once for each
+// activation and without branches: the way out is executed once, straight through, and what a branch jumps over is fetched all
+// the same (256x128 tiles, 2048x4096x1024 NT: plain 19.5 us; ReLU 22.0 by epilogue_vector, 21.2 with a branch per
+// choice and 32 rows, 20.1 so; bias and GELU 23.1 and 22.2; 1000x14336x4096 96.8 and 94.8, 92.4 without a step; 2402x1288x752 13.0 and 12.5).
+// The bias is asked for here: before the K loop it is level.
+struct NoStep {};
+template <class C>
+struct FusedStep {
+    f32x4 column[C::NB];                                           // bias of the lane's columns
+    float row[C::MB];                                              // ... of its rows
+    // m, n: first row and column of the wave tile
+    PEAK_DEVM FusedStep(const GemmArgs &p, int lane, int64_t m, int64_t n)
+    {
+#pragma unroll
+        for (int nb = 0; nb < C::NB; ++nb) column[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int mb = 0; mb < C::MB; ++mb) row[mb] = 0.0f;
+        if (p.hook.bias_kind == BIAS_PER_COLUMN && p.N >= 4) {
+#pragma unroll
+            for (int nb = 0; nb < C::NB; ++nb) {
+                const int64_t at = n + nb * 16 + 4 * (lane >> 4);
+                column[nb] = load_loose<f32x4, 4>(p.hook.bias + (at < p.N - 4 ? at : p.N - 4));
+            }
+        } else if (p.hook.bias_kind == BIAS_PER_ROW) {
+#pragma unroll
+            for (int mb = 0; mb < C::MB; ++mb) {
+                const int64_t at = m + mb * 16 + (lane & 15);
+                row[mb] = p.hook.bias[at < p.M ? at : p.M - 1];
+            }
+        }
+    }
+    // row block mb of the wave tile: x[4 * nb + v], already scaled
+    template <int ACT>
+    PEAK_DEVM void apply(int mb, float (&x)[4 * C::NB]) const
+    {
+#pragma unroll
+        for (int e = 0; e < 4 * C::NB; ++e) x[e] = x[e] + column[e / 4][e % 4] + row[mb];
+        hook_apply(ACT, false, x, x);
+    }
+};
+template <class C, int ACT_>
+struct FusedAct {
+    const FusedStep<C> &step;
+    PEAK_DEVM void apply(int mb, float (&x)[4 * C::NB]) const { step.template apply<ACT_>(mb, x); }
+};
+
 template <class C, int SLABS, class WriteSlab, class Write16>
 PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, int wm, int wn, int64_t m0, int64_t n0,
                              const PartialOut &po, WriteSlab &&write_slab, Write16 &&write16)
@@ -829,7 +879,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
     // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
     if constexpr (C::DT != DT_F32) {
-        if ((interior || p.N % 8 == 0) && !po.base && !c_f32 && p.beta == 0.0f && !hooked) {
+        if ((interior || p.N % 8 == 0) && !po.base && !c_f32 && p.beta == 0.0f && (!hooked || C::FUSED16)) {
             constexpr int LPR = C::WTN * 2 / 16, RPI = 64 / LPR;       // lanes per row, rows per store instruction
             constexpr int SROW16 = C::WTN * 2 + 16;
             constexpr int G = 32 / RPI;
@@ -837,17 +887,17 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             char *scr16 = lds + wave * (32 * SROW16);
             const int64_t m_first = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
             uint16_t *out = (uint16_t *)p.C + m_first * p.ldc + n;
-            auto plain = [&](auto edge_c) {
+            auto plain = [&](auto edge_c, const auto &step) {
                 constexpr bool EDGE = decltype(edge_c)::value != 0;
                 const int rows_ok = n < p.N ? (int)(p.M - m_first < C::WTM ? p.M - m_first : C::WTM) : 0;   // ... that C has (EDGE)
-                write16(0, scr16);
+                write16(0, scr16, step);
 #pragma unroll
                 for (int mi = 0; mi < SLABS; ++mi) {
                     u32x4 v[G];
 #pragma unroll
                     for (int g = 0; g < G; ++g)
                         v[g] = *(const u32x4 *)(scr16 + (g * RPI + orow) * SROW16 + ocol * 2);
-                    if (mi + 1 < SLABS) write16(mi + 1, scr16);      // in-order LDS: lands after the reads above
+                    if (mi + 1 < SLABS) write16(mi + 1, scr16, step);      // in-order LDS: lands after the reads above
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
                         const int r = mi * 32 + g * RPI;
@@ -859,8 +909,17 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             };
             // interior tiles without the masks where the launches are short enough for them to show (0.1 us of 3.4); the
             // large wave tiles take one form, two drove the 8-wave 256x256 kernels 9 to 47 registers past the register file
-            if (C::WTM * C::WTN < 128 * 64 && interior) plain(IC<0>{});
-            else plain(IC<1>{});
+            if constexpr (C::FUSED16) {
+                if (hooked) {
+                    const FusedStep<C> step(p, lane, m0 + wm * C::WTM, n0 + wn * C::WTN);
+                    if (p.hook.act == ACT_RELU) plain(IC<1>{}, FusedAct<C, ACT_RELU>{step});
+                    else if (p.hook.act == ACT_GELU_TANH) plain(IC<1>{}, FusedAct<C, ACT_GELU_TANH>{step});
+                    else plain(IC<1>{}, FusedAct<C, ACT_NONE>{step});
+                    return;
+                }
+            }
+            if (C::WTM * C::WTN < 128 * 64 && interior) plain(IC<0>{}, NoStep{});
+            else plain(IC<1>{}, NoStep{});
             return;
         }
     }
@@ -1662,7 +1721,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
             }
     };
     // ... or, for plain runs of the 16-bit kernels, already scaled and rounded
-    auto write16 = [&](int mi, char *scr16) {
+    auto write16 = [&](int mi, char *scr16, NoStep) {
         constexpr int SROW16 = C::WTN * 2 + 16;
 #pragma unroll
         for (int ni = 0; ni < C::NI; ++ni)
