@@ -21,6 +21,7 @@ VariantGroup variants_f32();
 VariantGroup variants_ta();
 VariantGroup variants_skinny();
 VariantGroup variants_mf16();
+VariantGroup variants_mf16t();
 VariantGroup variants_mf16s();
 VariantGroup variants_mf16d();
 VariantGroup variants_mf16r();
