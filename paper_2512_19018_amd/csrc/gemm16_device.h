@@ -46,7 +46,7 @@ struct Cfg16 {
     static constexpr bool A_KM = A_KM_;                      // A stored K x M: staged as [k][m] rows
     static constexpr bool B_KN = B_KN_;                      // B stored K x N: staged as [k][n] rows
     static constexpr int ESZ = 2, EPC = 8;
-    static constexpr bool FUSED16 = true;
+    static constexpr int FUSED16 = 2;
     static_assert(BK_ == 64 || BK_ == 128, "k per stage");
     static constexpr int BM = TILE_, BN = TILE_N_, RB = BK_ * 2, CPR = RB / 16, BK = BK_;
     static constexpr int WAVES_M = 2, WAVES_N = 2, NW = 4, NT = 256;

@@ -29,8 +29,7 @@ struct CfgAny {
     static constexpr int DT = DT_;
     static constexpr bool A_KM = A_KM_, B_KN = B_KN_;
     static constexpr int ESZ = DT_ == DT_F32 ? 4 : 2, EPC = 16 / ESZ;
-    // (FusedStep here: level with a step, launches without one up to 1 % behind, 512x4096x1024 NT 8.43 us against 8.39)
-    static constexpr bool FUSED16 = false;
+    static constexpr int FUSED16 = DT_ != DT_F32 ? 1 : 0;   // (see FusedStep)
     static constexpr int BM = BM_, BN = BN_, RB = RB_, CPR = RB_ / 16, BK = RB_ / ESZ;
     static constexpr int WAVES_M = WM_, WAVES_N = WN_, WAVES_K = WK_;
     static constexpr int PLACES = WM_ * WN_, NW = PLACES * WK_, NT = NW * 64;
@@ -654,20 +653,25 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
             for (int nb = 0; nb < C::NB; ++nb)
                 *(f32x4 *)(scr + (16 * h + r16) * SROW + (nb * 16 + 4 * q) * 4) = acc[2 * sl + h][nb];
     };
-    auto write16 = [&](int sl, char *scr16, NoStep) {
+    auto write16 = [&](int sl, char *scr16, const auto &step) {
         constexpr int SROW16 = C::WTN * 2 + 16;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            float x[4 * C::NB];
+#pragma unroll
+            for (int e = 0; e < 4 * C::NB; ++e) x[e] = acc[2 * sl + h][e / 4][e % 4] * p.alpha;
+            if constexpr (!std::is_same_v<std::decay_t<decltype(step)>, NoStep>) step.apply(2 * sl + h, x);
 #pragma unroll
             for (int nb = 0; nb < C::NB; ++nb) {
                 union { u32x2 u; _Float16 hh[4]; __bf16 bb[4]; } pk;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    if (C::DT == DT_F16) pk.hh[j] = (_Float16)(acc[2 * sl + h][nb][j] * p.alpha);
-                    else pk.bb[j] = (__bf16)(acc[2 * sl + h][nb][j] * p.alpha);
+                    if (C::DT == DT_F16) pk.hh[j] = (_Float16)x[4 * nb + j];
+                    else pk.bb[j] = (__bf16)x[4 * nb + j];
                 }
                 *(u32x2 *)(scr16 + (16 * h + r16) * SROW16 + ((nb * 4 + q) ^ h) * 8) = pk.u;
             }
+        }
     };
     epilogue_slabs<C, C::WTM / 32>(p, lds, wave, lane, wm, wn, m0, n0, splitk_out(p, slice), write_slab, write16);
 #endif

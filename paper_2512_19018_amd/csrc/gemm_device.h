@@ -127,7 +127,7 @@ struct Cfg {
     static constexpr int DT = DT_;
     static constexpr int ESZ = DT_ == DT_F32 ? 4 : 2;
     static constexpr int EPC = 16 / ESZ;              // elements per 16-byte chunk
-    static constexpr bool FUSED16 = false;            // (see FusedStep)
+    static constexpr int FUSED16 = 0;                 // (see FusedStep)
     static constexpr int BM = BM_, BN = BN_, RB = RB_;
     static constexpr int CPR = RB_ / 16;              // chunks per tile row
     static constexpr int BK = RB_ / ESZ;              // t_k
@@ -809,12 +809,13 @@ PEAK_DEV void epilogue_vector(const GemmArgs &p, char *scr, int lane, int wm, in
     }
 }
 
-// The fused step where a slab of 16-bit C goes through LDS already rounded (the 16x16x32 kernels, FUSED16), on the accumulators'
+// The fused step where a slab of 16-bit C goes through LDS already rounded (FUSED16: 1 with an activation, 2 any), on the accumulators'
 // way out: half the LDS traffic of epilogue_vector, which took any launch with a step before.  Written out once for each
 // activation and without branches: the way out is executed once, straight through, and what a branch jumps over is fetched all
 // the same (256x128 tiles, 2048x4096x1024 NT: plain 19.5 us; ReLU 22.0 by epilogue_vector, 21.2 with a branch per
 // choice and 32 rows, 20.1 so; bias and GELU 23.1 and 22.2; 1000x14336x4096 96.8 and 94.8, 92.4 without a step; 2402x1288x752 13.0 and 12.5).
-// The bias is asked for here: before the K loop it is level.
+// The bias is asked for here: before the K loop it is level.  Ring kernels, 300x3072x2048 NT: bias alone 9.58 us by epilogue_vector,
+// 9.73 so, with ReLU 9.77 and 9.74, with GELU 10.00 and 9.92, GELU and a bias per row 10.15 and 9.79.
 struct NoStep {};
 template <class C>
 struct FusedStep {
@@ -879,7 +880,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     // Rows r and r + 16 would meet in the same banks (row stride = 4 banks mod 64), so the
     // 8-byte groups of rows 16..31 swap places pairwise; the reader swaps them back.
     if constexpr (C::DT != DT_F32) {
-        if ((interior || p.N % 8 == 0) && !po.base && !c_f32 && p.beta == 0.0f && (!hooked || C::FUSED16)) {
+        if ((interior || p.N % 8 == 0) && !po.base && !c_f32 && p.beta == 0.0f && (!hooked || C::FUSED16 > (p.hook.act == ACT_NONE ? 1 : 0))) {
             constexpr int LPR = C::WTN * 2 / 16, RPI = 64 / LPR;       // lanes per row, rows per store instruction
             constexpr int SROW16 = C::WTN * 2 + 16;
             constexpr int G = 32 / RPI;
@@ -909,12 +910,12 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             };
             // interior tiles without the masks where the launches are short enough for them to show (0.1 us of 3.4); the
             // large wave tiles take one form, two drove the 8-wave 256x256 kernels 9 to 47 registers past the register file
-            if constexpr (C::FUSED16) {
+            if constexpr (C::FUSED16 > 0) {
                 if (hooked) {
                     const FusedStep<C> step(p, lane, m0 + wm * C::WTM, n0 + wn * C::WTN);
                     if (p.hook.act == ACT_RELU) plain(IC<1>{}, FusedAct<C, ACT_RELU>{step});
-                    else if (p.hook.act == ACT_GELU_TANH) plain(IC<1>{}, FusedAct<C, ACT_GELU_TANH>{step});
-                    else plain(IC<1>{}, FusedAct<C, ACT_NONE>{step});
+                    else if (C::FUSED16 < 2 || p.hook.act == ACT_GELU_TANH) plain(IC<1>{}, FusedAct<C, ACT_GELU_TANH>{step});
+                    else if constexpr (C::FUSED16 == 2) plain(IC<1>{}, FusedAct<C, ACT_NONE>{step});
                     return;
                 }
             }
@@ -923,37 +924,104 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
             return;
         }
     }
-    // Plain runs of the fp32 kernels on interior tiles, K slices among them: straight through, without the choices below
-    // (652x4536x16 TN 7.8 us without them, 8.9 with; 4096x4096x64 NT 31.0 and 32.7; 256^3 4.3 and 4.8).
-    if constexpr (C::DT == DT_F32) {
-        if (interior && (po.base || (p.beta == 0.0f && !hooked))) {
-            constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
-            constexpr int GR = G < 8 ? G : 8;                          // ... of which at most eight in registers
-            const int orow = lane / LPR, ocol = (lane % LPR) * 4;
-            const float alpha = po.base ? 1.0f : p.alpha;
-            const int64_t ld = po.base ? po.ld : p.ldc, m = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
-            float *out = po.base ? po.base + (m - po.m_org) * ld + (n - po.n_org) : (float *)p.C + m * ld + n;
+    const bool out32 = C::DT == DT_F32 || c_f32 || po.base;
+    // fp32 C and K slices without a fused step, where the tile's columns are whole 16-byte pieces: straight through, without the
+    // choices below (fp32 652x4536x16 TN 7.8 us without them, 8.9 with; 4096x4096x64 NT 31.0 and 32.7; 256^3 4.3 and 4.8).
+    // Likewise 16-bit kernels' (epilogue_vector and so: bf16 512x4096x14336 NN in eight slices 66.5 us and 65.2, 512x2048x8192 NN in four
+    // 26.2 and 25.6) and, on interior tiles, with C_in: 4096x4096x2000 TN into fp32 C 69.5 and 67.5, 2048x1024x2048 18.4 and 17.5, fp32
+    // 512^3 6.55 and 6.03, 256^3 5.03 and 4.54.  With the loads of C_in masked for edge tiles, each is waited for by itself (69.8 and 89.8).
+    // (not the 32x32 kernels of 16 bits: their 8-wave 256x256 tiles have no registers left for another form)
+    if constexpr (C::DT == DT_F32 || C::FUSED16 > 0) {
+        const bool adds = !po.base && p.beta != 0.0f;
+        if (out32 && !hooked && (adds ? interior : interior || p.N % 4 == 0)) {
+            auto straight = [&](auto beta_c, auto edge_c) {
+                constexpr bool BETA = decltype(beta_c)::value != 0, EDGE = decltype(edge_c)::value != 0;
+                constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
+                constexpr int GR = G < 8 ? G : 8, RUNS = SLABS * (G / GR);     // ... of which at most eight in registers
+                const int orow = lane / LPR, ocol = (lane % LPR) * 4;
+                const float alpha = po.base ? 1.0f : p.alpha;
+                const int64_t ld = po.base ? po.ld : p.ldc, m = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
+                float *out = po.base ? po.base + (m - po.m_org) * ld + (n - po.n_org) : (float *)p.C + m * ld + n;
+                const int rows_ok = n < p.N ? (int)(p.M - m < C::WTM ? p.M - m : C::WTM) : 0;       // ... that C has (EDGE)
+                f32x4 c_in[RUNS][GR];
+                auto fetch = [&](int run) {                                   // C_in, asked for a run ahead
+                    if constexpr (BETA) {
+#pragma unroll
+                        for (int g = 0; g < GR; ++g)
+                            if (!EDGE || (run * GR + g) * RPI < rows_ok) c_in[run][g] = load_loose<f32x4, 4>((const char *)out + (int64_t)(run * GR + g) * RPI * ld * 4);
+                    }
+                };
+                fetch(0);
+                write_slab(0, scr);
+#pragma unroll
+                for (int run = 0; run < RUNS; ++run) {
+                    const int first = run % (G / GR) * GR;
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
+                    f32x4 v[GR];
+#pragma unroll
+                    for (int g = 0; g < GR; ++g) v[g] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4);
+                    if (first + GR == G && run + 1 < RUNS) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
+                    if (run + 1 < RUNS) fetch(run + 1);
+#pragma unroll
+                    for (int g = 0; g < GR; ++g) {
+                        union { u32x4 u; f32x4 f; } o;
+                        o.f = v[g] * alpha;
+                        if constexpr (BETA) o.f += c_in[run][g] * p.beta;
+                        if (!EDGE || (run * GR + g) * RPI < rows_ok) store_loose<u32x4, 4>((char *)out + (int64_t)(run * GR + g) * RPI * ld * 4, o.u);
+                    }
+                }
+            };
+            if (adds) straight(IC<1>{}, IC<0>{});
+            else if (C::WTM * C::WTN < 128 * 64 && interior) straight(IC<0>{}, IC<0>{});
+            else straight(IC<0>{}, IC<1>{});
+            return;
+        }
+    }
+    // 16-bit C with C_in, without a fused step, on interior tiles: likewise (bf16 4096^3 NT 100.2 and 98.2 us, 2048^3 21.3 and 19.5,
+    // 512x4096x1024 NT in 128x64 ring tiles 9.60 and 8.88)
+    if constexpr (C::DT != DT_F32 && C::FUSED16 > 0) {
+        if (!out32 && !hooked && interior) {
+            constexpr int LPR = C::WTN / 8, RPI = 64 / LPR, G = 32 / RPI;
+            constexpr int GR = G < 8 ? G : 8, RUNS = SLABS * (G / GR);
+            const int orow = lane / LPR, ocol = (lane % LPR) * 8;
+            const float alpha = p.alpha, beta = p.beta;
+            uint16_t *out = (uint16_t *)p.C + (m0 + wm * C::WTM + orow) * p.ldc + n0 + wn * C::WTN + ocol;
+            u32x4 c_in[RUNS][GR];
+            auto fetch = [&](int run) {
+#pragma unroll
+                for (int g = 0; g < GR; ++g) c_in[run][g] = load_loose<u32x4, 2>(out + (int64_t)(run * GR + g) * RPI * p.ldc);
+            };
+            fetch(0);
             write_slab(0, scr);
 #pragma unroll
-            for (int run = 0; run < SLABS * (G / GR); ++run) {
+            for (int run = 0; run < RUNS; ++run) {
                 const int first = run % (G / GR) * GR;
                 asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
-                f32x4 v[GR];
+                __builtin_amdgcn_sched_barrier(0);
+                f32x4 v[GR][2];
 #pragma unroll
-                for (int g = 0; g < GR; ++g) v[g] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4);
-                if (first + GR == G && run + 1 < SLABS * (G / GR)) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
+                for (int g = 0; g < GR; ++g)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) v[g][h] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4 + 16 * h);
+                if (first + GR == G && run + 1 < RUNS) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
+                if (run + 1 < RUNS) fetch(run + 1);
 #pragma unroll
                 for (int g = 0; g < GR; ++g) {
-                    union { u32x4 u; f32x4 f; } o;
-                    o.f = v[g] * alpha;
-                    store_loose<u32x4, 4>((char *)out + (int64_t)(run * GR + g) * RPI * ld * 4, o.u);
+                    union { u32x4 u; _Float16 h[8]; __bf16 b[8]; } c, o;
+                    c.u = c_in[run][g];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float x = v[g][e / 4][e % 4] * alpha + beta * (C::DT == DT_F16 ? (float)c.h[e] : (float)c.b[e]);
+                        if (C::DT == DT_F16) o.h[e] = (_Float16)x;
+                        else o.b[e] = (__bf16)x;
+                    }
+                    store_loose<u32x4, 2>(out + (int64_t)(run * GR + g) * RPI * p.ldc, o.u);
                 }
             }
             return;
         }
     }
-    const bool out32 = C::DT == DT_F32 || c_f32 || po.base;
     const int epl = out32 ? 4 : 8;
     const int64_t left = p.N - (n0 + wn * C::WTN);                     // columns of C in the wave tile and beyond
     if (interior || p.N % epl == 0) {
