@@ -563,13 +563,13 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 
 // Few tiles and a deep K in 16 bits, in microseconds: the 256x256 tile by its K tiles (1.25 each), smaller ones, which ask for
 // about twice the bytes per multiply-add, by their way into the CU, 58 bytes per ns with the operands from HBM (54 to 65 in 14
-// products, 62 with 128 k per stage, 61 to 64 in 9), 90 from the last-level cache (80 to 101), where operands up to 100 MB are taken
+// products, 62 with 128 k per stage, 61 to 64 in 9), 90 from the last-level cache (80 to 101), where operands up to 90 MB are taken
 // to be; none sooner than the operands come from HBM (a single row of 256x256 tiles 4.6 TB/s); all with what the partials cost out and back.
 static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split), rounds = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
     const double partials = split > 1 ? 2.0 + 0.33 * 4.0e-6 * split * (double)d.M * (double)d.N : 0.0;
-    const double bytes = 2.0 * ((double)d.M + (double)d.N) * (double)d.K, rate = bytes <= 100.0e6 ? 90.0 : v.bk >= 128 ? 62.0 : 58.0;
+    const double bytes = 2.0 * ((double)d.M + (double)d.N) * (double)d.K, rate = bytes <= 90.0e6 ? 90.0 : v.bk >= 128 ? 62.0 : 58.0;
     double us = 6.0 + 1.25 * (double)ktiles;
     if (v.bm * v.bn < 256 * 256) us = 6.0 + (double)(ktiles * v.bk) * 2.0 * (v.bm + v.bn) / 1000.0 / rate;
     us *= (double)rounds;
@@ -579,7 +579,7 @@ static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
 
 // The 256x256 tile in as many K slices as fill the chip in place of the choice by tiled_cost, which keeps to few partials and
 // does not know where the operands come from, where that is 13 % ahead by these prices.
-// Times of the choice by tiled_cost over those of the slices: 38 drawn products of 152 to 4480 rows that this decides 1.06 to 1.47, 1.22 in
+// Times of the choice by tiled_cost over those of the slices: 54 drawn products of 152 to 4480 rows that this decides 0.99 to 1.47, 1.20 in
 // the mean, each run with other operands than the last (512x4096x14336 NN, two slices of 128x128, 78.7 us, in eight of 256x256 64.9;
 // 391x5504x11392 NN unsplit 102.0, in five 69.3); 40 others with one set of operands over and over, in the last-level cache, 0.90 to
 // 1.12, 1.00 in the mean.  Where it sees less than 13 % the slices lost up to 4 %, with operands that fit the cache up to 16 %.
