@@ -164,7 +164,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     int slice, tile, sk_pos = -1;
     if (p.sk_tiles == 0) {
         const int pos = order_of_block(bid, tiles * p.split);
-        slice = __builtin_amdgcn_readfirstlane(pos / tiles);
+        slice = __builtin_amdgcn_readfirstlane(quotient((uint32_t)pos, p.by_tiles));
         tile = pos - slice * tiles;
     } else if (bid < whole) {
         slice = -1;                                         // the whole of K
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     }
     int tm, tn;
     if (p.sk_tiles != 0) tile = order_of_block(tile, tiles);
-    tile_in_order(tile, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    tile_in_order(p, tile, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
 
     const int kt_begin = slice < 0 ? 0 : slice * p.ktiles_per_slice;
@@ -316,8 +316,9 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_EU) void gemm16_kernel(const Ge
     // K rotation: this workgroup walks its K tiles starting at tile `rot` and wraps round (only the order
     // of the sum over k changes).  Off (0) unless the plan asks for it: where every tile streams rows of its
     // own from HBM, workgroups that all read the same k range at once load few memory channels at a time.
-    const int xcd = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
-    const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + xcd) % KT));
+    int rot = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
+    if (p.rot_m | p.rot_n) rot = (int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + rot) % KT);
+    rot = __builtin_amdgcn_readfirstlane(rot);
     auto next_offsets = [&](int kt) {
         int kr = (kt < KT ? kt : KT - 1) + rot;
         if (kr >= KT) kr -= KT;

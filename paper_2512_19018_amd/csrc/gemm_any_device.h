@@ -324,9 +324,9 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
 
     const int tiles = p.tiles_m * p.tiles_n;
     const int pos = order_of_block(blockIdx.x, tiles * p.split);
-    const int slice = __builtin_amdgcn_readfirstlane(pos / tiles);
+    const int slice = __builtin_amdgcn_readfirstlane(quotient((uint32_t)pos, p.by_tiles));
     int tm, tn;
-    tile_in_order(pos - slice * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    tile_in_order(p, pos - slice * tiles, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int kt_begin = slice * p.ktiles_per_slice;
     int kt_end = kt_begin + p.ktiles_per_slice;
@@ -530,8 +530,9 @@ __global__ __launch_bounds__(C::NT, C::EU) void gemm_any_kernel(const GemmArgs p
         else dA.init(p.A, p.lda, m0, p.M, kbase, p.K, tail_k, wave_all, lane);
         if constexpr (C::B_KN) nB.init(p.B, p.ldb, n0, p.b_cols, kbase, p.K, tail_k, wave_all, lane);
         else dB.init(p.B, p.ldb, n0, p.N, kbase, p.K, tail_k, wave_all, lane);
-        const int xcd = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
-        const int rot = __builtin_amdgcn_readfirstlane((int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + xcd) % KT));
+        int rot = p.rot_x ? (int)((blockIdx.x & 7) * (uint32_t)KT >> 3) : 0;
+        if (p.rot_m | p.rot_n) rot = (int)(((int64_t)tn * p.rot_n + (int64_t)tm * p.rot_m + rot) % KT);
+        rot = __builtin_amdgcn_readfirstlane(rot);
         auto issue = [&](int kt, int stage) {
             int kr = kt + rot;
             if (kr >= KT) kr -= KT;

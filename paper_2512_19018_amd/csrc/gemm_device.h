@@ -46,6 +46,11 @@ struct Hook {
     int32_t act;
 };
 
+// Division by a number that the host knows: 2^32 over it, rounded down (2^32 - 1 for 1); the quotient it gives is one short at most.
+struct Divisor {
+    uint32_t d, r;
+};
+
 struct GemmArgs {
     const void *A;
     const void *B;
@@ -66,6 +71,8 @@ struct GemmArgs {
                               // (fp32 partials [slice][tile][BM][BN] in ws), all others take the whole of K; 0: off
     uint32_t flags;
     Hook hook;
+    Divisor by_tiles, by_band, by_group, by_last;   // tiles_m * tiles_n; tiles of a band; rows of a band and of the last one
+    Divisor by_reduce;                              // workgroups across C of the K slices' sum
 };
 
 #define PEAK_DEV static __device__ __forceinline__
@@ -627,19 +634,22 @@ PEAK_DEV int order_of_block(int t, int total)
     const int base = total >> 3, rem = total & 7;
     return xcd * base + (xcd < rem ? xcd : rem) + idx;
 }
-PEAK_DEV void tile_in_order(int L, int tiles_m, int tiles_n, int group_m, int &tm, int &tn)
+// (The quotients by the host's reciprocals: a workgroup works out its tile before it can ask for anything.  The compiler's four divisions,
+// and one in 64 bits for a K rotation that most launches do not have, took 0.1 to 0.3 us of each launch: fp32 256^3 NN 4.54 us and 4.22,
+// 512^3 6.03 and 5.69; bf16 512x4096x1024 NT 8.35 and 8.17, 100x4096x4096 11.19 and 11.05, 2048x2048x512 9.17 and 8.89.)
+PEAK_DEV int quotient(uint32_t n, const Divisor &by)
 {
-    const int band = group_m * tiles_n;
-    const int g = L / band;
-    const int first = g * group_m;
-    const int gsz = (tiles_m - first) < group_m ? (tiles_m - first) : group_m;
-    const int w = L - g * band;
-    tm = first + w % gsz;
-    tn = w / gsz;
+    const uint32_t q = __umulhi(n, by.r);
+    return (int)(n - q * by.d >= by.d ? q + 1 : q);
 }
-PEAK_DEV void tile_of_block(int t, int tiles_m, int tiles_n, int group_m, int &tm, int &tn)
+PEAK_DEV void tile_in_order(const GemmArgs &p, int L, int &tm, int &tn)
 {
-    tile_in_order(order_of_block(t, tiles_m * tiles_n), tiles_m, tiles_n, group_m, tm, tn);
+    const int g = quotient((uint32_t)L, p.by_band);
+    const int first = g * p.group_m, left = p.tiles_m - first;
+    const bool last = left < p.group_m;
+    const int gsz = last ? left : p.group_m, w = L - g * (int)p.by_band.d;
+    tn = last ? quotient((uint32_t)w, p.by_last) : quotient((uint32_t)w, p.by_group);
+    tm = first + w - tn * gsz;
 }
 
 // ---------------------------------------------------------------------------
@@ -932,49 +942,54 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     // 512^3 6.55 and 6.03, 256^3 5.03 and 4.54.  With the loads of C_in masked for edge tiles, each is waited for by itself (69.8 and 89.8).
     // (not the 32x32 kernels of 16 bits: their 8-wave 256x256 tiles have no registers left for another form)
     if constexpr (C::DT == DT_F32 || C::FUSED16 > 0) {
-        const bool adds = !po.base && p.beta != 0.0f;
-        if (out32 && !hooked && (adds ? interior : interior || p.N % 4 == 0)) {
-            auto straight = [&](auto beta_c, auto edge_c) {
-                constexpr bool BETA = decltype(beta_c)::value != 0, EDGE = decltype(edge_c)::value != 0;
-                constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
-                constexpr int GR = G < 8 ? G : 8, RUNS = SLABS * (G / GR);     // ... of which at most eight in registers
-                const int orow = lane / LPR, ocol = (lane % LPR) * 4;
-                const float alpha = po.base ? 1.0f : p.alpha;
-                const int64_t ld = po.base ? po.ld : p.ldc, m = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
-                float *out = po.base ? po.base + (m - po.m_org) * ld + (n - po.n_org) : (float *)p.C + m * ld + n;
-                const int rows_ok = n < p.N ? (int)(p.M - m < C::WTM ? p.M - m : C::WTM) : 0;       // ... that C has (EDGE)
-                f32x4 c_in[RUNS][GR];
-                auto fetch = [&](int run) {                                   // C_in, asked for a run ahead
-                    if constexpr (BETA) {
+        auto straight = [&](auto beta_c, auto edge_c) {
+            constexpr bool BETA = decltype(beta_c)::value != 0, EDGE = decltype(edge_c)::value != 0;
+            constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
+            constexpr int GR = G < 8 ? G : 8, RUNS = SLABS * (G / GR);     // ... of which at most eight in registers
+            const int orow = lane / LPR, ocol = (lane % LPR) * 4;
+            const float alpha = po.base ? 1.0f : p.alpha;
+            const int64_t ld = po.base ? po.ld : p.ldc, m = m0 + wm * C::WTM + orow, n = n0 + wn * C::WTN + ocol;
+            float *out = po.base ? po.base + (m - po.m_org) * ld + (n - po.n_org) : (float *)p.C + m * ld + n;
+            const int rows_ok = n < p.N ? (int)(p.M - m < C::WTM ? p.M - m : C::WTM) : 0;       // ... that C has (EDGE)
+            f32x4 c_in[RUNS][GR];
+            auto fetch = [&](int run) {                                   // C_in, asked for a run ahead
+                if constexpr (BETA) {
 #pragma unroll
-                        for (int g = 0; g < GR; ++g)
-                            if (!EDGE || (run * GR + g) * RPI < rows_ok) c_in[run][g] = load_loose<f32x4, 4>((const char *)out + (int64_t)(run * GR + g) * RPI * ld * 4);
-                    }
-                };
-                fetch(0);
-                write_slab(0, scr);
-#pragma unroll
-                for (int run = 0; run < RUNS; ++run) {
-                    const int first = run % (G / GR) * GR;
-                    asm volatile("" ::: "memory");
-                    __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
-                    f32x4 v[GR];
-#pragma unroll
-                    for (int g = 0; g < GR; ++g) v[g] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4);
-                    if (first + GR == G && run + 1 < RUNS) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
-                    if (run + 1 < RUNS) fetch(run + 1);
-#pragma unroll
-                    for (int g = 0; g < GR; ++g) {
-                        union { u32x4 u; f32x4 f; } o;
-                        o.f = v[g] * alpha;
-                        if constexpr (BETA) o.f += c_in[run][g] * p.beta;
-                        if (!EDGE || (run * GR + g) * RPI < rows_ok) store_loose<u32x4, 4>((char *)out + (int64_t)(run * GR + g) * RPI * ld * 4, o.u);
-                    }
+                    for (int g = 0; g < GR; ++g)
+                        if (!EDGE || (run * GR + g) * RPI < rows_ok) c_in[run][g] = load_loose<f32x4, 4>((const char *)out + (int64_t)(run * GR + g) * RPI * ld * 4);
                 }
             };
-            if (adds) straight(IC<1>{}, IC<0>{});
-            else if (C::WTM * C::WTN < 128 * 64 && interior) straight(IC<0>{}, IC<0>{});
-            else straight(IC<0>{}, IC<1>{});
+            fetch(0);
+            write_slab(0, scr);
+#pragma unroll
+            for (int run = 0; run < RUNS; ++run) {
+                const int first = run % (G / GR) * GR;
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);         // one slab's accumulators out of the accumulation registers at a time
+                f32x4 v[GR];
+#pragma unroll
+                for (int g = 0; g < GR; ++g) v[g] = *(const f32x4 *)(scr + ((first + g) * RPI + orow) * SROW + ocol * 4);
+                if (first + GR == G && run + 1 < RUNS) write_slab(run / (G / GR) + 1, scr);   // in-order LDS: lands after the reads above
+                if (run + 1 < RUNS) fetch(run + 1);
+#pragma unroll
+                for (int g = 0; g < GR; ++g) {
+                    union { u32x4 u; f32x4 f; } o;
+                    o.f = v[g] * alpha;
+                    if constexpr (BETA) o.f += c_in[run][g] * p.beta;
+                    if (!EDGE || (run * GR + g) * RPI < rows_ok) store_loose<u32x4, 4>((char *)out + (int64_t)(run * GR + g) * RPI * ld * 4, o.u);
+                }
+            }
+        };
+        if (out32 && interior && (po.base || (p.beta == 0.0f && !hooked))) {
+            straight(IC<0>{}, IC<C::WTM * C::WTN < 128 * 64 ? 0 : 1>{});
+            return;
+        }
+        if (out32 && !hooked && interior) {
+            straight(IC<1>{}, IC<0>{});
+            return;
+        }
+        if (out32 && !hooked && p.N % 4 == 0 && (po.base || p.beta == 0.0f)) {
+            straight(IC<0>{}, IC<1>{});
             return;
         }
     }
@@ -1096,9 +1111,9 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     const int tiles = p.tiles_m * p.tiles_n;
     const int bid = blockIdx.x;
     const int pos = order_of_block(bid, tiles * p.split);
-    const int slice = __builtin_amdgcn_readfirstlane(pos / tiles);
+    const int slice = __builtin_amdgcn_readfirstlane(quotient((uint32_t)pos, p.by_tiles));
     int tm, tn;
-    tile_in_order(pos - slice * tiles, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    tile_in_order(p, pos - slice * tiles, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
 
     const int kt_begin = slice * p.ktiles_per_slice;
@@ -1217,7 +1232,7 @@ __global__ __launch_bounds__(C::NT) void gemm_kernel(const GemmArgs p)
     // wraps around.  Workgroups that share an A or B panel in one XCD's L2 start
     // at different tiles, so one of them touches a chunk first and the others,
     // a step or two later, find it in L2 instead of all waiting on the same miss.
-    const int rot = __builtin_amdgcn_readfirstlane(((tm & 7) * p.rot_m + (tn & 3) * p.rot_n) % KT);
+    const int rot = p.rot_m | p.rot_n ? __builtin_amdgcn_readfirstlane(((tm & 7) * p.rot_m + (tn & 3) * p.rot_n) % KT) : 0;
     auto rotated = [&](int kt) {
         const int kr = kt + rot;
         return kr >= KT ? kr - KT : kr;
@@ -1833,8 +1848,7 @@ constexpr int REDUCE_ROWS = 8, REDUCE_COLS = 128;
 template <int DT>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs p)
 {
-    const uint32_t nbx = (uint32_t)((p.N + REDUCE_COLS - 1) / REDUCE_COLS);
-    const uint32_t by = blockIdx.x / nbx, bx = blockIdx.x - by * nbx;
+    const uint32_t by = (uint32_t)quotient(blockIdx.x, p.by_reduce), bx = blockIdx.x - by * p.by_reduce.d;
     const int64_t m = (int64_t)by * REDUCE_ROWS + threadIdx.x / (REDUCE_COLS / 4);
     const int64_t n = (int64_t)bx * REDUCE_COLS + threadIdx.x % (REDUCE_COLS / 4) * 4;
     if (m >= p.M || n >= p.N) return;
@@ -1873,7 +1887,7 @@ __global__ __launch_bounds__(256) void streamk_reduce_kernel(const GemmArgs p)
     const int q = blockIdx.x * 256 + threadIdx.x;                 // 4-column group within the tile
     if (q >= BM * (BN / 4)) return;
     int tm, tn;
-    tile_of_block(p.tiles_m * p.tiles_n - p.sk_tiles + r, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    tile_in_order(p, order_of_block(p.tiles_m * p.tiles_n - p.sk_tiles + r, p.tiles_m * p.tiles_n), tm, tn);
     const int row = q / (BN / 4), col = (q % (BN / 4)) * 4;
     const int64_t m = (int64_t)tm * BM + row, n = (int64_t)tn * BN + col;
     if (m >= p.M || n >= p.N) return;

@@ -60,7 +60,7 @@ __global__ __launch_bounds__(C::NT) void skinny_kernel(const GemmArgs p)
 {
     __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tn = blockIdx.x % p.tiles_n, slice = blockIdx.x / p.tiles_n;
+    const int slice = quotient(blockIdx.x, p.by_tiles), tn = (int)blockIdx.x - slice * p.tiles_n;   // (one row of tiles)
     const int64_t n0 = (int64_t)tn * C::BN;
 
     const int kt_begin = slice * p.ktiles_per_slice;
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(C::NT) void skinny_kernel(const GemmArgs p)
     // lie a power of two apart, which concentrates the requests of the whole chip on a few
     // memory channels; started at different tiles they spread over all of them.  Only the
     // order of the sum over k changes.
-    const int rot = (int)(((int64_t)tn * p.rot_n) % KT);
+    const int rot = (int)((uint32_t)tn * (uint32_t)p.rot_n % (uint32_t)KT);
     auto issue = [&](int kt, int stage) {
         int kc = (kt < KT ? kt : KT - 1) + rot;          // past the end: refetch the last tile into a free stage
         if (kc >= KT) kc -= KT;
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(C::NT) void skinny_kn_kernel(const GemmArgs p)
 {
     __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tn = blockIdx.x % p.tiles_n, slice = blockIdx.x / p.tiles_n;
+    const int slice = quotient(blockIdx.x, p.by_tiles), tn = (int)blockIdx.x - slice * p.tiles_n;   // (one row of tiles)
     const int64_t n0 = (int64_t)tn * C::BN;
     const int r16 = lane & 15, q = lane >> 4;
 
