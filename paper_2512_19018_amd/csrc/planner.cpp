@@ -864,7 +864,7 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
     if (forced_split <= 0 && streamk == 0 && table_split < 0) streamk = 1;
     plan_geometry(&p->g, d, pick, forced_split > 0 ? forced_split : (table_split > 0 ? table_split : 0), streamk);
     int deep = -1, slices = 0;
-    if (own_choice && forced_split <= 0 && streamk == 0 && p->g.sk_tiles == 0 && deep_split(d, pick, p->g.split, &deep, &slices)) {
+    if (own_choice && forced_split <= 0 && p->g.sk_tiles == 0 && deep_split(d, pick, p->g.split, &deep, &slices)) {
         p->small = p->g;
         plan_geometry(&p->g, d, deep, slices);
     }

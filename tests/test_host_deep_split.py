@@ -34,10 +34,13 @@ def test_when_the_slices_are_taken(dt, ta, tb, M, N, K, deep):
 def test_only_the_selectors_own_choice_changes():
     M, N, K = 392, 5504, 11392
     own, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K)
-    for flags in (pg.force_flags(split=2), pg.force_flags(streamk=True)):
-        f, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K, flags=flags)
-        assert f["small"] == "none", f
+    f, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K, flags=pg.force_flags(split=2))
+    assert f["small"] == "none", f
     assert own["small"] != "none"
+    # an ordinary K split: neither what rules hybrid stream-K out nor what asks for it, without a last round to cut, changes it
+    for streamk in (False, True):
+        f, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K, flags=pg.force_flags(streamk=streamk))
+        assert f == own, (streamk, f)
     f, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K, pad=1)       # no rows for the 256x256 tile's copies
     assert f["small"] == "none"
     f, _ = fields_of(pg.PEAK_DT_F32, 0, 0, M, N, K)
