@@ -263,3 +263,13 @@ def test_fp32_tiles_of_one_sum_only_far_ahead(ta, tb, M, N, K):
 @pytest.mark.parametrize("ta,tb,M,N,K", [(0, 0, 748, 1752, 32), (1, 0, 2348, 492, 12), (0, 1, 240, 4740, 16), (0, 1, 968, 1268, 64)])
 def test_fp32_64x64_rings_at_short_k(ta, tb, M, N, K):
     assert "_m64x64q3" in plan("f32", ta, tb, M, N, K)[1]
+
+
+@pytest.mark.parametrize("dt,ta,tb,M,N,K", [
+    ("bf16", 0, 1, 1024, 5120, 5120), ("f16", 0, 0, 2048, 4096, 14336), ("bf16", 0, 0, 2048, 28672, 8192), ("bf16", 1, 0, 2048, 28672, 8192),
+    ("bf16", 1, 1, 2048, 28672, 8192), ("bf16", 0, 1, 1024, 4096, 14336), ("bf16", 0, 1, 2048, 2048, 512), ("f32", 0, 0, 3072, 3072, 3072)])
+def test_layer_shapes_run_without_a_workspace(dt, ta, tb, M, N, K):
+    """Products of layers that peak_gemm_run_static, and a run without workspace, have always taken."""
+    p, name, split, _, _ = plan(dt, ta, tb, M, N, K)
+    small = dict(w.split("=", 1) for w in p.info().split() if "=" in w)["small"]
+    assert p.workspace_bytes == 0 or small != "none", p.info()
