@@ -108,7 +108,9 @@ peak_status_t peak_gemm_create(const peak_gemm_desc_t *desc, peak_gemm_plan_t **
  * plans that do not split K).  Plans of large products with few tiles and a deep
  * K ("small=" in peak_gemm_plan_info) take up to 96 MB for partials; given less, or
  * none where that plan needs none, a run takes the plan with fewer K slices that
- * the description names.  The workspace holds fp32 partial tiles of the
+ * the description names (such plans are chosen for operands that come from device
+ * memory, as where a program does other work between two runs; with operands still in the
+ * last-level cache the other plan may be some per cent ahead).  The workspace holds fp32 partial tiles of the
  * Split-K step (Section 4.1, Table 2) and, for a streaming plan on an A stored
  * K x M, the copy of A with rows along K that the run writes first (Section
  * 4.1, Table 2, Transpose). */

@@ -563,8 +563,9 @@ static int select_variant(const peak_gemm_desc_t &d, bool staged_only)
 
 // Few tiles and a deep K in 16 bits, in microseconds: the 256x256 tile by its K tiles (1.25 each), smaller ones, which ask for
 // about twice the bytes per multiply-add, by their way into the CU, 58 bytes per ns with the operands from HBM (54 to 65 in 14
-// products, 62 with 128 k per stage, 61 to 64 in 9), 90 from the last-level cache (80 to 101), where operands up to 90 MB are taken
-// to be; none sooner than the operands come from HBM (a single row of 256x256 tiles 4.6 TB/s); all with what the partials cost out and back.
+// products, 62 with 128 k per stage, 61 to 64 in 9), 90 where they are small enough to stay in the last-level cache while a program
+// does something else (to 90 MB); none sooner than the operands come from HBM (a single row of 256x256 tiles 4.6 TB/s); all with
+// what the partials cost out and back.
 static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split), rounds = cdiv(cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, num_cu());
@@ -577,12 +578,26 @@ static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
     return us + partials;
 }
 
+// The same for a program that runs one product over and over: operands up to the size of the last-level cache then come from there.
+// The more workgroups, the less each gets (112 bytes per ns alone, 72 with a workgroup on every CU).  Fitted to 323 products
+// of 90 to 256 MB that deep_us decides, 7 % (root mean square) for the smaller tiles and 5 % for the 256x256 one.
+constexpr double LAST_LEVEL_CACHE = 256.0e6;
+static double deep_warm_us(const Variant &v, const peak_gemm_desc_t &d, int split)
+{
+    const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split), groups = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, rounds = cdiv(groups, num_cu());
+    const double share = (double)groups / (double)(rounds * num_cu()), megabytes = split > 1 ? 4.0e-6 * split * (double)d.M * (double)d.N : 0.0;
+    if (v.bm * v.bn >= 256 * 256) return 10.8 + (double)(rounds * ktiles) * (0.65 + 0.66 * share) + 0.23 * megabytes;
+    return 2.3 + (double)(rounds * ktiles * v.bk) * 2.0 * (v.bm + v.bn) / 1000.0 * (0.0089 + 0.0050 * share) + 0.61 * megabytes;
+}
+
 // The 256x256 tile in as many K slices as fill the chip in place of the choice by tiled_cost, which keeps to few partials and
-// does not know where the operands come from, where that is 13 % ahead by these prices.
-// Times of the choice by tiled_cost over those of the slices: 54 drawn products of 152 to 4480 rows that this decides 0.99 to 1.47, 1.20 in
-// the mean, each run with other operands than the last (512x4096x14336 NN, two slices of 128x128, 78.7 us, in eight of 256x256 64.9;
-// 391x5504x11392 NN unsplit 102.0, in five 69.3); 40 others with one set of operands over and over, in the last-level cache, 0.90 to
-// 1.12, 1.00 in the mean.  Where it sees less than 13 % the slices lost up to 4 %, with operands that fit the cache up to 16 %.
+// does not know where the operands come from: where that is 13 % ahead with operands from HBM by deep_us, and, since a plan does not
+// know either, no more than 4 % behind by deep_warm_us where they fit the last-level cache.
+// Times of the choice by tiled_cost over those of the slices, over 466 drawn products of 90 to 256 MB that deep_us alone would take.  The
+// 372 that are taken: each run with other operands than the last 1.25 in the mean (0.98 to 1.58), with one set over and over 1.04
+// (0.94 and less for one in twenty).  The 94 that are not: 1.16 and 0.94 (271x2304x18800 NN, fourteen slices, 1.15 and 0.87; 320x7168x7168 TT, four,
+// 1.06 and 0.83).  Beyond 256 MB, where both come from HBM, 1.22 and 1.17 (22 products, 0.97 at least).  512x4096x14336 NN in eight slices for
+// two of 128x128: 78 us and 64, over and over 58 and 61; 391x5504x11392 NN in five, unsplit before: 100 and 66, 65 and 59.
 // Partials to 96 MB: the run has the choice by tiled_cost as its stand-in where the workspace holds less.
 static bool deep_split(const peak_gemm_desc_t &d, int present, int present_split, int *variant, int *split)
 {
@@ -600,7 +615,8 @@ static bool deep_split(const peak_gemm_desc_t &d, int present, int present_split
             if (us < best) { best = us; *variant = i; *split = s; found = true; }
         }
     }
-    return found;
+    if (!found || 2.0 * ((double)d.M + (double)d.N) * (double)d.K > LAST_LEVEL_CACHE) return found;
+    return deep_warm_us(g_variants[*variant], d, *split) * 0.96 <= deep_warm_us(pv, d, present_split);
 }
 
 // Products whose rows do not suit the 16-byte copies of the other tiled kernels, by those on aligned copies of the operands

@@ -31,6 +31,19 @@ def test_when_the_slices_are_taken(dt, ta, tb, M, N, K, deep):
         assert 4 * split * M * N <= 96e6 and nbytes >= 4 * split * M * N
 
 
+@pytest.mark.parametrize("dt,ta,tb,M,N,K,deep", [
+    # operands that fit the last-level cache; slices over the plan of fewer partials, from there and from HBM:
+    ("f16", 1, 1, 320, 7168, 7168, False), ("f16", 1, 1, 384, 6643, 9088, False),          # 0.83 and 1.06, 0.84 and 1.09
+    ("f16", 0, 0, 271, 2304, 18800, False), ("f16", 0, 0, 4384, 352, 11840, False),        # 0.87 and 1.15, 0.86 and 1.12
+    ("bf16", 0, 0, 391, 5504, 11392, True), ("bf16", 0, 0, 512, 4096, 14336, True),        # 1.10 and 1.52, 0.96 to 0.98 and 1.22
+    ("bf16", 1, 0, 640, 4160, 11072, True),                                                # 1.02 and 1.47
+    # ... and that do not
+    ("bf16", 0, 0, 144, 4992, 27752, True), ("f16", 0, 0, 5376, 384, 24896, True)])        # 1.37, 1.11
+def test_products_that_a_program_may_repeat_with_operands_in_the_cache(dt, ta, tb, M, N, K, deep):
+    f, _ = fields_of(DTYPES[dt], ta, tb, M, N, K)
+    assert (f["small"] != "none") == deep, f
+
+
 def test_only_the_selectors_own_choice_changes():
     M, N, K = 392, 5504, 11392
     own, _ = fields_of(pg.PEAK_DT_BF16, 0, 0, M, N, K)
