@@ -151,6 +151,10 @@ size_t peak_gemm_workspace_bytes(const peak_gemm_plan_t *plan);
  * The caller keeps ownership of every buffer and of the stream.  Runs of one
  * plan that overlap in time must use different workspaces.  Results are
  * bit-identical from run to run for a given plan (no floating-point atomics).
+ * Within one C the order of the sum over k may differ from tile to tile: plans
+ * whose workgroups start at different K tiles ("rot=" and "xcdrot=1" in
+ * peak_gemm_plan_info) and those that cut their last tiles ("streamk=").  Equal
+ * rows of A, or columns of B, then give results that agree within rounding only.
  * M == 0 or N == 0: returns PEAK_OK and launches nothing.
  */
 peak_status_t peak_gemm_run(peak_gemm_plan_t *plan, float alpha,

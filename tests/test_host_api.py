@@ -457,3 +457,21 @@ def test_tile_order_and_k_rotation_of_the_plans():
     assert "_m128x128" in single and "(tiles 1x224)" in single and " rot=0,1 " in single
     assert " rot=0,5 " in info(16, 16384, 16384, bf, 0, 1)
     assert " rot=0,0 " in info(16, 28672, 8192, bf, 0, 0)        # B stored K x N: contiguous pieces of a k-row
+
+
+@pytest.mark.parametrize("name,M,K,split,on", [
+    ("bf16_m128x128w4a3_nt", 264, 4040, 1, True), ("bf16_m128x128w4a3_nt", 264, 4032, 1, False),      # 64 K tiles and 63
+    ("f16_m256x256w4a3_tt", 264, 4096, 1, True), ("bf16_m64x64q5_nt", 264, 4096, 1, True), ("f16_m32x64k128q3_nt", 100, 4096, 1, True),
+    ("bf16_m256x128w4a3_nt", 264, 8192, 2, True), ("bf16_m256x128w4a3_nt", 264, 8064, 2, False),      # a slice's depth counts
+    ("bf16_m128x128w4a3_nn", 264, 8192, 1, False), ("bf16_m64x64q5_tn", 264, 8192, 1, False),         # B stored K x N
+    ("bf16_m128x128w4a3_nt", 100, 8192, 1, False),                                                    # one row of tiles: by tile column
+    ("f32_m64x64q3_nt", 264, 8192, 1, False), ("bf16_d128x128w4_nt", 264, 8192, 1, False), ("bf16_r64x64_nt", 264, 8192, 1, False)])
+def test_when_the_xcds_start_at_different_k(name, M, K, split, on, monkeypatch):
+    names = [pg.peak_gemm_variant_name(i) for i in range(pg.peak_gemm_variant_count())]
+    dt = {"f32": pg.PEAK_DT_F32, "f16": pg.PEAK_DT_F16, "bf16": pg.PEAK_DT_BF16}[name.split("_")[0]]
+    def info():
+        with pg.Plan(M, 1096, K, dt, int(name[-2] == "t"), int(name[-1] == "t"), flags=pg.force_flags(variant=names.index(name), split=split)) as p:
+            return p.info()
+    assert (" xcdrot=%d " % on) in info(), info()
+    monkeypatch.setenv("PEAK_GEMM_ROT", "0,0")
+    assert " rot=0,0 xcdrot=0 " in info(), info()
