@@ -20,6 +20,8 @@
 
 #include <type_traits>
 
+#include "tile_order.h"
+
 namespace peak {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -44,11 +46,6 @@ struct Hook {
     const float *bias;        // device, fp32: N values (per column) or M values (per row)
     int32_t bias_kind;
     int32_t act;
-};
-
-// Division by a number that the host knows: 2^32 over it, rounded down (2^32 - 1 for 1); the quotient it gives is one short at most.
-struct Divisor {
-    uint32_t d, r;
 };
 
 struct GemmArgs {
@@ -617,39 +614,6 @@ PEAK_DEV void store4(void *C, int64_t idx, const float x[4], float alpha, float 
     float b[4];
     hook_bias4(hk, m, n, nvalid, b);
     store4<DT>(C, idx, x, alpha, beta, nvalid, hook_active(hk), hk.act, hk.bias_kind != BIAS_NONE, b);
-}
-
-// Tile order (the paper's Block-Swizzle, made XCD-aware): consecutive workgroup
-// ids go round-robin to the 8 XCDs, each with its own L2.  Give every XCD a
-// contiguous run of the band-ordered tile list, so the tiles an XCD works on at
-// one time share A row panels and B column panels in that L2.  A plan that splits
-// K orders (slice, tile) as one list: with few tiles an XCD then holds one stretch
-// of K of many tiles, where dealing out each slice by itself gave it the same few
-// tiles in every slice and nothing that two of them share (bf16 1768x160x7784 TN
-// in 6 slices 22.6 -> 16.3 us, f16 640x448x16512 NN in 12 30.5 -> 23.1, 1280x1144x18248
-// NN in 5 77.9 -> 67.2; 51 split plans 7 % with warm operands, 5 % from HBM).
-PEAK_DEV int order_of_block(int t, int total)
-{
-    const int xcd = t & 7, idx = t >> 3;
-    const int base = total >> 3, rem = total & 7;
-    return xcd * base + (xcd < rem ? xcd : rem) + idx;
-}
-// (The quotients by the host's reciprocals: a workgroup works out its tile before it can ask for anything.  The compiler's four divisions,
-// and one in 64 bits for a K rotation that most launches do not have, took 0.1 to 0.3 us of each launch: fp32 256^3 NN 4.54 us and 4.22,
-// 512^3 6.03 and 5.69; bf16 512x4096x1024 NT 8.35 and 8.17, 100x4096x4096 11.19 and 11.05, 2048x2048x512 9.17 and 8.89.)
-PEAK_DEV int quotient(uint32_t n, const Divisor &by)
-{
-    const uint32_t q = __umulhi(n, by.r);
-    return (int)(n - q * by.d >= by.d ? q + 1 : q);
-}
-PEAK_DEV void tile_in_order(const GemmArgs &p, int L, int &tm, int &tn)
-{
-    const int g = quotient((uint32_t)L, p.by_band);
-    const int first = g * p.group_m, left = p.tiles_m - first;
-    const bool last = left < p.group_m;
-    const int gsz = last ? left : p.group_m, w = L - g * (int)p.by_band.d;
-    tn = last ? quotient((uint32_t)w, p.by_last) : quotient((uint32_t)w, p.by_group);
-    tm = first + w - tn * gsz;
 }
 
 // ---------------------------------------------------------------------------

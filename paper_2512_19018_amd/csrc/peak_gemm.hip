@@ -145,7 +145,6 @@ __global__ __launch_bounds__(256) void pack_kernel(const PackOperand a, const Pa
     }
 }
 
-static Divisor divisor(int d) { return Divisor{(uint32_t)d, d == 1 ? 0xFFFFFFFFu : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)d)}; }
 static int esize_of(int dt) { return dt == PEAK_DT_F32 ? 4 : 2; }
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -250,20 +249,14 @@ static peak_status_t run_plan(peak_gemm_plan_t *p, float alpha, const void *A, c
     // diagnostic build: an unsplit run writes 64 bytes of time stamps per wave into the workspace, if one that large is given
     if (g->split == 1 && workspace && workspace_bytes >= (size_t)g->tiles_m * g->tiles_n * (v.nt / 64) * 64) a.ws = (float *)workspace;
 #endif
-    a.tiles_m = g->tiles_m; a.tiles_n = g->tiles_n;
+    set_tile_order(a, g->tiles_m, g->tiles_n, g->group_m);
     a.split = g->split;
     a.ktiles_per_slice = g->ktiles_per_slice;
     a.ktiles_total = g->ktiles_total;
-    a.group_m = g->group_m;
     a.rot_m = g->rot_m;
     a.rot_n = g->rot_n;
     a.rot_x = g->rot_x;
     a.sk_tiles = g->sk_tiles;
-    const int last_rows = a.tiles_m % a.group_m ? a.tiles_m % a.group_m : a.group_m;
-    a.by_tiles = divisor(a.tiles_m * a.tiles_n);
-    a.by_band = divisor(a.group_m * a.tiles_n);
-    a.by_group = divisor(a.group_m);
-    a.by_last = divisor(last_rows);
     a.by_reduce = divisor((int)cdiv(d.N, REDUCE_COLS));
 
     int64_t nblocks = grid_blocks(*g);

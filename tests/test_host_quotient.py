@@ -1,18 +1,16 @@
-"""The kernels' division by the host's reciprocals (gemm_device.h: Divisor, quotient), the same arithmetic in Python."""
-import random
+"""Tiles and slices by the host's reciprocals: csrc/tile_order.h itself, which the kernels include, built with the host compiler and
+compared with plain division up to the 2^31 - 1 workgroups of a launch."""
+import os
+import shutil
+
+import pytest
+
+from tests.test_sanitizers import ROOT, SAN, _build_and_run
 
 
-def quotient(n, d):
-    r = 0xFFFFFFFF if d == 1 else 2 ** 32 // d
-    q = n * r >> 32
-    return q + 1 if n - q * d >= d else q
-
-
-def test_quotient_is_exact_below_2_to_31():
-    rng = random.Random(7)
-    divisors = [1, 2, 3, 4, 7, 8, 2 ** 31 - 1, 2 ** 30, 2 ** 16 + 1] + [rng.randrange(1, 2 ** rng.randrange(1, 32)) for _ in range(3000)]
-    for d in divisors:
-        top = (2 ** 31 - 1) // d * d
-        for n in {0, 1, d - 1, d, 2 * d - 1, 2 * d, top - 1, top, 2 ** 31 - 1, rng.randrange(2 ** 31)}:
-            if 0 <= n < 2 ** 31:
-                assert quotient(n, d) == n // d, (n, d)
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
+def test_tiles_and_slices_as_by_division(tmp_path):
+    exe = str(tmp_path / "tile_order")
+    out = _build_and_run(["g++", "-std=c++17", "-Wall", "-Wextra"] + SAN + [os.path.join(ROOT, "tests", "sanitize", "tile_order_main.cpp"), "-o", exe],
+                         exe, [], tmp_path)
+    assert "tile order clean" in out
