@@ -15,10 +15,11 @@ def gu():
     return gpu_util
 
 
-# rows and columns that end inside a tile, K inside a K tile, the last slice shorter
-@pytest.mark.parametrize("dtype,transA,transB,M,N,K", [
-    (pi.BF16, 0, 0, 391, 5504, 11392), (pi.F16, 0, 1, 340, 3700, 15152), (pi.BF16, 1, 0, 640, 4160, 11072), (pi.F16, 1, 1, 568, 3012, 19432)])
-def test_deep_split_and_its_stand_in(gu, oracle, dtype, transA, transB, M, N, K):
+# rows and columns that end inside a tile, K inside a K tile, the last slice shorter; whether the stand-in splits K itself
+@pytest.mark.parametrize("dtype,transA,transB,M,N,K,splits", [
+    (pi.BF16, 0, 0, 391, 5504, 11392, False), (pi.F16, 0, 1, 340, 3700, 15152, True), (pi.BF16, 1, 0, 640, 4160, 11072, False),
+    (pi.F16, 1, 1, 568, 3012, 19432, True)])
+def test_deep_split_and_its_stand_in(gu, oracle, dtype, transA, transB, M, N, K, splits):
     import torch
     pg = gu.pg
     g = np.random.default_rng(45)
@@ -34,14 +35,22 @@ def test_deep_split_and_its_stand_in(gu, oracle, dtype, transA, transB, M, N, K)
         assert "small=none" not in info and need > pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, info
         ws = torch.full((need + 16,), 0xFF, dtype=torch.uint8, device="cuda")                 # NaN wherever nothing is written
         seen = []
-        for ptr, nbytes in ((ws.data_ptr(), need), (ws.data_ptr(), need - 1), (ws.data_ptr(), pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES), (0, None)):
+        # whole, one byte short, as large as the fixed array, the entry point with that array; off its boundary, none
+        for at, nbytes, status in ((0, need, pg.PEAK_OK), (0, need - 1, pg.PEAK_OK), (0, pg.PEAK_GEMM_STATIC_WORKSPACE_BYTES, pg.PEAK_OK),
+                                   (None, None, pg.PEAK_OK), (16, need, pg.PEAK_ERR_INVALID_ARG if splits else pg.PEAK_OK),
+                                   (None, 0, pg.PEAK_ERR_WORKSPACE if splits else pg.PEAK_OK)):
             dC = gu.to_dev(gu.nan_fill(M, N, dtype))
             args = (plan.handle, 1.0, dA.data_ptr(), dB.data_ptr(), 0.0, dC.data_ptr())
-            status = pg.peak_gemm_run_static(*args, stream) if nbytes is None else pg.peak_gemm_run(*args, ptr, nbytes, stream)
-            assert status == pg.PEAK_OK, (info, nbytes)
+            ptr = 0 if at is None else ws.data_ptr() + at
+            got = pg.peak_gemm_run_static(*args, stream) if nbytes is None else pg.peak_gemm_run(*args, ptr, nbytes, stream)
+            assert got == status, (info, at, nbytes, got)
             torch.cuda.synchronize()
             got = gu.from_dev(dC, dtype)
-            gu.assert_elementwise(pi.to_f64(got, dtype)[rows], ref, bound, (info, nbytes))
+            if status != pg.PEAK_OK:                                                          # refused: nothing launched
+                assert np.array_equal(got, gu.nan_fill(M, N, dtype)), (info, at, nbytes)
+                continue
+            gu.assert_elementwise(pi.to_f64(got, dtype)[rows], ref, bound, (info, at, nbytes))
             seen.append(got)
         # the stand-in's bits whatever the smaller workspace
-        assert (seen[1] == seen[2]).all() and (seen[2] == seen[3]).all()
+        assert len(seen) == (4 if splits else 6)
+        assert all((x == seen[1]).all() for x in seen[2:])

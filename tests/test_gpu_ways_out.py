@@ -70,3 +70,20 @@ def test_fp32_c_and_slices_exact(gu, oracle, tile, dtype, transA, transB):
             else:
                 assert np.all(np.abs(got - ref) <= gu.U_OUT[dtype] * np.abs(ref)), (info, M, N, split)
             assert np.array_equal(raw[:, N:].view(np.uint8), C0[:, N:].view(np.uint8)), (info, M, N, alpha, beta, split)
+
+
+# C_in and a C of the operands' type: whole tiles, which go straight through, and edges, with rows of C on 16 bytes, 2, 6 and 12 off
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("dtype,transA,transB", [(pi.BF16, 0, 1), (pi.F16, 1, 0)])
+def test_16_bit_c_with_c_in_exact(gu, oracle, tile, dtype, transA, transB):
+    pg = gu.pg
+    vid = _variant(gu, "%s_%s_%s" % (pi.DTYPE_NAMES[dtype], tile, "tn" if transA else "nt"))
+    K = 64
+    for case, (M, N) in enumerate([(256, 256), (512, 768), (264, 520), (136, 72)]):
+        A, B = _ints(dtype, transA, transB, M, N, K, 8600 + case)
+        for pad, alpha, beta in [(0, 1.0, 1.0), (1, -1.0, 2.0), (3, 0.5, -1.0), (6, 1.0, 0.5)]:
+            C = pi.store(pi.small_int_matrix(8700 + case, 2, M, N, -8, 8, dtype), False, N + pad)
+            ref = oracle.gemm(dtype, transA, transB, M, N, K, alpha, A, B, beta, C)       # multiples of 0.5 below 512: exact in fp32
+            got, raw, info = gu.run_gemm(dtype, transA, transB, M, N, K, alpha, beta, A, B, C, flags=pg.force_flags(variant=vid, split=1))
+            assert np.all(np.abs(got - ref) <= gu.U_OUT[dtype] * np.abs(ref)), (info, M, N, pad, alpha, beta)
+            assert np.array_equal(raw[:, N:], C[:, N:]), (info, M, N, pad)
