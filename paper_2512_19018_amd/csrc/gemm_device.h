@@ -802,7 +802,7 @@ struct FusedStep {
         for (int nb = 0; nb < C::NB; ++nb) column[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb) row[mb] = 0.0f;
-        if (p.hook.bias_kind == BIAS_PER_COLUMN && p.N >= 4) {
+        if (p.hook.bias_kind == BIAS_PER_COLUMN) {                 // (N >= 8 here: a whole tile's columns, or whole 16-byte pieces)
 #pragma unroll
             for (int nb = 0; nb < C::NB; ++nb) {
                 const int64_t at = n + nb * 16 + 4 * (lane >> 4);
@@ -903,11 +903,13 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
     // choices below (fp32 652x4536x16 TN 7.8 us without them, 8.9 with; 4096x4096x64 NT 31.0 and 32.7; 256^3 4.3 and 4.8).
     // Likewise 16-bit kernels' (epilogue_vector and so: bf16 512x4096x14336 NN in eight slices 66.5 us and 65.2, 512x2048x8192 NN in four
     // 26.2 and 25.6) and, on interior tiles, with C_in: 4096x4096x2000 TN into fp32 C 69.5 and 67.5, 2048x1024x2048 18.4 and 17.5, fp32
-    // 512^3 6.55 and 6.03, 256^3 5.03 and 4.54.  With the loads of C_in masked for edge tiles, each is waited for by itself (69.8 and 89.8).
+    // 512^3 6.55 and 6.03, 256^3 5.03 and 4.54.  Edge tiles with C_in: loads under a mask are each waited for by themselves (69.8 and 89.8);
+    // addresses held inside C, which need no mask, have not been tried.
     // (not the 32x32 kernels of 16 bits: their 8-wave 256x256 tiles have no registers left for another form)
     if constexpr (C::DT == DT_F32 || C::FUSED16 > 0) {
         auto straight = [&](auto beta_c, auto edge_c) {
             constexpr bool BETA = decltype(beta_c)::value != 0, EDGE = decltype(edge_c)::value != 0;
+            static_assert(!(BETA && EDGE), "C_in is asked for without masks");
             constexpr int LPR = C::WTN / 4, RPI = 64 / LPR, G = 32 / RPI;  // lanes per row, rows per store instruction, row groups
             constexpr int GR = G < 8 ? G : 8, RUNS = SLABS * (G / GR);     // ... of which at most eight in registers
             const int orow = lane / LPR, ocol = (lane % LPR) * 4;
@@ -920,7 +922,7 @@ PEAK_DEV void epilogue_slabs(const GemmArgs &p, char *lds, int wave, int lane, i
                 if constexpr (BETA) {
 #pragma unroll
                     for (int g = 0; g < GR; ++g)
-                        if (!EDGE || (run * GR + g) * RPI < rows_ok) c_in[run][g] = load_loose<f32x4, 4>((const char *)out + (int64_t)(run * GR + g) * RPI * ld * 4);
+                        c_in[run][g] = load_loose<f32x4, 4>((const char *)out + (int64_t)(run * GR + g) * RPI * ld * 4);
                 }
             };
             fetch(0);
