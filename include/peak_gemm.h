@@ -215,7 +215,8 @@ peak_status_t peak_gemm_run_fused(peak_gemm_plan_t *plan, float alpha,
  * its own copy until the process ends).  The call allocates nothing.
  *
  *   PEAK_ERR_WORKSPACE  the plan, or its stand-in where it has one for small workspaces, needs more than PEAK_GEMM_STATIC_WORKSPACE_BYTES
- *                       (peak_gemm_workspace_bytes() tells beforehand); nothing is launched.
+ *                       (peak_gemm_workspace_bytes() tells beforehand, but for plans with such a stand-in: "pack=" other than 0
+ *                       or "small=" other than none in peak_gemm_plan_info); nothing is launched.
  *   PEAK_ERR_HIP        no current device, or the array's address could not be obtained.
  *
  * The array's device address is looked up on the first call on each device
