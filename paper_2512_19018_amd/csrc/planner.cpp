@@ -369,6 +369,25 @@ static int stream_split(const Variant &v, const peak_gemm_desc_t &d)
     return best;
 }
 
+constexpr double LAST_LEVEL_CACHE = 256.0 * 1024.0 * 1024.0;
+
+// Whether the XCDs start an eighth of the K tiles apart: 16 bits, B's rows along K and K deep.  Workgroups that all read the same k of
+// rows a power of two apart load few memory channels at a time, those of an XCD keep in step for its L2.  Time without over that with,
+// from HBM: 512x8192x8192 NT 73.6 us and 70.4, TT 75.0 and 71.4, 512x4096x4096 NT 30.4 and 29.8, 1000x14336x4096 92.0 and 90.7, 2472x1040x4200
+// 43.4 and 38.5; in the last-level cache level.  Not with B stored K x N, whose k-rows are contiguous (256x14336x4096 NN 45.0 us without and 46.2),
+// nor with a short K (512x4096x1024 NT 8.43 and 8.56).  Nor, of 329 drawn products (the 224 that it stays for 1.024 from HBM and 1.003 over and
+// over, 0.957 and 0.976 at least; the 105 others 0.991 and 0.998, 0.930 and 0.941 at least):
+//  - with operands beyond the last-level cache, which an XCD then reads again when the others are done with them (0.987 and 0.994; f16
+//    1280x10240x20992 TT 428 us without and 459, bf16 1472x8896x20864 NT 412 and 430);
+//  - with an A stored K x M that is most of what is read (0.992; f16 8096x256x4288 0.94, 11920x72x14840 0.96 in both states);
+//  - for K slices of the 256x256 tile, which lie at different k anyway, stream-K's among them (0.988; bf16 8704x2048x4608 NT 137 us and 141).
+static bool xcds_apart(const Variant &v, const peak_gemm_desc_t &d, int64_t depth, int split)
+{
+    if (!(v.mf16 || (v.ring && d.dtype != PEAK_DT_F32)) || v.tr || depth < 4096) return false;
+    if (2.0 * ((double)d.M + (double)d.N) * (double)d.K > LAST_LEVEL_CACHE || (d.transA && d.M > 8 * d.N)) return false;
+    return split == 1 || v.bm * v.bn < 256 * 256;
+}
+
 // streamk: 1 take hybrid stream-K wherever it applies, -1 never, 0 let the cost model decide
 static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, int forced_split, int streamk = 0)
 {
@@ -399,12 +418,8 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
     // ... except where a single row of tiles has every workgroup stream rows of B that no other reads: started one
     // K tile apart they spread over the memory channels (16x16x32 kernels; bf16 128x28672x8192 109 -> 103 us)
     if (v.mf16 && p->tiles_m == 1 && p->tiles_n > 1) p->rot_n = 1;
-    // ... and by XCD, an eighth of the K tiles apart, where B's rows run along K and K is deep: workgroups that all read the same k of
-    // rows a power of two apart load few memory channels at a time, those of an XCD keep in step for its L2.  16 bits, time over that
-    // without, from HBM: 512x8192x8192 NT 76.5 us -> 74.6, TT 77.1 -> 74.6, 700x4096x8192 TT 69.3 -> 62.5, 512x4096x4096 NT 30.8 ->
-    // 29.9, 1000x14336x4096 97.4 -> 96.3; in the last-level cache level to 1 % (4096^3 98.2 -> 97.7).  Not with B stored K x N, whose
-    // k-rows are contiguous (256x14336x4096 NN 45.0 and 46.2), nor with a short K (512x4096x1024 NT 8.43 and 8.56).
-    p->rot_x = (v.mf16 || (v.ring && d.dtype != PEAK_DT_F32)) && !v.tr && p->rot_n == 0 && (int64_t)p->ktiles_per_slice * v.bk >= 4096 ? 1 : 0;
+    // ... and by XCD, an eighth of the K tiles apart
+    p->rot_x = p->rot_n == 0 && xcds_apart(v, d, (int64_t)p->ktiles_per_slice * v.bk, p->split) ? 1 : 0;
     if (const char *e = getenv("PEAK_GEMM_GROUP_M")) {      // tuning knob: tile rows per band
         const int g = atoi(e);
         if (g >= 1 && g <= 64) p->group_m = g < p->tiles_m ? g : (p->tiles_m > 0 ? p->tiles_m : 1);
@@ -428,6 +443,7 @@ static void plan_geometry(Geometry *p, const peak_gemm_desc_t &d, int variant, i
             p->ktiles_per_slice = (int)cdiv(p->ktiles_total, S);
             p->split = (int)cdiv(p->ktiles_total, p->ktiles_per_slice);
             p->sk_tiles = sk_tiles;
+            p->rot_x = 0;                                    // (256x256 tiles, see xcds_apart)
             p->ws_bytes = (size_t)p->split * (size_t)sk_tiles * (size_t)v.bm * v.bn * sizeof(float);
         }
     }
@@ -581,7 +597,6 @@ static double deep_us(const Variant &v, const peak_gemm_desc_t &d, int split)
 // The same for a program that runs one product over and over: operands up to the size of the last-level cache then come from there.
 // The more workgroups, the less each gets (112 bytes per ns alone, 72 with a workgroup on every CU).  Fitted to 323 products
 // of 90 to 256 MB that deep_us decides, 7 % (root mean square) for the smaller tiles and 5 % for the 256x256 one.
-constexpr double LAST_LEVEL_CACHE = 256.0e6;
 static double deep_warm_us(const Variant &v, const peak_gemm_desc_t &d, int split)
 {
     const int64_t ktiles = cdiv(cdiv(d.K, v.bk), split), groups = cdiv(d.M, v.bm) * cdiv(d.N, v.bn) * split, rounds = cdiv(groups, num_cu());
@@ -615,7 +630,7 @@ static bool deep_split(const peak_gemm_desc_t &d, int present, int present_split
             if (us < best) { best = us; *variant = i; *split = s; found = true; }
         }
     }
-    if (!found || 2.0 * ((double)d.M + (double)d.N) * (double)d.K > LAST_LEVEL_CACHE) return found;
+    if (!found || 2.0 * ((double)d.M + (double)d.N) * (double)d.K > 256.0e6) return found;       // (what deep_warm_us is fitted to)
     return deep_warm_us(g_variants[*variant], d, *split) * 0.96 <= deep_warm_us(pv, d, present_split);
 }
 

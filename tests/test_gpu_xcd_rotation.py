@@ -49,7 +49,7 @@ def _exact(gu, oracle, name, dtype, transA, K, split):
     rows = [0, 1, 127, 128, 255, 256, 263]
     ref = oracle.gemm(dtype, transA, 1, M, N, K, 1.0, A, B, 0.0, None, rows=rows)
     got, _, info = gu.run_gemm(dtype, transA, 1, M, N, K, 1.0, 0.0, A, B, gu.nan_fill(M, N, pi.F32), flags=pg.force_flags(variant=vid, split=split), cdtype=pi.F32)
-    assert " xcdrot=1 " in info, info
+    assert (" xcdrot=%d " % (split == 1 or "256x256" not in name)) in info, info          # (slices of the largest tile start together)
     assert np.array_equal(got[rows], ref), info             # small integers: exact in fp32 in any order
 
 

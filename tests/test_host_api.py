@@ -465,13 +465,19 @@ def test_tile_order_and_k_rotation_of_the_plans():
     ("bf16_m256x128w4a3_nt", 264, 8192, 2, True), ("bf16_m256x128w4a3_nt", 264, 8064, 2, False),      # a slice's depth counts
     ("bf16_m128x128w4a3_nn", 264, 8192, 1, False), ("bf16_m64x64q5_tn", 264, 8192, 1, False),         # B stored K x N
     ("bf16_m128x128w4a3_nt", 100, 8192, 1, False),                                                    # one row of tiles: by tile column
+    ("bf16_m128x128w4a3_nt", 264, 98688, 1, True), ("bf16_m128x128w4a3_nt", 264, 98752, 1, False),    # operands of 256 MiB and above
+    ("f16_m128x128w4a3_tt", 8768, 4096, 1, True), ("f16_m128x128w4a3_tt", 8776, 4096, 1, False),      # A stored K x M, M at 8 N and above
+    ("f16_m128x128w4a3_nt", 8776, 4096, 1, True), ("f16_m256x256w4a3_tt", 264, 8192, 1, True),
+    ("f16_m256x256w4a3_tt", 264, 8192, 2, False), ("bf16_m256x256w4a3_nt", 15360, 4096, 0, False),    # slices of 256 x 256 tiles, and stream-K's
+    ("bf16_m256x256w4a3_nt", 15360, 4096, 1, True),
     ("f32_m64x64q3_nt", 264, 8192, 1, False), ("bf16_d128x128w4_nt", 264, 8192, 1, False), ("bf16_r64x64_nt", 264, 8192, 1, False)])
 def test_when_the_xcds_start_at_different_k(name, M, K, split, on, monkeypatch):
     names = [pg.peak_gemm_variant_name(i) for i in range(pg.peak_gemm_variant_count())]
     dt = {"f32": pg.PEAK_DT_F32, "f16": pg.PEAK_DT_F16, "bf16": pg.PEAK_DT_BF16}[name.split("_")[0]]
     def info():
-        with pg.Plan(M, 1096, K, dt, int(name[-2] == "t"), int(name[-1] == "t"), flags=pg.force_flags(variant=names.index(name), split=split)) as p:
+        flags = pg.force_flags(variant=names.index(name), split=split) if split else pg.force_flags(variant=names.index(name), streamk=True)
+        with pg.Plan(M, 1096, K, dt, int(name[-2] == "t"), int(name[-1] == "t"), flags=flags) as p:
             return p.info()
-    assert (" xcdrot=%d " % on) in info(), info()
+    assert (" xcdrot=%d " % on) in info() and (split or " streamk=0 " not in info()), info()
     monkeypatch.setenv("PEAK_GEMM_ROT", "0,0")
     assert " rot=0,0 xcdrot=0 " in info(), info()
